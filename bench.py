@@ -3,7 +3,8 @@
 A step is one pass of the whole hot path (layout, dispatch_send, dispatch_recv,
 combine_send, combine_reduce) over one synthetic batch that is already resident
 in HBM.  Prints ONE JSON line.  `value` is the achieved rate in GB/s: the
-algorithmic bytes of the staged data flow divided by the step time.
+algorithmic bytes of the data flow (one copy per token and destination rank into the
+receive buffers, unpack, replies, reduce) divided by the step time.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload dsv3_decode]
 """
@@ -20,11 +21,9 @@ HBM_PEAK_GBPS = 8000.0
 WRITES = {}          # per kernel: bytes written per step (filled by algorithmic_bytes)
 
 
-def algorithmic_bytes(wl, ttot, D, P, sizes, push=False, partial=False, ready=False):
-    """Bytes the method itself has to move (reads + writes), per kernel.  Staged
-    (default): pack into send buffers, scatter, unpack.  Push: the send kernels
-    write into the receive buffers, so the send-buffer write and the scatter's
-    read and write are not part of the method."""
+def algorithmic_bytes(wl, ttot, D, P, sizes, partial=False, ready=False):
+    """Bytes the method itself has to move (reads + writes), per kernel: rows stored into the
+    receive buffers, unpacked, expert rows stored into the reply buffers, reduced."""
     Be = sizes.expert_x_row_bytes + 4 * sizes.scales_per_row
     # a dispatched row as the method defines it; the library pads e4m3 wire rows to whole
     # 128-byte lines, and that padding is not counted as useful traffic
@@ -33,30 +32,24 @@ def algorithmic_bytes(wl, ttot, D, P, sizes, push=False, partial=False, ready=Fa
         Bx = Bw
     k = {
         "dispatch_pack_kernel": ttot * Bx + D * Bw,
-        "fabric_copy_kernel(dispatch)": 2 * D * Bw,
         "dispatch_unpack_kernel": D * Bw + P * Be,
         "combine_pack_kernel": 2 * P * Bc,
-        "fabric_copy_kernel(combine)": 2 * P * Bc,
         "combine_reduce_kernel": P * Bc + ttot * Bc,
     }
-    if partial:      # one reply row per received row: P rows read, D written, D moved, D read
+    if partial:      # one reply row per received row: P rows read, D written, D read
         del k["combine_pack_kernel"]
         k["combine_partial_pack_kernel"] = P * Bc + D * Bc
-        k["fabric_copy_kernel(combine)"] = 2 * D * Bc
         k["combine_reduce_kernel"] = D * Bc + ttot * Bc
-    if push:
-        del k["fabric_copy_kernel(dispatch)"], k["fabric_copy_kernel(combine)"]
     if wl.dispatch_dtype != "bf16" and not ready:
         k["dispatch_pack_e4m3_kernel"] = k.pop("dispatch_pack_kernel")
     # bytes each kernel writes (the rest it reads): for the one-directional ceilings
     WRITES.clear()
     WRITES.update({"dispatch_pack_kernel": D * Bw, "dispatch_pack_e4m3_kernel": D * Bw,
-                   "fabric_copy_kernel(dispatch)": D * Bw, "dispatch_unpack_kernel": P * Be,
+                   "dispatch_unpack_kernel": P * Be,
                    "combine_pack_kernel": P * Bc, "combine_partial_pack_kernel": D * Bc,
-                   "fabric_copy_kernel(combine)": (D if partial else P) * Bc,
                    "combine_reduce_kernel": ttot * Bc})
-    dispatch = sum(v for n, v in k.items() if n.startswith(("dispatch", "fabric_copy_kernel(d")))
-    combine = sum(v for n, v in k.items() if n.startswith(("combine", "fabric_copy_kernel(c")))
+    dispatch = sum(v for n, v in k.items() if n.startswith("dispatch"))
+    combine = sum(v for n, v in k.items() if n.startswith("combine"))
     return k, dispatch, combine
 
 
@@ -71,7 +64,7 @@ def step_time(workloads, harness, torch, name, steps, warmup, two_streams=False,
     cf = None if wl.zipf_alpha > 0 else (1.1 if wl.tokens >= 2048 else 1.5)
     sh = harness.make_shuffle(inp, capacity_factor=cf, **mode)
     _, bd, bc = algorithmic_bytes(wl, st["tokens_total"], st["dedup_rows"], st["pairs"], sh.sizes,
-                                  mode.get("peer_push", False), mode.get("partial_sums", False))
+                                  mode.get("partial_sums", False))
     y = sh.expert_x
     if wl.dispatch_dtype != "bf16":
         y = torch.zeros((wl.n_ranks, sh.expert_capacity_rows, wl.hidden), dtype=torch.bfloat16,
@@ -119,7 +112,7 @@ def compare_modes(workloads, harness, torch, name, variants, steps, rounds=4):
         two = kw.pop("two_streams", False)
         sh = harness.make_shuffle(inp, capacity_factor=cf, **kw)
         _, bd, bc = algorithmic_bytes(wl, st["tokens_total"], st["dedup_rows"], st["pairs"], sh.sizes,
-                                      kw.get("peer_push", False), kw.get("partial_sums", False))
+                                      kw.get("partial_sums", False))
         if two:
             fn = lambda sh=sh: harness.run_step_two_streams(sh, dev, expert_y=sh.expert_x, streams=streams)
         else:
@@ -238,9 +231,7 @@ def main():
                     help="send calls on a second stream: the receivers wait on the arrival counters "
                          "while the fabric copy runs (reports the step time only)")
     ap.add_argument("--push", action="store_true",
-                    help="FL_FLAG_PEER_PUSH: send kernels store into the peers' receive buffers, no "
-                         "send buffer and no scatter; GB/s is then computed against the smaller byte "
-                         "count of that method")
+                    help="FL_FLAG_PEER_PUSH, which every send call now follows: accepted, same kernels")
     ap.add_argument("--partial-sums", action="store_true",
                     help="FL_FLAG_PARTIAL_SUMS: combine sends one bf16 partial sum per (token, expert "
                          "rank); another arithmetic than the default, fewer bytes")
@@ -251,11 +242,10 @@ def main():
                     help="e4m3 workloads: dispatch tokens that are already quantised (synthetic codes and "
                          "scales), the payload of the paper's microbenchmark, instead of quantising bf16")
     ap.add_argument("--private-rows", type=int, default=0,
-                    help="first rows per (source, destination) sent to private slots in a scatter "
-                         "of their own (ablation of section Ablation: Private Buffer Size)")
+                    help="first rows per (source, destination) sent to private slots (ablation of section Ablation: Private Buffer Size)")
     ap.add_argument("--headline-only", action="store_true",
                     help="skip the side measurements that launch the kernels at other sizes or in "
-                         "other modes (single-rank split, peer-push variant); for profiler runs")
+                         "other modes (single-rank split, other orderings); for profiler runs")
     ap.add_argument("--profile-steps", type=int, default=200)
     ap.add_argument("--counters", action="store_true",
                     help="short run for `rocprofv3 --pmc`: a few steps plus one plain 1 GiB copy "
@@ -301,7 +291,7 @@ def main():
                               max_private_rows=args.private_rows, peer_push=args.push,
                               partial_sums=args.partial_sums)
     ttot, D, P = stats["tokens_total"], stats["dedup_rows"], stats["pairs"]
-    per_kernel, bytes_dispatch, bytes_combine = algorithmic_bytes(wl, ttot, D, P, sh.sizes, args.push, args.partial_sums, args.ready_e4m3)
+    per_kernel, bytes_dispatch, bytes_combine = algorithmic_bytes(wl, ttot, D, P, sh.sizes, args.partial_sums, args.ready_e4m3)
     bytes_step = bytes_dispatch + bytes_combine
 
     expert_y = None
@@ -560,28 +550,6 @@ def main():
                       "unit": "GB/s"}
         del g
 
-    # The same step with FL_FLAG_PEER_PUSH, beside the headline: fewer bytes by
-    # construction, so its GB/s is computed against its own byte count.
-    push_line = None
-    if not args.push and not big and not args.progressive and not args.headline_only and not args.partial_sums \
-            and not args.ready_e4m3:
-        shp = harness.make_shuffle(inp, capacity_factor=cf, max_private_rows=args.private_rows,
-                                   peer_push=True, stream_ordered=args.stream_ordered)
-        _, pd, pc = algorithmic_bytes(wl, ttot, D, P, shp.sizes, True)
-        for _ in range(args.warmup):
-            harness.run_hot_path(shp, dev, expert_y)
-        torch.cuda.synchronize()
-        p0 = time.perf_counter()
-        for _ in range(args.steps):
-            harness.run_hot_path(shp, dev, expert_y)
-        torch.cuda.synchronize()
-        pms = (time.perf_counter() - p0) * 1e3 / args.steps
-        assert shp.status() == 0
-        shp.close()
-        push_line = {"ms_per_step": round(pms, 4), "step_us": round(pms * 1e3, 1), "algorithmic_bytes": pd + pc,
-                     "value": round((pd + pc) / (pms * 1e-3) / 1e9, 1), "unit": "GB/s",
-                     "frac_of_hbm_peak": round((pd + pc) / (pms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)}
-
     # The modes and workloads that are not the headline, measured in the same run: the
     # fabric that keeps the arrival-counter contract with no ordering assumed (one stream,
     # and with senders and receivers on two streams), and the other four named workloads.
@@ -599,11 +567,10 @@ def main():
             "FL_FLAG_STREAM_ORDERED (no announce, no gate kernels)": {"stream_ordered": True},
             "FL_FLAG_PROGRESSIVE_RECV, one stream": {"progressive_recv": True},
             "FL_FLAG_PROGRESSIVE_RECV, two streams": {"progressive_recv": True, "two_streams": True},
-            "FL_FLAG_PEER_PUSH (fewer bytes by construction)": {"peer_push": True},
         }, steps=max(20, min(args.steps, 100)))
         interleaved = interleaved_caller_work(workloads, harness, torch)
         others = {}
-        for name, note in [("tiny", "launch-bound: eleven kernels on a few KB"),
+        for name, note in [("tiny", "launch-bound: nine kernels on a few KB"),
                            ("qwen3_skew", "cache-assisted: the working set partly fits the 256 MB last-level cache"),
                            ("dsv3_fp8", "e4m3 dispatch quantised on the fly, bf16 combine"),
                            ("dsv3_prefill", "4096 tokens per rank, payload calls cut into launches of 2 ranks")]:
@@ -621,7 +588,7 @@ def main():
             cpu_inp = workloads.token_chunk(inp, 0, 128)
             st = workloads.describe(cpu_inp)
             _, cd, cc = algorithmic_bytes(wl, st["tokens_total"], st["dedup_rows"], st["pairs"], sh.sizes,
-                                          args.push, args.partial_sums, args.ready_e4m3)
+                                          args.partial_sums, args.ready_e4m3)
             cpu_bytes, what = cd + cc, f"steps over the first 128 tokens per rank of {wl.name}"
         reps, c0 = 0, time.perf_counter()
         while reps < 40 and (reps == 0 or time.perf_counter() - c0 < 12.0):
@@ -658,7 +625,7 @@ def main():
         "config": {"workload": wl.name, "ranks_simulated": wl.n_ranks, "experts": wl.n_experts,
                    "tokens_per_rank": wl.tokens, "hidden": wl.hidden, "top_k": wl.top_k,
                    "dedup_rows": D, "pairs": P, "capacity_factor": cf, "private_rows": int(sh.sizes.private_rows),
-                   "method": "peer push (no send buffer, no scatter)" if args.push else "staged (pack, scatter, unpack)",
+                   "method": "rows stored into the receive buffers by the send kernels (no send buffer), unpacked there",
                    "combine": "sender-side bf16 partial sums" if args.partial_sums else "fp32 sum in k order",
                    "dispatch_input": "ready-made e4m3 codes + scales" if args.ready_e4m3 else "bf16",
                    "ordering": ordering_name(args),
@@ -683,9 +650,9 @@ def main():
                         for k in kern_us if k in per_kernel},
         "hip_graph_replay": graph_line,
         "step_us": round(ms_per_step * 1e3, 1),
-        "gbps_note": "GB/s divides each method's OWN algorithmic bytes by its step time: compare methods "
-                     "by step_us, not by GB/s (peer push moves fewer bytes and is the faster method)",
-        "peer_push_variant": push_line,
+        "gbps_note": "GB/s divides the method's OWN algorithmic bytes by its step time: compare methods "
+                     "by step_us, not by GB/s.  Lines from before the send buffers were dropped counted 4649 MB "
+                     "for the decode step, 1.6 times what it moves now",
         "modes_measured_in_turns": modes,
         "other_workloads": others,
         "interleaved_caller_work": interleaved,

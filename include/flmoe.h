@@ -2,12 +2,12 @@
  * flmoe - MoE expert-parallel dispatch/combine token shuffle for MI355X (gfx950).
  *
  * C ABI of the shared library.  One GPU hosts the whole expert-parallel group as
- * simulated ranks; the "fabric" between ranks is a device-side copy whose
- * completion is signalled only through per-source arrival counters (the
- * paper's ImmCounter idea, section TransferEngine / Completion Notification:
- * a counter advances when payload has been delivered, a receiver compares it
- * with what the exchanged counts tell it to expect, and nothing else orders
- * transfers).
+ * simulated ranks; the "fabric" between ranks is the send kernels' stores into the
+ * receive buffers, whose completion is signalled only through per-source arrival
+ * counters (the paper's ImmCounter idea, section TransferEngine / Completion
+ * Notification: a counter advances when payload has been delivered, a receiver
+ * compares it with what the exchanged counts tell it to expect, and nothing else
+ * orders transfers).
  *
  * Problem statement (section MoE Dispatch/Combine, Architecture): N ranks host E
  * experts (expert e lives on rank e / (E/N)); every rank holds up to T tokens of
@@ -22,9 +22,9 @@
  *   - Tensors are rank-major: element [r] of the leading dimension belongs to
  *     simulated rank r.  Each call acts for ranks [rank_begin, rank_begin +
  *     rank_count); code acting for rank r reads only rank r's tensors and
- *     receive buffers, and writes other ranks' memory only through the fabric
- *     copy and its counters.  Ranks on separate GPUs would each pass rank_count = 1
- *     (their calls then run at the same time, each on its own device).
+ *     receive buffers, and writes other ranks' memory only by storing into their
+ *     receive buffers and arrival counters.  Ranks on separate GPUs would each pass
+ *     rank_count = 1 (their calls then run at the same time, each on its own device).
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  The
  *     five shuffle calls only enqueue kernels: they never synchronise, never
  *     allocate, and can be captured in a HIP graph.  A call that moves several GB
@@ -102,39 +102,30 @@ extern "C" {
  *     receive kernel proper, on a full grid.  Waiting occupies one wave per rank.
  * What a rank still orders itself is its OWN five calls of a step, and one step after
  * the other (one stream per rank does that, or events).  That also covers the re-use of
- * the two staging buffers of a context (combine replies land in the senders' dispatch
- * send buffers, the dispatch receive buffers become the combine send buffers; the paper
- * puts a barrier before buffers are re-used, section Combine): rank d issues
- * combine_send after its dispatch_recv, whose gate passed only after EVERY peer's
- * announce kernel had run, and a peer's announce kernel runs only after all of that
- * peer's dispatch payload kernels have ended, so nobody reads a send buffer any more
- * when the first reply is written into it; and rank s issues the next step's
- * dispatch_send after its combine_reduce, whose gate passed only after every peer's
- * combine payload kernels had ended, so nobody reads a combine send buffer any more
- * when the next step's rows are written into it.  (On one GPU a waiting gate kernel
- * occupies its hardware queue: enqueue the sends of a phase before the receives that
- * wait for them whenever streams may share a queue.)
+ * the receive buffers (the paper puts a barrier before buffers are re-used, section
+ * Combine): rank d writes replies into s's combine receive buffer after its
+ * dispatch_recv, whose gate passed only after EVERY peer's announce kernel of this step had
+ * run, so s's combine_reduce of the step before has ended; and rank s issues the next
+ * step's dispatch_send after its combine_reduce, whose gate passed only after every
+ * peer's announce kernel had run behind its combine kernels, so no peer reads its dispatch
+ * receive buffer or the sidecars any more when the next step's rows are written there.
+ * (On one GPU a waiting gate kernel occupies its hardware queue: enqueue the sends of a
+ * phase before the receives that wait for them whenever streams may share a queue.)
  *
  * FL_FLAG_STREAM_ORDERED: the caller promises that each send call precedes the matching
  * receive call in stream order (one stream, or events between streams).  The library
- * then launches no announce and no gate kernels (four launches fewer per step): one
- * wave of the last payload kernel of a send call advances the counters while other
- * waves may still be storing, so here the counters are bookkeeping that only the
+ * then launches no announce and no gate kernels (four launches fewer per step): the
+ * first block of a sender's payload kernel advances the counters while other blocks may
+ * still be storing, so here the counters are bookkeeping that only the
  * kernel boundary makes trustworthy - they are still checked (bounded) by the
  * receivers, but they do not signal completion by themselves. */
 #define FL_FLAG_STREAM_ORDERED 2
 /* Every peer's receive buffer can be stored to directly, as between ranks of one
  * node (section Dispatch: within a node the send kernel pushes payloads over the
- * load/store interconnect instead of handing them to the NIC; here: always, all
- * simulated ranks live on one GPU).  The send calls then write each row and its
- * sidecar straight into the destination's receive buffer: no send buffer is
- * filled and no scatter kernel runs; the arrival counters advance as in the
- * staged path (by the announce kernel, inside the kernel that stores the payload
- * with FL_FLAG_STREAM_ORDERED, per workgroup with FL_FLAG_PROGRESSIVE_RECV).
- * Receivers, counters, capacities and every result
- * are unchanged; only the bytes moved per step shrink (one write per sent row
- * instead of write + read + write).  Combines with the other flags and
- * max_private_rows. */
+ * load/store interconnect instead of handing them to the NIC).  All simulated ranks live
+ * on one GPU, where that always holds: the send calls of every context write each row
+ * and its sidecar straight into the destination's receive buffer, with or without this
+ * flag, and no send buffer is filled.  The flag is accepted and changes nothing. */
 #define FL_FLAG_PEER_PUSH 4
 /* Combine with sender-side partial sums (section Comparison with DeepEP and the
  * prefill results of section Performance: pre-accumulating on the sending side
@@ -152,7 +143,7 @@ extern "C" {
 /* Receivers that start on each source's rows as soon as that source has landed,
  * whatever the other sources do (not with FL_FLAG_STREAM_ORDERED).  Senders write their
  * payload through to memory with device-scope stores, wait for the acknowledgement and
- * every wave adds what it delivered, so a receiver sees a source complete as early as
+ * every block adds what it delivered, so a receiver sees a source complete as early as
  * possible; the receive kernels poll the counters themselves, invalidate their caches
  * whenever they come to rely on arrivals they had not seen before, and run on grids
  * capped to a fraction of the machine so that pollers can never keep senders from
@@ -190,11 +181,10 @@ typedef struct fl_moe_config {
     int64_t spin_limit;     /* polls of an arrival counter before FL_STATUS_TIMEOUT (a waiting wave
                                polls about every 2 us); 0 = default, about 2 s                    */
     int32_t max_private_rows; /* P: the first P rows a source sends to a destination go to fixed
-                               private slots at the head of the destination's receive buffer, in a
-                               scatter of their own that needs no exchanged counts; only the rows
-                               beyond P are packed into the shared contiguous range (section
+                               private slots at the head of the destination's receive buffer; only the
+                               rows beyond P are packed into the shared contiguous range (section
                                Dispatch, figure "Dispatch into private and contiguous buffers";
-                               section Ablation: Private Buffer Size).  0 = one scatter into the
+                               section Ablation: Private Buffer Size).  0 = all rows into the
                                shared range; values above T act as T.  The receive buffer grows by
                                N*P rows per rank; recv_capacity_rows bounds the shared range only. */
     int32_t reserved;       /* must be 0 */
@@ -206,7 +196,7 @@ typedef struct fl_moe_sizes {
     int64_t expert_capacity_rows; /* also the rank stride, in rows, of expert_x/expert_y  */
     int64_t send_capacity_rows;   /* T * min(K, N)                                        */
     int64_t x_row_bytes;          /* 2*H                                                  */
-    int64_t wire_row_bytes;       /* bytes of one dispatched row in the send/receive
+    int64_t wire_row_bytes;       /* bytes of one dispatched row in the receive
                                      buffers: 2*H, or H + 4*H/128 rounded up to 128 for e4m3 */
     int64_t expert_x_row_bytes;   /* 2*H or H                                             */
     int64_t scales_per_row;       /* 0 or H/128                                           */
@@ -237,8 +227,8 @@ typedef struct fl_moe_layout_view {
 
 /* Test/diagnostic view of internal buffers (layouts are the library's own). */
 typedef struct fl_moe_debug_view {
-    void *buf_a;              /* per rank: dispatch send buffer / combine receive buffer  */
-    void *buf_b;              /* per rank: dispatch receive buffer / combine send buffer  */
+    void *buf_a;              /* per rank: combine receive buffer                         */
+    void *buf_b;              /* per rank: dispatch receive buffer                        */
     int64_t buf_a_rank_bytes;
     int64_t buf_b_rank_bytes;
     uint32_t *arrive_route;   /* [N][N] route records received, [destination][source]      */
@@ -309,13 +299,13 @@ int fl_moe_layout_static(const fl_moe_config *cfg /*host*/, const int32_t *indic
                          const int32_t *num_tokens, const fl_moe_layout_out *out /*host*/,
                          void *stream);
 
-/* Step 2 (section Dispatch: tokens are copied into send buffers, a contiguous
- * source per peer, then scattered).  x [N][T][H] bf16; all T rows of a rank
+/* Step 2 (section Dispatch: tokens are scattered to a contiguous range of every
+ * destination's receive buffer).  x [N][T][H] bf16; all T rows of a rank
  * must be addressable (rows of absent tokens may be read, they are never used).
- * Packs one copy of each token per distinct destination rank (quantising to
- * e4m3 when configured), copies every (source, destination) segment into the
- * destination's receive buffer and announces every transfer, empty ones included,
- * on arrive_disp[destination][source]: its payload in 16-byte units plus one. */
+ * Stores one copy of each token per distinct destination rank (quantised to
+ * e4m3 when configured) into the rows of the destination's receive buffer that the
+ * exchanged counts reserved, and announces every transfer, empty ones included, on
+ * arrive_disp[destination][source]: its payload in 16-byte units plus one. */
 int fl_moe_dispatch_send(fl_moe_ctx *ctx, int rank_begin, int rank_count, const void *x,
                          void *stream);
 
@@ -349,8 +339,8 @@ int fl_moe_dispatch_recv(fl_moe_ctx *ctx, int rank_begin, int rank_count, void *
 
 /* Step 4 (section Combine: a single scatter per peer re-using the routing
  * information).  expert_y [N][expert_capacity_rows][H] bf16, same row layout as
- * expert_x.  Packs each peer's rows contiguously, copies them into the peer's
- * combine receive buffer and announces every reply, empty ones included, on
+ * expert_x.  Stores each peer's rows contiguously into the peer's combine receive
+ * buffer and announces every reply, empty ones included, on
  * arrive_comb[peer][this rank] (units plus one, as in dispatch).  Call it once per
  * fl_moe_layout, after fl_moe_dispatch_recv. */
 int fl_moe_combine_send(fl_moe_ctx *ctx, int rank_begin, int rank_count, const void *expert_y,
@@ -400,12 +390,10 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
 /* Diagnostic: overrides a launch-shape knob of the copy kernels (results never
  * change).  knob 0 = rows per workgroup of the unpack / combine-pack kernels
  * (0 = chosen from the row size, at most 64), knob 1 = row loads issued together
- * per thread in combine_reduce (0 = all K, at most 8), knob 2 = waves per row in
- * the fabric kernel (0 = chosen from the row size, else 1..16), knob 3 =
+ * per thread in combine_reduce (0 = all K, at most 8), knobs 2 and 4 = accepted without
+ * effect (they shaped a copy kernel that is no longer launched), knob 3 =
  * workgroups per token in the pack kernel (0 = chosen from the row size, at
- * most 16), knob 4 = size in MiB of the receive buffers a fabric launch may
- * write above which it uses streaming instead of cached stores (default 2560),
- * knob 5 = percentage of the rows uniform routing would bring to a rank that the
+ * most 16), knob 5 = percentage of the rows uniform routing would bring to a rank that the
  * grids of the receive-side and reply kernels are sized for (default 200; 0 = the
  * whole capacity; a rank that holds more is served by the kernels' row loops),
  * knob 6 = payload in MiB one launch should move per direction: a call whose ranks
@@ -413,10 +401,10 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
  * groups of about this size (default 860; 0 = always one launch per kernel;
  * contexts with FL_FLAG_PROGRESSIVE_RECV are never cut), knob 7 = eighths of the
  * machine's resident-workgroup slots the polling receive kernels of
- * FL_FLAG_PROGRESSIVE_RECV may take (default 3), knob 8 = order in which the fabric kernel
- * takes the destinations of a sender (0 = ascending, 1 = descending, 2 = starting with
- * the sender's right-hand neighbour and wrapping round; a test switch: nothing may depend
- * on the order in which transfers are carried out), knob 9 = workgroups that share one
+ * FL_FLAG_PROGRESSIVE_RECV may take (default 3), knob 8 = order in which the send kernels
+ * take a sender's rows (0 = ascending, 1 = descending, 2 = starting in the middle and
+ * wrapping round; a test switch: nothing may depend on the order in which transfers are
+ * carried out), knob 9 = workgroups that share one
  * token in combine_reduce, each summing a slice of the row (0 = chosen from the row
  * size).  A value of -1 restores a knob's default. */
 int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value);
@@ -449,7 +437,7 @@ int fl_moe_debug_read(const void *src, size_t bytes, void *sink, void *stream);
  * since the last collect to per-kernel totals, and fl_moe_profile_read returns
  * totals (ms) and launch counts for kernel ids 0..FL_KERNEL_COUNT-1.  At most
  * 512 launches between two collects are timed; further ones run untimed. */
-#define FL_KERNEL_COUNT 14
+#define FL_KERNEL_COUNT 11
 int fl_moe_profile_enable(fl_moe_ctx *ctx, int on);
 int fl_moe_profile_collect(fl_moe_ctx *ctx, void *stream);
 int fl_moe_profile_read(fl_moe_ctx *ctx, double *total_ms /*host [FL_KERNEL_COUNT]*/,

@@ -26,14 +26,12 @@ struct Dims {
     int MW;               // words per sidecar row: KM, or 2*KM when the routing weights travel too
     int tune_rows;        // rows per block of the copy kernels (0 = by row size)
     int tune_reduce;      // loads in flight per thread in the reduce kernel (0 = all K)
-    int tune_waves;       // waves per row in the fabric kernel (0 = by row size)
     int tune_slices;      // blocks per token in the pack kernel (0 = by row size)
-    int tune_stream_mb;   // fabric uses streaming stores when a launch may write more than this many MiB
     int tune_grid_pct;    // row-kernel grids cover this percentage of the rows uniform routing would
                           // bring (0 = the whole capacity); kernels loop over whatever is beyond
     long long typ_recv_rows, typ_pair_rows;   // per rank, under uniform routing: received rows, pairs
     int tune_parts;       // workgroups per token in the reduce kernel (0 = by row size)
-    int tune_order;       // test switch: order in which the fabric kernel takes a sender's destinations
+    int tune_order;       // test switch: order in which the send kernels take their rows
     int tune_cap8;        // progressive receivers: eighths of the machine's block slots their grids may take
 };
 
@@ -53,8 +51,8 @@ struct Tables {
     unsigned *arrive_route;                                   // [N dst][N src] route records received
     // Payload counters, monotone: a completed transfer adds its payload in 16-byte units
     // plus one (default: by the announce kernel behind the payload kernels; stream-ordered
-    // callers: by one wave of the last payload kernel; progressive mode: the units by every
-    // copying wave); expect_* is advanced by the receiver's own planning block from the
+    // callers: by the send kernel's first block; progressive mode: the units by every
+    // copying block); expect_* is advanced by the receiver's own planning block from the
     // counts it was sent, so a receiver waits for arrive >= expect per source.
     unsigned *arrive_disp, *arrive_comb;                      // [N dst][N src]
     unsigned *expect_disp, *expect_comb;                      // [N dst][N src]
@@ -64,7 +62,8 @@ struct Tables {
     int *M;               // [N][N]
     int *send_off;        // [N][N+1]
     int *comb_off;        // [N][N+1]
-    int *send_row;        // [N][T][K]  row in the send buffer for the first slot of each destination, else -1
+    int *send_row;        // [N][T][K]  for the first slot of each destination: number of this copy among all
+                          //            copies the source sends, ordered by (destination, token); else -1
     unsigned *pair_meta;  // [N][T][K]  (local expert << 24) | rank of the token among the source's tokens of that expert
     int *comb_pos;        // [N][T][K]
     // written by the receiving side of the layout step
@@ -77,30 +76,27 @@ struct Tables {
     int *comb_dst_off;    // [N d][N s]       row in s's combine receive buffer where d's reply starts
     int *ret_off;         // [N d][N s]       partial sums: row in s's buffer where d's shares start,
                           //                  = rows s sent to lower ranks, so a share returns to the
-                          //                  row of s's send buffer its token copy left from
+                          //                  row that send_row gives its token copy
     int *base_x;          // [N][El][N]       first expert-major row of (local expert, source)
     int *cs_base;         // [N][N][El]       first combine-send row of (source, local expert)
     int *cs_off;          // [N][N+1]         first combine-send row of each source
     int *plan_ok;         // [N]
     int *gate_disp;       // [N] default mode: 1 once the gate kernel saw every source's dispatch payload complete
     int *gate_comb;       // [N] the same for the combine replies
-    unsigned *send_meta;  // [N][send_cap][MW]
     unsigned *recv_meta;  // [N][recv_rows][MW]
-    int2 *fab_dst_disp;   // [N][send_cap]    (destination rank, row there) of every send row
-    int2 *fab_dst_comb;   // [N][expert_cap]  same for the combine send rows
-    char *bufA;           // [N][bufA_rank_bytes]  dispatch send / combine receive
-    char *bufB;           // [N][bufB_rank_bytes]  dispatch receive / combine send
+    char *bufA;           // [N][bufA_rank_bytes]  combine receive buffer
+    char *bufB;           // [N][bufB_rank_bytes]  dispatch receive buffer
 };
 
 constexpr unsigned kNoEntry = 0xFFFFFFFFu;
 
 // ---------------------------------------------------------------- atomics
 // FENCED names the progressive mode, in which senders and receivers overlap in time
-// inside their kernels: every sending wave reports the units it delivered and the
+// inside their kernels: every sending block reports the units it delivered and the
 // receive kernels poll.  On gfx950 each XCD has its own L2, so a payload only
 // becomes visible to a receiver on another XCD once it has left the sender's L2.
 // An agent-scope release fence would write back the whole L2 (measured: 5x to 25x
-// slower fabric kernel, depending on how many waves fence).  Instead the sender
+// slower copy kernel, depending on how many waves fence).  Instead the sender
 // writes the payload with device-scope stores (sc1: written through to memory),
 // waits until its own stores are acknowledged, and only then updates the counter;
 // the receiver polls the counter with device-scope loads and, once it has arrived,
@@ -234,18 +230,13 @@ __device__ inline int seg_of_short(const int *off, int n, int x, int *start) {
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 __device__ inline v4u ld_stream(const v4u *p) { return __builtin_nontemporal_load(p); }
 __device__ inline void st_stream(v4u *p, v4u v) { __builtin_nontemporal_store(v, p); }
-// Fabric payload store.  Progressive mode: device scope, written through to memory so
-// that another XCD can see it without an L2 write-back.  Otherwise: an
-// ordinary cached store while the receive buffers are small enough for the caches
-// to absorb a good part of them (measured: 17 % faster fabric kernel at the decode
-// shape, the kernels after it 4 % slower, the step 5 % faster), a streaming store
-// when they are far larger than the caches (at the prefill shape cached stores were
-// 4 % slower).
-template <bool FENCED, bool STREAMING>
+// Payload store into a peer's receive buffer.  Progressive mode: device scope, written
+// through to memory so that another XCD can see it without an L2 write-back.  Otherwise
+// a streaming store.
+template <bool FENCED>
 __device__ inline void st_payload(v4u *p, v4u v) {
     if (FENCED) asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
-    else if (STREAMING) __builtin_nontemporal_store(v, p);
-    else *p = v;
+    else __builtin_nontemporal_store(v, p);
 }
 
 // A block copies `nrows` rows of `nvec` vectors each; vector v of the chunk lies
@@ -263,7 +254,7 @@ __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of
                 if (b + i * NT < nvec) r[i] = ld_stream(s + b + i * NT);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (b + i * NT < nvec) st_payload<FENCED, true>(d + b + i * NT, r[i]);
+                if (b + i * NT < nvec) st_payload<FENCED>(d + b + i * NT, r[i]);
         }
         return;
     }
@@ -283,7 +274,7 @@ __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int v = b + i * NT;
-            if (v < total) st_payload<FENCED, true>((v4u *)dst_of(row[i]) + col[i], r[i]);
+            if (v < total) st_payload<FENCED>((v4u *)dst_of(row[i]) + col[i], r[i]);
         }
     }
 }

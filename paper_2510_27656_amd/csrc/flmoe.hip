@@ -24,20 +24,17 @@ static __device__ __align__(256) unsigned char scratch[FL_STATIC_SCRATCH_BYTES];
 namespace {
 
 enum KernelId {
-    KID_ROUTE_LAYOUT = 0, KID_DISPATCH_PACK, KID_DISPATCH_FABRIC,
-    KID_DISPATCH_UNPACK, KID_COMBINE_PACK, KID_COMBINE_FABRIC, KID_COMBINE_REDUCE,
-    KID_DISPATCH_PACK_E4M3, KID_DISPATCH_FABRIC_PRIVATE, KID_COMBINE_PARTIAL_PACK, KID_GATE_DISPATCH,
-    KID_GATE_COMBINE, KID_ANNOUNCE_DISPATCH, KID_ANNOUNCE_COMBINE
+    KID_ROUTE_LAYOUT = 0, KID_DISPATCH_PACK, KID_DISPATCH_UNPACK, KID_COMBINE_PACK, KID_COMBINE_REDUCE,
+    KID_DISPATCH_PACK_E4M3, KID_COMBINE_PARTIAL_PACK, KID_GATE_DISPATCH, KID_GATE_COMBINE,
+    KID_ANNOUNCE_DISPATCH, KID_ANNOUNCE_COMBINE
 };
 const char *kKernelNames[FL_KERNEL_COUNT] = {
-    "route_layout_kernel", "dispatch_pack_kernel", "fabric_copy_kernel(dispatch)",
-    "dispatch_unpack_kernel", "combine_pack_kernel", "fabric_copy_kernel(combine)",
-    "combine_reduce_kernel", "dispatch_pack_e4m3_kernel", "fabric_copy_kernel(dispatch, private slots)",
-    "combine_partial_pack_kernel", "arrival_gate_kernel(dispatch)", "arrival_gate_kernel(combine)",
-    "announce_kernel(dispatch)", "announce_kernel(combine)"};
+    "route_layout_kernel", "dispatch_pack_kernel", "dispatch_unpack_kernel", "combine_pack_kernel",
+    "combine_reduce_kernel", "dispatch_pack_e4m3_kernel", "combine_partial_pack_kernel",
+    "arrival_gate_kernel(dispatch)", "arrival_gate_kernel(combine)", "announce_kernel(dispatch)",
+    "announce_kernel(combine)"};
 
 constexpr int kEventPool = 512;
-constexpr long long kMaxFabricBlocks = 1 << 16;   // waves loop cheaply (no barriers)
 constexpr long long kMaxRowBlocks = 1 << 18;      // blocks with barriers: loop only when far oversized
 constexpr long long kDefaultSpin = 1 << 20;       // polls about 2 us apart: gives up after about 2 s
 
@@ -107,13 +104,15 @@ int resolve(const fl_moe_config *c, Dims *D) {
         // wire rows start on 128-byte lines: measured 5-10 % faster pack and unpack than 16-byte packing
         D->Bw = (long long)align_up((size_t)(D->H + 4ll * D->scales_per_row), 128);
     }
-    const long long a1 = D->send_cap * D->Bw, a2 = (long long)D->T * D->K * D->Bc;
+    // bufA receives the combine replies, bufB the dispatched rows.  (bufB keeps room for a whole expert
+    // layout: workspace_bytes is what callers have planned their memory with.)
+    const long long need_a = (long long)D->T * D->K * D->Bc;
     const long long b1 = D->recv_rows * D->Bw, b2 = D->expert_cap * D->Bc;
     // Large payload buffers start on 2 MB boundaries of the workspace, rank by rank (the
     // page size the driver maps big allocations with): measured 3 % faster unpack at the
     // decode shape than 256-byte packing.  Small ones stay packed.
-    const size_t need_a = (size_t)(a1 > a2 ? a1 : a2), need_b = (size_t)(b1 > b2 ? b1 : b2);
-    D->bufA_rank_bytes = (long long)align_up(need_a, need_a >= kBigPage ? kBigPage : 256);
+    const size_t need_b = (size_t)(b1 > b2 ? b1 : b2);
+    D->bufA_rank_bytes = (long long)align_up((size_t)need_a, (size_t)need_a >= kBigPage ? kBigPage : 256);
     D->bufB_rank_bytes = (long long)align_up(need_b, need_b >= kBigPage ? kBigPage : 256);
     // arrival counters count 16-byte units in 32 bits with a wrap-safe comparison
     if ((long long)D->T * (D->Bc / 16) >= (1ll << 31)) return FL_ERR_INVALID_ARG;
@@ -125,9 +124,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->TT = need < tt ? need : tt;
     D->tune_rows = 0;
     D->tune_reduce = 0;
-    D->tune_waves = 0;
     D->tune_slices = 0;
-    D->tune_stream_mb = 2560;
     D->tune_grid_pct = 200;
     D->tune_cap8 = 3;
     D->tune_order = 0;
@@ -174,10 +171,7 @@ size_t carve(const Dims &D, void *base, Tables *W, size_t *total) {
     W->send_row = c.take<int>(N * T * K);
     W->pair_meta = c.take<unsigned>(N * T * K);
     W->comb_pos = c.take<int>(N * T * K);
-    W->send_meta = c.take<unsigned>(N * (size_t)D.send_cap * D.MW);
     W->recv_meta = c.take<unsigned>(N * (size_t)D.recv_rows * D.MW);
-    W->fab_dst_disp = c.take<int2>(N * (size_t)D.send_cap);
-    W->fab_dst_comb = c.take<int2>(N * (size_t)D.expert_cap);
     if ((size_t)D.bufA_rank_bytes >= kBigPage) c.cur = align_up(c.cur, kBigPage);
     W->bufA = c.take<char>(N * (size_t)D.bufA_rank_bytes);
     if ((size_t)D.bufB_rank_bytes >= kBigPage) c.cur = align_up(c.cur, kBigPage);
@@ -187,15 +181,6 @@ size_t carve(const Dims &D, void *base, Tables *W, size_t *total) {
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
-
-// Waves that share one row in the fabric kernel: enough that a lane has at most
-// a handful of 16-byte vectors.
-int waves_per_row(long long row_bytes, int tune_waves) {
-    if (tune_waves >= 1 && tune_waves <= 16) return tune_waves;
-    // about 4 KB per wave: one counter update per wave, and those updates serialise in L2
-    const long long w = (row_bytes + 4095) / 4096;
-    return (int)(w < 1 ? 1 : w > 4 ? 4 : w);
-}
 
 // Blocks that share one token in the pack kernel (each takes a slice of the row).
 int pack_slices(long long row_bytes, int tune_slices) {
@@ -509,7 +494,7 @@ int fl_moe_layout_static(const fl_moe_config *cfg, const int32_t *indices, const
 }
 
 static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *x, const float *weights,
-                               const float *ready_scales, bool streaming, void *stream) {
+                               const float *ready_scales, void *stream) {
     int e = check_ranks(ctx, rb, rc);
     if (e != FL_OK) return e;
     if (!x || !ctx->indices) return FL_ERR_INVALID_ARG;
@@ -520,28 +505,20 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
     hipStream_t st = (hipStream_t)stream;
     const Dims &D = ctx->D;
     const Tables &W = ctx->W;
-    // fenced: every wave reports what it delivered (progressive receivers); in_kernel: the last
-    // payload kernel of the call also advances the counters (stream-ordered callers); otherwise
-    // a kernel of its own does, behind the payload kernels in this (the sender's) stream
-    const bool push = D.flags & FL_FLAG_PEER_PUSH, fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;
-    const bool in_kernel = D.flags & FL_FLAG_STREAM_ORDERED;
+    // fenced: every block reports what it delivered (progressive receivers).  Otherwise the send kernel's
+    // first block advances the counters (stream-ordered callers), or a kernel of its own does, behind
+    // the payload kernels in this (the sender's) stream.
+    const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;
+    const char *xp = (const char *)x;
     if (D.dtype == FL_DTYPE_E4M3_BLOCK128 && !ready_scales) {
         LaunchTimer t(ctx, KID_DISPATCH_PACK_E4M3, st);
-        const char *xp = (const char *)x;
         auto go = [&](auto threads) {
             constexpr int QT = decltype(threads)::value;
             const int per_block = QT / kQuantLanes;              // quantisation blocks per workgroup
             const int slices = (D.scales_per_row + per_block - 1) / per_block;
-            const dim3 grid((unsigned)D.T * slices, rc), block(QT);
-            if (push && fenced)
-                dispatch_pack_e4m3_kernel<true, true, QT><<<grid, block, 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                                  ctx->num_tokens, slices, weights);
-            else if (push)
-                dispatch_pack_e4m3_kernel<true, false, QT><<<grid, block, 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                                   ctx->num_tokens, slices, weights);
-            else
-                dispatch_pack_e4m3_kernel<false, false, QT><<<grid, block, 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                                    ctx->num_tokens, slices, weights);
+            auto kernel = fenced ? dispatch_pack_e4m3_kernel<true, QT> : dispatch_pack_e4m3_kernel<false, QT>;
+            kernel<<<dim3((unsigned)D.T * slices, rc), dim3(QT), 0, st>>>(D, W, rb, xp, ctx->indices,
+                                                                          ctx->num_tokens, slices, weights);
         };
         if (D.scales_per_row > 256 / kQuantLanes) go(std::integral_constant<int, 512>{});
         else go(std::integral_constant<int, 256>{});
@@ -550,79 +527,22 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
         // bf16 rows, or e4m3 codes the caller quantised itself (their scales go along)
         const long long src_row = ready_scales ? D.Be : D.Bx;
         const int slices = pack_slices(src_row, D.tune_slices);
-        const dim3 grid((unsigned)D.T * slices, rc), block(kPackThreads);
-        const char *xp = (const char *)x;
-        if (push && fenced)
-            dispatch_pack_kernel<true, true><<<grid, block, 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                     ctx->num_tokens, slices, weights, src_row, ready_scales);
-        else if (push)
-            dispatch_pack_kernel<true, false><<<grid, block, 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                      ctx->num_tokens, slices, weights, src_row, ready_scales);
-        else
-            dispatch_pack_kernel<false, false><<<grid, block, 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                       ctx->num_tokens, slices, weights, src_row, ready_scales);
+        auto kernel = fenced ? dispatch_pack_kernel<true> : dispatch_pack_kernel<false>;
+        kernel<<<dim3((unsigned)D.T * slices, rc), dim3(kPackThreads), 0, st>>>(
+            D, W, rb, xp, ctx->indices, ctx->num_tokens, slices, weights, src_row, ready_scales);
     }
-    auto announce = [&]() {                   // counter-ordered mode: the transfers are announced once
-        if (fenced || in_kernel || !call.last) return;   // every payload kernel of the call has ended
+    if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {   // once, behind every payload kernel of the call
         LaunchTimer t(ctx, KID_ANNOUNCE_DISPATCH, st);
         announce_kernel<<<dim3(call.rank_count), dim3(kWave), 0, st>>>(D, W, call.rank_begin, W.send_off,
                                                                         W.arrive_disp, (unsigned)(D.Bw / 16));
-    };
-    if (push) {                               // the rows are already in the peers' receive buffers
-        announce();
-        return launch_status();
     }
-    FabricArgs A;
-    A.src_base = W.bufA; A.src_rank_stride = D.bufA_rank_bytes;
-    A.dst_base = W.bufB; A.dst_rank_stride = D.bufB_rank_bytes;
-    A.seg_off = W.send_off; A.row_dst = W.fab_dst_disp; A.row_cap = D.send_cap;
-    A.src_meta = W.send_meta; A.src_meta_rank_stride = D.send_cap * D.MW;
-    A.dst_meta = W.recv_meta; A.dst_meta_rank_stride = D.recv_rows * D.MW;
-    A.dst_row_lo = 0;
-    A.announce = 0;
-    A.order = D.tune_order;
-    A.arrive = W.arrive_disp;
-    A.row_bytes = D.Bw; A.waves_per_row = waves_per_row(D.Bw, D.tune_waves);
-    const int wpb = kCopyThreads / kWave;
-    // a multiple of waves_per_row blocks keeps every row's waves at a fixed stride
-    const unsigned gx = capped_grid((D.send_cap * A.waves_per_row + wpb - 1) / wpb, rc, kMaxFabricBlocks,
-                                     A.waves_per_row);
-    if (D.P > 0) {
-        // First scatter: the rows bound for private slots.  Their targets follow from the
-        // sender's own counts alone, so this launch reads nothing a peer produced.
-        A.announce = D.P >= D.T ? (in_kernel ? 1 : fenced ? 2 : 0) : 0;   // the call's last copy kernel announces
-        LaunchTimer t(ctx, KID_DISPATCH_FABRIC_PRIVATE, st);
-        const unsigned g1 = capped_grid(((long long)D.N * D.P * A.waves_per_row + wpb - 1) / wpb, rc,
-                                        kMaxFabricBlocks, A.waves_per_row);
-        if (fenced)
-            fabric_private_kernel<true, true><<<dim3(g1, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        else if (streaming)
-            fabric_private_kernel<false, true><<<dim3(g1, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        else
-            fabric_private_kernel<false, false><<<dim3(g1, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        A.dst_row_lo = D.N * D.P;             // second scatter: the rest, into the shared range
-    }
-    if (D.P < D.T) {                          // with P = T every row has a private slot
-        A.announce = in_kernel ? 1 : fenced ? 2 : 0;
-        LaunchTimer t(ctx, KID_DISPATCH_FABRIC, st);
-        if (fenced)
-            fabric_copy_kernel<true, 0, true><<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        else if (streaming)
-            fabric_copy_kernel<false, 0, true><<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        else
-            fabric_copy_kernel<false, 0, false><<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-    }
-    announce();
     return launch_status();
 }
 
 static int dispatch_send_impl(fl_moe_ctx *ctx, int rb, int rc, const void *x, const float *weights,
                               const float *ready_scales, void *stream) {
-    if (!ctx) return FL_ERR_INVALID_ARG;
-    // cached or streaming stores in the scatter: decided by what the whole call writes
-    const bool streaming = (long long)rc * ctx->D.send_cap * ctx->D.Bw > ((long long)ctx->D.tune_stream_mb << 20);
     return for_rank_groups(ctx, rb, rc, [&](int r, int n, CallSpan call) {
-        return dispatch_send_range(ctx, r, n, call, x, weights, ready_scales, streaming, stream);
+        return dispatch_send_range(ctx, r, n, call, x, weights, ready_scales, stream);
     });
 }
 
@@ -715,8 +635,7 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
     const Dims &D = ctx->D;
     const Tables &W = ctx->W;
     const int rbk = rows_per_block(D.Bc, D.tune_rows);
-    const bool push = D.flags & FL_FLAG_PEER_PUSH, fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;
-    const bool in_kernel = D.flags & FL_FLAG_STREAM_ORDERED;     // as in dispatch_send_range
+    const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;      // as in dispatch_send_range
     const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
     // rows a rank sends back: one per pair, or with partial sums one per received row
     const long long worst_recv = (long long)D.N * D.T;
@@ -729,52 +648,19 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
         const char *yp = (const char *)expert_y;
         if (partial) {
             LaunchTimer t(ctx, KID_COMBINE_PARTIAL_PACK, st);
-            if (push && fenced) combine_partial_pack_kernel<true, true><<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
-            else if (push) combine_partial_pack_kernel<true, false><<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
-            else combine_partial_pack_kernel<false, false><<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
+            auto kernel = fenced ? combine_partial_pack_kernel<true> : combine_partial_pack_kernel<false>;
+            kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         } else {
             LaunchTimer t(ctx, KID_COMBINE_PACK, st);
-            if (push && fenced) combine_pack_kernel<true, true><<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
-            else if (push) combine_pack_kernel<true, false><<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
-            else combine_pack_kernel<false, false><<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
+            auto kernel = fenced ? combine_pack_kernel<true> : combine_pack_kernel<false>;
+            kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         }
     }
-    auto announce = [&]() {
-        if (fenced || in_kernel || !call.last) return;
+    if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {
         LaunchTimer t(ctx, KID_ANNOUNCE_COMBINE, st);
         announce_kernel<<<dim3(call.rank_count), dim3(kWave), 0, st>>>(
             D, W, call.rank_begin, partial ? W.recv_off : W.cs_off, W.arrive_comb, (unsigned)(D.Bc / 16));
-    };
-    if (push) {                               // the rows are already in the sources' receive buffers
-        announce();
-        return launch_status();
     }
-    FabricArgs A;
-    A.src_base = W.bufB; A.src_rank_stride = D.bufB_rank_bytes;
-    A.dst_base = W.bufA; A.dst_rank_stride = D.bufA_rank_bytes;
-    A.seg_off = partial ? W.recv_off : W.cs_off; A.row_dst = W.fab_dst_comb; A.row_cap = D.expert_cap;
-    A.src_meta = nullptr; A.src_meta_rank_stride = 0;
-    A.dst_meta = nullptr; A.dst_meta_rank_stride = 0;
-    A.dst_row_lo = 0;
-    A.announce = in_kernel ? 1 : fenced ? 2 : 0;
-    A.order = D.tune_order;
-    A.arrive = W.arrive_comb;
-    A.row_bytes = D.Bc; A.waves_per_row = waves_per_row(D.Bc, D.tune_waves);
-    const int wpb = kCopyThreads / kWave;
-    const unsigned gxf = capped_grid((reply_grid * A.waves_per_row + wpb - 1) / wpb, rc,
-                                      kMaxFabricBlocks, A.waves_per_row);
-    {
-        LaunchTimer t(ctx, KID_COMBINE_FABRIC, st);
-        // what the launch can write: every rank gets back at most T*K rows
-        const bool streaming = (long long)D.N * D.T * D.K * D.Bc > ((long long)D.tune_stream_mb << 20);
-        if (fenced)
-            fabric_copy_kernel<true, 1, true><<<dim3(gxf, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        else if (streaming)
-            fabric_copy_kernel<false, 1, true><<<dim3(gxf, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-        else
-            fabric_copy_kernel<false, 1, false><<<dim3(gxf, rc), dim3(kCopyThreads), 0, st>>>(D, W, A, rb);
-    }
-    announce();
     return launch_status();
 }
 
@@ -924,9 +810,8 @@ int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value) {
     switch (knob) {
         case 0: if (value > kMaxRowsPerBlock) return FL_ERR_INVALID_ARG; ctx->D.tune_rows = dflt ? 0 : value; break;
         case 1: if (value > 8) return FL_ERR_INVALID_ARG; ctx->D.tune_reduce = dflt ? 0 : value; break;
-        case 2: ctx->D.tune_waves = dflt ? 0 : value; break;
+        case 2: case 4: break;                 // shaped a copy kernel that is no longer launched: accepted, no effect
         case 3: if (value > 16) return FL_ERR_INVALID_ARG; ctx->D.tune_slices = dflt ? 0 : value; break;
-        case 4: ctx->D.tune_stream_mb = dflt ? 2560 : value; break;
         case 5: if (value > 1000) return FL_ERR_INVALID_ARG; ctx->D.tune_grid_pct = dflt ? 200 : value; break;
         case 6: ctx->launch_mb = dflt ? kLaunchMiB : value; break;
         case 7: if (value > 8 || value == 0) return FL_ERR_INVALID_ARG; ctx->D.tune_cap8 = dflt ? 3 : value; break;

@@ -1,11 +1,18 @@
-// The memory-bound half of the shuffle: pack, fabric copy, unpack, reduce.
+// The memory-bound half of the shuffle: send, unpack, send back, reduce.
 //
-// Paper, section MoE Dispatch/Combine.  Dispatch: input tokens are copied into
-// send buffers, a contiguous source per peer, then scattered; the receiver waits
-// for all transfers and re-orders tokens into the grouped-GEMM layout.  Combine:
-// one scatter per peer re-using the routing information, then a locally computed
-// weighted sum.  Every kernel moves whole rows with 16-byte accesses; nothing
-// here is a contraction, so there is no MFMA.
+// Paper, section MoE Dispatch/Combine.  Dispatch: one copy of every token per
+// destination rank goes to a range of that rank's receive buffer which the exchanged
+// counts reserved; the receiver waits for all transfers and re-orders tokens into the
+// grouped-GEMM layout.  Combine: one scatter per peer re-using the routing information,
+// then a locally computed weighted sum.  Every kernel moves whole rows with 16-byte
+// accesses; nothing here is a contraction, so there is no MFMA.
+//
+// The fabric is the send kernels' own stores.  The paper packs rows into a send buffer,
+// because a NIC wants one contiguous source per peer, and pushes from the send kernel
+// itself where the peer's memory can be stored to (section Dispatch, within a node).
+// Here every receive buffer can, so there is no send buffer: staging the rows cost a write,
+// a read and a kernel in each direction (DeepSeek-V3 decode step, 128 tokens per rank:
+// 761 us with the staging copy, 516 without; 4 tokens per rank: 71 and 57).
 #pragma once
 #include "common.h"
 
@@ -24,13 +31,12 @@ constexpr int kMaxRowsPerBlock = 64;
 //
 // Stream-ordered mode: one add per (sender, receiver) announces the whole
 // transfer, like the single immediate a NIC delivers after a WRITE (section
-// TransferEngine, ImmCounter).  It is issued once per sender inside the kernel of
-// the send call that writes into the receivers' buffers (the scatter kernel, or
-// with PUSH the pack kernel): receivers are ordered after that kernel by the
-// stream, so they find counters and payload complete together, and no extra
-// launch is spent.  (Per-wave announcements, as in progressive mode, cost more than
-// they give here: adds to one counter from many compute dies serialise at about
-// 0.2 us each, which made skewed routing several times slower.)
+// TransferEngine, ImmCounter).  It is issued once per sender inside the send kernel:
+// receivers are ordered after that kernel by the stream, so they find counters and
+// payload complete together, and no extra launch is spent.  (Per-block announcements, as
+// in progressive mode, cost more than they give here: adds to one counter from many
+// compute dies serialise at about 0.2 us each, which made skewed routing several times
+// slower.)
 // off = the sender's row of the segment table ([N + 1] row offsets by receiver);
 // threads first, first + step, ... each take one receiver.  only_the_ones: the
 // payload units are reported by the waves that deliver them (progressive mode).
@@ -42,29 +48,36 @@ __device__ inline void announce_transfers(const int *off, unsigned *arrive, unsi
     }
 }
 
+// Test switch (knob 8): the order in which a send kernel takes its `n` units of work.  Nothing may
+// depend on it: 0 = ascending, 1 = descending, 2 = starting in the middle and wrapping round.
+__device__ inline int in_order(int order, int i, int n) {
+    if (order == 1) return n - 1 - i;
+    if (order == 2) return i + n / 2 < n ? i + n / 2 : i + n / 2 - n;
+    return i;
+}
+
 // ------------------------------------------------------------------ dispatch: pack
 // `slices` blocks per token (s, t), each taking a slice of the row (so a thread
-// usually has a single vector): the slice is read once and written once per
-// distinct destination rank, at send_off[s][d] + (rank of t among s's tokens
-// bound for d).  Each copy carries a sidecar of K words naming, for every expert
-// of the token that lives on d, the local expert and the token's rank among s's
-// tokens of that expert; the receiver turns that into an expert-major row.
+// usually has a single vector): the slice is read once and stored once per
+// distinct destination rank d, into the row of d's receive buffer that follows from
+// (rank of t among s's tokens bound for d).  Each copy carries a sidecar of K words
+// naming, for every expert of the token that lives on d, the local expert and the
+// token's rank among s's tokens of that expert; the receiver turns that into an
+// expert-major row.
 //
-// PUSH (every peer's receive buffer can be stored to, section Dispatch: within a
-// node payloads are pushed from the send kernel): the copies and their sidecars
-// go straight into the destinations' receive buffers; no send buffer is filled
-// and no scatter follows.  FENCED (progressive mode, PUSH only): device-scope
-// stores, and the block adds the 16-byte units it wrote to
-// arrive[destination][source] itself once they are acknowledged; stream-ordered
-// with PUSH, the sender's first block announces the whole transfers.
-template <bool PUSH, bool FENCED>
+// FENCED (progressive mode): device-scope stores, and the block adds the 16-byte
+// units it wrote to arrive[destination][source] itself once they are acknowledged;
+// stream-ordered, the sender's first block announces the whole transfers; otherwise
+// the announce kernel does.
+template <bool FENCED>
 __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ x,
     const int *__restrict__ indices, const int *__restrict__ num_tokens, int slices,
     const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */,
     long long src_row_bytes /* bytes of one row of x: 2*H, or H for ready-made e4m3 codes */,
     const float *__restrict__ src_scales /* [N][T][H/128] with ready-made codes, else null */) {
-    const int s = rank_begin + blockIdx.y, t = blockIdx.x / slices, slice = blockIdx.x % slices;
+    const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
+    const int t = in_order(D.tune_order, blockIdx.x / slices, D.T);
     const int tid = threadIdx.x;
     const int K = D.K, El = D.El;
     // The slice's payload depends on nothing but (s, t): its loads are issued first, so
@@ -79,9 +92,9 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     for (int i = 0; i < 4; ++i)
         if (v0 + tid + i * kPackThreads < v1) r[i] = ld_stream(src + v0 + tid + i * kPackThreads);
     const int plan_ok = W.plan_ok[s];
-    // with PUSH no scatter kernel follows: the sender's first block announces the transfers (a
-    // sender without tokens still announces its empty ones), unless an announce kernel will
-    if (PUSH && (FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)
+    // the sender's first block announces the transfers (a sender without tokens still announces
+    // its empty ones), unless an announce kernel will
+    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,
                            tid, kPackThreads, FENCED);
     if (!plan_ok || t >= num_tokens[s]) return;
@@ -98,24 +111,21 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
         if (my_row >= 0)                       // this copy's row in d's receive buffer
             target = recv_buffer_row(D.N, D.P, s, my_row - W.send_off[(size_t)s * (D.N + 1) + my_d],
                                      W.dst_off[(size_t)s * D.N + my_d]);
-        s_row[tid] = (PUSH && my_row >= 0) ? target : my_row;
+        s_row[tid] = my_row >= 0 ? target : -1;
     }
     __syncthreads();
-    if (slice == 0 && tid < K && my_row >= 0) {   // sidecar and fabric target of this copy
-        unsigned *meta = PUSH ? W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW
-                              : W.send_meta + ((size_t)s * D.send_cap + my_row) * D.MW;
+    if (slice == 0 && tid < K && my_row >= 0) {   // sidecar of this copy
+        unsigned *meta = W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW;
         int m = 0;
         for (int k = 0; k < K; ++k)
             if (s_dst[k] == my_d) {
-                st_word<PUSH && FENCED>((int *)meta + m, (int)s_meta[k]);
+                st_word<FENCED>((int *)meta + m, (int)s_meta[k]);
                 if (D.MW > D.KM)   // the weight of that expert, for the expert rank's partial sum
-                    st_word<PUSH && FENCED>((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
+                    st_word<FENCED>((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
                 ++m;
             }
-        for (; m < D.KM; ++m) st_word<PUSH && FENCED>((int *)meta + m, (int)kNoEntry);
-        if (!PUSH) W.fab_dst_disp[(size_t)s * D.send_cap + my_row] = make_int2(my_d, target);
+        for (; m < D.KM; ++m) st_word<FENCED>((int *)meta + m, (int)kNoEntry);
     }
-    char *sendbuf = W.bufA + (size_t)s * D.bufA_rank_bytes;
     for (int b = v0 + tid; b < v1; b += 4 * kPackThreads) {
         if (b != v0 + tid) {                   // later batches (rows beyond 8 KB per slice)
 #pragma unroll
@@ -125,12 +135,12 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
         for (int k = 0; k < K; ++k) {
             const int row = s_row[k];          // uniform: one copy per distinct destination
             if (row < 0) continue;
-            char *base = PUSH ? W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes : sendbuf;
+            char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
             v4u *dst = (v4u *)(base + (size_t)row * D.Bw);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (b + i * kPackThreads < v1)
-                    st_payload<PUSH && FENCED, true>(dst + b + i * kPackThreads, r[i]);
+                    st_payload<FENCED>(dst + b + i * kPackThreads, r[i]);
         }
     }
     // Ready-made e4m3 codes (section Kernel Microbenchmarks: the dispatched token is 7168
@@ -144,8 +154,8 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                 for (int k = 0; k < K; ++k) {
                     const int row = s_row[k];
                     if (row < 0) continue;
-                    char *base = PUSH ? W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes : sendbuf;
-                    st_payload<PUSH && FENCED, true>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
+                    st_payload<FENCED>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
                 }
             }
         } else {
@@ -154,13 +164,13 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                 for (int k = 0; k < K; ++k) {
                     const int row = s_row[k];
                     if (row < 0) continue;
-                    char *base = PUSH ? W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes : sendbuf;
-                    st_word<PUSH && FENCED>((int *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
+                    st_word<FENCED>((int *)(base + (size_t)row * D.Bw + D.Be) + v, val);
                 }
             }
         }
     }
-    if (PUSH && FENCED) {                      // what this block delivered, per destination
+    if (FENCED) {                      // what this block delivered, per destination
         stores_done<FENCED>();
         __syncthreads();
         const unsigned units = (unsigned)(v1 - v0) + (with_scales ? (unsigned)((D.Bw - D.Be) / 16) : 0u);
@@ -215,13 +225,14 @@ constexpr int kQuantLanes = 8;     // lanes per 128-element block: 16 bf16 value
 // workgroups of 256; more blocks per lane group measured no gain); every lane loads
 // 32 bytes, takes part in an 8-lane max, and stores 16 bytes of e4m3 per destination
 // copy; the scales go out as 16-byte vectors from LDS.
-template <bool PUSH, bool FENCED, int QT>   // PUSH, FENCED as in dispatch_pack_kernel
+template <bool FENCED, int QT>   // FENCED as in dispatch_pack_kernel
 __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ x,
     const int *__restrict__ indices, const int *__restrict__ num_tokens, int slices,
     const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */) {
     constexpr int kQuantThreads = QT;
-    const int s = rank_begin + blockIdx.y, t = blockIdx.x / slices, slice = blockIdx.x % slices;
+    const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
+    const int t = in_order(D.tune_order, blockIdx.x / slices, D.T);
     const int tid = threadIdx.x;
     const int K = D.K, El = D.El;
     // as in dispatch_pack_kernel, the payload loads go first
@@ -236,7 +247,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         in1 = ld_stream(src + 1);
     }
     const int plan_ok = W.plan_ok[s];
-    if (PUSH && (FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)   // as in dispatch_pack_kernel
+    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)   // as in dispatch_pack_kernel
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,
                            tid, kQuantThreads, FENCED);
     if (!plan_ok || t >= num_tokens[s]) return;
@@ -253,22 +264,20 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         if (my_row >= 0)
             target = recv_buffer_row(D.N, D.P, s, my_row - W.send_off[(size_t)s * (D.N + 1) + my_d],
                                      W.dst_off[(size_t)s * D.N + my_d]);
-        s_row[tid] = (PUSH && my_row >= 0) ? target : my_row;
+        s_row[tid] = my_row >= 0 ? target : -1;
     }
     __syncthreads();
     if (slice == 0 && tid < K && my_row >= 0) {
-        unsigned *meta = PUSH ? W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW
-                              : W.send_meta + ((size_t)s * D.send_cap + my_row) * D.MW;
+        unsigned *meta = W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW;
         int m = 0;
         for (int k = 0; k < K; ++k)
             if (s_dst[k] == my_d) {
-                st_word<PUSH && FENCED>((int *)meta + m, (int)s_meta[k]);
+                st_word<FENCED>((int *)meta + m, (int)s_meta[k]);
                 if (D.MW > D.KM)   // the weight of that expert, for the expert rank's partial sum
-                    st_word<PUSH && FENCED>((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
+                    st_word<FENCED>((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
                 ++m;
             }
-        for (; m < D.KM; ++m) st_word<PUSH && FENCED>((int *)meta + m, (int)kNoEntry);
-        if (!PUSH) W.fab_dst_disp[(size_t)s * D.send_cap + my_row] = make_int2(my_d, target);
+        for (; m < D.KM; ++m) st_word<FENCED>((int *)meta + m, (int)kNoEntry);
     }
     float f[16];
     const unsigned w[8] = {in0.x, in0.y, in0.z, in0.w, in1.x, in1.y, in1.z, in1.w};
@@ -303,21 +312,20 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     }
     const int blk0 = slice * (kQuantThreads / kQuantLanes);
     const int nsv = (min(nblk - blk0, kQuantThreads / kQuantLanes)) / 4;   // scale vectors of this block
-    char *sendbuf = W.bufA + (size_t)s * D.bufA_rank_bytes;
     for (int k = 0; k < K; ++k) {
         const int row = s_row[k];
         if (row < 0) continue;
-        char *dst = (PUSH ? W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes : sendbuf) + (size_t)row * D.Bw;
-        if (live) st_payload<PUSH && FENCED, true>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
+        char *dst = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes + (size_t)row * D.Bw;
+        if (live) st_payload<FENCED>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
         if (scale_vectors) {
             if (tid < nsv)
-                st_payload<PUSH && FENCED, true>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
+                st_payload<FENCED>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
                                                  ((const v4u *)s_scale)[tid]);
         } else if (live && sub == 0) {
-            st_word<PUSH && FENCED>((int *)(dst + D.Be) + blk, __float_as_int(scale));
+            st_word<FENCED>((int *)(dst + D.Be) + blk, __float_as_int(scale));
         }
     }
-    if (PUSH && FENCED) {
+    if (FENCED) {
         // Units of the row this block wrote: 8 per quantisation block of codes, and the
         // 16-byte units its scales fall into (blocks start on multiples of 32 scales, so
         // no unit is shared between blocks; the row's last unit may be part padding).
@@ -331,138 +339,6 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
             add_counter(W.arrive_disp + (size_t)my_d * D.N + s,
                         (unsigned)(n_live * 8 + (n_live + 3) / 4 + (slice == 0 ? pad_units : 0)));
     }
-}
-
-// ------------------------------------------------------------------ fabric copy
-// The stand-in for the NIC scatter: every row of a source's send buffer is
-// copied into the row of the destination's receive buffer that the exchanged
-// counts reserved for it (the target of each row was recorded when the row was
-// packed, so a wave needs one small load before its payload loads; a version
-// that searched the offset tables per wave measured 25 % slower).  Waves work on
-// their own: a row is shared by `waves_per_row` waves, each copies its slice
-// with four loads in flight.  No barrier, no shared memory, no ticket.  In
-// progressive mode (FENCED) a wave then adds the number of 16-byte units it
-// delivered to arrive[destination][source] with an atomic whose result nobody
-// waits for: the counters only ever say "this much of source s's payload has
-// landed", in whatever order waves finish.  Otherwise nobody may look before the
-// kernel has ended: the whole transfers are announced by the announce kernel
-// behind it (default) or, for stream-ordered callers, by one wave per sender
-// inside it (announce_transfers).
-struct FabricArgs {
-    const char *src_base; long long src_rank_stride;
-    char *dst_base;       long long dst_rank_stride;
-    const int *seg_off;   // [N][N+1] segment starts in the source buffer; [N] = rows in use
-    const int2 *row_dst;  // [N][row_cap] (destination rank, row in its buffer) of every source row
-    long long row_cap;
-    const unsigned *src_meta; long long src_meta_rank_stride;   // in words; may be null
-    unsigned *dst_meta;       long long dst_meta_rank_stride;
-    unsigned *arrive;     // [N dst][N src]
-    long long row_bytes;
-    int waves_per_row;    // 1..16
-    int dst_row_lo;       // rows whose target row is below this belong to the private-slot scatter
-    int announce;         // this launch also advances arrive[.][s] (announce_transfers): 1 = by the whole
-                          // transfers (stream-ordered mode), 2 = by the ones only (progressive mode, where
-                          // the waves report the payload they deliver)
-    int order;            // test switch: order in which a sender's rows (sorted by destination) are
-                          // taken: 0 = as stored, 1 = last destination first, 2 = starting with the
-                          // sender's right-hand neighbour and wrapping round
-};
-
-// One wave's share of one row: slice `sub` of `G` (vectors v with (v / 64) % G ==
-// sub), the sidecar when it is slice 0, and in progressive mode the count of
-// 16-byte units it delivered, added to arrive[destination][source].
-template <bool FENCED, bool STREAMING>
-__device__ inline void fabric_send_row(const Dims &D, const FabricArgs &A, int s, int src_row,
-                                       int dst_rank, int dst_row, int sub, int lane) {
-    const int G = A.waves_per_row, N = D.N;
-    const int nvec = (int)(A.row_bytes / 16);
-    const int step = G * kWave;
-    const v4u *src =
-        (const v4u *)(A.src_base + (size_t)s * A.src_rank_stride + (size_t)src_row * A.row_bytes);
-    v4u *dst = (v4u *)(A.dst_base + (size_t)dst_rank * A.dst_rank_stride + (size_t)dst_row * A.row_bytes);
-    for (int b = sub * kWave + lane; b < nvec; b += 4 * step) {
-        v4u v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (b + j * step < nvec) v[j] = ld_stream(src + b + j * step);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (b + j * step < nvec) st_payload<FENCED, STREAMING>(dst + b + j * step, v[j]);
-    }
-    if (A.src_meta && sub == 0) {          // the sidecar travels with the row
-        const int mv = D.MW / 4;
-        const v4u *ms =
-            (const v4u *)(A.src_meta + (size_t)s * A.src_meta_rank_stride) + (size_t)src_row * mv;
-        v4u *md = (v4u *)(A.dst_meta + (size_t)dst_rank * A.dst_meta_rank_stride) + (size_t)dst_row * mv;
-        if (lane < mv) st_payload<FENCED, STREAMING>(md + lane, ms[lane]);
-    }
-    if (FENCED) {          // stream-ordered launches announce whole transfers instead (announce_transfers)
-        const int full = nvec / step, rem = nvec - full * step;
-        const int mine = full * kWave + min(max(rem - sub * kWave, 0), kWave);
-        stores_done<FENCED>();
-        if (lane == 0 && mine > 0) add_counter(A.arrive + (size_t)dst_rank * N + s, (unsigned)mine);
-    }
-}
-
-template <bool FENCED, int PHASE, bool STREAMING>   // PHASE only names the launch: 0 dispatch, 1 combine
-__global__ __launch_bounds__(kCopyThreads) void fabric_copy_kernel(Dims D, Tables W,
-                                                                   FabricArgs A, int rank_begin) {
-    const int s = rank_begin + blockIdx.y, N = D.N;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = blockIdx.x * (kCopyThreads / kWave) + threadIdx.x / kWave;   // within rank s
-    const int G = A.waves_per_row;
-    const int sub = wave % G;
-    const int row_stride = (int)(gridDim.x * (kCopyThreads / kWave)) / G;   // grid is a multiple of G waves
-    const int ok = W.plan_ok[s];
-    const int total = ok ? A.seg_off[(size_t)s * (N + 1) + N] : 0;   // step skipped: nothing sent
-    // The first row's target is fetched together with the two loads above; capacities
-    // are upper bounds, so the grid may be smaller than the rows in use and a wave loops.
-    int i = wave / G;
-    if (A.order == 0) {
-        int2 t = make_int2(0, 0);
-        if (i < A.row_cap) t = A.row_dst[(size_t)s * A.row_cap + i];
-        while (i < total) {
-            if (t.y >= A.dst_row_lo)       // rows below went out with the private-slot scatter
-                fabric_send_row<FENCED, STREAMING>(D, A, s, i, t.x, t.y, sub, lane);
-            i += row_stride;
-            if (i < total) t = A.row_dst[(size_t)s * A.row_cap + i];
-        }
-    } else {                               // the same rows, visited in another order of destinations
-        const int shift = A.order == 2 ? A.seg_off[(size_t)s * (N + 1) + (s + 1) % N] : 0;
-        for (; i < total; i += row_stride) {
-            const int row = A.order == 1 ? total - 1 - i : (i + shift) % total;
-            const int2 t = A.row_dst[(size_t)s * A.row_cap + row];
-            if (t.y >= A.dst_row_lo) fabric_send_row<FENCED, STREAMING>(D, A, s, row, t.x, t.y, sub, lane);
-        }
-    }
-    if (A.announce && wave == 0 && ok)
-        announce_transfers(A.seg_off + (size_t)s * (N + 1), A.arrive, (unsigned)(A.row_bytes / 16), s, N, lane, kWave,
-                           A.announce == 2);
-}
-
-// First scatter of a dispatch with private slots (section Dispatch: tokens up to
-// a fixed limit go to private buffers on every peer before the routes are
-// known).  Slot q = d * P + i of source s stands for the i-th row s sends to d;
-// it exists when i < M[s][d], a number s counted itself, and lands in row
-// s * P + i of d's receive buffer.  Nothing here was derived from a peer's counts.
-template <bool FENCED, bool STREAMING>
-__global__ __launch_bounds__(kCopyThreads) void fabric_private_kernel(Dims D, Tables W,
-                                                                      FabricArgs A, int rank_begin) {
-    const int s = rank_begin + blockIdx.y, N = D.N, P = D.P;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = blockIdx.x * (kCopyThreads / kWave) + threadIdx.x / kWave;
-    const int G = A.waves_per_row;
-    const int sub = wave % G;
-    const int slot_stride = (int)(gridDim.x * (kCopyThreads / kWave)) / G;
-    if (!W.plan_ok[s]) return;
-    for (int q = wave / G; q < N * P; q += slot_stride) {
-        const int d = q / P, i = q - d * P;
-        const int lo = A.seg_off[(size_t)s * (N + 1) + d], hi = A.seg_off[(size_t)s * (N + 1) + d + 1];
-        if (i < hi - lo) fabric_send_row<FENCED, STREAMING>(D, A, s, lo + i, d, s * P + i, sub, lane);
-    }
-    if (A.announce && wave == 0)
-        announce_transfers(A.seg_off + (size_t)s * (N + 1), A.arrive, (unsigned)(A.row_bytes / 16), s, N, lane, kWave,
-                           A.announce == 2);
 }
 
 // ------------------------------------------------------------------ announce
@@ -722,25 +598,22 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_kernel(
 }
 
 // ------------------------------------------------------------------ combine: pack
-// Rank d gathers, for every source s, the rows of its experts that belong to s
-// (contiguous per expert in the grouped layout) into one contiguous reply:
-// combine-send row q of source s and local expert j comes from expert-major row
-// base_x[d][j][s] + (q - cs_base[d][s][j]).
-//
-// PUSH: the rows go straight into the sources' combine receive buffers; FENCED as
-// in the dispatch pack kernel (the block adds each row's units to
-// arrive[source][this rank] itself).
-template <bool PUSH, bool FENCED>
+// Rank d sends every source s the rows of its experts that belong to s (contiguous
+// per expert in the grouped layout) as one contiguous reply, into s's combine receive
+// buffer: reply row q of source s and local expert j comes from expert-major row
+// base_x[d][j][s] + (q - cs_base[d][s][j]).  FENCED as in the dispatch pack kernel (the
+// block adds each row's units to arrive[source][this rank] itself).
+template <bool FENCED>
 __global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
     __shared__ int off[FL_MAX_RANKS + 1];
     __shared__ int src_row[kMaxRowsPerBlock];
-    __shared__ int2 push_to[kMaxRowsPerBlock];     // PUSH: (source rank, row of its combine receive buffer)
+    __shared__ int2 push_to[kMaxRowsPerBlock];     // (source rank, row of its combine receive buffer)
     if (!W.plan_ok[d]) return;
     const int nvec = (int)(D.Bc / 16);
-    // with PUSH the rank's first block announces the replies (a rank without rows its empty ones)
-    if (PUSH && (FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)
+    // the rank's first block announces the replies (a rank without rows its empty ones)
+    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)
         announce_transfers(W.cs_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads,
                            FENCED);
     // grids are sized from capacities: blocks beyond the rows in use leave at once
@@ -750,38 +623,29 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
     __syncthreads();
     const char *yd = expert_y + (size_t)d * D.expert_cap * D.Bc;
     // capacities are upper bounds, so the grid may be smaller than the rows in use
-    for (int q0 = blockIdx.x * rows_per_block; q0 < total; q0 += gridDim.x * rows_per_block) {
-        const int q1 = min(q0 + rows_per_block, total);
+    const int chunks = (total + rows_per_block - 1) / rows_per_block;
+    for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
+        const int q0 = in_order(D.tune_order, c, chunks) * rows_per_block, q1 = min(q0 + rows_per_block, total);
         if (tid < q1 - q0) {
             const int q = q0 + tid;
             const int s = seg_of(off, N, q);
             int first;                         // first reply row of (source s, local expert j)
             const int j = seg_of_short(W.cs_base + ((size_t)d * N + s) * El, El, q, &first);
             src_row[tid] = W.base_x[((size_t)d * El + j) * N + s] + (q - first);
-            const int2 to = make_int2(s, W.comb_dst_off[(size_t)d * N + s] + (q - off[s]));
-            if (PUSH) push_to[tid] = to;
-            else W.fab_dst_comb[(size_t)d * D.expert_cap + q] = to;
+            push_to[tid] = make_int2(s, W.comb_dst_off[(size_t)d * N + s] + (q - off[s]));
         }
         __syncthreads();
-        if (PUSH) {
-            copy_rows_flat<kCopyThreads, FENCED>(
-                q1 - q0, nvec, tid,
-                [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
-                [&](int r) {
-                    return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Bc;
-                });
-            if (FENCED) {
-                stores_done<FENCED>();
-                __syncthreads();
-                if (tid < q1 - q0)
-                    add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
-            }
-        } else {
-            char *out = W.bufB + (size_t)d * D.bufB_rank_bytes + (size_t)q0 * D.Bc;
-            copy_rows_flat<kCopyThreads>(
-                q1 - q0, nvec, tid,
-                [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
-                [&](int r) { return out + (size_t)r * D.Bc; });
+        copy_rows_flat<kCopyThreads, FENCED>(
+            q1 - q0, nvec, tid,
+            [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
+            [&](int r) {
+                return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Bc;
+            });
+        if (FENCED) {
+            stores_done<FENCED>();
+            __syncthreads();
+            if (tid < q1 - q0)
+                add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
         }
         __syncthreads();                       // the row plan is rewritten by the next chunk
     }
@@ -802,9 +666,9 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // multiply-add chain, in the order of the row's sidecar (ascending k), of
 // weight * expert output over the token's experts on d, rounded to bf16.  The
 // share of received row number i from source s goes back to row
-// ret_off[d][s] + i of s's buffer, the row of s's send buffer the token copy
-// left from, so s finds it through its own send_row table.
-template <bool PUSH, bool FENCED>
+// ret_off[d][s] + i of s's combine receive buffer, the position of the token copy among
+// all copies s sent, so s finds it through its own send_row table.
+template <bool FENCED>
 __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
@@ -815,7 +679,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
     __shared__ int2 share_to[kMaxRowsPerBlock];
     if (!W.plan_ok[d]) return;
     const int nvec = (int)(D.Bc / 16);
-    if (PUSH && (FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)   // as in combine_pack_kernel
+    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)   // as in combine_pack_kernel
         announce_transfers(W.recv_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads,
                            FENCED);
     const int total = W.recv_off[(size_t)d * (N + 1) + N];
@@ -823,8 +687,9 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
     if (tid <= N) off[tid] = W.recv_off[(size_t)d * (N + 1) + tid];
     __syncthreads();
     const char *yd = expert_y + (size_t)d * D.expert_cap * D.Bc;
-    for (int r0 = blockIdx.x * rows_per_block; r0 < total; r0 += gridDim.x * rows_per_block) {
-        const int r1 = min(r0 + rows_per_block, total);
+    const int chunks = (total + rows_per_block - 1) / rows_per_block;
+    for (int c = blockIdx.x; c < chunks; c += gridDim.x) {
+        const int r0 = in_order(D.tune_order, c, chunks) * rows_per_block, r1 = min(r0 + rows_per_block, total);
         if (tid < r1 - r0) {
             const int r = r0 + tid;
             const int s = seg_of(off, N, r);
@@ -840,9 +705,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
                 ++n;
             }
             src_cnt[tid] = n;
-            const int2 to = make_int2(s, W.ret_off[(size_t)d * N + s] + i);
-            share_to[tid] = to;
-            if (!PUSH) W.fab_dst_comb[(size_t)d * D.expert_cap + r] = to;
+            share_to[tid] = make_int2(s, W.ret_off[(size_t)d * N + s] + i);
         }
         __syncthreads();
         const int chunk = (r1 - r0) * nvec;
@@ -873,13 +736,11 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
                 v4u o;
                 o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
                 o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
-                char *dst = PUSH ? W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes +
-                                       (size_t)share_to[row[u]].y * D.Bc
-                                 : W.bufB + (size_t)d * D.bufB_rank_bytes + (size_t)(r0 + row[u]) * D.Bc;
-                st_payload<PUSH && FENCED, true>((v4u *)dst + col[u], o);
+                char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Bc;
+                st_payload<FENCED>((v4u *)dst + col[u], o);
             }
         }
-        if (PUSH && FENCED) {
+        if (FENCED) {
             stores_done<FENCED>();
             __syncthreads();
             if (tid < r1 - r0)

@@ -23,7 +23,7 @@ FL_FLAG_STREAM_ORDERED = 2
 FL_FLAG_PEER_PUSH = 4
 FL_FLAG_PARTIAL_SUMS = 8
 FL_FLAG_PROGRESSIVE_RECV = 16
-FL_KERNEL_COUNT = 14
+FL_KERNEL_COUNT = 11
 
 
 class fl_moe_config(C.Structure):

@@ -112,7 +112,7 @@ def run_step_two_streams(sh: flmoe.MoEShuffle, dev, identity=False, send_order=N
     with stream_ordered=True).  Receive calls are enqueued on stream A right after the
     layout, send calls on stream B: the receivers' gate kernels (or, with
     progressive_recv, the receive kernels themselves) poll the arrival counters while
-    the fabric copy is still running or has not started.  Events order only what the
+    the send kernels are still running or have not started.  Events order only what the
     re-use of the two staging buffers needs.  send_order: list of (rank_begin,
     rank_count) launches for the send calls, default one launch for all ranks."""
     N = sh.N
@@ -135,7 +135,7 @@ def run_step_two_streams(sh: flmoe.MoEShuffle, dev, identity=False, send_order=N
         unpacked = torch.cuda.Event()
         unpacked.record(a)
     with torch.cuda.stream(b):
-        b.wait_event(unpacked)                   # the receive buffer becomes the combine send buffer
+        b.wait_event(unpacked)                   # no reply before this step's rows are out of the receive buffer
         for rg in reversed(order):
             sh.combine_send(y, rg)
     with torch.cuda.stream(a):

@@ -201,12 +201,12 @@ def timeline(trace_csv, bench_log, out_md, title, command, foreign=False):
     early = late = 0
     for st in steps:
         waiter = span(st, lambda n: "arrival_gate" in n or "dispatch_unpack_kernel<true" in n)
-        sender = span(st, lambda n: "fabric_copy_kernel" in n and ", 0," in n)
+        sender = span(st, lambda n: "dispatch_pack" in n)
         if waiter and sender:
             early += waiter[0] < sender[0]
             late += waiter[1] > sender[0]
     out.append(f"\nIn {early} of {len(steps)} traced steps the first waiting receive-side kernel of the dispatch "
-               f"(gate kernel, or the polling unpack kernel) started before the dispatch fabric kernel did, and in "
+               f"(gate kernel, or the polling unpack kernel) started before the dispatch send kernel did, and in "
                f"{late} it was still running when that kernel started: the receivers were waiting on the counters, "
                "not on stream order.")
     j = _json_line(bench_log)
