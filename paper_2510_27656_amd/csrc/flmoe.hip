@@ -39,6 +39,7 @@ constexpr long long kMaxRowBlocks = 1 << 18;      // blocks with barriers: loop 
 constexpr long long kDefaultSpin = 1 << 20;       // polls about 2 us apart: gives up after about 2 s
 
 constexpr size_t kBigPage = 2u << 20;
+constexpr int kCachedReplyMiB = 1024;
 constexpr int kLaunchMiB = 860;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -125,6 +126,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->tune_rows = 0;
     D->tune_reduce = 0;
     D->tune_slices = 0;
+    D->tune_cached_mb = kCachedReplyMiB;
     D->tune_grid_pct = 200;
     D->tune_cap8 = 3;
     D->tune_order = 0;
@@ -626,7 +628,8 @@ int fl_moe_dispatch_recv(fl_moe_ctx *ctx, int rb, int rc, void *expert_x, float 
     });
 }
 
-static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *expert_y, void *stream) {
+static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *expert_y, bool cached,
+                              void *stream) {
     int e = check_ranks(ctx, rb, rc);
     if (e != FL_OK) return e;
     if (!expert_y) return FL_ERR_INVALID_ARG;
@@ -648,11 +651,13 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
         const char *yp = (const char *)expert_y;
         if (partial) {
             LaunchTimer t(ctx, KID_COMBINE_PARTIAL_PACK, st);
-            auto kernel = fenced ? combine_partial_pack_kernel<true> : combine_partial_pack_kernel<false>;
+            auto kernel = fenced ? combine_partial_pack_kernel<true, true>
+                          : cached ? combine_partial_pack_kernel<false, true> : combine_partial_pack_kernel<false, false>;
             kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         } else {
             LaunchTimer t(ctx, KID_COMBINE_PACK, st);
-            auto kernel = fenced ? combine_pack_kernel<true> : combine_pack_kernel<false>;
+            auto kernel = fenced ? combine_pack_kernel<true, true>
+                          : cached ? combine_pack_kernel<false, true> : combine_pack_kernel<false, false>;
             kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         }
     }
@@ -665,8 +670,11 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
 }
 
 int fl_moe_combine_send(fl_moe_ctx *ctx, int rb, int rc, const void *expert_y, void *stream) {
+    if (!ctx) return FL_ERR_INVALID_ARG;
+    // replies in cached stores up to this much in the whole call (st_payload has both sides' figures)
+    const bool cached = (long long)rc * ctx->D.T * ctx->D.K * ctx->D.Bc <= ((long long)ctx->D.tune_cached_mb << 20);
     return for_rank_groups(ctx, rb, rc, [&](int r, int n, CallSpan call) {
-        return combine_send_range(ctx, r, n, call, expert_y, stream);
+        return combine_send_range(ctx, r, n, call, expert_y, cached, stream);
     });
 }
 
@@ -810,8 +818,9 @@ int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value) {
     switch (knob) {
         case 0: if (value > kMaxRowsPerBlock) return FL_ERR_INVALID_ARG; ctx->D.tune_rows = dflt ? 0 : value; break;
         case 1: if (value > 8) return FL_ERR_INVALID_ARG; ctx->D.tune_reduce = dflt ? 0 : value; break;
-        case 2: case 4: break;                 // shaped a copy kernel that is no longer launched: accepted, no effect
+        case 2: break;                         // shaped a copy kernel that is no longer launched: accepted, no effect
         case 3: if (value > 16) return FL_ERR_INVALID_ARG; ctx->D.tune_slices = dflt ? 0 : value; break;
+        case 4: ctx->D.tune_cached_mb = dflt ? kCachedReplyMiB : value; break;
         case 5: if (value > 1000) return FL_ERR_INVALID_ARG; ctx->D.tune_grid_pct = dflt ? 200 : value; break;
         case 6: ctx->launch_mb = dflt ? kLaunchMiB : value; break;
         case 7: if (value > 8 || value == 0) return FL_ERR_INVALID_ARG; ctx->D.tune_cap8 = dflt ? 3 : value; break;

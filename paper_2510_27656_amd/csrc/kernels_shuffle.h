@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (b + i * kPackThreads < v1)
-                    st_payload<FENCED>(dst + b + i * kPackThreads, r[i]);
+                    st_payload<FENCED, true>(dst + b + i * kPackThreads, r[i]);
         }
     }
     // Ready-made e4m3 codes (section Kernel Microbenchmarks: the dispatched token is 7168
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                     const int row = s_row[k];
                     if (row < 0) continue;
                     char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
-                    st_payload<FENCED>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    st_payload<FENCED, true>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
                 }
             }
         } else {
@@ -316,10 +316,10 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         const int row = s_row[k];
         if (row < 0) continue;
         char *dst = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes + (size_t)row * D.Bw;
-        if (live) st_payload<FENCED>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
+        if (live) st_payload<FENCED, true>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
         if (scale_vectors) {
             if (tid < nsv)
-                st_payload<FENCED>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
+                st_payload<FENCED, true>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
                                                  ((const v4u *)s_scale)[tid]);
         } else if (live && sub == 0) {
             st_word<FENCED>((int *)(dst + D.Be) + blk, __float_as_int(scale));
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_kernel(
 // buffer: reply row q of source s and local expert j comes from expert-major row
 // base_x[d][j][s] + (q - cs_base[d][s][j]).  FENCED as in the dispatch pack kernel (the
 // block adds each row's units to arrive[source][this rank] itself).
-template <bool FENCED>
+template <bool FENCED, bool CACHED>   // CACHED: see st_payload
 __global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
             push_to[tid] = make_int2(s, W.comb_dst_off[(size_t)d * N + s] + (q - off[s]));
         }
         __syncthreads();
-        copy_rows_flat<kCopyThreads, FENCED>(
+        copy_rows_flat<kCopyThreads, FENCED, CACHED>(
             q1 - q0, nvec, tid,
             [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
             [&](int r) {
@@ -668,7 +668,7 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // share of received row number i from source s goes back to row
 // ret_off[d][s] + i of s's combine receive buffer, the position of the token copy among
 // all copies s sent, so s finds it through its own send_row table.
-template <bool FENCED>
+template <bool FENCED, bool CACHED>   // CACHED: see st_payload
 __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
@@ -737,7 +737,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
                 o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
                 o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
                 char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Bc;
-                st_payload<FENCED>((v4u *)dst + col[u], o);
+                st_payload<FENCED, CACHED>((v4u *)dst + col[u], o);
             }
         }
         if (FENCED) {

@@ -45,7 +45,7 @@ def check_tables(sh, ref, N):
 
 def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_split=False,
                     ordering="counters", private_rows=0, push=False, partial=False, launch_mb=None,
-                    capacities=None):
+                    capacities=None, cached_mb=None):
     """ordering: "counters" = the default mode (the arrival counters are the only ordering:
     announce and gate kernels), "stream" = FL_FLAG_STREAM_ORDERED, "progressive" =
     FL_FLAG_PROGRESSIVE_RECV."""
@@ -63,6 +63,8 @@ def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_sp
     try:
         if launch_mb is not None:        # payload per launch above which a call is cut into rank groups
             flmoe.fl_moe_debug_tune(sh.ctx, 6, launch_mb)
+        if cached_mb is not None:        # replies per call above which they are stored past the caches
+            flmoe.fl_moe_debug_tune(sh.ctx, 4, cached_mb)
         if wl.dispatch_dtype == "bf16":
             sh.expert_x.view(torch.int16).fill_(POISON)
         sh.out.view(torch.int16).fill_(POISON)
@@ -170,6 +172,14 @@ def test_parity_in_the_other_ordering_modes(name, form):
     kernels that poll themselves (FL_FLAG_PROGRESSIVE_RECV)."""
     inp = wlmod.make_inputs(CASES[name]())
     sh, _, _ = run_and_compare(inp, ordering=form)
+    sh.close()
+
+
+@pytest.mark.parametrize("partial", [False, True])
+@pytest.mark.parametrize("name", ["ragged_520", "multi_tile"])
+def test_replies_past_the_caches(name, partial):
+    """Calls that write more than a GiB of replies use streaming stores; here every call does."""
+    sh, _, _ = run_and_compare(wlmod.make_inputs(CASES[name]()), partial=partial, cached_mb=0)
     sh.close()
 
 
