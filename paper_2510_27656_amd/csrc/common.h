@@ -14,7 +14,7 @@ struct Dims {
     int N, E, El, T, K, H;
     int dtype, align, flags;
     int TT;               // tokens per LDS tile of the counting blocks (multiple of 32)
-    int route_len;        // ints one rank pushes to every peer: C[E] | M[N] | comb_off[N] | valid
+    int route_len;        // ints of one route record (route_record_words)
     int scales_per_row;   // 0 or H/128
     long long recv_cap, expert_cap, send_cap;   // rows per rank
     int P;                // private rows per (source, destination) at the head of a receive buffer
@@ -164,33 +164,35 @@ __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *e
 }
 
 // ---------------------------------------------------------------- scans / search
+// Inclusive scan over the wave, all 64 lanes active: within rows of 16 lanes by shifts, then the
+// last lane of each row (of each half) carried into the next.  Six data-parallel adds; through
+// LDS permutes the same scan takes some ten times as long.
 __device__ inline int wave_incl_scan(int v) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        int n = __shfl_up(v, o);
-        if (lane >= o) v += n;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);    // row_shr:1, lanes without a source add 0
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);    // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);    // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);    // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);    // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);    // row_bcast:31 into rows 2 and 3
     return v;
 }
 
-// Exclusive scan over the block (one value per thread, blockDim <= 1024).
-// tmp: LDS int[17].  *total receives the block sum.  Contains barriers.
-__device__ inline int block_excl_scan(int v, int *tmp, int *total) {
+// Exclusive scan over the block (one value per thread, blockDim <= 1024); only the first
+// `waves` waves hold values other than zero.  tmp: LDS int[17].  *total receives the block
+// sum.  Contains two barriers.
+__device__ inline int block_excl_scan(int v, int *tmp, int *total, int waves) {
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    const int nw = (blockDim.x + kWave - 1) / kWave;
-    int inc = wave_incl_scan(v);
+    const int inc = wid < waves ? wave_incl_scan(v) : 0;
     __syncthreads();
     if (lane == kWave - 1) tmp[wid] = inc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < nw; ++w) { int t = tmp[w]; tmp[w] = acc; acc += t; }
-        tmp[16] = acc;
+    int before = 0, all = 0;
+    for (int w = 0; w < waves; ++w) {          // the same words for every thread
+        if (w == wid) before = all;
+        all += tmp[w];
     }
-    __syncthreads();
-    *total = tmp[16];
-    return inc - v + tmp[wid];
+    *total = all;
+    return inc - v + before;
 }
 
 // Largest i in [0, n) with off[i] <= x; needs off[0] <= x.  With equal

@@ -16,10 +16,15 @@
 
 using namespace flmoe;
 
+// A configuration fits fl_moe_layout_static when its tables, with E + 2N + 1 words per route record, fit
+// FL_STATIC_SCRATCH_BYTES.  Records are shorter than that except for a few ranks with a few experts, where
+// they may take up to 12 words more (N <= 9: under 4 KB in all): the slack behind the array.
+constexpr int kStaticSlack = 64 << 10;
+
 // Scratch of fl_moe_layout_static, part of the device image: every GPU the library
 // is loaded on holds its own copy at its own address.  In host code this name is
 // only a handle for hipGetSymbolAddress, never a device address.
-static __device__ __align__(256) unsigned char scratch[FL_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[FL_STATIC_SCRATCH_BYTES + kStaticSlack];
 
 namespace {
 
@@ -80,7 +85,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
 
     D->N = c->n_ranks; D->E = c->n_experts; D->El = El; D->T = c->max_tokens; D->K = c->top_k;
     D->H = c->hidden; D->dtype = c->dispatch_dtype; D->align = c->expert_align; D->flags = c->flags;
-    D->route_len = D->E + 2 * D->N + 1;
+    D->route_len = route_record_words(D->E, D->N, D->T);
     D->KM = (D->K + 3) / 4 * 4;
     D->MW = (c->flags & FL_FLAG_PARTIAL_SUMS) ? 2 * D->KM : D->KM;
     const long long NT = (long long)D->N * D->T;
@@ -120,7 +125,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->spin_limit = c->spin_limit ? c->spin_limit : kDefaultSpin;
     // Largest LDS tile of the counting kernel that stays under 60 KB.
     int tt = 32;
-    while (tt < 1024 && route_count_lds_bytes(D->E, D->N, tt * 2) <= 60 * 1024) tt *= 2;
+    while (tt < 1024 && route_count_lds_bytes(D->E, D->N, D->K, tt * 2) <= 60 * 1024) tt *= 2;
     const int need = (D->T + 31) / 32 * 32;
     D->TT = need < tt ? need : tt;
     D->tune_rows = 0;
@@ -264,6 +269,18 @@ int check_ranks(const fl_moe_ctx *ctx, int rb, int rc) {
 
 int launch_status() { return hipGetLastError() == hipSuccess ? FL_OK : FL_ERR_HIP; }
 
+// Counting blocks per source: one per tile of tokens, as long as they and the planning blocks fit on the
+// machine together (two 1024-thread blocks on each of 256 compute units); beyond that a block walks
+// several tiles.
+void launch_layout(const Dims &D, const Tables &W, int rb, int rc, const int32_t *indices, const int32_t *num_tokens,
+                   hipStream_t st) {
+    const int tiles = (D.T + D.TT - 1) / D.TT;
+    const int parts = std::min(tiles, std::max(1, 512 / rc - 1));
+    const size_t lds = std::max(route_count_lds_bytes(D.E, D.N, D.K, D.TT), route_plan_lds_bytes(D.E, D.N, D.El));
+    route_layout_kernel<<<dim3(rc * (parts + 1)), dim3(kRouteThreads), lds, st>>>(D, W, rb, rc, parts, indices,
+                                                                                  num_tokens);
+}
+
 // Ranks one launch of a payload kernel serves.  A launch that walks many GB runs
 // measurably slower than the same work cut into launches of somewhat under a GB
 // (a plain copy: 6.1 TB/s in 1 GiB launches, 5.7 TB/s as one 12 GiB launch; the
@@ -327,8 +344,9 @@ int static_scratch(void **ptr) {
 
 // What route_layout_kernel keeps outside the caller-visible tables, carved from
 // `base` (nullptr: measure only).  The counters come first, in one run of
-// *clear_words 32-bit words at `base` that every call clears.  Returns the bytes needed.
-size_t carve_static(const Dims &D, void *base, Tables *W, size_t *clear_words) {
+// *clear_words 32-bit words at `base` that every call clears.  Returns the bytes needed
+// with `record_words` words per route record.
+size_t carve_static(const Dims &D, void *base, Tables *W, size_t *clear_words, int record_words) {
     Carver c(base);
     const size_t N = D.N, El = D.El, T = D.T, K = D.K;
     W->epoch_route = c.take<unsigned>(N);
@@ -336,7 +354,7 @@ size_t carve_static(const Dims &D, void *base, Tables *W, size_t *clear_words) {
     W->expect_disp = c.take<unsigned>(N * N);
     W->expect_comb = c.take<unsigned>(N * N);
     *clear_words = align_up(c.cur, 256) / sizeof(unsigned);
-    W->routes = c.take<int>(N * N * D.route_len);
+    W->routes = c.take<int>(N * N * record_words);
     W->recv_shared_off = c.take<int>(N * N);
     W->dst_off = c.take<int>(N * N);
     W->comb_dst_off = c.take<int>(N * N);
@@ -443,10 +461,7 @@ int fl_moe_layout(fl_moe_ctx *ctx, int rb, int rc, const int32_t *indices,
     ctx->num_tokens = num_tokens;
     {
         LaunchTimer t(ctx, KID_ROUTE_LAYOUT, st);
-        const size_t lds_count = route_count_lds_bytes(D.E, D.N, D.TT);
-        const size_t lds_plan = route_plan_lds_bytes(D.E, D.N, D.El);
-        route_layout_kernel<<<dim3(2 * rc), dim3(kRouteThreads), lds_count > lds_plan ? lds_count : lds_plan, st>>>(
-            D, ctx->W, rb, rc, indices, num_tokens);
+        launch_layout(D, ctx->W, rb, rc, indices, num_tokens, st);
     }
     if (view) {
         const Tables &W = ctx->W;
@@ -474,11 +489,12 @@ int fl_moe_layout_static(const fl_moe_config *cfg, const int32_t *indices, const
     Tables W;
     memset(&W, 0, sizeof(W));
     size_t clear_words = 0;
-    if (carve_static(D, nullptr, &W, &clear_words) > FL_STATIC_SCRATCH_BYTES) return FL_ERR_STATIC_LIMIT;
+    if (carve_static(D, nullptr, &W, &clear_words, D.E + 2 * D.N + 1) > FL_STATIC_SCRATCH_BYTES)
+        return FL_ERR_STATIC_LIMIT;
     void *ptr = nullptr;
     e = static_scratch(&ptr);
     if (e != FL_OK) return e;
-    carve_static(D, ptr, &W, &clear_words);
+    carve_static(D, ptr, &W, &clear_words, D.route_len);
     W.C = out->counts; W.M = out->dedup_counts; W.G = out->tokens_per_expert;
     W.send_off = out->send_off; W.recv_off = out->recv_off; W.expert_off = out->expert_off;
     W.comb_off = out->comb_off; W.comb_pos = out->comb_pos; W.plan_ok = out->plan_ok;
@@ -488,10 +504,7 @@ int fl_moe_layout_static(const fl_moe_config *cfg, const int32_t *indices, const
     // counters and epochs must start at zero, everything else is written before it is read.
     clear_words_kernel<<<dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, st>>>(
         (unsigned *)ptr, clear_words, W.status);
-    const size_t lds_count = route_count_lds_bytes(D.E, D.N, D.TT);
-    const size_t lds_plan = route_plan_lds_bytes(D.E, D.N, D.El);
-    route_layout_kernel<<<dim3(2 * D.N), dim3(kRouteThreads), lds_count > lds_plan ? lds_count : lds_plan, st>>>(
-        D, W, 0, D.N, indices, num_tokens);
+    launch_layout(D, W, 0, D.N, indices, num_tokens, st);
     return launch_status();
 }
 

@@ -5,27 +5,49 @@
 // these per-expert counts to determine a unique range in each contiguous receive
 // buffer (Architecture).  The paper computes the ranges on a host proxy; here
 // both halves run on the device.
+//
+// Bound by latency: a few KB per rank go through one chain of load, count, scan,
+// exchange, scan.  So every link is one round of independent loads or one pass of
+// all the block's threads, and what can be worked out before a wait is.  32 ranks, 256
+// experts, top 8, kernel time with one counting block per source, 32-bit records stored
+// word by word and tables that single threads walked -> now: 4 tokens per rank 17.0 ->
+// 11.9 us, 128: 18.9 -> 14.9, 2048: 66.4 -> 22.6 (10 of them the count of all tokens).
 #pragma once
 #include "common.h"
 
 namespace flmoe {
 
 constexpr int kRouteThreads = 1024;
-constexpr int kPlanThreads = 1024;
+constexpr int kRoutePreload = 4;             // pair ids a thread fetches before it knows the token count
 
 // Words per row of the LDS bit matrices: the words in use, padded to an odd
 // number so that rows do not all start in the same bank.
 __host__ __device__ inline int route_row_stride(int TT) { return (TT / 32) | 1; }
 
-__host__ __device__ inline size_t route_count_lds_bytes(int E, int N, int TT) {
+__host__ __device__ inline size_t route_count_lds_bytes(int E, int N, int K, int TT) {
     size_t rows = (size_t)E + N;
     return rows * route_row_stride(TT) * 2 * sizeof(unsigned) + rows * 4 * sizeof(int) +
-           32 * sizeof(int);
+           (rows + 4) * sizeof(int) + 32 * sizeof(int) + (size_t)TT * K * sizeof(unsigned short);
 }
 
-// One block per source rank s.
+// Route record, one per (receiver, source): a 16-byte head (valid, first row of the
+// receiver's reply in the source's combine receive buffer), then the source's E expert
+// counts and N per-rank counts.  Counts are at most T, so they travel as 16-bit
+// numbers (32-bit where T does not fit): 592 bytes at 256 experts and 32 ranks.
+__host__ __device__ inline bool route_wide(int T) { return T > 65535; }
+__host__ __device__ inline int route_record_words(int E, int N, int T) {
+    const int words = route_wide(T) ? E + N : (E + N + 1) / 2;
+    return 4 + (words + 3) / 4 * 4;
+}
+
+// e / El for 0 <= e < 1024 and El <= 256 by a multiplication: m = ceil(2^20 / El),
+// exact because e * (El - 1) < 2^20.
+__device__ inline unsigned div_magic(int El) { return ((1u << 20) + El - 1) / (unsigned)El; }
+__device__ inline int div_by(unsigned e, unsigned m) { return (int)((e * m) >> 20); }
+
+// Block `part` of the `parts` blocks of source rank s.
 //
-// For every tile of TT tokens the block keeps two LDS bit matrices: row e of the
+// For every tile of TT tokens a block keeps two LDS bit matrices: row e of the
 // first has bit t set when token t lists expert e, row d of the second when any
 // of token t's experts lives on rank d (OR-ing makes the per-destination
 // de-duplication free and the result independent of thread order).  The rank of
@@ -35,14 +57,18 @@ __host__ __device__ inline size_t route_count_lds_bytes(int E, int N, int TT) {
 // which is the stable counting-sort position the canonical (source rank, token
 // index) order needs, with no ticket atomics.
 //
-// Pass 1 counts (per row totals over all tiles), one block scan over the E + N
-// totals turns them into offsets, pass 2 rebuilds each tile's bits (kept from
-// pass 1 when there is a single tile) and writes every pair's final positions.
+// One tile (T <= TT): its popcounts are the counts.  Several: the tiles are shared out
+// over the blocks, and every block first counts all of the source's tokens with LDS
+// adds (and, apart, those before its own first tile), one token per thread: counting
+// them again in every block costs less than the blocks would wait for each other's parts
+// unless there are many tokens, and keeps a counting block from ever waiting.  One scan over the E + N totals gives the offsets.  The last pass
+// writes every pair's final positions.
 //
-// Outputs for rank s: C[s][.], M[s][.], send_off[s][.], comb_off[s][.], per pair
-// send_row / pair_meta / comb_pos; the route record (C | M | comb_off | valid) is
-// pushed into every peer's routes[peer][s] and arrive_route[peer][s] is bumped.
-__device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W, int s,
+// Outputs for rank s: by part 0, C[s][.], M[s][.], send_off[s][.], comb_off[s][.] and the
+// route record, which is pushed into every peer's routes[peer][s] before
+// arrive_route[peer][s] is bumped; by every part, send_row / pair_meta / comb_pos of the
+// pairs of its tiles.
+__device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W, int s, int part, int parts,
                                                   const int *__restrict__ indices,
                                                   const int *__restrict__ num_tokens, unsigned *lds) {
     const int tid = threadIdx.x;
@@ -50,108 +76,188 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
     const int rows = E + N;
     const int Wn = D.TT / 32;                              // words in use per row
     const int Wd = route_row_stride(D.TT);                 // row stride in words
-    unsigned *bits = lds;                                  // [rows][Wd]
+    const unsigned by_el = div_magic(El);
+    unsigned *record = lds;                                // [4 + rows] packed counts, 16-byte aligned
+    unsigned *bits = record + (rows + 4 + 3) / 4 * 4;      // [rows][Wd]
     unsigned *pre = bits + (size_t)rows * Wd;              // [rows][Wd] popcount prefix inside the tile
     int *count = (int *)(pre + (size_t)rows * Wd);         // [rows] hits over all tiles (C | M)
     int *start = count + rows;                             // [rows] exclusive scan of count
     int *base = start + rows;                              // [rows] hits in the tiles before the current one
-    int *total_hits = base + rows;                         // [rows] copy of the totals (pass 2 reuses count)
-    int *scan_tmp = total_hits + rows;                     // [32]
+    int *hits = base + rows;                               // [rows] hits of the current tile
+    int *scan_tmp = hits + rows;                           // [17]
+    unsigned short *ids = (unsigned short *)(scan_tmp + 20);   // [TT * K] expert ids of the tile
     __shared__ int bad;
 
+    const int *idx_s = indices + (size_t)s * D.T * K;
+    const int tiles = (D.T + D.TT - 1) / D.TT;             // of the capacity; the tokens in use may fill fewer
+    const int per = (tiles + parts - 1) / parts;
+    const int tile0 = part * per;
+    // the first ids go out together with the token count (the array has T rows whatever is in use)
+    int early[kRoutePreload];
+#pragma unroll
+    for (int i = 0; i < kRoutePreload; ++i) {
+        const int p = tid + i * kRouteThreads;
+        early[i] = p < min(D.TT, D.T - tile0 * D.TT) * K ? idx_s[(size_t)tile0 * D.TT * K + p] : 0;
+    }
     int Ts = num_tokens[s];
     if (tid == 0) bad = (Ts < 0 || Ts > D.T) ? 1 : 0;
-    Ts = max(0, min(Ts, D.T));
-    const int ntiles = (Ts + D.TT - 1) / D.TT;
     for (int r = tid; r < rows; r += kRouteThreads) { count[r] = 0; base[r] = 0; }
-    const int *idx_s = indices + (size_t)s * D.T * K;
+    for (int i = tid; i < rows * Wd; i += kRouteThreads) bits[i] = 0;
+    Ts = max(0, min(Ts, D.T));
+    const int used = (Ts + D.TT - 1) / D.TT;
+    __syncthreads();
 
-    // bits and in-tile popcount prefixes of one tile; returns each row's hits in tile_hits
-    auto fill_tile = [&](int t0, int nt, int *tile_hits, bool accumulate) {
-        for (int i = tid; i < rows * Wd; i += kRouteThreads) bits[i] = 0;
-        __syncthreads();
-        for (int p = tid; p < nt * K; p += kRouteThreads) {
+    // bits (already cleared), ids, in-tile popcount prefixes and row totals of one tile
+    auto fill_tile = [&](int t0, int nt) {
+        auto take = [&](int p, int e) {
+            const bool ok = e >= 0 && e < E;
+            ids[p] = (unsigned short)(ok ? e : 0xFFFF);
+            if (!ok) { bad = 1; return; }
             const int tl = p / K;
-            const int e = idx_s[(size_t)t0 * K + p];
-            if (e < 0 || e >= E) { bad = 1; continue; }
             const unsigned bit = 1u << (tl & 31);
             const unsigned old = atomicOr(&bits[(size_t)e * Wd + (tl >> 5)], bit);
             if (old & bit) bad = 1;                        // same expert twice in one token
-            atomicOr(&bits[(size_t)(E + e / El) * Wd + (tl >> 5)], bit);
+            atomicOr(&bits[(size_t)(E + div_by(e, by_el)) * Wd + (tl >> 5)], bit);
+        };
+#pragma unroll
+        for (int i = 0; i < kRoutePreload; ++i) {
+            const int p = tid + i * kRouteThreads;
+            if (p < nt * K) take(p, t0 == tile0 * D.TT ? early[i] : idx_s[(size_t)t0 * K + p]);
         }
+        for (int p = tid + kRoutePreload * kRouteThreads; p < nt * K; p += kRouteThreads)
+            take(p, idx_s[(size_t)t0 * K + p]);
         __syncthreads();
         for (int r = tid; r < rows; r += kRouteThreads) {
             int run = 0;
-            for (int w = 0; w < Wn; ++w) {
-                pre[(size_t)r * Wd + w] = run;
-                run += __popc(bits[(size_t)r * Wd + w]);
+            for (int w0 = 0; w0 < Wn; w0 += 4) {
+                unsigned b[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) b[i] = w0 + i < Wn ? bits[(size_t)r * Wd + w0 + i] : 0u;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (w0 + i < Wn) pre[(size_t)r * Wd + w0 + i] = run;
+                    run += __popc(b[i]);
+                }
             }
-            tile_hits[r] = accumulate ? tile_hits[r] + run : run;
+            hits[r] = run;
         }
         __syncthreads();
     };
 
-    // pass 1: totals over all tiles
-    __syncthreads();
-    for (int tile = 0; tile < ntiles; ++tile) {
-        const int t0 = tile * D.TT;
-        fill_tile(t0, min(D.TT, Ts - t0), count, true);
+    if (tiles == 1) {
+        fill_tile(0, Ts);
+        for (int r = tid; r < rows; r += kRouteThreads) count[r] = hits[r];
+    } else {                                               // one token per thread and turn
+        // the LDS adds are what this pass takes its time for: where both counts fit, one word holds the
+        // total in its lower and the hits before this block's tiles in its upper half
+        const bool wide = route_wide(D.T);
+        const int mine = min(tile0 * D.TT, Ts);
+        for (int t = tid; t < Ts; t += kRouteThreads) {
+            const int one = !wide && t < mine ? 0x10001 : 1;
+            int id[FL_MAX_TOPK], owner[FL_MAX_TOPK];
+#pragma unroll
+            for (int k = 0; k < FL_MAX_TOPK; ++k) id[k] = k < K ? idx_s[(size_t)t * K + k] : 0;
+#pragma unroll
+            for (int k = 0; k < FL_MAX_TOPK; ++k) {
+                const int e = id[k];
+                const bool ok = e >= 0 && e < E;
+                owner[k] = ok ? div_by(e, by_el) : -1;
+                if (k < K) {
+                    bool first = true, again = !ok;
+#pragma unroll
+                    for (int k2 = 0; k2 < FL_MAX_TOPK; ++k2)
+                        if (k2 < k) {
+                            again |= id[k2] == e;          // same expert twice in one token
+                            first &= owner[k2] != owner[k];
+                        }
+                    if (again) bad = 1;
+                    if (ok) {
+                        atomicAdd(&count[e], one);
+                        if (first) atomicAdd(&count[E + owner[k]], one);
+                        if (wide && t < mine) {
+                            atomicAdd(&base[e], 1);
+                            if (first) atomicAdd(&base[E + owner[k]], 1);
+                        }
+                    }
+                }
+            }
+        }
+        if (!wide) {
+            __syncthreads();
+            for (int r = tid; r < rows; r += kRouteThreads) {
+                const unsigned c = (unsigned)count[r];
+                count[r] = (int)(c & 0xFFFFu);
+                base[r] = (int)(c >> 16);
+            }
+        }
     }
+    __syncthreads();
 
-    // one exclusive scan over the E + N totals (two slots per thread)
+    // one exclusive scan over the E + N totals (two slots per thread); the record is packed on the way
     {
         const int a = 2 * tid < rows ? count[2 * tid] : 0;
         const int b = 2 * tid + 1 < rows ? count[2 * tid + 1] : 0;
         int total;
-        const int ex = block_excl_scan(a + b, scan_tmp, &total);
-        if (2 * tid < rows) { start[2 * tid] = ex; total_hits[2 * tid] = a; }
-        if (2 * tid + 1 < rows) { start[2 * tid + 1] = ex + a; total_hits[2 * tid + 1] = b; }
+        const int ex = block_excl_scan(a + b, scan_tmp, &total, (rows + 2 * kWave - 1) / (2 * kWave));
+        if (2 * tid < rows) {
+            start[2 * tid] = ex;
+            if (route_wide(D.T)) record[4 + 2 * tid] = (unsigned)a;
+            else record[4 + tid] = (unsigned)a | (unsigned)b << 16;
+        }
+        if (2 * tid + 1 < rows) {
+            start[2 * tid + 1] = ex + a;
+            if (route_wide(D.T)) record[4 + 2 * tid + 1] = (unsigned)b;
+        }
     }
     __syncthreads();
     // start[e] = first combine-receive row of expert e; start[E + d] = pairs + send_off[d]
     const int pairs_total = start[E];
-    if (tid < E) W.C[(size_t)s * E + tid] = count[tid];
-    if (tid < N) {
-        W.M[(size_t)s * N + tid] = count[E + tid];
-        W.send_off[(size_t)s * (N + 1) + tid] = start[E + tid] - pairs_total;
-        W.comb_off[(size_t)s * (N + 1) + tid] = start[tid * El];
-    }
-    if (tid == 0) {
-        W.send_off[(size_t)s * (N + 1) + N] = start[E + N - 1] + count[E + N - 1] - pairs_total;
-        W.comb_off[(size_t)s * (N + 1) + N] = pairs_total;
+    if (part == 0) {
+        // Everything a peer needs is known now (every index was seen, so `bad` is final): the
+        // record goes out before the pair tables, which only this rank's later kernels read, so
+        // the peers' planning overlaps with them.
+        const int valid = bad ? 0 : 1;
+        const int R2 = D.route_len / 2;                    // stored as 8-byte words
+        for (int i = tid; i < N * R2; i += kRouteThreads) {
+            const int peer = i / R2, f = i - peer * R2;
+            unsigned long long v = ((const unsigned long long *)record)[f];
+            if (f == 0) v = (unsigned long long)(unsigned)start[peer * El] << 32 | (unsigned)valid;
+            __hip_atomic_store((unsigned long long *)(W.routes + ((size_t)peer * N + s) * D.route_len) + f, v,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        stores_done<true>();
+        __syncthreads();
+        if (tid < N) add_counter(W.arrive_route + (size_t)tid * N + s, 1u);
+        if (bad && tid == 0) latch_status(W.status, FL_STATUS_BAD_INDEX);
+        if (tid < E) W.C[(size_t)s * E + tid] = count[tid];
+        if (tid < N) {
+            W.M[(size_t)s * N + tid] = count[E + tid];
+            W.send_off[(size_t)s * (N + 1) + tid] = start[E + tid] - pairs_total;
+            W.comb_off[(size_t)s * (N + 1) + tid] = start[tid * El];
+        }
+        if (tid == 0) {
+            W.send_off[(size_t)s * (N + 1) + N] = start[E + N - 1] + count[E + N - 1] - pairs_total;
+            W.comb_off[(size_t)s * (N + 1) + N] = pairs_total;
+        }
     }
 
-    // Everything a peer needs is known now (pass 1 saw every index, so `bad` is final):
-    // the record goes out before pass 2, whose per-pair tables only this rank's later
-    // kernels read, so the peers' planning overlaps with it.
-    const int valid = bad ? 0 : 1;
-    if (bad && tid == 0) latch_status(W.status, FL_STATUS_BAD_INDEX);
-
-    // Route exchange: push this rank's record (C | M | comb_off | valid, all still in
-    // LDS) into every peer's table, then notify.
-    const int RL = D.route_len;
-    for (int i = tid; i < N * RL; i += kRouteThreads) {
-        const int peer = i / RL, f = i - peer * RL;
-        int v;
-        if (f < E + N) v = total_hits[f];
-        else if (f < E + 2 * N) v = start[(f - E - N) * El];
-        else v = valid;
-        st_word<true>(&W.routes[((size_t)peer * N + s) * RL + f], v);
-    }
-    stores_done<true>();
-    __syncthreads();
-    if (tid < N) add_counter(W.arrive_route + (size_t)tid * N + s, 1u);
-
-    // pass 2: final position of every pair
-    for (int tile = 0; tile < ntiles; ++tile) {
+    // final position of every pair of this block's tiles
+    for (int tile = tile0; tile < min(tile0 + per, used); ++tile) {
         const int t0 = tile * D.TT, nt = min(D.TT, Ts - t0);
-        if (ntiles > 1) fill_tile(t0, nt, count, false);   // count[] now holds this tile's hits
+        if (tiles > 1) {
+            if (tile > tile0) {                            // behind the tile before
+                __syncthreads();
+                for (int r = tid; r < rows; r += kRouteThreads) base[r] += hits[r];
+                for (int i = tid; i < rows * Wd; i += kRouteThreads) bits[i] = 0;
+                __syncthreads();
+            }
+            fill_tile(t0, nt);
+        }
         for (int p = tid; p < nt * K; p += kRouteThreads) {
             const int tl = p / K, k = p - tl * K;
-            const size_t g = (size_t)t0 * K + p;
-            const int e = idx_s[g];
-            if (e < 0 || e >= E) continue;
-            const int d = e / El;
+            const int e = ids[p];
+            if (e == 0xFFFF) continue;
+            const int d = div_by(e, by_el);
             const unsigned below = (1u << (tl & 31)) - 1u;
             const int w = tl >> 5;
             const int re = e, rd = E + d;
@@ -159,51 +265,66 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
                 base[re] + pre[(size_t)re * Wd + w] + __popc(bits[(size_t)re * Wd + w] & below);
             const int rank_d =
                 base[rd] + pre[(size_t)rd * Wd + w] + __popc(bits[(size_t)rd * Wd + w] & below);
-            // first slot of this token bound for rank d?  The token's earlier ids are fetched
-            // together (predicated, independent loads) rather than one per loop turn.
-            int before[FL_MAX_TOPK];
-#pragma unroll
-            for (int k2 = 0; k2 < FL_MAX_TOPK; ++k2) before[k2] = k2 < k ? idx_s[g - k + k2] : -1;
-            bool first = true;
-#pragma unroll
-            for (int k2 = 0; k2 < FL_MAX_TOPK; ++k2)
-                if (before[k2] >= 0 && before[k2] < E && before[k2] / El == d) first = false;
-            const size_t o = (size_t)s * D.T * K + g;
+            bool first = true;                             // first slot of this token bound for rank d?
+            for (int k2 = 1; k2 <= k; ++k2) {
+                const unsigned e2 = ids[p - k2];
+                if (e2 != 0xFFFFu && div_by(e2, by_el) == d) first = false;
+            }
+            const size_t o = ((size_t)s * D.T + t0) * K + p;
             W.comb_pos[o] = start[re] + rank_e;
             W.pair_meta[o] = ((unsigned)(e - d * El) << 24) | (unsigned)rank_e;
             W.send_row[o] = first ? start[rd] - pairs_total + rank_d : -1;
-        }
-        if (ntiles > 1) {
-            __syncthreads();
-            for (int r = tid; r < rows; r += kRouteThreads) base[r] += count[r];
-            __syncthreads();
         }
     }
 }
 
 __host__ __device__ inline size_t route_plan_lds_bytes(int E, int N, int El) {
-    return ((size_t)E /*G_all*/ + (size_t)N * El /*own counts*/ + (size_t)N * N /*M*/ + El + 1 +
-            3 * (size_t)N + 8) * sizeof(int);
+    return ((size_t)3 * E /*all ranks' totals, own columns, own row*/ + (size_t)N * N /*M*/ + El + 1 +
+            3 * (size_t)N + 8) * sizeof(int) + (size_t)N * sizeof(unsigned long long);
 }
 
-// One block per rank r: waits for the route records of all sources, stages what
-// it needs from them in LDS with one wide round of loads, then derives every
+// One block per rank r: waits for the route records of all sources, fetches what
+// it needs from them with one wide round of loads, then derives every
 // table rank r needs for the step.  All ranks see the same records, so all reach
 // the same verdict on validity and capacity: a bad step is skipped by everyone
 // without further communication.
+template <bool WIDE>
 __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W, int r, unsigned *lds) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    constexpr int kWaves = kRouteThreads / kWave;
     const int E = D.E, N = D.N, El = D.El, RL = D.route_len;
-    int *G_all = (int *)lds;              // [E]      tokens per expert over all sources
+    unsigned long long *ptot = (unsigned long long *)lds;   // [N] rows of each rank's expert layout, padding included
+    int *G_all = (int *)(ptot + N);       // [E]      tokens per expert over all sources
     int *Cown = G_all + E;                // [N][El]  counts of rank r's experts per source
-    int *Mall = Cown + N * El;            // [N][N]   de-duplicated counts, [source][destination]
+    int *Crow = Cown + E;                 // [E]      rank r's own counts
+    int *Mall = Crow + E;                 // [N][N]   de-duplicated counts, [source][destination]
     int *eoff = Mall + N * N;             // [El+1]   expert offsets of rank r
     int *csoff = eoff + El + 1;           // [N]      first combine-send row of each source
+    int *len = csoff + N;                 // [N]      pairs of each source on rank r
+    int *mine = len + N;                  // [N]      pairs of rank r on each rank
     __shared__ int flag, invalid, over;
     const int *rt = W.routes + (size_t)r * N * RL;
+    const unsigned by_el = div_magic(El);
+    // entry f (counts of experts, then of ranks) of source s's record: its place, and the count there
+    auto place = [&](int s, int f) { return s * RL * (WIDE ? 1 : 2) + (WIDE ? 4 : 8) + f; };
+    auto entry = [&](int at) -> int { return WIDE ? rt[at] : (int)((const unsigned short *)rt)[at]; };
+    // where this thread's loads will go, worked out before the wait
+    constexpr int kPer = WIDE ? 4 : 8;                 // counts per 16-byte vector
+    const int vecs = (E + kPer - 1) / kPer;            // the last one may reach into the rank counts
+    const int parts = kRouteThreads / vecs;
+    const int v = tid % vecs, part = tid / vecs;
+    const int te = tid < E ? tid : 0, td = div_by(te, by_el);
+    const int own_at = place(td, r * El + te - td * El), row_at = place(r, te);
+    int m_at[4];                                       // N * N <= 4096
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int at = tid + i * kRouteThreads;
+        m_at[i] = at < N * N ? place(at / N, E + at % N) : -1;
+    }
 
     if (tid == 0) { flag = 0; invalid = 0; over = 0; }
-    for (int e = tid; e < E; e += kPlanThreads) G_all[e] = 0;
+    for (int e = tid; e < E; e += kRouteThreads) G_all[e] = 0;
+    if (tid < N) { ptot[tid] = 0; len[tid] = 0; mine[tid] = 0; }
     __syncthreads();
     if (wid == 0) {
         // Rank r has planned epoch_route[r] steps so far (only this block touches the
@@ -221,22 +342,43 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
         return;
     }
 
-    // One wide round of loads.  Expert columns: each thread sums a residue class of
-    // the sources for one expert (all its loads are independent), LDS adds the parts.
+    // One wide round of loads, all independent.  Expert totals: a thread takes one 16-byte vector of
+    // counts from every `parts`-th source, LDS adds the parts.
     {
-        const int parts = max(1, kPlanThreads / E);
-        for (int i = tid; i < E * parts; i += kPlanThreads) {
-            const int e = i % E, part = i / E;
-            int acc = 0;
-            for (int s = part; s < N; s += parts) acc += rt[(size_t)s * RL + e];
-            atomicAdd(&G_all[e], acc);
+        int acc[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) acc[i] = 0;
+        if (part < parts)
+            for (int s0 = part; s0 < N; s0 += 4 * parts) {
+                v4u q[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (s0 + u * parts < N) q[u] = ((const v4u *)(rt + (size_t)(s0 + u * parts) * RL))[1 + v];
+                    else q[u] = v4u{0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        if (WIDE) acc[w % kPer] += (int)q[u][w];
+                        else { acc[2 * w % kPer] += (int)(q[u][w] & 0xFFFFu); acc[(2 * w + 1) % kPer] += (int)(q[u][w] >> 16); }
+                    }
+            }
+        const int own = entry(own_at), row = entry(row_at);
+        int m[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = m_at[i] >= 0 ? entry(m_at[i]) : 0;
+        if (tid < N) {
+            if (rt[(size_t)tid * RL] == 0) invalid = 1;
+            W.comb_dst_off[(size_t)r * N + tid] = rt[(size_t)tid * RL + 1];
         }
-        for (int i = tid; i < N * El; i += kPlanThreads)
-            Cown[i] = rt[(size_t)(i / El) * RL + r * El + (i % El)];
-        for (int i = tid; i < N * N; i += kPlanThreads)
-            Mall[i] = rt[(size_t)(i / N) * RL + E + (i % N)];
-        if (tid < N && rt[(size_t)tid * RL + E + 2 * N] == 0) invalid = 1;
-        if (tid < N) W.comb_dst_off[(size_t)r * N + tid] = rt[(size_t)tid * RL + E + N + r];
+        if (tid < E) { Cown[tid] = own; Crow[tid] = row; }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (m_at[i] >= 0) Mall[tid + i * kRouteThreads] = m[i];
+        if (part < parts && part < N)
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                if (v * kPer + i < E) atomicAdd(&G_all[v * kPer + i], acc[i]);
     }
     __syncthreads();
     if (invalid) {
@@ -244,56 +386,65 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
         return;
     }
 
+    // sums over the experts of a rank: rows of its layout, pairs each way (E <= 1024: one turn)
+    if (tid < E) {
+        const int d = td, j = tid - d * El;
+        const unsigned g = (unsigned)G_all[tid], al = (unsigned)D.align;
+        atomicAdd(&ptot[d], (unsigned long long)(j + 1 < El && al > 1 ? (g + al - 1) / al * al : g));
+        atomicAdd(&len[d], Cown[tid]);        // index (source, local expert)
+        atomicAdd(&mine[d], Crow[tid]);
+    }
+    // wave = destination d, lane = source: the shared-range rows of lower sources
+    const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
+    for (int d = wid; d < N; d += kWaves) {
+        const int m = lane < N ? Mall[lane * N + d] : 0;
+        const int beyond = max(m - D.P, 0);   // rows past the source's private slots
+        int inc = wave_incl_scan(beyond);
+        if (lane == r) W.dst_off[(size_t)r * N + d] = inc - beyond;
+        if (lane == N - 1 && inc > D.recv_cap) over = 1;   // what d's shared range must hold
+        if (d == r) {
+            if (lane < N) W.recv_shared_off[(size_t)r * N + lane] = inc - beyond;
+            inc = wave_incl_scan(m);
+            if (lane < N) W.recv_off[(size_t)r * (N + 1) + lane] = inc - m;
+            if (lane == N - 1) W.recv_off[(size_t)r * (N + 1) + N] = inc;
+        }
+    }
+    if (partial)                              // wave = source, lane = rank: rows the source sent to ranks below r
+        for (int s = wid; s < N; s += kWaves) {
+            const int m = lane < N ? Mall[s * N + lane] : 0;
+            const int inc = wave_incl_scan(m);
+            if (lane == r) W.ret_off[(size_t)r * N + s] = inc - m;
+        }
+    __syncthreads();
+
     unsigned exp_units = 0;       // wave 0: lane = source; wave 1: lane = peer answering in combine
     if (wid == 0) {
-        // lane = source s: receive offsets and combine-send offsets of rank r
-        const int s = lane;
-        const int m = s < N ? Mall[s * N + r] : 0;
         // what source s will have added once its transfer to this rank is complete: the
         // payload in 16-byte units, plus one for the transfer itself (an empty one still counts)
-        exp_units = (unsigned)m * (unsigned)(D.Bw / 16) + 1u;
-        int inc = wave_incl_scan(m);
-        if (s < N) W.recv_off[(size_t)r * (N + 1) + s] = inc - m;
-        if (s == N - 1) W.recv_off[(size_t)r * (N + 1) + N] = inc;
-        const int beyond = max(m - D.P, 0);        // rows of s past its private slots
-        inc = wave_incl_scan(beyond);
-        if (s < N) W.recv_shared_off[(size_t)r * N + s] = inc - beyond;
-        int len = 0;
-        if (s < N)
-            for (int j = 0; j < El; ++j) len += Cown[s * El + j];
-        inc = wave_incl_scan(len);
-        if (s < N) { csoff[s] = inc - len; W.cs_off[(size_t)r * (N + 1) + s] = inc - len; }
-        if (s == N - 1) W.cs_off[(size_t)r * (N + 1) + N] = inc;
-        if ((D.flags & FL_FLAG_PARTIAL_SUMS) && s < N) {   // rows s sent to ranks below r
-            int before = 0;
-            for (int d2 = 0; d2 < r; ++d2) before += Mall[s * N + d2];
-            W.ret_off[(size_t)r * N + s] = before;
-        }
+        if (lane < N) exp_units = (unsigned)Mall[lane * N + r] * (unsigned)(D.Bw / 16) + 1u;
+        const int n = lane < N ? len[lane] : 0;
+        const int inc = wave_incl_scan(n);
+        if (lane < N) { csoff[lane] = inc - n; W.cs_off[(size_t)r * (N + 1) + lane] = inc - n; }
+        if (lane == N - 1) W.cs_off[(size_t)r * (N + 1) + N] = inc;
     } else if (wid == 1) {
-        // lane = rank d: capacity verdict for every rank, start of r's segment at d,
-        // size of d's reply to rank r
-        const int d = lane;
-        if (d < N) {
-            long long recv_rows = 0;
-            int before_me = 0;
-            for (int s = 0; s < N; ++s) {
-                const int m = Mall[s * N + d];
-                if (s < r) before_me += max(m - D.P, 0);
-                recv_rows += max(m - D.P, 0);              // what d's shared range must hold
+        if (lane < N) {           // with partial sums one share per row r sent to the peer
+            exp_units = (unsigned)(partial ? Mall[r * N + lane] : mine[lane]) * (unsigned)(D.Bc / 16) + 1u;
+            if (ptot[lane] > (unsigned long long)D.expert_cap) over = 1;
+        }
+    } else if (wid == 2) {        // offsets of rank r's experts, 64 at a time
+        const unsigned al = (unsigned)D.align;
+        unsigned carry = 0;
+        for (int j0 = 0; j0 < El; j0 += kWave) {
+            const int j = j0 + lane;
+            const unsigned g = j < El ? (unsigned)G_all[r * El + j] : 0u;
+            const unsigned room = j + 1 < El && al > 1 ? (g + al - 1) / al * al : g;
+            const unsigned inc = (unsigned)wave_incl_scan((int)room);
+            if (j < El) {
+                eoff[j] = (int)(carry + inc - room);
+                if (j == El - 1) eoff[El] = (int)(carry + inc);
+                W.G[(size_t)r * El + j] = (int)g;
             }
-            W.dst_off[(size_t)r * N + d] = before_me;
-            int mine = 0;
-            for (int j = 0; j < El; ++j) mine += rt[(size_t)r * RL + d * El + j];
-            if (D.flags & FL_FLAG_PARTIAL_SUMS) mine = Mall[r * N + d];   // one share per row r sent to d
-            exp_units = (unsigned)mine * (unsigned)(D.Bc / 16) + 1u;
-            long long p = 0;
-            for (int j = 0; j < El; ++j) {
-                const int g = G_all[d * El + j];
-                if (d == r) { eoff[j] = (int)p; W.G[(size_t)r * El + j] = g; }
-                p += (j + 1 < El) ? ((long long)g + D.align - 1) / D.align * D.align : g;
-            }
-            if (d == r) eoff[El] = (int)p;
-            if (recv_rows > D.recv_cap || p > D.expert_cap) over = 1;
+            carry += (unsigned)__shfl((int)inc, kWave - 1);
         }
     }
     __syncthreads();
@@ -301,41 +452,49 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
         if (tid == 0) { W.plan_ok[r] = 0; latch_status(W.status, FL_STATUS_CAPACITY); }
         return;
     }
-    for (int j = tid; j <= El; j += kPlanThreads) W.expert_off[(size_t)r * (El + 1) + j] = eoff[j];
-    // base_x[j][s] = expert_off[j] + rows of lower sources in expert j;
-    // cs_base[s][j] = cs_off[s] + rows of lower experts for source s
-    for (int i = tid; i < El * N; i += kPlanThreads) {
-        const int j = i / N, s = i - j * N;
-        int acc = eoff[j];
-        for (int s2 = 0; s2 < s; ++s2) acc += Cown[s2 * El + j];
-        W.base_x[(size_t)r * El * N + i] = acc;
-        const int s3 = i / El, j3 = i - s3 * El;
-        int acc3 = csoff[s3];
-        for (int j2 = 0; j2 < j3; ++j2) acc3 += Cown[s3 * El + j2];
-        W.cs_base[((size_t)r * N + s3) * El + j3] = acc3;
+    for (int j = tid; j <= El; j += kRouteThreads) W.expert_off[(size_t)r * (El + 1) + j] = eoff[j];
+    // base_x[j][s] = expert_off[j] + rows of lower sources in expert j (a wave per expert, lane = source);
+    // cs_base[s][j] = cs_off[s] + rows of lower experts for source s (a wave per source, lane = expert)
+    for (int job = wid; job < El + N; job += kWaves) {
+        if (job < El) {
+            const int c = lane < N ? Cown[lane * El + job] : 0;
+            const int inc = wave_incl_scan(c);
+            if (lane < N) W.base_x[((size_t)r * El + job) * N + lane] = eoff[job] + inc - c;
+        } else {
+            const int s = job - El;
+            int carry = csoff[s];
+            for (int j0 = 0; j0 < El; j0 += kWave) {
+                const int c = j0 + lane < El ? Cown[s * El + j0 + lane] : 0;
+                const int inc = wave_incl_scan(c);
+                if (j0 + lane < El) W.cs_base[((size_t)r * N + s) * El + j0 + lane] = carry + inc - c;
+                carry += __shfl(inc, kWave - 1);
+            }
+        }
     }
     if (wid == 0 && lane < N) W.expect_disp[(size_t)r * N + lane] += exp_units;
     if (wid == 1 && lane < N) W.expect_comb[(size_t)r * N + lane] += exp_units;
     if (tid == 0) W.plan_ok[r] = 1;
 }
 
-// One launch for both halves of the layout step: blocks [0, rank_count) count for
-// their source rank and push its route record, blocks [rank_count, 2 * rank_count)
-// plan for their rank as soon as the records of all sources have arrived.  The
-// planning blocks poll the message counters (bounded) while the counting blocks
-// run: workgroups are dispatched in index order and all of them fit on the
-// machine at once (two 1024-thread blocks per compute unit, at most 128 blocks),
-// so a poller never keeps a counter from starting.  Records cross compute dies
-// inside one kernel, hence device-scope stores and one cache invalidation per
-// planning block in every mode.
+// One launch for both halves of the layout step: the first rank_count * parts blocks
+// count (the first rank_count of them, part 0 of every source, push the route records),
+// the last rank_count plan for their rank as soon as the records of all sources have
+// arrived.  The planning blocks poll the message counters (bounded) while the counting
+// blocks run: workgroups are dispatched in index order, so every counting block has its
+// place before a poller takes one, and a poller never keeps a counter from starting.
+// Records cross compute dies inside one kernel, hence device-scope stores and one cache
+// invalidation per planning block in every mode.
 __global__ __launch_bounds__(kRouteThreads) void route_layout_kernel(
-    Dims D, Tables W, int rank_begin, int rank_count, const int *__restrict__ indices,
+    Dims D, Tables W, int rank_begin, int rank_count, int parts, const int *__restrict__ indices,
     const int *__restrict__ num_tokens) {
-    extern __shared__ unsigned lds[];
-    if ((int)blockIdx.x < rank_count)
-        route_count_block(D, W, rank_begin + blockIdx.x, indices, num_tokens, lds);
+    extern __shared__ __align__(16) unsigned lds[];
+    const int b = blockIdx.x;
+    if (b < rank_count * parts)
+        route_count_block(D, W, rank_begin + b % rank_count, b / rank_count, parts, indices, num_tokens, lds);
+    else if (route_wide(D.T))
+        route_plan_block<true>(D, W, rank_begin + b - rank_count * parts, lds);
     else
-        route_plan_block(D, W, rank_begin + blockIdx.x - rank_count, lds);
+        route_plan_block<false>(D, W, rank_begin + b - rank_count * parts, lds);
 }
 
 }  // namespace flmoe

@@ -175,6 +175,25 @@ def test_parity_in_the_other_ordering_modes(name, form):
     sh.close()
 
 
+# (ranks, experts, tokens, top-k): one tile of the counting block exactly, one token more, a last tile with
+# one token; several tiles per block; the most rows (experts + ranks) a block can have; an odd number of
+# them, fewer than one vector, and one expert; token counts that need 32-bit records, with several tiles
+LAYOUT_EDGES = [(4, 32, 1024, 4), (4, 32, 1025, 4), (32, 256, 513, 8), (32, 256, 1024, 8), (64, 64, 1500, 3),
+                (64, 1024, 70, 16), (64, 1024, 2200, 2), (3, 9, 600, 5), (1, 1, 33, 1), (2, 4, 65536, 2),
+                (1, 3, 70000, 1)]
+
+
+@pytest.mark.parametrize("ragged", [False, True])
+@pytest.mark.parametrize("shape", LAYOUT_EDGES, ids=str)
+def test_layout_at_the_edges_of_tiles_blocks_and_records(shape, ragged):
+    """Whole steps with the shortest rows, so that the tables of the layout step decide: bit for bit."""
+    N, E, T, K = shape
+    wl = wlmod.custom("edges", N, E, T, 8, K, seed=T + K, ragged=ragged)
+    sh, _, _ = run_and_compare(wlmod.make_inputs(wl), align=4 if T < 5000 else 1, zero_pad=True, capacity_factor=2.5,
+                               private_rows=3 if ragged else 0)
+    sh.close()
+
+
 @pytest.mark.parametrize("partial", [False, True])
 @pytest.mark.parametrize("name", ["ragged_520", "multi_tile"])
 def test_replies_past_the_caches(name, partial):
