@@ -141,17 +141,23 @@ def _check(code, where):
         raise FlMoeError(code, where)
 
 
+# Handles and addresses go to the library as plain integers (its argument types turn them into pointers), and
+# the current stream's handle is read without building a stream object: the five calls of a small step are
+# bound by what the host does between launches (2 ranks x 16 tokens: 56 -> 44 us of host time per step).
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        return _raw_stream(_current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _ptr(t):
     if t is None:
-        return C.c_void_p(0)
+        return None
     assert t.is_cuda and t.is_contiguous()
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # ------------------------------------------------------------------ the C calls, same names
@@ -194,7 +200,7 @@ def fl_moe_dispatch_send(ctx, rank_begin, rank_count, x, stream=None):
 
 def fl_moe_dispatch_send_e4m3(ctx, rank_begin, rank_count, codes, scales, weights=None, stream=None):
     _check(lib().fl_moe_dispatch_send_e4m3(ctx, rank_begin, rank_count, _ptr(codes), _ptr(scales),
-                                           _ptr(weights) if weights is not None else None,
+                                           _ptr(weights),
                                            _stream(stream)), "fl_moe_dispatch_send_e4m3")
 
 
