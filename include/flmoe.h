@@ -388,15 +388,15 @@ const char *fl_moe_strerror(int code);
 int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
 
 /* Diagnostic: overrides a launch-shape knob of the copy kernels (results never
- * change).  knob 0 = rows per workgroup of the unpack / combine-pack kernels
+ * change).  knob 0 = rows per workgroup of the polling unpack / combine-pack kernels
  * (0 = chosen from the row size, at most 64), knob 1 = row loads issued together
  * per thread in combine_reduce (0 = all K, at most 8), knob 2 = accepted without
  * effect (it shaped a copy kernel that is no longer launched), knob 3 =
  * workgroups per token in the pack kernel (0 = chosen from the row size, at
  * most 16), knob 4 = size in MiB of the replies a combine_send call may write above
  * which it uses streaming instead of cached stores (default 1024), knob 5 = percentage of the rows uniform routing would bring to a rank that the
- * grids of the receive-side and reply kernels are sized for (default 200; 0 = the
- * whole capacity; a rank that holds more is served by the kernels' row loops),
+ * grids of the receive-side and reply kernels are sized for (default: the mean plus six
+ * standard deviations; 0 = the whole capacity; a rank that holds more is served by the kernels' row loops),
  * knob 6 = payload in MiB one launch should move per direction: a call whose ranks
  * move more than three times as much is issued as several launches over rank
  * groups of about this size (default 860; 0 = always one launch per kernel;

@@ -28,8 +28,9 @@ struct Dims {
     int tune_reduce;      // loads in flight per thread in the reduce kernel (0 = all K)
     int tune_slices;      // blocks per token in the pack kernel (0 = by row size)
     int tune_cached_mb;   // combine replies are stored through the caches up to this many MiB per call
-    int tune_grid_pct;    // row-kernel grids cover this percentage of the rows uniform routing would
-                          // bring (0 = the whole capacity); kernels loop over whatever is beyond
+    int tune_grid_pct;    // row-kernel grids cover this percentage of the rows uniform routing would bring
+                          // (0 = the whole capacity, -1 = the mean and six standard deviations); kernels
+                          // loop over whatever is beyond
     long long typ_recv_rows, typ_pair_rows;   // per rank, under uniform routing: received rows, pairs
     int tune_parts;       // workgroups per token in the reduce kernel (0 = by row size)
     int tune_order;       // test switch: order in which the send kernels take their rows

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -132,7 +133,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->tune_reduce = 0;
     D->tune_slices = 0;
     D->tune_cached_mb = kCachedReplyMiB;
-    D->tune_grid_pct = 200;
+    D->tune_grid_pct = -1;
     D->tune_cap8 = 3;
     D->tune_order = 0;
     D->tune_parts = 0;
@@ -212,12 +213,23 @@ unsigned capped_grid(long long blocks_needed, int rank_count, long long max_bloc
     return (unsigned)(g < 1 ? 1 : g);
 }
 
-// Rows a row-kernel's grid is sized for: the capacity, or (tune_grid_pct) a percentage of
-// what uniform routing would bring; the kernels loop when a rank holds more.
+// Rows a row-kernel's grid is sized for: what uniform routing would bring and six times its
+// standard deviation (at most the square root of the mean), never more than the capacity; the
+// kernels loop when a rank holds more.  Idle blocks are not free: at twice the mean the unpack
+// of a 512-token step takes 651 us, at 1.25 times 624, its combine pack 649 and 637; with few
+// rows (4 tokens per rank, 29 rows) 1.25 times is too tight: 12.0 -> 13.2 us.
 long long grid_rows(const Dims &D, long long capacity, long long typical) {
-    if (D.tune_grid_pct <= 0) return capacity;
-    const long long want = typical * D.tune_grid_pct / 100 + 1;
+    if (D.tune_grid_pct == 0) return capacity;
+    const long long want = D.tune_grid_pct > 0 ? typical * D.tune_grid_pct / 100 + 1
+                                               : typical + (long long)(6.0 * std::sqrt((double)typical)) + 1;
     return want < capacity ? want : capacity;
+}
+
+// Waves that share a row in the unpack kernel: up to four 16-byte vectors per lane.
+int unpack_waves(const Dims &D) {
+    const long long vecs = D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0);
+    const long long w = (vecs + 4 * kWave - 1) / (4 * kWave);
+    return (int)(w > 16 ? 16 : w);
 }
 
 int rows_per_block(long long row_bytes, int tune_rows) {
@@ -591,20 +603,7 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
     const bool progressive = D.flags & FL_FLAG_PROGRESSIVE_RECV;
     // Default: a gate kernel of one wave per rank polls the rank's arrival counters, and the
     // unpack kernel runs behind it in the stream on a full grid.  Stream-ordered callers need
-    // no gate.  Progressive: the unpack kernel polls itself and starts on each
-    // source's rows as they land; it may be running while senders still need somewhere to
-    // run, so it takes at most three eighths of the resident-block slots (measured best), and
-    // to keep the memory system busy with that few waves a block moves 32 KB per turn.
-    int rbk = rows_per_block(D.Bw, D.tune_rows);
-    if (progressive && D.tune_rows == 0) {
-        long long r = (32768 + D.Bw - 1) / D.Bw;
-        rbk = (int)(r > kMaxRowsPerBlock ? kMaxRowsPerBlock : r);
-    }
-    const long long worst_rows = (long long)D.N * D.T;       // received rows in use never exceed this
-    const long long max_rows = D.recv_rows < worst_rows ? D.recv_rows : worst_rows;
-    unsigned gx = capped_grid((grid_rows(D, max_rows, D.typ_recv_rows) + rbk - 1) / rbk, rc,
-                              progressive ? (long long)ctx->cu_count * D.tune_cap8 : kMaxRowBlocks);
-    if (gx < (unsigned)D.El) gx = D.El;      // the first El-1 blocks also clear padding rows
+    // no gate.
     const int *gate = nullptr;
     if (gated && !progressive) {
         if (call.first) {
@@ -614,22 +613,32 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
         }
         gate = ctx->W.gate_disp;
     }
-    {
-        LaunchTimer t(ctx, KID_DISPATCH_UNPACK, st);
-        const dim3 grid(gx, rc), block(kCopyThreads);
-        char *ex = (char *)expert_x;
-        if (progressive && D.P)
-            dispatch_unpack_kernel<true, true><<<grid, block, 0, st>>>(D, ctx->W, rb, ex, expert_scales,
-                                                                       tokens_per_expert, rbk, gate);
-        else if (progressive)
-            dispatch_unpack_kernel<true, false><<<grid, block, 0, st>>>(D, ctx->W, rb, ex, expert_scales,
-                                                                        tokens_per_expert, rbk, gate);
-        else if (D.P)
-            dispatch_unpack_kernel<false, true><<<grid, block, 0, st>>>(D, ctx->W, rb, ex, expert_scales,
-                                                                        tokens_per_expert, rbk, gate);
-        else
-            dispatch_unpack_kernel<false, false><<<grid, block, 0, st>>>(D, ctx->W, rb, ex, expert_scales,
-                                                                         tokens_per_expert, rbk, gate);
+    const long long worst_rows = (long long)D.N * D.T;       // received rows in use never exceed this
+    const long long max_rows = D.recv_rows < worst_rows ? D.recv_rows : worst_rows;
+    const long long rows = grid_rows(D, max_rows, D.typ_recv_rows);
+    char *ex = (char *)expert_x;
+    LaunchTimer t(ctx, KID_DISPATCH_UNPACK, st);
+    if (progressive) {
+        // The unpack kernel polls itself and starts on each
+        // source's rows as they land; it may be running while senders still need somewhere to
+        // run, so it takes at most three eighths of the resident-block slots (measured best), and
+        // to keep the memory system busy with that few waves a block moves 32 KB per turn.
+        int rbk = rows_per_block(D.Bw, D.tune_rows);
+        if (D.tune_rows == 0) {
+            long long n = (32768 + D.Bw - 1) / D.Bw;
+            rbk = (int)(n > kMaxRowsPerBlock ? kMaxRowsPerBlock : n);
+        }
+        unsigned gx = capped_grid((rows + rbk - 1) / rbk, rc, (long long)ctx->cu_count * D.tune_cap8);
+        if (gx < (unsigned)D.El) gx = D.El;      // the first El-1 blocks also clear padding rows
+        auto kernel = D.P ? dispatch_unpack_polling_kernel<true> : dispatch_unpack_polling_kernel<false>;
+        kernel<<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, ctx->W, rb, ex, expert_scales, tokens_per_expert, rbk);
+    } else {
+        const int G = unpack_waves(D), wpb = kCopyThreads / kWave;
+        unsigned gx = capped_grid((rows * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);
+        if (gx < (unsigned)D.El) gx = (unsigned)((D.El + G - 1) / G * G);
+        auto kernel = D.P ? dispatch_unpack_kernel<true> : dispatch_unpack_kernel<false>;
+        kernel<<<dim3(gx, rc), dim3(kCopyThreads), kUnpackLdsBytes, st>>>(D, ctx->W, rb, ex, expert_scales,
+                                                                          tokens_per_expert, G, gate);
     }
     return launch_status();
 }
@@ -834,7 +843,7 @@ int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value) {
         case 2: break;                         // shaped a copy kernel that is no longer launched: accepted, no effect
         case 3: if (value > 16) return FL_ERR_INVALID_ARG; ctx->D.tune_slices = dflt ? 0 : value; break;
         case 4: ctx->D.tune_cached_mb = dflt ? kCachedReplyMiB : value; break;
-        case 5: if (value > 1000) return FL_ERR_INVALID_ARG; ctx->D.tune_grid_pct = dflt ? 200 : value; break;
+        case 5: if (value > 1000) return FL_ERR_INVALID_ARG; ctx->D.tune_grid_pct = value; break;
         case 6: ctx->launch_mb = dflt ? kLaunchMiB : value; break;
         case 7: if (value > 8 || value == 0) return FL_ERR_INVALID_ARG; ctx->D.tune_cap8 = dflt ? 3 : value; break;
         case 8: if (value > 2) return FL_ERR_INVALID_ARG; ctx->D.tune_order = dflt ? 0 : value; break;

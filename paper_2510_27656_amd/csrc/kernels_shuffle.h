@@ -397,47 +397,19 @@ __global__ __launch_bounds__(kWave) void arrival_gate_kernel(Dims D, Tables W, i
 }
 
 // ------------------------------------------------------------------ dispatch: unpack
-// Receiver half at rank d.  A block takes a chunk of received rows, waits
-// (bounded) for the arrival counters of the sources those rows came from, and
-// writes every row once per local expert that wants it, at
+// Receiver half at rank d: every received row is written once per local expert that
+// wants it, at
 //   base_x[d][local expert][source] + rank carried in the sidecar,
 // which is the (expert, source rank, token) order of the grouped layout.
 //
-// FENCED (progressive mode): the kernel may have been started before any payload
-// exists, on a grid that is a fraction of the machine, so a block walks many
-// chunks.  It keeps the set of sources it has seen complete: a chunk whose
-// sources are all in the set costs no poll; otherwise one wave polls the
-// counters of ALL sources at once (one load per lane), waits until the chunk's
-// own sources are complete, and invalidates the caches once, because it is about
-// to rely on arrivals it had not seen before.  That is the whole visibility
-// rule: payload and sidecar of a source are read only after its counter was
-// seen complete and the caches were invalidated after that observation (a line
-// fetched earlier, for a neighbouring row, may hold this source's bytes from
-// before they landed; a line fetched later cannot).  The chunk's first payload
-// loads are issued before its sidecars are decoded, so a chunk costs one memory
-// round trip, not four.
-template <bool FENCED, bool PRIVATE>   // PRIVATE: the receive buffer has private slots (P > 0)
-__global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_kernel(
-    Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
-    float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int rows_per_block,
-    const int *__restrict__ gate /* [N] or null: a gate kernel's verdict, 0 = its wait gave up */) {
-    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
-    __shared__ int off[FL_MAX_RANKS + 1];
-    __shared__ int dst_rows[kMaxRowsPerBlock][FL_MAX_TOPK];
-    __shared__ int dst_cnt[kMaxRowsPerBlock];
-    __shared__ int src_phys[kMaxRowsPerBlock];      // with private slots: buffer row of each received row
-    __shared__ int timed_out;
-    __shared__ unsigned long long seen_pub;         // FENCED: wave 0 publishes the set of complete sources
-    // first round of loads, all independent: the verdicts, the rows in use, the source offsets
-    const int plan_ok = W.plan_ok[d], gate_ok = gate ? gate[d] : 1;
-    const int total = W.recv_off[(size_t)d * (N + 1) + N];
-    const int off_mine = tid <= N ? W.recv_off[(size_t)d * (N + 1) + tid] : 0;
-    if (!plan_ok) return;
-    if (!gate_ok) return;                           // the arrival wait timed out (status already latched)
+// What both unpack kernels do beside the rows: block 0 hands the counts to the caller,
+// the first blocks clear the padding between the experts when asked to.
+__device__ inline void unpack_extras(const Dims &D, const Tables &W, int d, int tid, char *xd, float *expert_scales,
+                                     int *tokens_per_expert) {
+    const int El = D.El;
     if (blockIdx.x == 0)
         for (int j = tid; j < El; j += kCopyThreads)
             tokens_per_expert[(size_t)d * El + j] = W.G[(size_t)d * El + j];
-    char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
     if ((D.flags & FL_FLAG_ZERO_PAD) && (int)blockIdx.x < El - 1) {
         const int j = blockIdx.x;
         const long long lo = W.expert_off[(size_t)d * (El + 1) + j] + W.G[(size_t)d * El + j];
@@ -450,6 +422,145 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_kernel(
             for (long long v = tid; v < (hi - lo) * D.scales_per_row; v += kCopyThreads) sp[v] = 0.f;
         }
     }
+}
+
+// Rows that have landed before the kernel starts (behind a gate kernel, or in the caller's
+// stream order).  Bound by memory traffic in large steps and by the chain of dependent loads
+// in small ones, so a wave works alone, without LDS or barriers: offsets and verdicts in one
+// round, by a ballot over the offsets the row's source, then the wave's share of the row
+// together with the sidecar, then, lane k for the k-th copy, its place, then the stores.
+// (Loading the payload in the first round as well, before the number of rows is known, fetches
+// rows nobody has: 151 -> 205 us.)  Large steps want fewer loads in flight than a
+// compute unit can hold waves for: kUnpackLdsBytes keeps five workgroups on each instead of
+// eight (128 tokens, 14 KB rows: 160 us at eight, 156 at six, 147 at five and four; small
+// steps and shorter rows measure the same).  Against a block that planned its rows in LDS
+// first: 4 tokens 12.0 -> 9.7 us, 128: 151 -> 147, e4m3 75 -> 72, 6.7 KB rows 31 -> 29.
+constexpr int kUnpackLdsBytes = 32 << 10;
+template <bool PRIVATE>   // the receive buffer has private slots (P > 0): a row's place depends on its source
+__global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
+    Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
+    float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int waves_per_row,
+    const int *__restrict__ gate /* [N] or null: a gate kernel's verdict, 0 = its wait gave up */) {
+    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
+    const int lane = tid & (kWave - 1);
+    const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int G = waves_per_row, sub = wave % G;
+    const int row_step = (int)(gridDim.x * (kCopyThreads / kWave)) / G;     // the grid is a multiple of G blocks
+    const char *recv = W.bufB + (size_t)d * D.bufB_rank_bytes;
+    const int nvec = (int)(D.Be / 16);
+    // e4m3: when the scales of a row are a whole number of 16-byte vectors they are moved by
+    // the same loop (the vectors after the code bytes go to expert_scales)
+    const bool scales_as_vectors = D.scales_per_row > 0 && D.scales_per_row % 4 == 0;
+    const int rowvec = nvec + (scales_as_vectors ? D.scales_per_row / 4 : 0);
+    const int v0 = sub * kWave + lane, step = G * kWave;   // lane's first vector of the row, distance to the next
+    constexpr int U = 4;
+    v4u val[U];
+    unsigned m = kNoEntry;
+    auto load_batch = [&](int phys, int b) {
+        const v4u *src = (const v4u *)(recv + (size_t)phys * D.Bw);
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (b + i * step < rowvec) val[i] = ld_stream(src + b + i * step);
+    };
+    auto load_meta = [&](int phys) {
+        m = lane < K ? W.recv_meta[((size_t)d * D.recv_rows + phys) * D.MW + lane] : kNoEntry;
+    };
+    // first round of loads, all independent
+    int r = wave / G;
+    const int plan_ok = W.plan_ok[d], gate_ok = gate ? gate[d] : 1;
+    const int total = W.recv_off[(size_t)d * (N + 1) + N];
+    const int off = lane < N ? W.recv_off[(size_t)d * (N + 1) + lane] : 0x7fffffff;
+    const int shared_off = PRIVATE && lane < N ? W.recv_shared_off[(size_t)d * N + lane] : 0;
+    unsigned want = 0, have = 0;
+    if (!gate && lane < N) {
+        want = W.expect_disp[(size_t)d * N + lane];
+        have = ld_relaxed(W.arrive_disp + (size_t)d * N + lane);
+    }
+    if (!plan_ok || !gate_ok) return;               // step skipped, or the arrival wait timed out (already latched)
+    char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
+    unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
+    for (; r < total; r += row_step) {              // capacities are upper bounds: the grid may be smaller than the rows
+        const int s = __popcll(__ballot(off <= r)) - 1;
+        const int in_source = r - __builtin_amdgcn_readlane(off, s);
+        const int phys = PRIVATE ? recv_buffer_row(N, D.P, s, in_source, __builtin_amdgcn_readlane(shared_off, s)) : r;
+        if (!gate) {                                // stream order has made it so; checked, bounded
+            bool landed = (int)(__builtin_amdgcn_readlane(have, s) - __builtin_amdgcn_readlane(want, s)) >= 0;
+            if (!landed) {
+                for (long long spins = 0; !landed && spins < D.spin_limit; ++spins) {
+                    __builtin_amdgcn_s_sleep(64);
+                    landed = (int)(ld_relaxed(W.arrive_disp + (size_t)d * N + s) - __builtin_amdgcn_readlane(want, s)) >= 0;
+                }
+                if (!landed) {
+                    if (lane == 0) latch_status(W.status, FL_STATUS_TIMEOUT);
+                    return;
+                }
+            }
+        }
+        load_batch(phys, v0);
+        load_meta(phys);
+        // copies of this row: entries come first in the sidecar
+        const int n = __popcll(__ballot(m != kNoEntry));
+        int place = 0;
+        if (m != kNoEntry) place = W.base_x[((size_t)d * El + (m >> 24)) * N + s] + (int)(m & 0xFFFFFFu);
+        for (int b = v0; b < rowvec; b += U * step) {
+            if (b != v0) load_batch(phys, b);
+            for (int k = 0; k < n; ++k) {
+                const size_t dr = (size_t)__builtin_amdgcn_readlane(place, k);
+                v4u *dst = (v4u *)(xd + dr * D.Be);
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    const int v = b + i * step;
+                    if (v < nvec) st_stream(dst + v, val[i]);
+                    else if (v < rowvec)
+                        st_stream((v4u *)(expert_scales + ((size_t)d * D.expert_cap + dr) * D.scales_per_row) + (v - nvec),
+                                  val[i]);
+                }
+            }
+        }
+        if (D.scales_per_row && !scales_as_vectors && sub == 0) {   // odd scale counts: element by element
+            const float *ssrc = (const float *)(recv + (size_t)phys * D.Bw + D.Be);
+            for (int v = lane; v < D.scales_per_row; v += kWave) {
+                const float sc = ssrc[v];
+                for (int k = 0; k < n; ++k)
+                    expert_scales[((size_t)d * D.expert_cap + __builtin_amdgcn_readlane(place, k)) * D.scales_per_row + v] = sc;
+            }
+        }
+    }
+}
+
+// Progressive mode: a block takes a chunk of received rows at a time, waits (bounded) for the
+// arrival counters of the sources those rows came from, and plans their copies in LDS.
+// The kernel may have been started before any payload
+// exists, on a grid that is a fraction of the machine, so a block walks many
+// chunks.  It keeps the set of sources it has seen complete: a chunk whose
+// sources are all in the set costs no poll; otherwise one wave polls the
+// counters of ALL sources at once (one load per lane), waits until the chunk's
+// own sources are complete, and invalidates the caches once, because it is about
+// to rely on arrivals it had not seen before.  That is the whole visibility
+// rule: payload and sidecar of a source are read only after its counter was
+// seen complete and the caches were invalidated after that observation (a line
+// fetched earlier, for a neighbouring row, may hold this source's bytes from
+// before they landed; a line fetched later cannot).  The chunk's first payload
+// loads are issued before its sidecars are decoded, so a chunk costs one memory
+// round trip, not four.
+template <bool PRIVATE>   // the receive buffer has private slots (P > 0)
+__global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
+    Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
+    float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int rows_per_block) {
+    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
+    __shared__ int off[FL_MAX_RANKS + 1];
+    __shared__ int dst_rows[kMaxRowsPerBlock][FL_MAX_TOPK];
+    __shared__ int dst_cnt[kMaxRowsPerBlock];
+    __shared__ int src_phys[kMaxRowsPerBlock];      // with private slots: buffer row of each received row
+    __shared__ int timed_out;
+    __shared__ unsigned long long seen_pub;         // wave 0 publishes the set of complete sources
+    // first round of loads, all independent: the verdict, the rows in use, the source offsets
+    const int plan_ok = W.plan_ok[d];
+    const int total = W.recv_off[(size_t)d * (N + 1) + N];
+    const int off_mine = tid <= N ? W.recv_off[(size_t)d * (N + 1) + tid] : 0;
+    if (!plan_ok) return;
+    char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
+    unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
     // grids are sized from capacities: blocks beyond the rows in use leave at once
     if ((int)blockIdx.x * rows_per_block >= total) return;
     if (tid <= N) off[tid] = off_mine;
@@ -459,49 +570,41 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_kernel(
     const int nvec = (int)(D.Be / 16);
     const bool scales_as_vectors = D.scales_per_row > 0 && D.scales_per_row % 4 == 0;
     const int rowvec = nvec + (scales_as_vectors ? D.scales_per_row / 4 : 0);
-    unsigned long long seen = 0;                    // FENCED: sources seen complete (same in every thread)
-    unsigned my_expect = 0;                         // FENCED, wave 0: lane i holds what source i must deliver
-    if (FENCED && tid < N) my_expect = W.expect_disp[(size_t)d * N + tid];
+    unsigned long long seen = 0;                    // sources seen complete (same in every thread)
+    unsigned my_expect = 0;                         // wave 0: lane i holds what source i must deliver
+    if (tid < N) my_expect = W.expect_disp[(size_t)d * N + tid];
     // capacities are upper bounds, so the grid may be smaller than the rows in use
     for (int r0 = blockIdx.x * rows_per_block; r0 < total; r0 += gridDim.x * rows_per_block) {
         const int r1 = min(r0 + rows_per_block, total);
         const int s0 = seg_of(off, N, r0), s1 = seg_of(off, N, r1 - 1);
-        if (FENCED) {
-            const unsigned long long range = ((s1 - s0 == 63) ? ~0ull : ((1ull << (s1 - s0 + 1)) - 1)) << s0;
-            if (tid < kWave) {
-                if (range & ~seen) {                // uniform: every thread holds the same `seen`
-                    long long spins = 0;
-                    for (;;) {
-                        bool ok = false;
-                        if (tid < N) ok = (int)(ld_relaxed(W.arrive_disp + (size_t)d * N + tid) - my_expect) >= 0;
-                        seen |= __ballot(ok);
-                        if (!(range & ~seen)) break;
-                        if (++spins > D.spin_limit) {
-                            if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
-                            break;
-                        }
-                        __builtin_amdgcn_s_sleep(64);
+        const unsigned long long range = ((s1 - s0 == 63) ? ~0ull : ((1ull << (s1 - s0 + 1)) - 1)) << s0;
+        if (tid < kWave) {
+            if (range & ~seen) {                // uniform: every thread holds the same `seen`
+                long long spins = 0;
+                for (;;) {
+                    bool ok = false;
+                    if (tid < N) ok = (int)(ld_relaxed(W.arrive_disp + (size_t)d * N + tid) - my_expect) >= 0;
+                    seen |= __ballot(ok);
+                    if (!(range & ~seen)) break;
+                    if (++spins > D.spin_limit) {
+                        if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
+                        break;
                     }
-                    acquire_payload<FENCED>();      // arrivals not relied on before: drop what the caches hold
+                    __builtin_amdgcn_s_sleep(64);
                 }
-                if (tid == 0) seen_pub = seen;
+                acquire_payload<true>();      // arrivals not relied on before: drop what the caches hold
             }
-        } else if (!gate && tid < kWave) {          // behind a gate kernel the counters were seen complete
-            if (!wave_wait_counters(W.arrive_disp + (size_t)d * N + s0,
-                                    W.expect_disp + (size_t)d * N + s0, 0u, s1 - s0 + 1,
-                                    D.spin_limit)) {
-                if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
-            }
+            if (tid == 0) seen_pub = seen;
         }
         __syncthreads();
         if (timed_out) return;
-        if (FENCED) seen = seen_pub;
+        seen = seen_pub;
         // e4m3: when the scales of a row are a whole number of 16-byte vectors they are
         // moved by the same loop (the vectors after the code bytes go to expert_scales)
         const int chunk = (r1 - r0) * rowvec;
-        // U loads per thread in flight.  A full grid keeps the memory system busy with 4; the
-        // capped grid of polling receivers has fewer waves per compute unit and needs 8.
-        constexpr int U = FENCED ? 8 : 4;
+        // U loads per thread in flight: a full grid keeps the memory system busy with 4; the
+        // capped grid of polling receivers has fewer waves per compute unit and needs 8
+        constexpr int U = 8;
         auto load_batch = [&](int b, v4u *val, int *row, int *col) {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
@@ -555,11 +658,9 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_kernel(
                 }
             }
         };
-        if (FENCED && !PRIVATE) {
+        if (!PRIVATE) {
             // the first batch's loads go out before the sidecars are decoded: a chunk then
-            // costs one memory round trip instead of three in a row (polling receivers run with
-            // few waves per compute unit; with a full grid the extra registers cost more occupancy
-            // than the shorter chain gains: 156 against 154 us)
+            // costs one memory round trip instead of three in a row
             v4u val[U];
             int row[U], col[U];
             load_batch(tid, val, row, col);
