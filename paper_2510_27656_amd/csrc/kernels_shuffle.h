@@ -56,6 +56,37 @@ __device__ inline int in_order(int order, int i, int n) {
     return i;
 }
 
+// Where the copies of token (s, t) go.  Lane k < K of a block's first wave fetches the k-th expert's
+// entries, lane d < N rank d's offsets, all in the kernel's first round of loads (the tables hold
+// something for every t < T; it is used only once the step and the token are known to be valid).
+// One round instead of three in a row: e4m3 pack of 128 tokens per rank 57.5 -> 52.7 us (its one
+// workgroup per row had nothing else to do meanwhile), bf16 4 / 8 tokens 10.0 / 11.4 -> 9.4 / 10.8,
+// the same from 32 tokens on.
+struct CopyPlan {
+    int row, expert, send_off, dst_off;
+    unsigned meta;
+    __device__ inline void load(const Dims &D, const Tables &W, const int *indices, int s, size_t pair0, int lane) {
+        row = -1; expert = 0; meta = 0; send_off = 0; dst_off = 0;
+        if (lane < D.K) {
+            row = W.send_row[pair0 + lane];
+            expert = indices[pair0 + lane];
+            meta = W.pair_meta[pair0 + lane];
+        }
+        if (lane < D.N) {
+            send_off = W.send_off[(size_t)s * (D.N + 1) + lane];
+            dst_off = W.dst_off[(size_t)s * D.N + lane];
+        }
+    }
+    // destination rank of this lane's expert, and the row in its receive buffer when the token's copy
+    // for that rank belongs to this lane (the first of its experts there), else -1; whole wave
+    __device__ inline int target(const Dims &D, int s, int *dst) const {
+        const int d = expert / D.El;
+        *dst = d;
+        const int first = __shfl(send_off, d), shared = __shfl(dst_off, d);
+        return row >= 0 ? recv_buffer_row(D.N, D.P, s, row - first, shared) : -1;
+    }
+};
+
 // ------------------------------------------------------------------ dispatch: pack
 // `slices` blocks per token (s, t), each taking a slice of the row (so a thread
 // usually has a single vector): the slice is read once and stored once per
@@ -79,10 +110,10 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
     const int t = in_order(D.tune_order, blockIdx.x / slices, D.T);
     const int tid = threadIdx.x;
-    const int K = D.K, El = D.El;
-    // The slice's payload depends on nothing but (s, t): its loads are issued first, so
-    // that the validity check and the routing tables are fetched while they are in flight
-    // (x has T rows per rank, so the loads are in bounds for absent tokens too).
+    const int K = D.K;
+    // The slice's payload depends on nothing but (s, t), and neither do the routing tables'
+    // entries: everything the block needs is fetched in one round (x has T rows per rank, so
+    // the loads are in bounds for absent tokens too).
     const int nvec = (int)(src_row_bytes / 16);
     const int per = (nvec + slices - 1) / slices;          // vectors of this slice: [v0, v1)
     const int v0 = slice * per, v1 = min(v0 + per, nvec);
@@ -91,30 +122,26 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         if (v0 + tid + i * kPackThreads < v1) r[i] = ld_stream(src + v0 + tid + i * kPackThreads);
-    const int plan_ok = W.plan_ok[s];
+    const size_t pair0 = ((size_t)s * D.T + t) * K;
+    CopyPlan plan;
+    if (tid < kWave) plan.load(D, W, indices, s, pair0, tid);
+    const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
     // the sender's first block announces the transfers (a sender without tokens still announces
     // its empty ones), unless an announce kernel will
     if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,
                            tid, kPackThreads, FENCED);
-    if (!plan_ok || t >= num_tokens[s]) return;
+    if (!plan_ok || t >= tokens) return;
     __shared__ int s_row[FL_MAX_TOPK];
     __shared__ int s_dst[FL_MAX_TOPK];
     __shared__ unsigned s_meta[FL_MAX_TOPK];
-    const size_t pair0 = ((size_t)s * D.T + t) * K;
-    int my_row = -1, my_d = 0, target = 0;
-    if (tid < K) {                             // independent loads first, then one dependent level
-        my_row = W.send_row[pair0 + tid];
-        my_d = indices[pair0 + tid] / El;
-        s_meta[tid] = W.pair_meta[pair0 + tid];
-        s_dst[tid] = my_d;
-        if (my_row >= 0)                       // this copy's row in d's receive buffer
-            target = recv_buffer_row(D.N, D.P, s, my_row - W.send_off[(size_t)s * (D.N + 1) + my_d],
-                                     W.dst_off[(size_t)s * D.N + my_d]);
-        s_row[tid] = my_row >= 0 ? target : -1;
+    int target = -1, my_d = 0;                 // of this lane's copy: row in rank my_d's receive buffer
+    if (tid < kWave) {
+        target = plan.target(D, s, &my_d);
+        if (tid < K) { s_row[tid] = target; s_dst[tid] = my_d; s_meta[tid] = plan.meta; }
     }
     __syncthreads();
-    if (slice == 0 && tid < K && my_row >= 0) {   // sidecar of this copy
+    if (slice == 0 && tid < K && target >= 0) {   // sidecar of this copy
         unsigned *meta = W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW;
         int m = 0;
         for (int k = 0; k < K; ++k)
@@ -174,7 +201,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
         stores_done<FENCED>();
         __syncthreads();
         const unsigned units = (unsigned)(v1 - v0) + (with_scales ? (unsigned)((D.Bw - D.Be) / 16) : 0u);
-        if (tid < K && my_row >= 0 && units > 0)
+        if (tid < K && target >= 0 && units > 0)
             add_counter(W.arrive_disp + (size_t)my_d * D.N + s, units);
     }
 }
@@ -234,7 +261,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
     const int t = in_order(D.tune_order, blockIdx.x / slices, D.T);
     const int tid = threadIdx.x;
-    const int K = D.K, El = D.El;
+    const int K = D.K;
     // as in dispatch_pack_kernel, the payload loads go first
     const int nblk = D.scales_per_row;                          // 128-element blocks in the row
     const int blk = slice * (kQuantThreads / kQuantLanes) + tid / kQuantLanes;
@@ -246,28 +273,24 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         in0 = ld_stream(src);
         in1 = ld_stream(src + 1);
     }
-    const int plan_ok = W.plan_ok[s];
+    const size_t pair0 = ((size_t)s * D.T + t) * K;
+    CopyPlan plan;
+    if (tid < kWave) plan.load(D, W, indices, s, pair0, tid);
+    const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
     if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)   // as in dispatch_pack_kernel
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,
                            tid, kQuantThreads, FENCED);
-    if (!plan_ok || t >= num_tokens[s]) return;
+    if (!plan_ok || t >= tokens) return;
     __shared__ int s_row[FL_MAX_TOPK];
     __shared__ int s_dst[FL_MAX_TOPK];
     __shared__ unsigned s_meta[FL_MAX_TOPK];
-    const size_t pair0 = ((size_t)s * D.T + t) * K;
-    int my_row = -1, my_d = 0, target = 0;
-    if (tid < K) {
-        my_row = W.send_row[pair0 + tid];
-        my_d = indices[pair0 + tid] / El;
-        s_meta[tid] = W.pair_meta[pair0 + tid];
-        s_dst[tid] = my_d;
-        if (my_row >= 0)
-            target = recv_buffer_row(D.N, D.P, s, my_row - W.send_off[(size_t)s * (D.N + 1) + my_d],
-                                     W.dst_off[(size_t)s * D.N + my_d]);
-        s_row[tid] = my_row >= 0 ? target : -1;
+    int target = -1, my_d = 0;
+    if (tid < kWave) {
+        target = plan.target(D, s, &my_d);
+        if (tid < K) { s_row[tid] = target; s_dst[tid] = my_d; s_meta[tid] = plan.meta; }
     }
     __syncthreads();
-    if (slice == 0 && tid < K && my_row >= 0) {
+    if (slice == 0 && tid < K && target >= 0) {
         unsigned *meta = W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW;
         int m = 0;
         for (int k = 0; k < K; ++k)
@@ -335,7 +358,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         // the padding that brings a wire row to a whole number of 128-byte lines is nobody's
         // to write; the first block claims it so that a row's units add up to Bw / 16
         const int pad_units = (int)(D.Bw / 16) - (nblk * 8 + (nblk + 3) / 4);
-        if (tid < K && my_row >= 0 && n_live > 0)
+        if (tid < K && target >= 0 && n_live > 0)
             add_counter(W.arrive_disp + (size_t)my_d * D.N + s,
                         (unsigned)(n_live * 8 + (n_live + 3) / 4 + (slice == 0 ? pad_units : 0)));
     }
