@@ -225,9 +225,9 @@ long long grid_rows(const Dims &D, long long capacity, long long typical) {
     return want < capacity ? want : capacity;
 }
 
-// Waves that share a row in the unpack kernel: up to four 16-byte vectors per lane.
-int unpack_waves(const Dims &D) {
-    const long long vecs = D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0);
+// Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
+// to four vectors per lane.
+int waves_per_row(long long vecs) {
     const long long w = (vecs + 4 * kWave - 1) / (4 * kWave);
     return (int)(w > 16 ? 16 : w);
 }
@@ -633,11 +633,12 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
         auto kernel = D.P ? dispatch_unpack_polling_kernel<true> : dispatch_unpack_polling_kernel<false>;
         kernel<<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, ctx->W, rb, ex, expert_scales, tokens_per_expert, rbk);
     } else {
-        const int G = unpack_waves(D), wpb = kCopyThreads / kWave;
+        const int G = waves_per_row(D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0));
+        const int wpb = kCopyThreads / kWave;
         unsigned gx = capped_grid((rows * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);
         if (gx < (unsigned)D.El) gx = (unsigned)((D.El + G - 1) / G * G);
         auto kernel = D.P ? dispatch_unpack_kernel<true> : dispatch_unpack_kernel<false>;
-        kernel<<<dim3(gx, rc), dim3(kCopyThreads), kUnpackLdsBytes, st>>>(D, ctx->W, rb, ex, expert_scales,
+        kernel<<<dim3(gx, rc), dim3(kCopyThreads), kRowWavesLdsBytes, st>>>(D, ctx->W, rb, ex, expert_scales,
                                                                           tokens_per_expert, G, gate);
     }
     return launch_status();
@@ -671,16 +672,18 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
     {
         const dim3 grid(gx, rc), block(kCopyThreads);
         const char *yp = (const char *)expert_y;
+        LaunchTimer t(ctx, partial ? KID_COMBINE_PARTIAL_PACK : KID_COMBINE_PACK, st);
         if (partial) {
-            LaunchTimer t(ctx, KID_COMBINE_PARTIAL_PACK, st);
             auto kernel = fenced ? combine_partial_pack_kernel<true, true>
                           : cached ? combine_partial_pack_kernel<false, true> : combine_partial_pack_kernel<false, false>;
             kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
+        } else if (fenced) {
+            combine_pack_progressive_kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         } else {
-            LaunchTimer t(ctx, KID_COMBINE_PACK, st);
-            auto kernel = fenced ? combine_pack_kernel<true, true>
-                          : cached ? combine_pack_kernel<false, true> : combine_pack_kernel<false, false>;
-            kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
+            const int G = waves_per_row(D.Bc / 16), wpb = kCopyThreads / kWave;
+            const unsigned gw = capped_grid((reply_grid * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);
+            auto kernel = cached ? combine_pack_kernel<true> : combine_pack_kernel<false>;
+            kernel<<<dim3(gw, rc), block, kRowWavesLdsBytes, st>>>(D, W, rb, yp, G);
         }
     }
     if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {

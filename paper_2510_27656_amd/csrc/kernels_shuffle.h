@@ -454,11 +454,11 @@ __device__ inline void unpack_extras(const Dims &D, const Tables &W, int d, int 
 // together with the sidecar, then, lane k for the k-th copy, its place, then the stores.
 // (Loading the payload in the first round as well, before the number of rows is known, fetches
 // rows nobody has: 151 -> 205 us.)  Large steps want fewer loads in flight than a
-// compute unit can hold waves for: kUnpackLdsBytes keeps five workgroups on each instead of
+// compute unit can hold waves for: kRowWavesLdsBytes keeps five workgroups on each instead of
 // eight (128 tokens, 14 KB rows: 160 us at eight, 156 at six, 147 at five and four; small
 // steps and shorter rows measure the same).  Against a block that planned its rows in LDS
 // first: 4 tokens 12.0 -> 9.7 us, 128: 151 -> 147, e4m3 75 -> 72, 6.7 KB rows 31 -> 29.
-constexpr int kUnpackLdsBytes = 32 << 10;
+constexpr int kRowWavesLdsBytes = 32 << 10;
 template <bool PRIVATE>   // the receive buffer has private slots (P > 0): a row's place depends on its source
 __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
@@ -725,10 +725,64 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
 // Rank d sends every source s the rows of its experts that belong to s (contiguous
 // per expert in the grouped layout) as one contiguous reply, into s's combine receive
 // buffer: reply row q of source s and local expert j comes from expert-major row
-// base_x[d][j][s] + (q - cs_base[d][s][j]).  FENCED as in the dispatch pack kernel (the
-// block adds each row's units to arrive[source][this rank] itself).
-template <bool FENCED, bool CACHED>   // CACHED: see st_payload
-__global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
+// base_x[d][j][s] + (q - cs_base[d][s][j]).
+//
+// A wave works alone on its share of a row, as in the unpack kernel: the row's source by a
+// ballot over the reply offsets, its expert by one over the source's per-expert offsets
+// (fetched together with the expert rows they stand for), then the copy: three dependent
+// rounds of loads and no barrier, against five and two when a workgroup planned its rows in LDS.
+// Bound by memory traffic from 32 tokens on (6.5 TB/s at 128 tokens, the plain copy's rate),
+// by the chain below.  Before -> now: 4 tokens 11.6 -> 11.0 us, 8: 15.9 -> 15.0, 32: 40.7 -> 39.5,
+// 128: 144.5 -> 144, 512: 649 -> 631 (672 with eight workgroups per unit).
+template <bool CACHED>   // CACHED: see st_payload
+__global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
+    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
+    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
+    const int lane = tid & (kWave - 1);
+    const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int G = waves_per_row, sub = wave % G;
+    const int row_step = (int)(gridDim.x * (kCopyThreads / kWave)) / G;     // the grid is a multiple of G blocks
+    const int nvec = (int)(D.Bc / 16), v0 = sub * kWave + lane, step = G * kWave;
+    // one round of loads
+    const int plan_ok = W.plan_ok[d];
+    const int total = W.cs_off[(size_t)d * (N + 1) + N];
+    const int off = lane < N ? W.cs_off[(size_t)d * (N + 1) + lane] : 0x7fffffff;
+    const int reply = lane < N ? W.comb_dst_off[(size_t)d * N + lane] : 0;
+    if (!plan_ok) return;
+    // stream-ordered: the rank's first block announces the replies (a rank without rows its empty ones)
+    if ((D.flags & FL_FLAG_STREAM_ORDERED) && blockIdx.x == 0)
+        announce_transfers(W.cs_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads);
+    const char *yd = expert_y + (size_t)d * D.expert_cap * D.Bc;
+    for (int i = wave / G; i < total; i += row_step) {      // capacities are upper bounds: the grid may be smaller
+        const int q = in_order(D.tune_order, i, total);
+        const int s = __popcll(__ballot(off <= q)) - 1;
+        int src_row = 0;                                    // of the last expert whose rows for s start at or before q
+        for (int j0 = 0; j0 < El; j0 += kWave) {
+            const bool in = j0 + lane < El;
+            const int first = in ? W.cs_base[((size_t)d * N + s) * El + j0 + lane] : 0x7fffffff;
+            const int base = in ? W.base_x[((size_t)d * El + j0 + lane) * N + s] : 0;
+            const int j = __popcll(__ballot(first <= q)) - 1;
+            if (j >= 0) src_row = __builtin_amdgcn_readlane(base, j) + q - __builtin_amdgcn_readlane(first, j);
+            if (j < kWave - 1) break;
+        }
+        const v4u *src = (const v4u *)(yd + (size_t)src_row * D.Bc);
+        v4u *dst = (v4u *)(W.bufA + (size_t)s * D.bufA_rank_bytes +
+                           (size_t)(__builtin_amdgcn_readlane(reply, s) + q - __builtin_amdgcn_readlane(off, s)) * D.Bc);
+        for (int b = v0; b < nvec; b += 4 * step) {
+            v4u val[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b + u * step < nvec) val[u] = ld_stream(src + b + u * step);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (b + u * step < nvec) st_payload<false, CACHED>(dst + b + u * step, val[u]);
+        }
+    }
+}
+
+// Progressive mode: a workgroup per chunk of rows, written through; it adds each row's units
+// to arrive[source][this rank] itself, once per row rather than once per wave.
+__global__ __launch_bounds__(kCopyThreads) void combine_pack_progressive_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
     __shared__ int off[FL_MAX_RANKS + 1];
@@ -737,9 +791,9 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
     if (!W.plan_ok[d]) return;
     const int nvec = (int)(D.Bc / 16);
     // the rank's first block announces the replies (a rank without rows its empty ones)
-    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)
+    if (blockIdx.x == 0)
         announce_transfers(W.cs_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads,
-                           FENCED);
+                           true);
     // grids are sized from capacities: blocks beyond the rows in use leave at once
     const int total = W.cs_off[(size_t)d * (N + 1) + N];
     if ((int)blockIdx.x * rows_per_block >= total) return;
@@ -759,18 +813,15 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_kernel(
             push_to[tid] = make_int2(s, W.comb_dst_off[(size_t)d * N + s] + (q - off[s]));
         }
         __syncthreads();
-        copy_rows_flat<kCopyThreads, FENCED, CACHED>(
+        copy_rows_flat<kCopyThreads>(
             q1 - q0, nvec, tid,
             [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
             [&](int r) {
                 return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Bc;
             });
-        if (FENCED) {
-            stores_done<FENCED>();
-            __syncthreads();
-            if (tid < q1 - q0)
-                add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
-        }
+        stores_done<true>();
+        __syncthreads();
+        if (tid < q1 - q0) add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
         __syncthreads();                       // the row plan is rewritten by the next chunk
     }
 }
