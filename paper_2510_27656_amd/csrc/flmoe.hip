@@ -673,17 +673,16 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
         const dim3 grid(gx, rc), block(kCopyThreads);
         const char *yp = (const char *)expert_y;
         LaunchTimer t(ctx, partial ? KID_COMBINE_PARTIAL_PACK : KID_COMBINE_PACK, st);
-        if (partial) {
-            auto kernel = fenced ? combine_partial_pack_kernel<true, true>
-                          : cached ? combine_partial_pack_kernel<false, true> : combine_partial_pack_kernel<false, false>;
+        if (fenced) {
+            auto kernel = partial ? combine_partial_pack_progressive_kernel : combine_pack_progressive_kernel;
             kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
-        } else if (fenced) {
-            combine_pack_progressive_kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         } else {
             const int G = waves_per_row(D.Bc / 16), wpb = kCopyThreads / kWave;
             const unsigned gw = capped_grid((reply_grid * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);
-            auto kernel = cached ? combine_pack_kernel<true> : combine_pack_kernel<false>;
-            kernel<<<dim3(gw, rc), block, kRowWavesLdsBytes, st>>>(D, W, rb, yp, G);
+            auto kernel = partial ? cached ? combine_partial_pack_kernel<true> : combine_partial_pack_kernel<false>
+                                  : cached ? combine_pack_kernel<true> : combine_pack_kernel<false>;
+            // partial sums read several rows per row written: no need to hold back workgroups (see the kernel)
+            kernel<<<dim3(gw, rc), block, partial ? 0 : kRowWavesLdsBytes, st>>>(D, W, rb, yp, G);
         }
     }
     if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {

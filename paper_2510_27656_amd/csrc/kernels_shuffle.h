@@ -843,8 +843,76 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // share of received row number i from source s goes back to row
 // ret_off[d][s] + i of s's combine receive buffer, the position of the token copy among
 // all copies s sent, so s finds it through its own send_row table.
-template <bool FENCED, bool CACHED>   // CACHED: see st_payload
+//
+// A wave works alone on its share of a row, as in the unpack and combine pack kernels: the
+// row's source by a ballot, lane k for the sidecar's k-th entry, its expert row and its weight,
+// then the sum.  Bound by reads (P rows read, D written); workgroups are not held back here: the
+// same five per unit as the plain copy takes measured 30 us where all eight take 26 (6.7 KB rows).
+// Against a workgroup that planned its rows in LDS: 301 tokens x 8 ranks, 6.7 KB rows 30.6 -> 26.1 us;
+// 14 KB rows, 32 ranks: 8 tokens 20.4 -> 16.1, 128: 147 -> 136, 512: 641 -> 627.
+template <bool CACHED>   // CACHED: see st_payload
 __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
+    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
+    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
+    const int lane = tid & (kWave - 1);
+    const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int G = waves_per_row, sub = wave % G;
+    const int row_step = (int)(gridDim.x * (kCopyThreads / kWave)) / G;     // the grid is a multiple of G blocks
+    const int nvec = (int)(D.Bc / 16), v0 = sub * kWave + lane, step = G * kWave;
+    // one round of loads
+    const int plan_ok = W.plan_ok[d];
+    const int total = W.recv_off[(size_t)d * (N + 1) + N];
+    const int off = lane < N ? W.recv_off[(size_t)d * (N + 1) + lane] : 0x7fffffff;
+    const int ret = lane < N ? W.ret_off[(size_t)d * N + lane] : 0;
+    const int shared_off = D.P && lane < N ? W.recv_shared_off[(size_t)d * N + lane] : 0;
+    if (!plan_ok) return;
+    if ((D.flags & FL_FLAG_STREAM_ORDERED) && blockIdx.x == 0)   // as in combine_pack_kernel
+        announce_transfers(W.recv_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads);
+    const char *yd = expert_y + (size_t)d * D.expert_cap * D.Bc;
+    for (int c = wave / G; c < total; c += row_step) {
+        const int r = in_order(D.tune_order, c, total);
+        const int s = __popcll(__ballot(off <= r)) - 1;
+        const int i = r - __builtin_amdgcn_readlane(off, s);
+        const int phys = D.P ? recv_buffer_row(N, D.P, s, i, __builtin_amdgcn_readlane(shared_off, s)) : r;
+        const unsigned *meta = W.recv_meta + ((size_t)d * D.recv_rows + phys) * D.MW;
+        const unsigned m = lane < K ? meta[lane] : kNoEntry;
+        const unsigned weight = lane < K ? meta[D.KM + lane] : 0u;
+        const int n = __popcll(__ballot(m != kNoEntry));       // entries come first in the sidecar
+        int place = 0;
+        if (m != kNoEntry) place = W.base_x[((size_t)d * El + (m >> 24)) * N + s] + (int)(m & 0xFFFFFFu);
+        char *dst = W.bufA + (size_t)s * D.bufA_rank_bytes + (size_t)(__builtin_amdgcn_readlane(ret, s) + i) * D.Bc;
+        constexpr int U = 4;
+        for (int b = v0; b < nvec; b += U * step) {
+            float acc[U][8];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[u][e] = 0.f;
+            for (int k = 0; k < n; ++k) {
+                const v4u *src = (const v4u *)(yd + (size_t)__builtin_amdgcn_readlane(place, k) * D.Bc);
+                const float wk = __uint_as_float(__builtin_amdgcn_readlane(weight, k));
+                v4u y[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (b + u * step < nvec) y[u] = ld_stream(src + b + u * step);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (b + u * step < nvec) fma8(acc[u], wk, y[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (b + u * step < nvec) {
+                    v4u o;
+                    o.x = pack_bf16x2(acc[u][0], acc[u][1]); o.y = pack_bf16x2(acc[u][2], acc[u][3]);
+                    o.z = pack_bf16x2(acc[u][4], acc[u][5]); o.w = pack_bf16x2(acc[u][6], acc[u][7]);
+                    st_payload<false, CACHED>((v4u *)dst + b + u * step, o);
+                }
+        }
+    }
+}
+
+// Progressive mode: a workgroup per chunk of rows, written through, adding each row's units itself.
+__global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_progressive_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
     __shared__ int off[FL_MAX_RANKS + 1];
@@ -854,9 +922,9 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
     __shared__ int2 share_to[kMaxRowsPerBlock];
     if (!W.plan_ok[d]) return;
     const int nvec = (int)(D.Bc / 16);
-    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)   // as in combine_pack_kernel
+    if (blockIdx.x == 0)
         announce_transfers(W.recv_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads,
-                           FENCED);
+                           true);
     const int total = W.recv_off[(size_t)d * (N + 1) + N];
     if ((int)blockIdx.x * rows_per_block >= total) return;
     if (tid <= N) off[tid] = W.recv_off[(size_t)d * (N + 1) + tid];
@@ -912,15 +980,12 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
                 o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
                 o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
                 char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Bc;
-                st_payload<FENCED, CACHED>((v4u *)dst + col[u], o);
+                st_payload<true, true>((v4u *)dst + col[u], o);
             }
         }
-        if (FENCED) {
-            stores_done<FENCED>();
-            __syncthreads();
-            if (tid < r1 - r0)
-                add_counter(W.arrive_comb + (size_t)share_to[tid].x * N + d, (unsigned)nvec);
-        }
+        stores_done<true>();
+        __syncthreads();
+        if (tid < r1 - r0) add_counter(W.arrive_comb + (size_t)share_to[tid].x * N + d, (unsigned)nvec);
         __syncthreads();                       // the row plan is rewritten by the next chunk
     }
 }
