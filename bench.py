@@ -651,8 +651,8 @@ def main():
         "hip_graph_replay": graph_line,
         "step_us": round(ms_per_step * 1e3, 1),
         "gbps_note": "GB/s divides the method's OWN algorithmic bytes by its step time: compare methods "
-                     "by step_us, not by GB/s.  Lines from before the send buffers were dropped counted 4649 MB "
-                     "for the decode step, 1.6 times what it moves now",
+                     "by step_us, not by GB/s.  With send buffers the decode step counted 4649 MB, 1.6 times "
+                     "what it moves now",
         "modes_measured_in_turns": modes,
         "other_workloads": others,
         "interleaved_caller_work": interleaved,

@@ -27,7 +27,7 @@ constexpr int kMaxRowsPerBlock = 64;
 // is announced too (section TransferEngine: an immediate is delivered even for a
 // zero-size write) and a receiver that has seen all its counters complete knows that
 // every peer's send call has got as far as announcing - which is what makes the re-use
-// of the staging buffers safe without a separate barrier.
+// of the receive buffers safe without a separate barrier.
 //
 // Stream-ordered mode: one add per (sender, receiver) announces the whole
 // transfer, like the single immediate a NIC delivers after a WRITE (section

@@ -194,6 +194,27 @@ def test_layout_at_the_edges_of_tiles_blocks_and_records(shape, ragged):
     sh.close()
 
 
+# (ranks, experts, tokens, hidden, top-k, dtype): one vector per row; a wave's four vectors per lane one short,
+# full and one over; more vectors than sixteen waves take at once; more experts per rank than a wave has lanes,
+# exactly as many, and the most; e4m3 rows whose scales are and are not whole vectors, and the longest of them
+ROW_EDGES = [(4, 32, 30, 8, 4, "bf16"), (4, 32, 30, 2040, 4, "bf16"), (4, 32, 30, 2048, 4, "bf16"),
+             (4, 32, 30, 2056, 4, "bf16"), (2, 8, 9, 40000, 3, "bf16"), (2, 256, 24, 64, 8, "bf16"),
+             (3, 192, 24, 64, 8, "bf16"), (1, 256, 70, 64, 16, "bf16"), (64, 128, 6, 264, 16, "bf16"),
+             (4, 32, 30, 3968, 4, "e4m3"), (4, 32, 30, 4096, 4, "e4m3"), (2, 8, 9, 66048, 3, "e4m3")]
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(ordering="stream"), dict(private_rows=5), dict(partial=True),
+                                dict(partial=True, private_rows=3, ordering="stream")],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("shape", ROW_EDGES, ids=str)
+def test_rows_at_the_edges_of_a_waves_share(shape, kw):
+    """Whole steps where the kernels that move rows by single waves change their split: bit for bit."""
+    N, E, T, H, K, dtype = shape
+    wl = wlmod.custom("row_edges", N, E, T, H, K, seed=H + K, ragged=True, dispatch_dtype=dtype)
+    sh, _, _ = run_and_compare(wlmod.make_inputs(wl), align=4, zero_pad=True, **kw)
+    sh.close()
+
+
 @pytest.mark.parametrize("partial", [False, True])
 @pytest.mark.parametrize("name", ["ragged_520", "multi_tile"])
 def test_replies_past_the_caches(name, partial):
