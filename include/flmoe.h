@@ -388,7 +388,7 @@ const char *fl_moe_strerror(int code);
 int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
 
 /* Diagnostic: overrides a launch-shape knob of the copy kernels (results never
- * change).  knob 0 = rows per workgroup of the polling unpack / combine-pack kernels
+ * change).  knob 0 = rows per workgroup of the unpack / reply kernels that take chunks of rows
  * (0 = chosen from the row size, at most 64), knob 1 = row loads issued together
  * per thread in combine_reduce (0 = all K, at most 8), knob 2 = accepted without
  * effect (it shaped a copy kernel that is no longer launched), knob 3 =
@@ -416,6 +416,16 @@ int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value);
  * when the call is not cut; the last group may be smaller). */
 int fl_moe_debug_launch_groups(const fl_moe_config *cfg /*host*/, int rank_count, int launch_mb,
                                int *ranks_per_group /*host*/);
+
+/* Diagnostic, host only (no GPU needed): which forms of its kernels one launch over
+ * `rank_count` ranks of this configuration takes, on a whole MI355X. */
+typedef struct fl_moe_launch_plan {
+    int32_t unpack_by_chunks;    /* 1: dispatch_recv moves rows by workgroups that plan a chunk of rows,
+                                    0: by waves on their own                                        */
+    int32_t replies_by_chunks;   /* the same of combine_send                                        */
+} fl_moe_launch_plan;
+int fl_moe_debug_launch_plan(const fl_moe_config *cfg /*host*/, int rank_count,
+                             fl_moe_launch_plan *out /*host*/);
 
 /* Diagnostic: plain linear device copy of `bytes` bytes with 16-byte accesses
  * (multiple of 16, both pointers 16-byte aligned), in the launch shape that measured

@@ -255,7 +255,7 @@ __device__ inline void st_payload(v4u *p, v4u v) {
 // A block copies `nrows` rows of `nvec` vectors each; vector v of the chunk lies
 // in row v / nvec.  src_of(row) / dst_of(row) return the row's byte address.
 // All loads of a batch are issued before its stores.
-template <int NT, class SrcFn, class DstFn>
+template <int NT, bool FENCED, bool CACHED, class SrcFn, class DstFn>
 __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of, DstFn dst_of) {
     if (nrows == 1) {                          // one row per block: addresses are uniform
         const v4u *s = (const v4u *)src_of(0);
@@ -267,7 +267,7 @@ __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of
                 if (b + i * NT < nvec) r[i] = ld_stream(s + b + i * NT);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (b + i * NT < nvec) st_payload<true, true>(d + b + i * NT, r[i]);
+                if (b + i * NT < nvec) st_payload<FENCED, CACHED>(d + b + i * NT, r[i]);
         }
         return;
     }
@@ -287,7 +287,7 @@ __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int v = b + i * NT;
-            if (v < total) st_payload<true, true>((v4u *)dst_of(row[i]) + col[i], r[i]);
+            if (v < total) st_payload<FENCED, CACHED>((v4u *)dst_of(row[i]) + col[i], r[i]);
         }
     }
 }

@@ -45,6 +45,7 @@ constexpr long long kMaxRowBlocks = 1 << 18;      // blocks with barriers: loop 
 constexpr long long kDefaultSpin = 1 << 20;       // polls about 2 us apart: gives up after about 2 s
 
 constexpr size_t kBigPage = 2u << 20;
+constexpr int kComputeUnits = 256;                // of the part, where a context has not asked the device
 constexpr int kCachedReplyMiB = 1024;
 constexpr int kLaunchMiB = 860;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -225,6 +226,32 @@ long long grid_rows(const Dims &D, long long capacity, long long typical) {
     return want < capacity ? want : capacity;
 }
 
+// Whether the unpack or a reply kernel moves its rows by workgroups that plan a chunk of rows and copy it as one
+// run of vectors (true), or by a wave per row or share of a row (false).  Waves of their own have the shorter chain
+// of loads, but a short row leaves most lanes idle, and once there are more rows than waves fit on the machine at
+// once (five workgroups of four per compute unit) the rate at which waves start and end bounds the kernel, some
+// 0.6 ns per row however short.  16 ranks, top 8, us of unpack / combine pack, waves against chunks:
+//   128-byte rows: 16 tokens per rank 7.3 / 6.9 against 8.1 / 7.2, 32: 7.9 / 7.3 and 8.5 / 7.1, 64: 10.3 / 9.4 and
+//     8.4 / 6.9, 256: 23 / 21 and 9.4 / 8.3, 4096: 262 / 264 and 28 / 32
+//   1 KB rows: 64 tokens 11.2 / 12.7 and 10.9 / 10.7, 1024: 72 / 82 and 48 / 45
+//   2 KB rows: 32 tokens 8.6 / 10.6 and 10.4 / 10.3, 1024: 86 / 101 and 77 / 84
+//   3 KB rows: 1024 tokens 116 / 124 and 125 / 125, longer ones up to 7 % in favour of waves
+// The partial-sum pack reads several rows per row written, so its lanes have more to do: 1.5 KB rows, 1024 tokens
+// 76 and 65, 2 KB rows, 256 tokens 27.7 and 29.7.
+constexpr long long kChunkRowBytes = 2048, kChunkPartialRowBytes = 1536;
+constexpr long long kRowWavesPerUnit = 5 * kCopyThreads / kWave;
+bool by_chunks(const Dims &D, int cu_count, long long row_bytes, long long max_row_bytes, long long rows) {
+    return (D.flags & FL_FLAG_PROGRESSIVE_RECV) || (row_bytes <= max_row_bytes && rows > kRowWavesPerUnit * cu_count);
+}
+bool unpack_by_chunks(const Dims &D, int cu_count, int rank_count) {
+    return by_chunks(D, cu_count, D.Be, kChunkRowBytes, std::min(D.typ_recv_rows, D.recv_rows) * rank_count);
+}
+bool replies_by_chunks(const Dims &D, int cu_count, int rank_count) {
+    const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
+    const long long rows = partial ? std::min(D.typ_recv_rows, D.recv_rows) : std::min(D.typ_pair_rows, D.expert_cap);
+    return by_chunks(D, cu_count, D.Bc, partial ? kChunkPartialRowBytes : kChunkRowBytes, rows * rank_count);
+}
+
 // Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
 // to four vectors per lane.
 int waves_per_row(long long vecs) {
@@ -248,7 +275,7 @@ struct fl_moe_ctx {
     size_t workspace_bytes;
     const int32_t *indices = nullptr;
     const int32_t *num_tokens = nullptr;
-    int cu_count = 256;
+    int cu_count = kComputeUnits;
     int launch_mb = kLaunchMiB;   // payload a launch should move per direction, see ranks_per_launch
     // profiling
     int profile = 0;
@@ -618,20 +645,22 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
     const long long rows = grid_rows(D, max_rows, D.typ_recv_rows);
     char *ex = (char *)expert_x;
     LaunchTimer t(ctx, KID_DISPATCH_UNPACK, st);
-    if (progressive) {
-        // The unpack kernel polls itself and starts on each
+    if (unpack_by_chunks(D, ctx->cu_count, rc)) {
+        // Progressive: the unpack kernel polls itself and starts on each
         // source's rows as they land; it may be running while senders still need somewhere to
         // run, so it takes at most three eighths of the resident-block slots (measured best), and
         // to keep the memory system busy with that few waves a block moves 32 KB per turn.
         int rbk = rows_per_block(D.Bw, D.tune_rows);
-        if (D.tune_rows == 0) {
+        if (progressive && D.tune_rows == 0) {
             long long n = (32768 + D.Bw - 1) / D.Bw;
             rbk = (int)(n > kMaxRowsPerBlock ? kMaxRowsPerBlock : n);
         }
-        unsigned gx = capped_grid((rows + rbk - 1) / rbk, rc, (long long)ctx->cu_count * D.tune_cap8);
+        unsigned gx = capped_grid((rows + rbk - 1) / rbk, rc,
+                                  progressive ? (long long)ctx->cu_count * D.tune_cap8 : kMaxRowBlocks);
         if (gx < (unsigned)D.El) gx = D.El;      // the first El-1 blocks also clear padding rows
-        auto kernel = D.P ? dispatch_unpack_polling_kernel<true> : dispatch_unpack_polling_kernel<false>;
-        kernel<<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, ctx->W, rb, ex, expert_scales, tokens_per_expert, rbk);
+        auto kernel = progressive ? D.P ? dispatch_unpack_chunk_kernel<true, true> : dispatch_unpack_chunk_kernel<false, true>
+                                  : D.P ? dispatch_unpack_chunk_kernel<true, false> : dispatch_unpack_chunk_kernel<false, false>;
+        kernel<<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, ctx->W, rb, ex, expert_scales, tokens_per_expert, rbk, gate);
     } else {
         const int G = waves_per_row(D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0));
         const int wpb = kCopyThreads / kWave;
@@ -673,8 +702,10 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
         const dim3 grid(gx, rc), block(kCopyThreads);
         const char *yp = (const char *)expert_y;
         LaunchTimer t(ctx, partial ? KID_COMBINE_PARTIAL_PACK : KID_COMBINE_PACK, st);
-        if (fenced) {
-            auto kernel = partial ? combine_partial_pack_progressive_kernel : combine_pack_progressive_kernel;
+        if (replies_by_chunks(D, ctx->cu_count, rc)) {
+            auto kernel = fenced   ? partial ? combine_partial_pack_chunk_kernel<true, true> : combine_pack_chunk_kernel<true, true>
+                          : cached ? partial ? combine_partial_pack_chunk_kernel<false, true> : combine_pack_chunk_kernel<false, true>
+                                   : partial ? combine_partial_pack_chunk_kernel<false, false> : combine_pack_chunk_kernel<false, false>;
             kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         } else {
             const int G = waves_per_row(D.Bc / 16), wpb = kCopyThreads / kWave;
@@ -862,6 +893,17 @@ int fl_moe_debug_launch_groups(const fl_moe_config *cfg, int rank_count, int lau
     if (e != FL_OK) return e;
     if (rank_count < 1 || rank_count > D.N) return FL_ERR_INVALID_ARG;
     *ranks_per_group = ranks_per_launch(D, launch_mb < 0 ? kLaunchMiB : launch_mb, rank_count);
+    return FL_OK;
+}
+
+int fl_moe_debug_launch_plan(const fl_moe_config *cfg, int rank_count, fl_moe_launch_plan *out) {
+    if (!out) return FL_ERR_INVALID_ARG;
+    Dims D;
+    int e = resolve(cfg, &D);
+    if (e != FL_OK) return e;
+    if (rank_count < 1 || rank_count > D.N) return FL_ERR_INVALID_ARG;
+    out->unpack_by_chunks = unpack_by_chunks(D, kComputeUnits, rank_count);
+    out->replies_by_chunks = replies_by_chunks(D, kComputeUnits, rank_count);
     return FL_OK;
 }
 

@@ -551,9 +551,13 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     }
 }
 
-// Progressive mode: a block takes a chunk of received rows at a time, waits (bounded) for the
-// arrival counters of the sources those rows came from, and plans their copies in LDS.
-// The kernel may have been started before any payload
+// Short rows, and every row in progressive mode: a block takes a chunk of received rows at a time,
+// plans their copies in LDS and moves the chunk as one run of vectors, so that no lane idles however
+// short a row is; the wave kernel above is bound by the rate at which waves start then (rule and
+// both sides' times: short_rows in flmoe.hip).
+//
+// POLL (progressive mode): the block waits (bounded) for the arrival counters of the sources its
+// rows came from.  The kernel may have been started before any payload
 // exists, on a grid that is a fraction of the machine, so a block walks many
 // chunks.  It keeps the set of sources it has seen complete: a chunk whose
 // sources are all in the set costs no poll; otherwise one wave polls the
@@ -566,10 +570,11 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
 // before they landed; a line fetched later cannot).  The chunk's first payload
 // loads are issued before its sidecars are decoded, so a chunk costs one memory
 // round trip, not four.
-template <bool PRIVATE>   // the receive buffer has private slots (P > 0)
-__global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
+template <bool PRIVATE, bool POLL>   // PRIVATE: the receive buffer has private slots (P > 0)
+__global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
     Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
-    float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int rows_per_block) {
+    float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int rows_per_block,
+    const int *__restrict__ gate /* as in dispatch_unpack_kernel */) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
     __shared__ int off[FL_MAX_RANKS + 1];
     __shared__ int dst_rows[kMaxRowsPerBlock][FL_MAX_TOPK];
@@ -577,11 +582,11 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
     __shared__ int src_phys[kMaxRowsPerBlock];      // with private slots: buffer row of each received row
     __shared__ int timed_out;
     __shared__ unsigned long long seen_pub;         // wave 0 publishes the set of complete sources
-    // first round of loads, all independent: the verdict, the rows in use, the source offsets
-    const int plan_ok = W.plan_ok[d];
+    // first round of loads, all independent: the verdicts, the rows in use, the source offsets
+    const int plan_ok = W.plan_ok[d], gate_ok = gate ? gate[d] : 1;
     const int total = W.recv_off[(size_t)d * (N + 1) + N];
     const int off_mine = tid <= N ? W.recv_off[(size_t)d * (N + 1) + tid] : 0;
-    if (!plan_ok) return;
+    if (!plan_ok || !gate_ok) return;
     char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
     unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
     // grids are sized from capacities: blocks beyond the rows in use leave at once
@@ -593,15 +598,15 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
     const int nvec = (int)(D.Be / 16);
     const bool scales_as_vectors = D.scales_per_row > 0 && D.scales_per_row % 4 == 0;
     const int rowvec = nvec + (scales_as_vectors ? D.scales_per_row / 4 : 0);
-    unsigned long long seen = 0;                    // sources seen complete (same in every thread)
-    unsigned my_expect = 0;                         // wave 0: lane i holds what source i must deliver
-    if (tid < N) my_expect = W.expect_disp[(size_t)d * N + tid];
+    unsigned long long seen = 0;                    // POLL: sources seen complete (same in every thread)
+    unsigned my_expect = 0;                         // POLL, wave 0: lane i holds what source i must deliver
+    if (POLL && tid < N) my_expect = W.expect_disp[(size_t)d * N + tid];
     // capacities are upper bounds, so the grid may be smaller than the rows in use
     for (int r0 = blockIdx.x * rows_per_block; r0 < total; r0 += gridDim.x * rows_per_block) {
         const int r1 = min(r0 + rows_per_block, total);
         const int s0 = seg_of(off, N, r0), s1 = seg_of(off, N, r1 - 1);
-        const unsigned long long range = ((s1 - s0 == 63) ? ~0ull : ((1ull << (s1 - s0 + 1)) - 1)) << s0;
-        if (tid < kWave) {
+        if (POLL && tid < kWave) {
+            const unsigned long long range = ((s1 - s0 == 63) ? ~0ull : ((1ull << (s1 - s0 + 1)) - 1)) << s0;
             if (range & ~seen) {                // uniform: every thread holds the same `seen`
                 long long spins = 0;
                 for (;;) {
@@ -618,16 +623,21 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
                 acquire_payload<true>();      // arrivals not relied on before: drop what the caches hold
             }
             if (tid == 0) seen_pub = seen;
+        } else if (!POLL && !gate && tid < kWave) {    // stream order has made it so; checked, bounded
+            if (!wave_wait_counters(W.arrive_disp + (size_t)d * N + s0, W.expect_disp + (size_t)d * N + s0, 0u,
+                                    s1 - s0 + 1, D.spin_limit)) {
+                if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
+            }
         }
         __syncthreads();
         if (timed_out) return;
-        seen = seen_pub;
+        if (POLL) seen = seen_pub;
         // e4m3: when the scales of a row are a whole number of 16-byte vectors they are
         // moved by the same loop (the vectors after the code bytes go to expert_scales)
         const int chunk = (r1 - r0) * rowvec;
         // U loads per thread in flight: a full grid keeps the memory system busy with 4; the
         // capped grid of polling receivers has fewer waves per compute unit and needs 8
-        constexpr int U = 8;
+        constexpr int U = POLL ? 8 : 4;
         auto load_batch = [&](int b, v4u *val, int *row, int *col) {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
@@ -681,9 +691,10 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
                 }
             }
         };
-        if (!PRIVATE) {
+        if (POLL && !PRIVATE) {
             // the first batch's loads go out before the sidecars are decoded: a chunk then
-            // costs one memory round trip instead of three in a row
+            // costs one memory round trip instead of three in a row (polling receivers run with few
+            // waves per compute unit; on a full grid the registers it takes cost more than it gains)
             v4u val[U];
             int row[U], col[U];
             load_batch(tid, val, row, col);
@@ -705,16 +716,12 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_polling_kernel(
             }
         }
         if (D.scales_per_row && !scales_as_vectors) {   // odd scale counts: element by element
-            for (int r = r0; r < r1; ++r) {
-                const int n = dst_cnt[r - r0];
-                const int *dr = dst_rows[r - r0];
-                const float *ssrc =
-                    (const float *)(recv + (size_t)(PRIVATE ? src_phys[r - r0] : r) * D.Bw + D.Be);
-                for (int v = tid; v < D.scales_per_row; v += kCopyThreads) {
-                    const float val = ssrc[v];
-                    for (int i = 0; i < n; ++i)
-                        expert_scales[((size_t)d * D.expert_cap + dr[i]) * D.scales_per_row + v] = val;
-                }
+            for (int v = tid; v < (r1 - r0) * D.scales_per_row; v += kCopyThreads) {
+                const int row = v / D.scales_per_row, col = v - row * D.scales_per_row;
+                const int pr = PRIVATE ? src_phys[row] : r0 + row;
+                const float val = ((const float *)(recv + (size_t)pr * D.Bw + D.Be))[col];
+                for (int i = 0; i < dst_cnt[row]; ++i)
+                    expert_scales[((size_t)d * D.expert_cap + dst_rows[row][i]) * D.scales_per_row + col] = val;
             }
         }
         __syncthreads();                       // the row plan in LDS is rewritten by the next chunk
@@ -780,9 +787,11 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
     }
 }
 
-// Progressive mode: a workgroup per chunk of rows, written through; it adds each row's units
+// Short rows, and every row in progressive mode: a workgroup per chunk of rows, as in the unpack kernels.
+// FENCED (progressive mode): written through, and the workgroup adds each row's units
 // to arrive[source][this rank] itself, once per row rather than once per wave.
-__global__ __launch_bounds__(kCopyThreads) void combine_pack_progressive_kernel(
+template <bool FENCED, bool CACHED>
+__global__ __launch_bounds__(kCopyThreads) void combine_pack_chunk_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
     __shared__ int off[FL_MAX_RANKS + 1];
@@ -790,10 +799,11 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_progressive_kernel(
     __shared__ int2 push_to[kMaxRowsPerBlock];     // (source rank, row of its combine receive buffer)
     if (!W.plan_ok[d]) return;
     const int nvec = (int)(D.Bc / 16);
-    // the rank's first block announces the replies (a rank without rows its empty ones)
-    if (blockIdx.x == 0)
+    // the rank's first block announces the replies (a rank without rows its empty ones), unless an
+    // announce kernel will
+    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)
         announce_transfers(W.cs_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads,
-                           true);
+                           FENCED);
     // grids are sized from capacities: blocks beyond the rows in use leave at once
     const int total = W.cs_off[(size_t)d * (N + 1) + N];
     if ((int)blockIdx.x * rows_per_block >= total) return;
@@ -813,15 +823,17 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_progressive_kernel(
             push_to[tid] = make_int2(s, W.comb_dst_off[(size_t)d * N + s] + (q - off[s]));
         }
         __syncthreads();
-        copy_rows_flat<kCopyThreads>(
+        copy_rows_flat<kCopyThreads, FENCED, CACHED>(
             q1 - q0, nvec, tid,
             [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
             [&](int r) {
                 return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Bc;
             });
-        stores_done<true>();
-        __syncthreads();
-        if (tid < q1 - q0) add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
+        if (FENCED) {
+            stores_done<FENCED>();
+            __syncthreads();
+            if (tid < q1 - q0) add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
+        }
         __syncthreads();                       // the row plan is rewritten by the next chunk
     }
 }
@@ -911,8 +923,10 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
     }
 }
 
-// Progressive mode: a workgroup per chunk of rows, written through, adding each row's units itself.
-__global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_progressive_kernel(
+// Short rows, and every row in progressive mode: a workgroup per chunk of rows; FENCED, CACHED as in
+// combine_pack_chunk_kernel.
+template <bool FENCED, bool CACHED>
+__global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
     __shared__ int off[FL_MAX_RANKS + 1];
@@ -922,9 +936,9 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_progressive
     __shared__ int2 share_to[kMaxRowsPerBlock];
     if (!W.plan_ok[d]) return;
     const int nvec = (int)(D.Bc / 16);
-    if (blockIdx.x == 0)
+    if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0)
         announce_transfers(W.recv_off + (size_t)d * (N + 1), W.arrive_comb, (unsigned)nvec, d, N, tid, kCopyThreads,
-                           true);
+                           FENCED);
     const int total = W.recv_off[(size_t)d * (N + 1) + N];
     if ((int)blockIdx.x * rows_per_block >= total) return;
     if (tid <= N) off[tid] = W.recv_off[(size_t)d * (N + 1) + tid];
@@ -980,12 +994,14 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_progressive
                 o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
                 o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
                 char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Bc;
-                st_payload<true, true>((v4u *)dst + col[u], o);
+                st_payload<FENCED, CACHED>((v4u *)dst + col[u], o);
             }
         }
-        stores_done<true>();
-        __syncthreads();
-        if (tid < r1 - r0) add_counter(W.arrive_comb + (size_t)share_to[tid].x * N + d, (unsigned)nvec);
+        if (FENCED) {
+            stores_done<FENCED>();
+            __syncthreads();
+            if (tid < r1 - r0) add_counter(W.arrive_comb + (size_t)share_to[tid].x * N + d, (unsigned)nvec);
+        }
         __syncthreads();                       // the row plan is rewritten by the next chunk
     }
 }

@@ -66,6 +66,10 @@ class fl_moe_debug_view(C.Structure):
                 ("expect_disp", C.c_void_p), ("expect_comb", C.c_void_p), ("status", C.c_void_p)]
 
 
+class fl_moe_launch_plan(C.Structure):
+    _fields_ = [("unpack_by_chunks", C.c_int32), ("replies_by_chunks", C.c_int32)]
+
+
 EXPORTS = ["fl_moe_query_sizes", "fl_moe_create", "fl_moe_destroy", "fl_moe_layout",
            "fl_moe_layout_static",
            "fl_moe_dispatch_send", "fl_moe_dispatch_send_weighted", "fl_moe_dispatch_send_e4m3",
@@ -73,7 +77,8 @@ EXPORTS = ["fl_moe_query_sizes", "fl_moe_create", "fl_moe_destroy", "fl_moe_layo
            "fl_moe_combine_send",
            "fl_moe_combine_reduce", "fl_moe_status", "fl_moe_reset", "fl_moe_required_capacities",
            "fl_moe_strerror", "fl_moe_debug_views",
-           "fl_moe_debug_tune", "fl_moe_debug_launch_groups", "fl_moe_debug_copy", "fl_moe_debug_fill", "fl_moe_debug_read", "fl_moe_profile_enable", "fl_moe_profile_collect", "fl_moe_profile_read",
+           "fl_moe_debug_tune", "fl_moe_debug_launch_groups", "fl_moe_debug_launch_plan",
+           "fl_moe_debug_copy", "fl_moe_debug_fill", "fl_moe_debug_read", "fl_moe_profile_enable", "fl_moe_profile_collect", "fl_moe_profile_read",
            "fl_moe_kernel_name", "fl_moe_build_id"]
 
 _lib = None
@@ -115,6 +120,7 @@ def lib():
         L.fl_moe_debug_views.argtypes = [vp, C.POINTER(fl_moe_debug_view)]
         L.fl_moe_debug_tune.argtypes = [vp, i32, i32]
         L.fl_moe_debug_launch_groups.argtypes = [C.POINTER(fl_moe_config), i32, i32, C.POINTER(C.c_int)]
+        L.fl_moe_debug_launch_plan.argtypes = [C.POINTER(fl_moe_config), i32, C.POINTER(fl_moe_launch_plan)]
         L.fl_moe_debug_copy.argtypes = [vp, vp, C.c_size_t, vp]
         L.fl_moe_debug_fill.argtypes = [vp, C.c_size_t, vp]
         L.fl_moe_debug_read.argtypes = [vp, C.c_size_t, vp, vp]
@@ -259,6 +265,12 @@ def fl_moe_debug_launch_groups(cfg: fl_moe_config, rank_count: int, launch_mb: i
     _check(lib().fl_moe_debug_launch_groups(C.byref(cfg), rank_count, launch_mb, C.byref(out)),
            "fl_moe_debug_launch_groups")
     return out.value
+
+
+def fl_moe_debug_launch_plan(cfg: fl_moe_config, rank_count: int) -> fl_moe_launch_plan:
+    out = fl_moe_launch_plan()
+    _check(lib().fl_moe_debug_launch_plan(C.byref(cfg), rank_count, C.byref(out)), "fl_moe_debug_launch_plan")
+    return out
 
 
 def fl_moe_debug_copy(dst, src, nbytes, stream=None):

@@ -136,6 +136,34 @@ def test_large_calls_are_cut_into_rank_groups_small_ones_are_not():
     assert lib.fl_moe_debug_launch_groups(C.byref(c), 32, -1, None) == flmoe.FL_ERR_INVALID_ARG
 
 
+# (change to 16 ranks x 8 experts, 1024 tokens, 128-byte rows; unpack, replies by chunks of rows?)
+@pytest.mark.parametrize("kw,unpack,replies", [
+    (dict(), 1, 1),
+    (dict(max_tokens=16), 0, 0),                       # rows fit on the machine as one wave each
+    (dict(max_tokens=40), 0, 0),                       # 5 120 replies: as many as there are waves
+    (dict(max_tokens=41), 0, 1),
+    (dict(hidden=1024), 1, 1),
+    (dict(hidden=1032), 0, 0),                         # rows of more than 2 KB
+    (dict(hidden=2048, dispatch_dtype=1), 1, 0),       # 2 KB of codes, replies of 4 KB
+    (dict(flags=flmoe.FL_FLAG_PARTIAL_SUMS, hidden=768), 1, 1),
+    (dict(flags=flmoe.FL_FLAG_PARTIAL_SUMS, hidden=776), 1, 0),
+    (dict(flags=flmoe.FL_FLAG_PROGRESSIVE_RECV, hidden=7168, max_tokens=1), 1, 1),
+    (dict(recv_capacity_rows=300, expert_capacity_rows=300), 0, 0),
+])
+def test_many_short_rows_are_moved_by_chunks(kw, unpack, replies):
+    """Waves on their own start and end at a bounded rate: 16 ranks of 4096 tokens with 128-byte rows took 689 us a
+    step by waves and 222 by chunks.  Longer rows, and few rows, go by waves."""
+    c = dict(n_ranks=16, n_experts=128, max_tokens=1024, top_k=8, hidden=64)
+    c.update(kw)
+    plan = flmoe.fl_moe_debug_launch_plan(cfg(**c), 16)
+    assert (plan.unpack_by_chunks, plan.replies_by_chunks) == (unpack, replies)
+    single = flmoe.fl_moe_debug_launch_plan(cfg(**dict(c, max_tokens=40)), 1)      # a rank by itself has few rows
+    if not c.get("flags", 0) & flmoe.FL_FLAG_PROGRESSIVE_RECV:
+        assert (single.unpack_by_chunks, single.replies_by_chunks) == (0, 0)
+    with pytest.raises(flmoe.FlMoeError):
+        flmoe.fl_moe_debug_launch_plan(cfg(**c), 17)
+
+
 def test_static_layout_entry_point_checks_its_arguments_before_touching_a_gpu():
     """fl_moe_layout_static validates on the host first: null or misaligned pointers, bad
     configurations and configurations beyond its static scratch array are refused without

@@ -215,6 +215,27 @@ def test_rows_at_the_edges_of_a_waves_share(shape, kw):
     sh.close()
 
 
+# (tokens, hidden, dtype) at 8 ranks x 64 experts, top 8, enough rows for the kernels that take chunks of rows:
+# one vector per row, rows that share a load instruction and do not divide the workgroup, the longest rows that
+# go by chunks; e4m3 rows whose scales are and are not whole vectors
+CHUNK_EDGES = [(900, 8, "bf16"), (900, 72, "bf16"), (900, 768, "bf16"), (900, 1024, "bf16"), (900, 128, "e4m3"),
+               (900, 512, "e4m3"), (900, 1920, "e4m3")]
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(ordering="stream"), dict(private_rows=30), dict(cached_mb=0),
+                                dict(partial=True, cached_mb=0), dict(partial=True, private_rows=30, ordering="stream")],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("shape", CHUNK_EDGES, ids=str)
+def test_many_short_rows(shape, kw):
+    """Whole steps whose rows are moved by workgroups that plan a chunk of rows: bit for bit."""
+    T, H, dtype = shape
+    wl = wlmod.custom("short_rows", 8, 64, T, H, 8, seed=H, ragged=True, dispatch_dtype=dtype)
+    sh, _, _ = run_and_compare(wlmod.make_inputs(wl), align=4, zero_pad=True, capacity_factor=1.5, **kw)
+    plan = flmoe.fl_moe_debug_launch_plan(sh.cfg, 8)
+    assert plan.unpack_by_chunks and (plan.replies_by_chunks or H > (768 if kw.get("partial") else 1024))
+    sh.close()
+
+
 @pytest.mark.parametrize("partial", [False, True])
 @pytest.mark.parametrize("name", ["ragged_520", "multi_tile"])
 def test_replies_past_the_caches(name, partial):
