@@ -260,7 +260,9 @@ int fl_moe_destroy(fl_moe_ctx *ctx);
  * expert and distinct tokens per destination rank with LDS bit matrices and
  * popcount prefix scans (deterministic, no ticket atomics), pushes the counts to
  * every peer, and derives all offsets of the step from the counts it received.
- * Both arrays must stay unchanged until the step's combine_reduce has run.
+ * Both arrays must stay unchanged until the step's combine_reduce has run.  The ids of
+ * tokens at or beyond num_tokens[r] are never read: an array may end with those of the last
+ * token in use.
  * `view` (host, may be NULL) receives pointers to the resulting tables. */
 int fl_moe_layout(fl_moe_ctx *ctx, int rank_begin, int rank_count, const int32_t *indices,
                   const int32_t *num_tokens, fl_moe_layout_view *view /*host*/, void *stream);
@@ -352,7 +354,8 @@ int fl_moe_combine_send(fl_moe_ctx *ctx, int rank_begin, int rank_count, const v
  *   out[s][t] = bf16( sum_{k=0..K-1} weights[s][t][k] * float(y of pair (s,t,k)) )
  * fp32 accumulator starting at +0, fused multiply-add, k ascending, one final
  * round-to-nearest-even; no division by the weight sum.  Rows t >= num_tokens[s]
- * are not written. */
+ * are not written.  All N*T*K weights must be addressable (those of absent tokens may be
+ * read, they are never used). */
 int fl_moe_combine_reduce(fl_moe_ctx *ctx, int rank_begin, int rank_count, const float *weights,
                           void *out, void *stream);
 

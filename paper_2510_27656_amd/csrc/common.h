@@ -65,7 +65,7 @@ struct Tables {
     int *send_off;        // [N][N+1]
     int *comb_off;        // [N][N+1]
     int *send_row;        // [N][T][K]  for the first slot of each destination: number of this copy among all
-                          //            copies the source sends, ordered by (destination, token); else -1
+                          //            copies the source sends, ordered by (destination, token); else ~destination
     unsigned *pair_meta;  // [N][T][K]  (local expert << 24) | rank of the token among the source's tokens of that expert
     int *comb_pos;        // [N][T][K]
     // written by the receiving side of the layout step

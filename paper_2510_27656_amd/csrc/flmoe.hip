@@ -571,8 +571,8 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
             const int per_block = QT / kQuantLanes;              // quantisation blocks per workgroup
             const int slices = (D.scales_per_row + per_block - 1) / per_block;
             auto kernel = fenced ? dispatch_pack_e4m3_kernel<true, QT> : dispatch_pack_e4m3_kernel<false, QT>;
-            kernel<<<dim3((unsigned)D.T * slices, rc), dim3(QT), 0, st>>>(D, W, rb, xp, ctx->indices,
-                                                                          ctx->num_tokens, slices, weights);
+            kernel<<<dim3((unsigned)D.T * slices, rc), dim3(QT), 0, st>>>(D, W, rb, xp, ctx->num_tokens, slices,
+                                                                          weights);
         };
         if (D.scales_per_row > 256 / kQuantLanes) go(std::integral_constant<int, 512>{});
         else go(std::integral_constant<int, 256>{});
@@ -583,7 +583,7 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
         const int slices = pack_slices(src_row, D.tune_slices);
         auto kernel = fenced ? dispatch_pack_kernel<true> : dispatch_pack_kernel<false>;
         kernel<<<dim3((unsigned)D.T * slices, rc), dim3(kPackThreads), 0, st>>>(
-            D, W, rb, xp, ctx->indices, ctx->num_tokens, slices, weights, src_row, ready_scales);
+            D, W, rb, xp, ctx->num_tokens, slices, weights, src_row, ready_scales);
     }
     if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {   // once, behind every payload kernel of the call
         LaunchTimer t(ctx, KID_ANNOUNCE_DISPATCH, st);

@@ -18,7 +18,7 @@
 namespace flmoe {
 
 constexpr int kRouteThreads = 1024;
-constexpr int kRoutePreload = 4;             // pair ids a thread fetches before it knows the token count
+constexpr int kRoutePreload = 4;             // pair ids a thread fetches while the bit matrices are being cleared
 
 // Words per row of the LDS bit matrices: the words in use, padded to an odd
 // number so that rows do not all start in the same bank.
@@ -92,18 +92,19 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
     const int tiles = (D.T + D.TT - 1) / D.TT;             // of the capacity; the tokens in use may fill fewer
     const int per = (tiles + parts - 1) / parts;
     const int tile0 = part * per;
-    // the first ids go out together with the token count (the array has T rows whatever is in use)
+    int Ts = num_tokens[s];                                // on its way while the counters are cleared
+    for (int r = tid; r < rows; r += kRouteThreads) { count[r] = 0; base[r] = 0; }
+    if (tid == 0) bad = (Ts < 0 || Ts > D.T) ? 1 : 0;
+    Ts = max(0, min(Ts, D.T));
+    // the first ids are on their way while the bit matrices are cleared; never those of absent tokens,
+    // which need not exist
     int early[kRoutePreload];
 #pragma unroll
     for (int i = 0; i < kRoutePreload; ++i) {
         const int p = tid + i * kRouteThreads;
-        early[i] = p < min(D.TT, D.T - tile0 * D.TT) * K ? idx_s[(size_t)tile0 * D.TT * K + p] : 0;
+        early[i] = p < min(D.TT, Ts - tile0 * D.TT) * K ? idx_s[(size_t)tile0 * D.TT * K + p] : 0;
     }
-    int Ts = num_tokens[s];
-    if (tid == 0) bad = (Ts < 0 || Ts > D.T) ? 1 : 0;
-    for (int r = tid; r < rows; r += kRouteThreads) { count[r] = 0; base[r] = 0; }
     for (int i = tid; i < rows * Wd; i += kRouteThreads) bits[i] = 0;
-    Ts = max(0, min(Ts, D.T));
     const int used = (Ts + D.TT - 1) / D.TT;
     __syncthreads();
 
@@ -273,7 +274,7 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
             const size_t o = ((size_t)s * D.T + t0) * K + p;
             W.comb_pos[o] = start[re] + rank_e;
             W.pair_meta[o] = ((unsigned)(e - d * El) << 24) | (unsigned)rank_e;
-            W.send_row[o] = first ? start[rd] - pairs_total + rank_d : -1;
+            W.send_row[o] = first ? start[rd] - pairs_total + rank_d : ~d;
         }
     }
 }

@@ -61,15 +61,15 @@ __device__ inline int in_order(int order, int i, int n) {
 // something for every t < T; it is used only once the step and the token are known to be valid).
 // One round instead of three in a row: e4m3 pack of 128 tokens per rank 57.5 -> 52.7 us (its one
 // workgroup per row had nothing else to do meanwhile), bf16 4 / 8 tokens 10.0 / 11.4 -> 9.4 / 10.8,
-// the same from 32 tokens on.
+// the same from 32 tokens on.  The caller's expert ids are not read again: those of absent tokens
+// need not exist, so fetching them would have to wait for the token count.
 struct CopyPlan {
-    int row, expert, send_off, dst_off;
+    int row, send_off, dst_off;
     unsigned meta;
-    __device__ inline void load(const Dims &D, const Tables &W, const int *indices, int s, size_t pair0, int lane) {
-        row = -1; expert = 0; meta = 0; send_off = 0; dst_off = 0;
+    __device__ inline void load(const Dims &D, const Tables &W, int s, size_t pair0, int lane) {
+        row = -1; meta = 0; send_off = 0x7fffffff; dst_off = 0;
         if (lane < D.K) {
             row = W.send_row[pair0 + lane];
-            expert = indices[pair0 + lane];
             meta = W.pair_meta[pair0 + lane];
         }
         if (lane < D.N) {
@@ -80,7 +80,12 @@ struct CopyPlan {
     // destination rank of this lane's expert, and the row in its receive buffer when the token's copy
     // for that rank belongs to this lane (the first of its experts there), else -1; whole wave
     __device__ inline int target(const Dims &D, int s, int *dst) const {
-        const int d = expert / D.El;
+        int d = ~row;                          // named by the entry itself ...
+        for (int k = 0; k < D.K; ++k) {        // ... or the last rank whose copies start at or before this one
+            const int n = __builtin_amdgcn_readlane(row, k);
+            const int at = __popcll(__ballot(send_off <= n)) - 1;
+            if (row >= 0 && (int)(threadIdx.x & (kWave - 1)) == k) d = at;
+        }
         *dst = d;
         const int first = __shfl(send_off, d), shared = __shfl(dst_off, d);
         return row >= 0 ? recv_buffer_row(D.N, D.P, s, row - first, shared) : -1;
@@ -102,8 +107,7 @@ struct CopyPlan {
 // the announce kernel does.
 template <bool FENCED>
 __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
-    Dims D, Tables W, int rank_begin, const char *__restrict__ x,
-    const int *__restrict__ indices, const int *__restrict__ num_tokens, int slices,
+    Dims D, Tables W, int rank_begin, const char *__restrict__ x, const int *__restrict__ num_tokens, int slices,
     const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */,
     long long src_row_bytes /* bytes of one row of x: 2*H, or H for ready-made e4m3 codes */,
     const float *__restrict__ src_scales /* [N][T][H/128] with ready-made codes, else null */) {
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
         if (v0 + tid + i * kPackThreads < v1) r[i] = ld_stream(src + v0 + tid + i * kPackThreads);
     const size_t pair0 = ((size_t)s * D.T + t) * K;
     CopyPlan plan;
-    if (tid < kWave) plan.load(D, W, indices, s, pair0, tid);
+    if (tid < kWave) plan.load(D, W, s, pair0, tid);
     const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
     // the sender's first block announces the transfers (a sender without tokens still announces
     // its empty ones), unless an announce kernel will
@@ -254,8 +258,7 @@ constexpr int kQuantLanes = 8;     // lanes per 128-element block: 16 bf16 value
 // copy; the scales go out as 16-byte vectors from LDS.
 template <bool FENCED, int QT>   // FENCED as in dispatch_pack_kernel
 __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
-    Dims D, Tables W, int rank_begin, const char *__restrict__ x,
-    const int *__restrict__ indices, const int *__restrict__ num_tokens, int slices,
+    Dims D, Tables W, int rank_begin, const char *__restrict__ x, const int *__restrict__ num_tokens, int slices,
     const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */) {
     constexpr int kQuantThreads = QT;
     const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
@@ -275,7 +278,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     }
     const size_t pair0 = ((size_t)s * D.T + t) * K;
     CopyPlan plan;
-    if (tid < kWave) plan.load(D, W, indices, s, pair0, tid);
+    if (tid < kWave) plan.load(D, W, s, pair0, tid);
     const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
     if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)   // as in dispatch_pack_kernel
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,

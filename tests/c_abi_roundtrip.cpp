@@ -197,6 +197,78 @@ int main() {
     }
 
     FL_CALL(fl_moe_destroy(ctx));
+
+    // 4. Expert ids of absent tokens need not exist: an array that ends with the last used token's ids, at the
+    //    end of a 2 MiB allocation of its own, through the layout and send calls of a context and the static
+    //    layout.  All other tensors are whole.
+    {
+        const int T4 = 40000, K4 = 4, H4 = 8, used = 11072;       // 3 * 40000 + 11072 tokens of 4 ids are 2 MiB
+        const int nt4[N] = {T4, 1234, 0, used};
+        const size_t ids = ((size_t)(N - 1) * T4 + used) * K4;
+        if (ids * 4 != 2u << 20) return 15;
+        fl_moe_config c4 = cfg;
+        c4.max_tokens = T4; c4.top_k = K4; c4.hidden = H4;
+        fl_moe_sizes s4;
+        FL_CALL(fl_moe_query_sizes(&c4, &s4));
+        std::vector<int32_t> idx4(ids), want(N * El, 0), got(N * El);
+        for (size_t p = 0; p < ids; ++p) {
+            const size_t token = p / K4;
+            idx4[p] = (int32_t)((3 * token + 5 * (p % K4)) % E);              // 0, 5, 10, 15 apart
+            if ((int)(token % T4) < nt4[token / T4]) ++want[idx4[p]];
+        }
+        void *ws4 = nullptr, *x4 = nullptr, *ex4 = nullptr, *y4 = nullptr;
+        int32_t *i4 = nullptr, *n4 = nullptr, *t4 = nullptr;
+        float *w4 = nullptr;
+        const size_t tokens4 = (size_t)N * T4;
+        HIP_OK(hipMalloc(&ws4, s4.workspace_bytes));
+        HIP_OK(hipMalloc(&x4, tokens4 * H4 * 2));
+        HIP_OK(hipMalloc(&y4, tokens4 * H4 * 2));
+        HIP_OK(hipMalloc(&ex4, (size_t)N * s4.expert_capacity_rows * H4 * 2));
+        HIP_OK(hipMalloc((void **)&i4, ids * 4));
+        HIP_OK(hipMalloc((void **)&n4, N * 4));
+        HIP_OK(hipMalloc((void **)&t4, N * El * 4));
+        HIP_OK(hipMalloc((void **)&w4, tokens4 * K4 * 4));
+        std::vector<uint16_t> hx(tokens4 * H4), hy(tokens4 * H4);
+        for (size_t i = 0; i < hx.size(); ++i) hx[i] = (uint16_t)(0x3f80 + ((uint32_t)i * 2654435761u >> 25));   // 1 .. 2
+        std::vector<float> hw(tokens4 * K4, 0.25f);
+        HIP_OK(hipMemcpy(x4, hx.data(), hx.size() * 2, hipMemcpyHostToDevice));
+        HIP_OK(hipMemcpy(w4, hw.data(), hw.size() * 4, hipMemcpyHostToDevice));
+        HIP_OK(hipMemcpy(i4, idx4.data(), ids * 4, hipMemcpyHostToDevice));
+        HIP_OK(hipMemcpy(n4, nt4, N * 4, hipMemcpyHostToDevice));
+        FL_CALL(fl_moe_create(&c4, ws4, s4.workspace_bytes, &ctx));
+        FL_CALL(fl_moe_layout(ctx, 0, N, i4, n4, nullptr, st));
+        FL_CALL(fl_moe_dispatch_send(ctx, 0, N, x4, st));
+        FL_CALL(fl_moe_dispatch_recv(ctx, 0, N, ex4, nullptr, t4, st));
+        FL_CALL(fl_moe_combine_send(ctx, 0, N, ex4, st));
+        FL_CALL(fl_moe_combine_reduce(ctx, 0, N, w4, y4, st));
+        FL_CALL(fl_moe_status(ctx, &status, st));
+        if (status != 0) { std::fprintf(stderr, "short index array: device status %d\n", status); return 16; }
+        HIP_OK(hipMemcpy(got.data(), t4, got.size() * 4, hipMemcpyDeviceToHost));
+        HIP_OK(hipMemcpy(hy.data(), y4, hy.size() * 2, hipMemcpyDeviceToHost));
+        if (got != want) { std::fprintf(stderr, "short index array: tokens_per_expert\n"); return 17; }
+        for (int s = 0; s < N; ++s)
+            if (std::memcmp(&hy[(size_t)s * T4 * H4], &hx[(size_t)s * T4 * H4], (size_t)nt4[s] * H4 * 2) != 0) {
+                std::fprintf(stderr, "short index array: rank %d's output differs from its tokens\n", s);
+                return 18;
+            }
+        const size_t sizes[10] = {(size_t)N * E, (size_t)N * N, (size_t)N * El, (size_t)N * (N + 1),
+                                  (size_t)N * (N + 1), (size_t)N * (El + 1), (size_t)N * (N + 1),
+                                  tokens4 * K4, (size_t)N, 1};
+        size_t total = 0;
+        for (size_t v : sizes) total += v;
+        int32_t *tab = nullptr, *p[10];
+        HIP_OK(hipMalloc((void **)&tab, total * 4));
+        size_t at = 0;
+        for (int i = 0; i < 10; ++i) { p[i] = tab + at; at += sizes[i]; }
+        const fl_moe_layout_out lo = {p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], p[9]};
+        FL_CALL(fl_moe_layout_static(&c4, i4, n4, &lo, st));
+        HIP_OK(hipStreamSynchronize(st));
+        HIP_OK(hipMemcpy(got.data(), p[2], got.size() * 4, hipMemcpyDeviceToHost));
+        if (got != want) { std::fprintf(stderr, "short index array: static layout\n"); return 19; }
+        FL_CALL(fl_moe_destroy(ctx));
+        HIP_OK(hipFree(tab)); HIP_OK(hipFree(ws4)); HIP_OK(hipFree(x4)); HIP_OK(hipFree(y4)); HIP_OK(hipFree(ex4));
+        HIP_OK(hipFree(i4)); HIP_OK(hipFree(n4)); HIP_OK(hipFree(t4)); HIP_OK(hipFree(w4));
+    }
     HIP_OK(hipStreamDestroy(st));
     HIP_OK(hipFree(ws)); HIP_OK(hipFree(d_x)); HIP_OK(hipFree(d_ex)); HIP_OK(hipFree(d_out));
     HIP_OK(hipFree(d_idx)); HIP_OK(hipFree(d_nt)); HIP_OK(hipFree(d_tpe)); HIP_OK(hipFree(d_w));
