@@ -172,7 +172,7 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
                             first &= owner[k2] != owner[k];
                         }
                     if (again) bad = 1;
-                    if (ok) {
+                    else {                                 // a token counts once per expert, as in the bit matrices
                         atomicAdd(&count[e], one);
                         if (first) atomicAdd(&count[E + owner[k]], one);
                         if (wide && t < mine) {

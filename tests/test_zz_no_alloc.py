@@ -110,6 +110,39 @@ def test_bad_index_and_capacity_are_reported_in_the_callers_status_word():
     assert (out["plan_ok"].cpu().numpy() == 0).all()
 
 
+# one tile of tokens; several; so many that repeated ids would overflow 16-bit counts; 32-bit records
+@pytest.mark.parametrize("N,E,T,K", [(4, 32, 50, 4), (4, 32, 2500, 4), (2, 32, 40000, 4), (1, 8, 70000, 3)])
+@pytest.mark.parametrize("fault", ["repeated", "one repeated", "too large", "negative"])
+def test_bad_ids_in_any_tile_are_found_and_counted_once(N, E, T, K, fault):
+    """An id outside the range or repeated inside a token is reported wherever it stands; the counts are those of
+    the bit matrices whatever the tokens list: a token counts once per expert and once per rank."""
+    wl = wlmod.custom("bad_ids", N, E, T, 8, K, seed=T)
+    inp = wlmod.make_inputs(wl)
+    dev = harness.to_device(inp)
+    ids = dev["indices"].clone()
+    if fault == "repeated":
+        ids[...] = ids[..., :1]
+    elif fault == "one repeated":
+        ids[N - 1, T - 1, K - 1] = ids[N - 1, T - 1, 0]
+    else:
+        ids[0, T - 3, 1] = E if fault == "too large" else -1
+    cfg = flmoe.fl_moe_config(N, E, T, K, 8, 0, 1, 0, 0, 0, 0, 0, 0)
+    out = out_buffers(wl)
+    flmoe.fl_moe_layout_static(cfg, ids, dev["num_tokens"], out)
+    torch.cuda.synchronize()
+    assert int(out["status"][0]) == flmoe.FL_STATUS_BAD_INDEX
+    assert (out["plan_ok"].cpu().numpy() == 0).all()
+    ids = ids.cpu().long()
+    listed = torch.zeros((N, T, E + 1), dtype=torch.bool)
+    listed.scatter_(2, torch.where((ids < 0) | (ids >= E), E, ids), True)
+    listed = listed[..., :E]
+    assert (out["counts"].cpu() == listed.sum(1)).all()
+    assert (out["dedup_counts"].cpu() == listed.view(N, T, N, E // N).any(3).sum(1)).all()
+    flmoe.fl_moe_layout_static(cfg, dev["indices"], dev["num_tokens"], out)
+    torch.cuda.synchronize()
+    assert int(out["status"][0]) == 0 and (out["plan_ok"].cpu().numpy() == 1).all()
+
+
 def test_sizes_beyond_the_static_array_are_refused():
     wl = wlmod.WORKLOADS["dsv3_prefill"]           # 4096 tokens per rank: per-pair tables of 8 MB
     cfg = flmoe.fl_moe_config(wl.n_ranks, wl.n_experts, wl.tokens, wl.top_k, wl.hidden, 0, 1, 0,
