@@ -426,6 +426,8 @@ typedef struct fl_moe_launch_plan {
     int32_t unpack_by_chunks;    /* 1: dispatch_recv moves rows by workgroups that plan a chunk of rows,
                                     0: by waves on their own                                        */
     int32_t replies_by_chunks;   /* the same of combine_send                                        */
+    int64_t recv_grid_rows;      /* received rows per rank that the grid of dispatch_recv is sized for  */
+    int64_t reply_grid_rows;     /* the same of the rows a rank sends back, for combine_send's grid     */
 } fl_moe_launch_plan;
 int fl_moe_debug_launch_plan(const fl_moe_config *cfg /*host*/, int rank_count,
                              fl_moe_launch_plan *out /*host*/);

@@ -138,9 +138,9 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->tune_cap8 = 3;
     D->tune_order = 0;
     D->tune_parts = 0;
-    {   // a token reaches a given rank with probability 1 - (1 - 1/N)^K when experts are drawn uniformly
+    {   // a token reaches a given rank unless its K distinct experts, drawn uniformly, all live elsewhere
         double miss = 1.0;
-        for (int k = 0; k < D->K; ++k) miss *= 1.0 - 1.0 / D->N;
+        for (int k = 0; k < D->K; ++k) miss *= std::max(0.0, (double)(D->E - El - k) / (D->E - k));
         D->typ_recv_rows = (long long)(NT * (1.0 - miss)) + 1;
         D->typ_pair_rows = (long long)D->T * D->K;
     }
@@ -250,6 +250,13 @@ bool replies_by_chunks(const Dims &D, int cu_count, int rank_count) {
     const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
     const long long rows = partial ? std::min(D.typ_recv_rows, D.recv_rows) : std::min(D.typ_pair_rows, D.expert_cap);
     return by_chunks(D, cu_count, D.Bc, partial ? kChunkPartialRowBytes : kChunkRowBytes, rows * rank_count);
+}
+
+long long recv_grid_rows(const Dims &D) {        // received rows: unpack, partial-sum pack
+    return grid_rows(D, std::min(D.recv_rows, (long long)D.N * D.T), D.typ_recv_rows);
+}
+long long reply_grid_rows(const Dims &D) {       // rows a rank sends back: one per pair, or one per received row
+    return D.flags & FL_FLAG_PARTIAL_SUMS ? recv_grid_rows(D) : grid_rows(D, D.expert_cap, D.typ_pair_rows);
 }
 
 // Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
@@ -640,9 +647,7 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
         }
         gate = ctx->W.gate_disp;
     }
-    const long long worst_rows = (long long)D.N * D.T;       // received rows in use never exceed this
-    const long long max_rows = D.recv_rows < worst_rows ? D.recv_rows : worst_rows;
-    const long long rows = grid_rows(D, max_rows, D.typ_recv_rows);
+    const long long rows = recv_grid_rows(D);
     char *ex = (char *)expert_x;
     LaunchTimer t(ctx, KID_DISPATCH_UNPACK, st);
     if (unpack_by_chunks(D, ctx->cu_count, rc)) {
@@ -692,11 +697,7 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
     const int rbk = rows_per_block(D.Bc, D.tune_rows);
     const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;      // as in dispatch_send_range
     const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
-    // rows a rank sends back: one per pair, or with partial sums one per received row
-    const long long worst_recv = (long long)D.N * D.T;
-    const long long reply_rows = partial ? (D.recv_rows < worst_recv ? D.recv_rows : worst_recv)
-                                         : D.expert_cap;
-    const long long reply_grid = grid_rows(D, reply_rows, partial ? D.typ_recv_rows : D.typ_pair_rows);
+    const long long reply_grid = reply_grid_rows(D);
     const unsigned gx = capped_grid((reply_grid + rbk - 1) / rbk, rc, kMaxRowBlocks);
     {
         const dim3 grid(gx, rc), block(kCopyThreads);
@@ -904,6 +905,8 @@ int fl_moe_debug_launch_plan(const fl_moe_config *cfg, int rank_count, fl_moe_la
     if (rank_count < 1 || rank_count > D.N) return FL_ERR_INVALID_ARG;
     out->unpack_by_chunks = unpack_by_chunks(D, kComputeUnits, rank_count);
     out->replies_by_chunks = replies_by_chunks(D, kComputeUnits, rank_count);
+    out->recv_grid_rows = recv_grid_rows(D);
+    out->reply_grid_rows = reply_grid_rows(D);
     return FL_OK;
 }
 

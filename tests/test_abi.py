@@ -2,6 +2,7 @@
 include/flmoe.h declares, and its host-only entry points validate arguments.
 No kernel is launched here."""
 import ctypes as C
+import math
 import os
 import re
 
@@ -162,6 +163,25 @@ def test_many_short_rows_are_moved_by_chunks(kw, unpack, replies):
         assert (single.unpack_by_chunks, single.replies_by_chunks) == (0, 0)
     with pytest.raises(flmoe.FlMoeError):
         flmoe.fl_moe_debug_launch_plan(cfg(**c), 17)
+
+
+@pytest.mark.parametrize("N,El,K,T", [(8, 1, 8, 1024), (16, 1, 8, 4096), (8, 2, 8, 4096), (2, 2, 3, 500), (32, 8, 8, 128),
+                                      (1, 16, 4, 77), (4, 1, 1, 64), (64, 16, 16, 300)])
+def test_grids_cover_the_mean_and_six_deviations_of_uniform_routing(N, El, K, T):
+    """A token's experts are distinct, so with few experts per rank it reaches more ranks than K independent draws
+    would: it misses a rank in C(E - El, K) of C(E, K) choices."""
+    E = N * El
+    for flags in (0, flmoe.FL_FLAG_PARTIAL_SUMS):
+        plan = flmoe.fl_moe_debug_launch_plan(cfg(n_ranks=N, n_experts=E, max_tokens=T, top_k=K, hidden=4096,
+                                                  flags=flags), N)
+        hit = 1 - math.comb(E - El, K) / math.comb(E, K)
+        mean, room = N * T * hit, N * T                      # a rank never receives more than every token
+        assert plan.recv_grid_rows >= min(room, mean + 6 * math.sqrt(N * T * hit * (1 - hit)))
+        assert plan.recv_grid_rows <= min(room, mean + 6 * math.sqrt(mean) + 3)
+        if flags:
+            assert plan.reply_grid_rows == plan.recv_grid_rows
+        else:
+            assert min(N * T * min(K, El), T * K + 6 * math.sqrt(T * K)) <= plan.reply_grid_rows <= T * K + 6 * math.sqrt(T * K) + 3
 
 
 def test_static_layout_entry_point_checks_its_arguments_before_touching_a_gpu():
