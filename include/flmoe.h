@@ -396,8 +396,9 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
  * per thread in combine_reduce (0 = all K, at most 8), knob 2 = accepted without
  * effect (it shaped a copy kernel that is no longer launched), knob 3 =
  * workgroups per token in the pack kernel (0 = chosen from the row size, at
- * most 16), knob 4 = size in MiB of the replies a combine_send call may write above
- * which it uses streaming instead of cached stores (default 1024), knob 5 = percentage of the rows uniform routing would bring to a rank that the
+ * most 16), knob 4 = size in MiB of all ranks' replies above
+ * which combine_send uses streaming instead of cached stores (default 1024; half of it when a
+ * call serves part of the ranks), knob 5 = percentage of the rows uniform routing would bring to a rank that the
  * grids of the receive-side and reply kernels are sized for (default: the mean plus six
  * standard deviations; 0 = the whole capacity; a rank that holds more is served by the kernels' row loops),
  * knob 6 = payload in MiB one launch should move per direction: a call whose ranks
@@ -426,6 +427,7 @@ typedef struct fl_moe_launch_plan {
     int32_t unpack_by_chunks;    /* 1: dispatch_recv moves rows by workgroups that plan a chunk of rows,
                                     0: by waves on their own                                        */
     int32_t replies_by_chunks;   /* the same of combine_send                                        */
+    int32_t replies_cached;      /* combine_send stores replies through the caches (0: past them)   */
     int64_t recv_grid_rows;      /* received rows per rank that the grid of dispatch_recv is sized for  */
     int64_t reply_grid_rows;     /* the same of the rows a rank sends back, for combine_send's grid     */
 } fl_moe_launch_plan;

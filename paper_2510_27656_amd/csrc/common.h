@@ -27,7 +27,7 @@ struct Dims {
     int tune_rows;        // rows per block of the copy kernels (0 = by row size)
     int tune_reduce;      // loads in flight per thread in the reduce kernel (0 = all K)
     int tune_slices;      // blocks per token in the pack kernel (0 = by row size)
-    int tune_cached_mb;   // combine replies are stored through the caches up to this many MiB per call
+    int tune_cached_mb;   // combine replies are stored through the caches up to this many MiB of the group (replies_cached)
     int tune_grid_pct;    // row-kernel grids cover this percentage of the rows uniform routing would bring
                           // (0 = the whole capacity, -1 = the mean and six standard deviations); kernels
                           // loop over whatever is beyond

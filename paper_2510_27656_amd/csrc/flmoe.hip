@@ -46,7 +46,7 @@ constexpr long long kDefaultSpin = 1 << 20;       // polls about 2 us apart: giv
 
 constexpr size_t kBigPage = 2u << 20;
 constexpr int kComputeUnits = 256;                // of the part, where a context has not asked the device
-constexpr int kCachedReplyMiB = 1024;
+constexpr int kCachedReplyMiB = 1024;             // see replies_cached
 constexpr int kLaunchMiB = 860;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -257,6 +257,19 @@ long long recv_grid_rows(const Dims &D) {        // received rows: unpack, parti
 }
 long long reply_grid_rows(const Dims &D) {       // rows a rank sends back: one per pair, or one per received row
     return D.flags & FL_FLAG_PARTIAL_SUMS ? recv_grid_rows(D) : grid_rows(D, D.expert_cap, D.typ_pair_rows);
+}
+
+// Whether a combine_send call over `rank_count` ranks stores its replies through the caches (st_payload).  All
+// ranks' replies are written before the first reduce, whatever number of calls they come in, so the bytes of the
+// whole group decide; calls for part of the ranks gain nothing earlier already.  us of a step, rows of 14 KB,
+// streaming against cached:
+//   one call: 0.9 GiB of replies 1004 and 997, 1.75 GiB 2018 and 2049
+//   rank by rank: 0.44 GiB 1217 and 1220, 0.9 GiB 1721 and 1761, 1.75 GiB 2704 and 2794, 3.5 GiB 4622 and 4834
+// Partial sums write fewer rows but read as many; counted by pairs as well, the line fits them too (0.9 GiB of
+// pairs 988 and 968, 1.3 GiB 1236 and 1248).
+bool replies_cached(const Dims &D, int rank_count) {
+    const long long limit = (long long)D.tune_cached_mb << 20;
+    return (long long)D.N * D.T * D.K * D.Bc <= (rank_count < D.N ? limit / 2 : limit);
 }
 
 // Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
@@ -727,8 +740,7 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
 
 int fl_moe_combine_send(fl_moe_ctx *ctx, int rb, int rc, const void *expert_y, void *stream) {
     if (!ctx) return FL_ERR_INVALID_ARG;
-    // replies in cached stores up to this much in the whole call (st_payload has both sides' figures)
-    const bool cached = (long long)rc * ctx->D.T * ctx->D.K * ctx->D.Bc <= ((long long)ctx->D.tune_cached_mb << 20);
+    const bool cached = replies_cached(ctx->D, rc);
     return for_rank_groups(ctx, rb, rc, [&](int r, int n, CallSpan call) {
         return combine_send_range(ctx, r, n, call, expert_y, cached, stream);
     });
@@ -905,6 +917,7 @@ int fl_moe_debug_launch_plan(const fl_moe_config *cfg, int rank_count, fl_moe_la
     if (rank_count < 1 || rank_count > D.N) return FL_ERR_INVALID_ARG;
     out->unpack_by_chunks = unpack_by_chunks(D, kComputeUnits, rank_count);
     out->replies_by_chunks = replies_by_chunks(D, kComputeUnits, rank_count);
+    out->replies_cached = replies_cached(D, rank_count);
     out->recv_grid_rows = recv_grid_rows(D);
     out->reply_grid_rows = reply_grid_rows(D);
     return FL_OK;
