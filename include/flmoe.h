@@ -428,6 +428,8 @@ typedef struct fl_moe_launch_plan {
                                     0: by waves on their own                                        */
     int32_t replies_by_chunks;   /* the same of combine_send                                        */
     int32_t replies_cached;      /* combine_send stores replies through the caches (0: past them)   */
+    int32_t layout_blocks;       /* counting blocks per source of the layout call ...               */
+    int32_t layout_tiles;        /* ... and the tiles of tokens they share out, in equal runs       */
     int64_t recv_grid_rows;      /* received rows per rank that the grid of dispatch_recv is sized for  */
     int64_t reply_grid_rows;     /* the same of the rows a rank sends back, for combine_send's grid     */
 } fl_moe_launch_plan;

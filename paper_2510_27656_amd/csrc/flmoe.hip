@@ -329,12 +329,19 @@ int check_ranks(const fl_moe_ctx *ctx, int rb, int rc) {
 int launch_status() { return hipGetLastError() == hipSuccess ? FL_OK : FL_ERR_HIP; }
 
 // Counting blocks per source: one per tile of tokens, as long as they and the planning blocks fit on the
-// machine together (two 1024-thread blocks on each of 256 compute units); beyond that a block walks
-// several tiles.
-void launch_layout(const Dims &D, const Tables &W, int rb, int rc, const int32_t *indices, const int32_t *num_tokens,
-                   hipStream_t st) {
+// machine together (two 1024-thread blocks on each compute unit); beyond that a block walks several
+// tiles, and there are only as many blocks as the tiles so dealt out need: every block counts all of the
+// source's tokens, also one that would own no tile.
+int layout_parts(const Dims &D, int cu_count, int rank_count) {
     const int tiles = (D.T + D.TT - 1) / D.TT;
-    const int parts = std::min(tiles, std::max(1, 512 / rc - 1));
+    const int most = std::min(tiles, std::max(1, 2 * cu_count / rank_count - 1));
+    const int per_block = (tiles + most - 1) / most;
+    return (tiles + per_block - 1) / per_block;
+}
+
+void launch_layout(const Dims &D, const Tables &W, int cu_count, int rb, int rc, const int32_t *indices,
+                   const int32_t *num_tokens, hipStream_t st) {
+    const int parts = layout_parts(D, cu_count, rc);
     const size_t lds = std::max(route_count_lds_bytes(D.E, D.N, D.K, D.TT), route_plan_lds_bytes(D.E, D.N, D.El));
     route_layout_kernel<<<dim3(rc * (parts + 1)), dim3(kRouteThreads), lds, st>>>(D, W, rb, rc, parts, indices,
                                                                                   num_tokens);
@@ -520,7 +527,7 @@ int fl_moe_layout(fl_moe_ctx *ctx, int rb, int rc, const int32_t *indices,
     ctx->num_tokens = num_tokens;
     {
         LaunchTimer t(ctx, KID_ROUTE_LAYOUT, st);
-        launch_layout(D, ctx->W, rb, rc, indices, num_tokens, st);
+        launch_layout(D, ctx->W, ctx->cu_count, rb, rc, indices, num_tokens, st);
     }
     if (view) {
         const Tables &W = ctx->W;
@@ -563,7 +570,7 @@ int fl_moe_layout_static(const fl_moe_config *cfg, const int32_t *indices, const
     // counters and epochs must start at zero, everything else is written before it is read.
     clear_words_kernel<<<dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, st>>>(
         (unsigned *)ptr, clear_words, W.status);
-    launch_layout(D, W, 0, D.N, indices, num_tokens, st);
+    launch_layout(D, W, kComputeUnits, 0, D.N, indices, num_tokens, st);
     return launch_status();
 }
 
@@ -918,6 +925,8 @@ int fl_moe_debug_launch_plan(const fl_moe_config *cfg, int rank_count, fl_moe_la
     out->unpack_by_chunks = unpack_by_chunks(D, kComputeUnits, rank_count);
     out->replies_by_chunks = replies_by_chunks(D, kComputeUnits, rank_count);
     out->replies_cached = replies_cached(D, rank_count);
+    out->layout_blocks = layout_parts(D, kComputeUnits, rank_count);
+    out->layout_tiles = (D.T + D.TT - 1) / D.TT;
     out->recv_grid_rows = recv_grid_rows(D);
     out->reply_grid_rows = reply_grid_rows(D);
     return FL_OK;

@@ -68,6 +68,7 @@ class fl_moe_debug_view(C.Structure):
 
 class fl_moe_launch_plan(C.Structure):
     _fields_ = [("unpack_by_chunks", C.c_int32), ("replies_by_chunks", C.c_int32), ("replies_cached", C.c_int32),
+                ("layout_blocks", C.c_int32), ("layout_tiles", C.c_int32),
                 ("recv_grid_rows", C.c_int64), ("reply_grid_rows", C.c_int64)]
 
 

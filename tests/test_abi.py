@@ -194,6 +194,19 @@ def test_replies_are_cached_by_the_size_of_the_whole_group():
     assert not cached(512, 32) and not cached(512, 16) and not cached(512, 1)
 
 
+@pytest.mark.parametrize("N,El,T", [(64, 4, 4096), (32, 8, 8192), (32, 8, 2048), (1, 8, 1 << 20), (8, 16, 40000), (4, 4, 1),
+                                    (64, 16, 3000)])
+def test_every_counting_block_of_the_layout_owns_a_tile(N, El, T):
+    for ranks in {1, N // 2 or 1, N}:
+        plan = flmoe.fl_moe_debug_launch_plan(cfg(n_ranks=N, n_experts=N * El, max_tokens=T, hidden=8), ranks)
+        blocks, tiles = plan.layout_blocks, plan.layout_tiles
+        assert 1 <= blocks <= min(tiles, max(1, 512 // ranks - 1))          # with the planning blocks on 256 units
+        per_block = -(-tiles // blocks)
+        assert (blocks - 1) * per_block < tiles                             # the last block's first tile exists
+        if tiles <= 512 // ranks - 1:
+            assert blocks == tiles
+
+
 def test_static_layout_entry_point_checks_its_arguments_before_touching_a_gpu():
     """fl_moe_layout_static validates on the host first: null or misaligned pointers, bad
     configurations and configurations beyond its static scratch array are refused without
