@@ -112,15 +112,12 @@ int resolve(const fl_moe_config *c, Dims *D) {
         // wire rows start on 128-byte lines: measured 5-10 % faster pack and unpack than 16-byte packing
         D->Bw = (long long)align_up((size_t)(D->H + 4ll * D->scales_per_row), 128);
     }
-    // bufA receives the combine replies, bufB the dispatched rows.  (bufB keeps room for a whole expert
-    // layout: workspace_bytes is what callers have planned their memory with.)
-    const long long need_a = (long long)D->T * D->K * D->Bc;
-    const long long b1 = D->recv_rows * D->Bw, b2 = D->expert_cap * D->Bc;
+    // bufA receives the combine replies, bufB the dispatched rows.
+    const size_t need_a = (size_t)D->T * D->K * D->Bc, need_b = (size_t)D->recv_rows * D->Bw;
     // Large payload buffers start on 2 MB boundaries of the workspace, rank by rank (the
     // page size the driver maps big allocations with): measured 3 % faster unpack at the
     // decode shape than 256-byte packing.  Small ones stay packed.
-    const size_t need_b = (size_t)(b1 > b2 ? b1 : b2);
-    D->bufA_rank_bytes = (long long)align_up((size_t)need_a, (size_t)need_a >= kBigPage ? kBigPage : 256);
+    D->bufA_rank_bytes = (long long)align_up(need_a, need_a >= kBigPage ? kBigPage : 256);
     D->bufB_rank_bytes = (long long)align_up(need_b, need_b >= kBigPage ? kBigPage : 256);
     // arrival counters count 16-byte units in 32 bits with a wrap-safe comparison
     if ((long long)D->T * (D->Bc / 16) >= (1ll << 31)) return FL_ERR_INVALID_ARG;
