@@ -152,11 +152,15 @@ def _check(code, where):
 # Handles and addresses go to the library as plain integers (its argument types turn them into pointers), and
 # the current stream's handle is read without building a stream object: the five calls of a small step are
 # bound by what the host does between launches (2 ranks x 16 tokens: 56 -> 44 us of host time per step).
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+# A torch built without GPU support has neither function; the host-only queries work there.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
     if stream is None:
+        if _raw_stream is None or _current_device is None:
+            return torch.cuda.current_stream().cuda_stream
         return _raw_stream(_current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 

@@ -5,6 +5,8 @@ import ctypes as C
 import math
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -233,6 +235,16 @@ def test_static_layout_entry_point_checks_its_arguments_before_touching_a_gpu():
     assert L.fl_moe_layout_static(C.byref(big), fake, fake, C.byref(out), None) == flmoe.FL_ERR_STATIC_LIMIT
     assert b"static" in L.fl_moe_strerror(flmoe.FL_ERR_STATIC_LIMIT)
     assert flmoe.FL_STATIC_SCRATCH_BYTES == 8 << 20
+
+
+def test_host_only_queries_work_on_a_torch_without_gpu_functions():
+    code = ("import torch\n"
+            "for name in ('_cuda_getCurrentRawStream', '_cuda_getDevice'):\n"
+            "    if hasattr(torch._C, name): delattr(torch._C, name)\n"
+            "from paper_2510_27656_amd import flmoe\n"
+            "c = flmoe.fl_moe_config(2, 8, 16, 2, 256, 0, 1, 0, 0, 0, 0, 0, 0)\n"
+            "assert flmoe.fl_moe_query_sizes(c).workspace_bytes > 0\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=100)
 
 
 def test_loaded_library_was_built_from_the_sources_in_the_tree():
