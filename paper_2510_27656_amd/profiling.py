@@ -23,6 +23,7 @@ import re
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROFILES = os.path.join(ROOT, "profiles")
+POLLING_UNPACK = re.compile(r"dispatch_unpack_chunk_kernel<(true|false), true>")    # second argument: POLL
 
 
 def _json_line(path):
@@ -49,16 +50,9 @@ def _counter_rows(path, wanted=None):
 
 
 def kernel_label(name):
-    """bench.py's name of a kernel from its demangled name (the two fabric launches are
-    told apart by their PHASE template argument)."""
-    short = _short(name).replace("flmoe::", "")
-    key = short.split("<")[0]
-    if key == "fabric_copy_kernel":
-        return "fabric_copy_kernel(dispatch)" if re.search(r"<(true|false), 0[,>]", name) \
-            else "fabric_copy_kernel(combine)"
-    if key == "fabric_private_kernel":
-        return "fabric_copy_kernel(dispatch, private slots)"
-    return key
+    """bench.py's name of a kernel from its demangled name (the two forms of the row kernels go by
+    one name)."""
+    return _short(name).replace("flmoe::", "").split("<")[0].replace("_chunk_kernel", "_kernel")
 
 
 def kernel_trace(stats_csv, bench_log, out_md, title, command):
@@ -160,8 +154,8 @@ def counters(counter_csv, out_md, title, command, per_kernel_note=""):
 
 def timeline(trace_csv, bench_log, out_md, title, command, foreign=False):
     """One step of a two-stream run as a table of kernel start and end times per queue, and
-    how often, over all traced steps, a receive-side kernel (gate or polling receive kernel)
-    was already running when the send kernels it waits for started.
+    how often, over all traced steps, the kernel that waits for the dispatch (gate or polling
+    unpack kernel) ran before and while the send kernels ran that it waits for.
     foreign: also list the kernels that are not the library's (a caller's own work on another
     stream), by the first 40 characters of their names; the waiting statistic is left out then."""
     rows = [r for r in csv.DictReader(open(trace_csv)) if foreign or "flmoe" in r["Kernel_Name"]]
@@ -195,20 +189,23 @@ def timeline(trace_csv, bench_log, out_md, title, command, foreign=False):
         print("\n".join(out))
         return
 
-    def span(step, pred):
-        ks = [r for r in step if pred(r["Kernel_Name"])]
-        return (min(int(r["Start_Timestamp"]) for r in ks), max(int(r["End_Timestamp"]) for r in ks)) if ks else None
-    early = late = 0
+    # what waits for the dispatch: the first gate kernel of the step, or (progressive) the polling unpack kernel
+    early = during = 0
     for st in steps:
-        waiter = span(st, lambda n: "arrival_gate" in n or "dispatch_unpack_kernel<true" in n)
-        sender = span(st, lambda n: "dispatch_pack" in n)
-        if waiter and sender:
-            early += waiter[0] < sender[0]
-            late += waiter[1] > sender[0]
-    out.append(f"\nIn {early} of {len(steps)} traced steps the first waiting receive-side kernel of the dispatch "
-               f"(gate kernel, or the polling unpack kernel) started before the dispatch send kernel did, and in "
-               f"{late} it was still running when that kernel started: the receivers were waiting on the counters, "
-               "not on stream order.")
+        gates = [r for r in st if "arrival_gate" in r["Kernel_Name"]][:1]
+        waiters = gates or [r for r in st if POLLING_UNPACK.search(r["Kernel_Name"])]
+        senders = [r for r in st if "dispatch_pack" in r["Kernel_Name"]]
+        if not waiters or not senders:
+            raise SystemExit("a traced step has no kernel that waits for the dispatch, or no dispatch send kernel")
+        begin, end = int(waiters[0]["Start_Timestamp"]), max(int(r["End_Timestamp"]) for r in waiters)
+        sent_from = min(int(r["Start_Timestamp"]) for r in senders)
+        sent_to = max(int(r["End_Timestamp"]) for r in senders)
+        early += begin < sent_from
+        during += begin < sent_to and end > sent_from
+    out.append(f"\nIn {early} of {len(steps)} traced steps the kernel that waits for the dispatch (gate kernel, or the "
+               f"polling unpack kernel) started before the dispatch send kernel did, and in {during} it ran while that "
+               "kernel ran" + (": the receivers were waiting on the counters, not on stream order."
+                               if during == len(steps) else "."))
     j = _json_line(bench_log)
     out.append(f"\nStep time of that run (profiler attached): {j['ms_per_step'] * 1e3:.0f} us; library build id "
                f"{j.get('library_build_id', 'not recorded')}.")

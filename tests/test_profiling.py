@@ -10,8 +10,7 @@ import pytest
 from paper_2510_27656_amd import profiling
 
 UNPACK = "void flmoe::dispatch_unpack_kernel<false, false>(flmoe::Dims, flmoe::Tables, int)"
-FABRIC_D = "void flmoe::fabric_copy_kernel<false, 0, true>(flmoe::Dims, flmoe::Tables, flmoe::FabricArgs, int)"
-FABRIC_C = "void flmoe::fabric_copy_kernel<true, 1, false>(flmoe::Dims, flmoe::Tables, flmoe::FabricArgs, int)"
+CHUNKS = "void flmoe::dispatch_unpack_chunk_kernel<false, %s>(flmoe::Dims, flmoe::Tables, int)"
 COPY = "flmoe::plain_copy_kernel(unsigned int*, unsigned int const*, unsigned long)"
 
 
@@ -24,12 +23,55 @@ def write_counters(path, counter, per_kernel):
                 w.writerow([name, counter, v])
 
 
-def test_kernel_labels_tell_the_two_fabric_launches_apart():
-    assert profiling.kernel_label(UNPACK) == "dispatch_unpack_kernel"
-    assert profiling.kernel_label(FABRIC_D) == "fabric_copy_kernel(dispatch)"
-    assert profiling.kernel_label(FABRIC_C) == "fabric_copy_kernel(combine)"
-    assert profiling.kernel_label("void flmoe::fabric_private_kernel<false, true>(int)") \
-        == "fabric_copy_kernel(dispatch, private slots)"
+def test_kernel_labels_are_the_names_of_the_bench():
+    from paper_2510_27656_amd import flmoe
+    names = [flmoe.lib().fl_moe_kernel_name(i).decode() for i in range(flmoe.FL_KERNEL_COUNT)]
+    for kernel in (UNPACK, CHUNKS % "true", CHUNKS % "false", "void flmoe::combine_partial_pack_chunk_kernel<true, true>(int)",
+                   "void flmoe::combine_pack_kernel<true>(int)", "void flmoe::dispatch_pack_e4m3_kernel<false, 512>(int)"):
+        assert profiling.kernel_label(kernel) in names
+    assert profiling.kernel_label(CHUNKS % "true") == "dispatch_unpack_kernel"
+
+
+def write_trace(path, steps):
+    """steps: lists of (kernel name, start, end); a step begins with its layout kernel."""
+    with open(path, "w", newline="") as f:
+        w = csv.writer(f)
+        w.writerow(["Kernel_Name", "Queue_Id", "Start_Timestamp", "End_Timestamp"])
+        for i, step in enumerate(steps):
+            for name, start, end in step:
+                w.writerow([name, 1, 1000000 * i + start, 1000000 * i + end])
+
+
+LAYOUT, GATE, PACK = "flmoe::route_layout_kernel(int)", "flmoe::arrival_gate_kernel(int)", "void flmoe::dispatch_pack_kernel<false>(int)"
+TIMELINES = {
+    # the dispatch gate before and during the send kernel; the combine gate comes later and says nothing about it
+    "gate": ([(LAYOUT, 0, 10), (GATE, 11, 90), (PACK, 20, 80), (UNPACK, 95, 200), (GATE, 210, 300)], 1, 1),
+    # in the order of one stream: the dispatch gate after the send kernel, the combine gate later still
+    "ordered": ([(LAYOUT, 0, 10), (PACK, 11, 80), (GATE, 81, 90), (UNPACK, 95, 200), (GATE, 210, 300)], 0, 0),
+    "polling": ([(LAYOUT, 0, 10), (CHUNKS % "true", 15, 200), (PACK, 20, 80)], 1, 1),
+    "polling, started later": ([(LAYOUT, 0, 10), (PACK, 11, 80), (CHUNKS % "true", 15, 200)], 0, 1),
+}
+
+
+@pytest.mark.parametrize("form", list(TIMELINES))
+def test_timeline_says_waiting_only_when_the_receiver_overlapped_the_sender(form, tmp_path):
+    step, early, during = TIMELINES[form]
+    trace, log, out = tmp_path / "t.csv", tmp_path / "log", tmp_path / "t.md"
+    write_trace(trace, [step] * 5)
+    log.write_text(json.dumps({"ms_per_step": 0.3}) + "\n")
+    profiling.timeline(str(trace), str(log), str(out), "t", "cmd")
+    text = out.read_text()
+    assert f"In {5 * early} of 5 traced steps" in text and f"in {5 * during} it ran while" in text
+    assert ("waiting on the counters" in text) == bool(during)
+
+
+@pytest.mark.parametrize("step", [[(LAYOUT, 0, 10), (PACK, 11, 80), (CHUNKS % "false", 81, 200)], [(LAYOUT, 0, 10), (GATE, 11, 80)]])
+def test_timeline_without_a_waiting_or_a_send_kernel_is_an_error(step, tmp_path):
+    trace, log = tmp_path / "t.csv", tmp_path / "log"
+    write_trace(trace, [step] * 5)
+    log.write_text(json.dumps({"ms_per_step": 0.3}) + "\n")
+    with pytest.raises(SystemExit):
+        profiling.timeline(str(trace), str(log), str(tmp_path / "t.md"), "t", "cmd")
 
 
 def test_traffic_is_scaled_by_the_copy_kernel_and_tied_to_the_build(tmp_path, monkeypatch):
