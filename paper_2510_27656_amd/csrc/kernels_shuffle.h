@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     // the same loop (the vectors after the code bytes go to expert_scales)
     const bool scales_as_vectors = D.scales_per_row > 0 && D.scales_per_row % 4 == 0;
     const int rowvec = nvec + (scales_as_vectors ? D.scales_per_row / 4 : 0);
-    const int v0 = sub * kWave + lane, step = G * kWave;   // lane's first vector of the row, distance to the next
+    const int v0 = sub * kWave, step = G * kWave;          // the wave's first vectors of the row, distance to the next
     constexpr int U = 4;
     v4u val[U];
     unsigned m = kNoEntry;
@@ -522,14 +522,16 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
                 }
             }
         }
-        load_batch(phys, v0);
+        load_batch(phys, v0 + lane);
         load_meta(phys);
         // copies of this row: entries come first in the sidecar
         const int n = __popcll(__ballot(m != kNoEntry));
         int place = 0;
         if (m != kNoEntry) place = W.base_x[((size_t)d * El + (m >> 24)) * N + s] + (int)(m & 0xFFFFFFu);
-        for (int b = v0; b < rowvec; b += U * step) {
-            if (b != v0) load_batch(phys, b);
+        // the whole wave stays in these loops, lanes beyond the row idle: a copy's place may stand in any lane
+        for (int b0 = v0; b0 < rowvec; b0 += U * step) {
+            const int b = b0 + lane;
+            if (b0 != v0) load_batch(phys, b);
             for (int k = 0; k < n; ++k) {
                 const size_t dr = (size_t)__builtin_amdgcn_readlane(place, k);
                 v4u *dst = (v4u *)(xd + dr * D.Be);
@@ -545,10 +547,13 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
         }
         if (D.scales_per_row && !scales_as_vectors && sub == 0) {   // odd scale counts: element by element
             const float *ssrc = (const float *)(recv + (size_t)phys * D.Bw + D.Be);
-            for (int v = lane; v < D.scales_per_row; v += kWave) {
-                const float sc = ssrc[v];
-                for (int k = 0; k < n; ++k)
-                    expert_scales[((size_t)d * D.expert_cap + __builtin_amdgcn_readlane(place, k)) * D.scales_per_row + v] = sc;
+            for (int b = 0; b < D.scales_per_row; b += kWave) {
+                const int v = b + lane;
+                const float sc = v < D.scales_per_row ? ssrc[v] : 0.f;
+                for (int k = 0; k < n; ++k) {
+                    const size_t dr = (size_t)__builtin_amdgcn_readlane(place, k);
+                    if (v < D.scales_per_row) expert_scales[((size_t)d * D.expert_cap + dr) * D.scales_per_row + v] = sc;
+                }
             }
         }
     }
@@ -866,14 +871,14 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // Against a workgroup that planned its rows in LDS: 301 tokens x 8 ranks, 6.7 KB rows 30.6 -> 26.1 us;
 // 14 KB rows, 32 ranks: 8 tokens 20.4 -> 16.1, 128: 147 -> 136, 512: 641 -> 627.
 template <bool CACHED>   // CACHED: see st_payload
-__global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
+__global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
     const int lane = tid & (kWave - 1);
     const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
     const int G = waves_per_row, sub = wave % G;
     const int row_step = (int)(gridDim.x * (kCopyThreads / kWave)) / G;     // the grid is a multiple of G blocks
-    const int nvec = (int)(D.Bc / 16), v0 = sub * kWave + lane, step = G * kWave;
+    const int nvec = (int)(D.Bc / 16), v0 = sub * kWave, step = G * kWave;
     // one round of loads
     const int plan_ok = W.plan_ok[d];
     const int total = W.recv_off[(size_t)d * (N + 1) + N];
@@ -897,7 +902,9 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
         if (m != kNoEntry) place = W.base_x[((size_t)d * El + (m >> 24)) * N + s] + (int)(m & 0xFFFFFFu);
         char *dst = W.bufA + (size_t)s * D.bufA_rank_bytes + (size_t)(__builtin_amdgcn_readlane(ret, s) + i) * D.Bc;
         constexpr int U = 4;
-        for (int b = v0; b < nvec; b += U * step) {
+        // the whole wave, as in the unpack kernel; lanes beyond the row sum its last vector and store nothing
+        for (int b0 = v0; b0 < nvec; b0 += U * step) {
+            const int b = b0 + lane;
             float acc[U][8];
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -909,10 +916,10 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_kernel(
                 v4u y[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (b + u * step < nvec) y[u] = ld_stream(src + b + u * step);
+                    if (b0 + u * step < nvec) y[u] = ld_stream(src + min(b + u * step, nvec - 1));
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (b + u * step < nvec) fma8(acc[u], wk, y[u]);
+                    if (b0 + u * step < nvec) fma8(acc[u], wk, y[u]);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)

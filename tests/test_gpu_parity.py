@@ -200,6 +200,7 @@ def test_layout_at_the_edges_of_tiles_blocks_and_records(shape, ragged):
 ROW_EDGES = [(4, 32, 30, 8, 4, "bf16"), (4, 32, 30, 2040, 4, "bf16"), (4, 32, 30, 2048, 4, "bf16"),
              (4, 32, 30, 2056, 4, "bf16"), (2, 8, 9, 40000, 3, "bf16"), (2, 256, 24, 64, 8, "bf16"),
              (3, 192, 24, 64, 8, "bf16"), (1, 256, 70, 64, 16, "bf16"), (64, 128, 6, 264, 16, "bf16"),
+             (2, 64, 30, 8, 16, "bf16"), (1, 64, 30, 128, 16, "e4m3"),      # more copies than lanes with a vector or a scale
              (4, 32, 30, 3968, 4, "e4m3"), (4, 32, 30, 4096, 4, "e4m3"), (2, 8, 9, 66048, 3, "e4m3")]
 
 
