@@ -138,6 +138,10 @@ __device__ inline void latch_status(int *status, int bit) {
     __hip_atomic_fetch_or(status, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Whether a counter has reached its expectation; both wrap, so the difference is taken in unsigned words
+// (a signed one may be compiled into a plain comparison, which fails while they pass 2^31).
+__device__ inline bool arrived(unsigned have, unsigned want) { return (int)(have - want) >= 0; }
+
 // Bounded wait of one wavefront: lane i (< n) polls ctr[i] until it has reached
 // its expectation (wrap-safe comparison; `expect` is either one value for all or,
 // with expect_arr, one per counter).  Returns true when all n counters arrived,
@@ -155,7 +159,7 @@ __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *e
         if (expect_arr && i < n) expect = expect_arr[i];
         for (;;) {
             bool ok = true;
-            if (i < n) ok = (int)(ld_relaxed(ctr + i) - expect) >= 0;
+            if (i < n) ok = arrived(ld_relaxed(ctr + i), expect);
             if (__all(ok)) break;
             if (++spins > spin_limit) return false;
             __builtin_amdgcn_s_sleep(SLEEP);

@@ -410,7 +410,7 @@ __global__ __launch_bounds__(kWave) void arrival_gate_kernel(Dims D, Tables W, i
     unsigned have = lane < N ? ld_relaxed(arrive + (size_t)r * N + lane) : 0u;
     if (!plan_ok) return;                           // step skipped: the receive kernel leaves on plan_ok too
     bool ok = true;
-    for (long long spins = 0; !__all((int)(have - want) >= 0); ++spins) {      // wrap-safe, bounded
+    for (long long spins = 0; !__all(arrived(have, want)); ++spins) {      // bounded
         if (spins >= D.spin_limit) { ok = false; break; }
         __builtin_amdgcn_s_sleep(64);
         if (lane < N) have = ld_relaxed(arrive + (size_t)r * N + lane);
@@ -510,11 +510,12 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
         const int in_source = r - __builtin_amdgcn_readlane(off, s);
         const int phys = PRIVATE ? recv_buffer_row(N, D.P, s, in_source, __builtin_amdgcn_readlane(shared_off, s)) : r;
         if (!gate) {                                // stream order has made it so; checked, bounded
-            bool landed = (int)(__builtin_amdgcn_readlane(have, s) - __builtin_amdgcn_readlane(want, s)) >= 0;
+            const unsigned expected = (unsigned)__builtin_amdgcn_readlane(want, s);
+            bool landed = arrived((unsigned)__builtin_amdgcn_readlane(have, s), expected);
             if (!landed) {
                 for (long long spins = 0; !landed && spins < D.spin_limit; ++spins) {
                     __builtin_amdgcn_s_sleep(64);
-                    landed = (int)(ld_relaxed(W.arrive_disp + (size_t)d * N + s) - __builtin_amdgcn_readlane(want, s)) >= 0;
+                    landed = arrived(ld_relaxed(W.arrive_disp + (size_t)d * N + s), expected);
                 }
                 if (!landed) {
                     if (lane == 0) latch_status(W.status, FL_STATUS_TIMEOUT);
@@ -619,7 +620,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
                 long long spins = 0;
                 for (;;) {
                     bool ok = false;
-                    if (tid < N) ok = (int)(ld_relaxed(W.arrive_disp + (size_t)d * N + tid) - my_expect) >= 0;
+                    if (tid < N) ok = arrived(ld_relaxed(W.arrive_disp + (size_t)d * N + tid), my_expect);
                     seen |= __ballot(ok);
                     if (!(range & ~seen)) break;
                     if (++spins > D.spin_limit) {

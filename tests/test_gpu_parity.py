@@ -1446,6 +1446,39 @@ def test_withheld_arrival_counter_times_out_then_recovers(kw):
         sh.close()
 
 
+@pytest.mark.parametrize("near", [0x7FFFFFFE, 0xFFFFFFFE])
+@pytest.mark.parametrize("kw", [dict(), dict(stream_ordered=True), dict(progressive_recv=True)])
+def test_withheld_transfer_is_noticed_while_the_counters_pass_a_sign_or_zero(kw, near):
+    """A receiver whose expectation has passed 2^31 (or 2^32) while a counter has not must wait for it."""
+    inp, dev, sh = small_shuffle(spin_limit=200, **kw)
+    try:
+        ref = oracle_step(inp)
+        for name in ("arrive_disp", "expect_disp"):
+            sh.debug()[name].view(torch.int32).fill_(near - (1 << 32) if near >= 1 << 31 else near)
+        sh.layout(dev["indices"], dev["num_tokens"])
+        sh.dispatch_send(dev["x"])
+        torch.cuda.synchronize()
+        arrive = sh.debug()["arrive_disp"].view(torch.int32)
+        s, d = [(s, d) for s in range(4) for d in range(4) if ref.lay.M[s, d] > 0][0]
+        delivered = int(arrive[d, s])
+        arrive[d, s] = near - (1 << 32) if near >= 1 << 31 else near         # nothing of this transfer yet
+        sh.dispatch_recv()
+        torch.cuda.synchronize()
+        assert sh.status() == flmoe.FL_STATUS_TIMEOUT
+        arrive[d, s] = delivered
+        sh.dispatch_recv()
+        y = harness.expert_stage(sh, dev["gain"])
+        sh.combine_send(y)
+        out = sh.combine_reduce(dev["weights"])
+        torch.cuda.synchronize()
+        assert sh.status() == 0
+        for r in range(inp.wl.n_ranks):
+            n = inp.num_tokens[r]
+            assert (bits(out)[r, :n] == ref.out[r, :n]).all()
+    finally:
+        sh.close()
+
+
 @pytest.mark.parametrize("nbytes", [16, 4096, 4096 + 16, 65536 - 16, (1 << 20) + 48])
 def test_plain_copy_fill_and_read_kernels_stay_inside_their_buffers(nbytes):
     """The three diagnostic kernels (machine ceilings, counter calibration) on sizes that
