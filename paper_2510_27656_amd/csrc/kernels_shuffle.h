@@ -871,10 +871,19 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // same five per unit as the plain copy takes measured 30 us where all eight take 26 (6.7 KB rows).
 // Against a workgroup that planned its rows in LDS: 301 tokens x 8 ranks, 6.7 KB rows 30.6 -> 26.1 us;
 // 14 KB rows, 32 ranks: 8 tokens 20.4 -> 16.1, 128: 147 -> 136, 512: 641 -> 627.
+//
+// A sidecar is what a sender stored, and behind an arrival wait that gave up (the caller's calls are all
+// enqueued by then) it holds whatever was there before: the expert row it names is kept inside expert_y.
+__device__ inline int sidecar_expert_row(const Dims &D, const Tables &W, int d, int s, unsigned entry) {
+    const unsigned j = min(entry >> 24, (unsigned)D.El - 1u);
+    const unsigned row = (unsigned)W.base_x[((size_t)d * D.El + j) * D.N + s] + (entry & 0xFFFFFFu);
+    return (int)min(row, (unsigned)D.expert_cap - 1u);
+}
+
 template <bool CACHED>   // CACHED: see st_payload
 __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
-    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
+    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
     const int lane = tid & (kWave - 1);
     const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
     const int G = waves_per_row, sub = wave % G;
@@ -900,7 +909,7 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
         const unsigned weight = lane < K ? meta[D.KM + lane] : 0u;
         const int n = __popcll(__ballot(m != kNoEntry));       // entries come first in the sidecar
         int place = 0;
-        if (m != kNoEntry) place = W.base_x[((size_t)d * El + (m >> 24)) * N + s] + (int)(m & 0xFFFFFFu);
+        if (m != kNoEntry) place = sidecar_expert_row(D, W, d, s, m);
         char *dst = W.bufA + (size_t)s * D.bufA_rank_bytes + (size_t)(__builtin_amdgcn_readlane(ret, s) + i) * D.Bc;
         constexpr int U = 4;
         // the whole wave, as in the unpack kernel; lanes beyond the row sum its last vector and store nothing
@@ -939,7 +948,7 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
 template <bool FENCED, bool CACHED>
 __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
-    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
+    const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
     __shared__ int off[FL_MAX_RANKS + 1];
     __shared__ int src_rows[kMaxRowsPerBlock][FL_MAX_TOPK];
     __shared__ float src_w[kMaxRowsPerBlock][FL_MAX_TOPK];
@@ -965,10 +974,12 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
             const int phys = D.P ? recv_buffer_row(N, D.P, s, i, W.recv_shared_off[(size_t)d * N + s]) : r;
             const unsigned *meta = W.recv_meta + ((size_t)d * D.recv_rows + phys) * D.MW;
             int n = 0;
+            src_rows[tid][0] = 0;              // read below whatever the sidecar says
+            src_w[tid][0] = 0.f;
             for (int k = 0; k < K; ++k) {
                 const unsigned m = meta[k];
                 if (m == kNoEntry) break;
-                src_rows[tid][n] = W.base_x[((size_t)d * El + (int)(m >> 24)) * N + s] + (int)(m & 0xFFFFFFu);
+                src_rows[tid][n] = sidecar_expert_row(D, W, d, s, m);
                 src_w[tid][n] = __uint_as_float(meta[D.KM + k]);
                 ++n;
             }

@@ -1479,6 +1479,42 @@ def test_withheld_transfer_is_noticed_while_the_counters_pass_a_sign_or_zero(kw,
         sh.close()
 
 
+@pytest.mark.parametrize("stale", [0xAB, 0xFF])                            # entries far outside; none
+@pytest.mark.parametrize("hidden,tokens", [(520, 40), (64, 1500)])         # rows by waves; by chunks
+@pytest.mark.parametrize("kw", [dict(), dict(stream_ordered=True), dict(progressive_recv=True)])
+def test_partial_sums_after_a_dispatch_that_never_came_stay_in_bounds(kw, hidden, tokens, stale):
+    """All calls of a step are enqueued before its time-out can be seen, so the partial-sum pack runs on sidecars
+    nobody wrote: here bytes that name experts and rows far outside, or none.  The step is reported, and after a
+    reset the next step is right."""
+    wl = wlmod.custom("no_dispatch", 8, 64, tokens, hidden, 8, seed=3)
+    inp = wlmod.make_inputs(wl)
+    dev = harness.to_device(inp)
+    ref = oracle_step(inp, partial=True)
+    sh = harness.make_shuffle(inp, spin_limit=50, partial_sums=True, **kw)
+    try:
+        sh.layout(dev["indices"], dev["num_tokens"])
+        torch.cuda.synchronize()
+        positions = sh.layout_tables()["comb_pos"]
+        tables_end = positions.data_ptr() - sh.workspace.data_ptr() + positions.numel() * 4
+        sh.workspace[tables_end:].fill_(stale)         # sidecars and receive buffers
+        sh.out.view(torch.int16).fill_(POISON)
+        y = torch.zeros((8, sh.expert_capacity_rows, hidden), dtype=torch.bfloat16, device="cuda:0")
+        sh.dispatch_recv()
+        sh.combine_send(y)
+        sh.combine_reduce(dev["weights"])
+        torch.cuda.synchronize()
+        assert sh.status() & flmoe.FL_STATUS_TIMEOUT
+        sh.reset()
+        out = harness.run_step(sh, dev)
+        torch.cuda.synchronize()
+        assert sh.status() == 0
+        for r in range(8):
+            n = inp.num_tokens[r]
+            assert (bits(out)[r, :n] == ref.out_partial[r, :n]).all()
+    finally:
+        sh.close()
+
+
 @pytest.mark.parametrize("nbytes", [16, 4096, 4096 + 16, 65536 - 16, (1 << 20) + 48])
 def test_plain_copy_fill_and_read_kernels_stay_inside_their_buffers(nbytes):
     """The three diagnostic kernels (machine ceilings, counter calibration) on sizes that
