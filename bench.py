@@ -229,7 +229,7 @@ def main():
                          "kernels poll per source on capped grids")
     ap.add_argument("--overlap", action="store_true",
                     help="send calls on a second stream: the receivers wait on the arrival counters "
-                         "while the fabric copy runs (reports the step time only)")
+                         "while the send kernels run (reports the step time only)")
     ap.add_argument("--push", action="store_true",
                     help="FL_FLAG_PEER_PUSH, which every send call now follows: accepted, same kernels")
     ap.add_argument("--partial-sums", action="store_true",
@@ -551,8 +551,9 @@ def main():
         del g
 
     # The modes and workloads that are not the headline, measured in the same run: the
-    # fabric that keeps the arrival-counter contract with no ordering assumed (one stream,
-    # and with senders and receivers on two streams), and the other four named workloads.
+    # default, in which nothing but the arrival counters orders senders and receivers (one stream,
+    # and with senders and receivers on two streams), the other orderings, and the other four
+    # named workloads.
     side = args.workload == "dsv3_decode" and not args.headline_only and not (
         args.push or args.stream_ordered or args.progressive or args.partial_sums or args.private_rows
         or args.ready_e4m3)

@@ -41,7 +41,7 @@ const char *kKernelNames[FL_KERNEL_COUNT] = {
     "announce_kernel(combine)"};
 
 constexpr int kEventPool = 512;
-constexpr long long kMaxRowBlocks = 1 << 18;      // blocks with barriers: loop only when far oversized
+constexpr long long kMaxRowBlocks = 1 << 18;      // per launch of a row kernel; rows beyond are looped over
 constexpr long long kDefaultSpin = 1 << 20;       // polls about 2 us apart: gives up after about 2 s
 
 constexpr size_t kBigPage = 2u << 20;

@@ -113,7 +113,7 @@ def run_step_two_streams(sh: flmoe.MoEShuffle, dev, identity=False, send_order=N
     layout, send calls on stream B: the receivers' gate kernels (or, with
     progressive_recv, the receive kernels themselves) poll the arrival counters while
     the send kernels are still running or have not started.  Events order only what the
-    re-use of the two staging buffers needs.  send_order: list of (rank_begin,
+    re-use of the receive buffers needs.  send_order: list of (rank_begin,
     rank_count) launches for the send calls, default one launch for all ranks."""
     N = sh.N
     a, b = streams or (torch.cuda.Stream(), torch.cuda.Stream())
@@ -147,7 +147,7 @@ def run_step_two_streams(sh: flmoe.MoEShuffle, dev, identity=False, send_order=N
 
 def run_chunked(sh: flmoe.MoEShuffle, chunks, out_full: torch.Tensor, identity=False, with_expert=True):
     """Chunked prefill: one context sized for `sh.T` tokens per rank is stepped over a
-    list of (first token, uploaded chunk) pairs, so that the staging buffers hold one
+    list of (first token, uploaded chunk) pairs, so that the receive buffers hold one
     chunk instead of the whole batch (section Performance, prefill: transfers are not
     chunked there, and buffer memory limits which models can be deployed).  Every
     token's combined row lands in out_full [N][T_total][H]."""

@@ -45,7 +45,7 @@ def check_tables(sh, ref, N):
 
 def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_split=False,
                     ordering="counters", private_rows=0, push=False, partial=False, launch_mb=None,
-                    capacities=None, cached_mb=None):
+                    capacities=None, cached_mb=None, grid_pct=None):
     """ordering: "counters" = the default mode (the arrival counters are the only ordering:
     announce and gate kernels), "stream" = FL_FLAG_STREAM_ORDERED, "progressive" =
     FL_FLAG_PROGRESSIVE_RECV."""
@@ -63,8 +63,10 @@ def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_sp
     try:
         if launch_mb is not None:        # payload per launch above which a call is cut into rank groups
             flmoe.fl_moe_debug_tune(sh.ctx, 6, launch_mb)
-        if cached_mb is not None:        # replies per call above which they are stored past the caches
+        if cached_mb is not None:        # all ranks' replies above which they are stored past the caches
             flmoe.fl_moe_debug_tune(sh.ctx, 4, cached_mb)
+        if grid_pct is not None:         # grids for this percentage of the rows uniform routing brings
+            flmoe.fl_moe_debug_tune(sh.ctx, 5, grid_pct)
         if wl.dispatch_dtype == "bf16":
             sh.expert_x.view(torch.int16).fill_(POISON)
         sh.out.view(torch.int16).fill_(POISON)
@@ -542,7 +544,7 @@ def test_parity_at_the_limits_of_the_interface(name):
 
 def test_parity_random_shapes():
     """Forty seeded random shapes: ranks, experts per rank, top-k, hidden size (any
-    multiple of 8), ragged token counts, padding, zero fill, fabric mode, capacity."""
+    multiple of 8), ragged token counts, padding, zero fill, ordering mode, capacity."""
     rng = np.random.default_rng(2024)
     for trial in range(40):
         N = int(rng.choice([1, 2, 3, 4, 6, 8, 16]))
@@ -629,9 +631,9 @@ def test_large_calls_are_issued_as_several_launches_over_rank_groups(kw):
 @pytest.mark.parametrize("kw", [dict(), dict(push=True), dict(partial=True, private_rows=50),
                                 dict(ordering="stream"), dict(ordering="progressive")])
 def test_every_token_to_one_rank_is_served_by_the_row_loops(kw):
-    """Grids are sized for twice the rows uniform routing would bring; here one rank
-    hosts every chosen expert and receives N*T rows and N*T*K pairs, several times
-    that, so its kernels loop over their grids."""
+    """Grids are sized for the rows uniform routing would bring and six standard
+    deviations; here one rank hosts every chosen expert and receives N*T rows and N*T*K
+    pairs, several times that, so its kernels loop over their grids."""
     inp = wlmod.make_inputs(wlmod.custom("hot_rank", 8, 64, 300, 256, 4, seed=77, ragged=True))
     rng = np.random.default_rng(77)
     hot = 3
@@ -639,6 +641,19 @@ def test_every_token_to_one_rank_is_served_by_the_row_loops(kw):
         for t in range(300):
             inp.indices[s, t] = hot * 8 + rng.permutation(8)[:4]
     sh, _, _ = run_and_compare(inp, zero_pad=True, **kw)
+    sh.close()
+
+
+# (tokens, hidden): a row per wave, per two, per four, per sixteen waves in turns; many short rows, by chunks
+@pytest.mark.parametrize("shape", [(60, 264), (60, 2056), (60, 7168), (30, 40000), (2600, 64)], ids=str)
+@pytest.mark.parametrize("kw", [dict(), dict(ordering="stream"), dict(ordering="progressive"), dict(private_rows=7),
+                                dict(partial=True), dict(partial=True, private_rows=7, ordering="stream")],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+def test_row_loops_beyond_the_grid(shape, kw):
+    """Every kernel that loops over rows, on a grid for a hundredth of them: bit for bit."""
+    T, H = shape
+    wl = wlmod.custom("row_loops", 4, 8, T, H, 4, seed=H, ragged=True)
+    sh, _, _ = run_and_compare(wlmod.make_inputs(wl), grid_pct=1, **kw)
     sh.close()
 
 
@@ -746,7 +761,7 @@ def test_concurrent_send_and_receive_on_two_streams(name, shuffled, push, progre
             perm = np.random.default_rng(5).permutation(N)
             order = [(int(r), 1) for r in perm]
         for rep in range(3):
-            flmoe.fl_moe_debug_tune(sh.ctx, 8, rep)    # the fabric takes each sender's destinations in another order
+            flmoe.fl_moe_debug_tune(sh.ctx, 8, rep)    # the send kernels take each sender's rows in another order
             sh.out.view(torch.int16).fill_(POISON)
             out = harness.run_step_two_streams(sh, dev, wl.expert == "identity", order)
             torch.cuda.synchronize()
@@ -771,7 +786,7 @@ def test_one_stream_per_rank_no_cross_rank_events(push):
     """Every simulated rank issues its payload calls (rank_count = 1) on a stream of its
     own, as ranks on separate GPUs would; between the ranks there is no event and no
     common stream, only the arrival counters.  Each rank keeps its own calls in order
-    (its stream), which in the default mode is also all the re-use of the staging
+    (its stream), which in the default mode is also all the re-use of the receive
     buffers needs: a rank's gate passes only after every peer's announce kernel ran,
     and that kernel runs only after the peer's payload kernels have ended.  Steps
     follow each other without a device synchronisation; each step's results are
@@ -835,8 +850,8 @@ def test_one_stream_per_rank_no_cross_rank_events(push):
 def test_soak_two_streams_shuffled_senders_every_step_checked(progressive, steps):
     """Bounded soak of the path where only the arrival counters order senders and
     receivers: the decode workload, receive calls on one stream, one send call per
-    sender on another in a freshly shuffled order every step, the fabric kernel taking
-    each sender's destinations in a different order from step to step.  The first step
+    sender on another in a freshly shuffled order every step, the send kernels taking
+    each sender's rows in a different order from step to step.  The first step
     is compared with the oracle; every later step must reproduce its expert rows and
     its combined output bit for bit (outputs are poisoned before each step, so a
     receiver that ran ahead of its data cannot pass), with a clean status word."""
@@ -1138,7 +1153,7 @@ def test_chunked_steps_give_the_same_combined_output(chunk):
     """A context sized for `chunk` tokens per rank stepped over the batch: every chunk
     matches the oracle run on that chunk (tables, dispatched rows, combined rows), and
     the combined rows of all tokens equal those of the one-shot step, since a token's
-    sum does not depend on its neighbours.  The staging buffers shrink with the chunk."""
+    sum does not depend on its neighbours.  The receive buffers shrink with the chunk."""
     inp = wlmod.make_inputs(wlmod.custom("chunked", 4, 32, 100, 520, 4, seed=91, ragged=True))
     wl = inp.wl
     N, T = wl.n_ranks, wl.tokens
