@@ -390,28 +390,30 @@ const char *fl_moe_strerror(int code);
 
 int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
 
-/* Diagnostic: overrides a launch-shape knob of the copy kernels (results never
- * change).  knob 0 = rows per workgroup of the unpack / reply kernels that take chunks of rows
- * (0 = chosen from the row size, at most 64), knob 1 = row loads issued together
- * per thread in combine_reduce (0 = all K, at most 8), knob 2 = accepted without
- * effect (it shaped a copy kernel that is no longer launched), knob 3 =
- * workgroups per token in the pack kernel (0 = chosen from the row size, at
- * most 16), knob 4 = size in MiB of all ranks' replies above
- * which combine_send uses streaming instead of cached stores (default 1024; half of it when a
- * call serves part of the ranks), knob 5 = percentage of the rows uniform routing would bring to a rank that the
- * grids of the receive-side and reply kernels are sized for (default: the mean plus six
- * standard deviations; 0 = the whole capacity; a rank that holds more is served by the kernels' row loops),
- * knob 6 = payload in MiB one launch should move per direction: a call whose ranks
- * move more than three times as much is issued as several launches over rank
- * groups of about this size (default 860; 0 = always one launch per kernel;
- * contexts with FL_FLAG_PROGRESSIVE_RECV are never cut), knob 7 = eighths of the
- * machine's resident-workgroup slots the polling receive kernels of
- * FL_FLAG_PROGRESSIVE_RECV may take (default 3), knob 8 = order in which the send kernels
- * take a sender's rows (0 = ascending, 1 = descending, 2 = starting in the middle and
- * wrapping round; a test switch: nothing may depend on the order in which transfers are
- * carried out), knob 9 = workgroups that share one
- * token in combine_reduce, each summing a slice of the row (0 = chosen from the row
- * size).  A value of -1 restores a knob's default. */
+/* Diagnostic: overrides a launch-shape knob of the row kernels (results never change; a
+ * value of -1 restores a knob's default).
+ *   knob 0 = rows per workgroup of the unpack / reply kernels that take chunks of rows
+ *            (0 = chosen from the row size, at most 64)
+ *   knob 1 = row loads issued together per thread in combine_reduce (0 = all K, at most 8)
+ *   knob 2 = accepted without effect (it shaped a copy kernel that is no longer launched)
+ *   knob 3 = workgroups per token in the pack kernel (0 = chosen from the row size, at most 16)
+ *   knob 4 = size in MiB of all ranks' replies above which combine_send uses streaming instead
+ *            of cached stores (default 1024; half of it when a call serves part of the ranks)
+ *   knob 5 = percentage of the rows uniform routing would bring to a rank that the grids of the
+ *            receive-side and reply kernels are sized for (default: the mean plus six standard
+ *            deviations; 0 = the whole capacity; a rank that holds more is served by the
+ *            kernels' row loops)
+ *   knob 6 = payload in MiB one launch should move per direction: a call whose ranks move more
+ *            than three times as much is issued as several launches over rank groups of about
+ *            this size (default 860; 0 = always one launch per kernel; contexts with
+ *            FL_FLAG_PROGRESSIVE_RECV are never cut)
+ *   knob 7 = eighths of the machine's resident-workgroup slots the polling receive kernels of
+ *            FL_FLAG_PROGRESSIVE_RECV may take (default 3)
+ *   knob 8 = order in which the send kernels take a sender's rows (0 = ascending, 1 = descending,
+ *            2 = starting in the middle and wrapping round; a test switch: nothing may depend on
+ *            the order in which transfers are carried out)
+ *   knob 9 = workgroups that share one token in combine_reduce, each summing a slice of the row
+ *            (0 = chosen from the row size) */
 int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value);
 
 /* Diagnostic, host only (no GPU needed): how a payload call over `rank_count` ranks of

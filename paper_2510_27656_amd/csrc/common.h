@@ -24,7 +24,7 @@ struct Dims {
     long long spin_limit;
     int KM;               // sidecar entries per row: K rounded up to a multiple of 4
     int MW;               // words per sidecar row: KM, or 2*KM when the routing weights travel too
-    int tune_rows;        // rows per block of the copy kernels (0 = by row size)
+    int tune_rows;        // rows per block of the kernels that take chunks of rows (0 = by row size)
     int tune_reduce;      // loads in flight per thread in the reduce kernel (0 = all K)
     int tune_slices;      // blocks per token in the pack kernel (0 = by row size)
     int tune_cached_mb;   // combine replies are stored through the caches up to this many MiB of the group (replies_cached)

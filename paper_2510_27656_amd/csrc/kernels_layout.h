@@ -10,8 +10,9 @@
 // exchange, scan.  So every link is one round of independent loads or one pass of
 // all the block's threads, and what can be worked out before a wait is.  32 ranks, 256
 // experts, top 8, kernel time with one counting block per source, 32-bit records stored
-// word by word and tables that single threads walked -> now: 4 tokens per rank 17.0 ->
-// 11.9 us, 128: 18.9 -> 14.9, 2048: 66.4 -> 22.6 (10 of them the count of all tokens).
+// word by word and tables that single threads walked -> now: 4 tokens per rank 17.2 ->
+// 11.7 us, 128: 17.8 -> 12.3, 2048: 66.4 -> 22.3 (10 of them the count of all tokens);
+// several tiles per counting block, the call: 8192 tokens 243 -> 54.
 #pragma once
 #include "common.h"
 
@@ -61,8 +62,8 @@ __device__ inline int div_by(unsigned e, unsigned m) { return (int)((e * m) >> 2
 // over the blocks, and every block first counts all of the source's tokens with LDS
 // adds (and, apart, those before its own first tile), one token per thread: counting
 // them again in every block costs less than the blocks would wait for each other's parts
-// unless there are many tokens, and keeps a counting block from ever waiting.  One scan over the E + N totals gives the offsets.  The last pass
-// writes every pair's final positions.
+// unless there are many tokens, and keeps a counting block from ever waiting.  One scan over
+// the E + N totals gives the offsets.  The last pass writes every pair's final positions.
 //
 // Outputs for rank s: by part 0, C[s][.], M[s][.], send_off[s][.], comb_off[s][.] and the
 // route record, which is pushed into every peer's routes[peer][s] before

@@ -451,7 +451,7 @@ __device__ inline void unpack_extras(const Dims &D, const Tables &W, int d, int 
 }
 
 // Rows that have landed before the kernel starts (behind a gate kernel, or in the caller's
-// stream order).  Bound by memory traffic in large steps and by the chain of dependent loads
+// stream order), unless they are many and short.  Bound by memory traffic in large steps and by the chain of dependent loads
 // in small ones, so a wave works alone, without LDS or barriers: offsets and verdicts in one
 // round, by a ballot over the offsets the row's source, then the wave's share of the row
 // together with the sidecar, then, lane k for the k-th copy, its place, then the stores.
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
 // Short rows, and every row in progressive mode: a block takes a chunk of received rows at a time,
 // plans their copies in LDS and moves the chunk as one run of vectors, so that no lane idles however
 // short a row is; the wave kernel above is bound by the rate at which waves start then (rule and
-// both sides' times: short_rows in flmoe.hip).
+// both sides' times: by_chunks in flmoe.hip).
 //
 // POLL (progressive mode): the block waits (bounded) for the arrival counters of the sources its
 // rows came from.  The kernel may have been started before any payload
@@ -870,7 +870,8 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // then the sum.  Bound by reads (P rows read, D written); workgroups are not held back here: the
 // same five per unit as the plain copy takes measured 30 us where all eight take 26 (6.7 KB rows).
 // Against a workgroup that planned its rows in LDS: 301 tokens x 8 ranks, 6.7 KB rows 30.6 -> 26.1 us;
-// 14 KB rows, 32 ranks: 8 tokens 20.4 -> 16.1, 128: 147 -> 136, 512: 641 -> 627.
+// 14 KB rows, 32 ranks: 8 tokens 20.4 -> 16.1, 128: 147 -> 136, 512: 641 -> 627.  The launch bound keeps
+// it at 72 registers; one more and only six workgroups fit a unit: 2 KB rows, step 277 -> 286 us.
 //
 // A sidecar is what a sender stored, and behind an arrival wait that gave up (the caller's calls are all
 // enqueued by then) it holds whatever was there before: the expert row it names is kept inside expert_y.
