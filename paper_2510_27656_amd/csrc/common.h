@@ -64,8 +64,8 @@ struct Tables {
     int *M;               // [N][N]
     int *send_off;        // [N][N+1]
     int *comb_off;        // [N][N+1]
-    int *send_row;        // [N][T][K]  for the first slot of each destination: number of this copy among all
-                          //            copies the source sends, ordered by (destination, token); else ~destination
+    int *send_to;         // [N][T][K]  for the first slot of each destination: (destination << 24) | number of this
+                          //            copy among those the source sends there, in token order; else ~destination
     unsigned *pair_meta;  // [N][T][K]  (local expert << 24) | rank of the token among the source's tokens of that expert
     int *comb_pos;        // [N][T][K]
     // written by the receiving side of the layout step
@@ -77,8 +77,7 @@ struct Tables {
                           //                  beyond its private slots start in dst's shared range
     int *comb_dst_off;    // [N d][N s]       row in s's combine receive buffer where d's reply starts
     int *ret_off;         // [N d][N s]       partial sums: row in s's buffer where d's shares start,
-                          //                  = rows s sent to lower ranks, so a share returns to the
-                          //                  row that send_row gives its token copy
+                          //                  = rows s sent to lower ranks (send_off[s][d])
     int *base_x;          // [N][El][N]       first expert-major row of (local expert, source)
     int *cs_base;         // [N][N][El]       first combine-send row of (source, local expert)
     int *cs_off;          // [N][N+1]         first combine-send row of each source

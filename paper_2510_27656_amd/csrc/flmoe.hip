@@ -174,7 +174,7 @@ size_t carve(const Dims &D, void *base, Tables *W, size_t *total) {
     W->cs_base = c.take<int>(N * N * El);
     W->cs_off = c.take<int>(N * (N + 1));
     const size_t small = align_up(c.cur, 256);
-    W->send_row = c.take<int>(N * T * K);
+    W->send_to = c.take<int>(N * T * K);
     W->pair_meta = c.take<unsigned>(N * T * K);
     W->comb_pos = c.take<int>(N * T * K);
     W->recv_meta = c.take<unsigned>(N * (size_t)D.recv_rows * D.MW);
@@ -425,7 +425,7 @@ size_t carve_static(const Dims &D, void *base, Tables *W, size_t *clear_words, i
     W->base_x = c.take<int>(N * El * N);
     W->cs_base = c.take<int>(N * N * El);
     W->cs_off = c.take<int>(N * (N + 1));
-    W->send_row = c.take<int>(N * T * K);
+    W->send_to = c.take<int>(N * T * K);
     W->pair_meta = c.take<unsigned>(N * T * K);
     return align_up(c.cur, 256);
 }

@@ -67,7 +67,7 @@ __device__ inline int div_by(unsigned e, unsigned m) { return (int)((e * m) >> 2
 //
 // Outputs for rank s: by part 0, C[s][.], M[s][.], send_off[s][.], comb_off[s][.] and the
 // route record, which is pushed into every peer's routes[peer][s] before
-// arrive_route[peer][s] is bumped; by every part, send_row / pair_meta / comb_pos of the
+// arrive_route[peer][s] is bumped; by every part, send_to / pair_meta / comb_pos of the
 // pairs of its tiles.
 __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W, int s, int part, int parts,
                                                   const int *__restrict__ indices,
@@ -275,7 +275,7 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
             const size_t o = ((size_t)s * D.T + t0) * K + p;
             W.comb_pos[o] = start[re] + rank_e;
             W.pair_meta[o] = ((unsigned)(e - d * El) << 24) | (unsigned)rank_e;
-            W.send_row[o] = first ? start[rd] - pairs_total + rank_d : ~d;
+            W.send_to[o] = first ? d << 24 | rank_d : ~d;
         }
     }
 }

@@ -57,38 +57,30 @@ __device__ inline int in_order(int order, int i, int n) {
 }
 
 // Where the copies of token (s, t) go.  Lane k < K of a block's first wave fetches the k-th expert's
-// entries, lane d < N rank d's offsets, all in the kernel's first round of loads (the tables hold
+// entries, lane d < N rank d's offset, all in the kernel's first round of loads (the tables hold
 // something for every t < T; it is used only once the step and the token are known to be valid).
 // One round instead of three in a row: e4m3 pack of 128 tokens per rank 57.5 -> 52.7 us (its one
 // workgroup per row had nothing else to do meanwhile), bf16 4 / 8 tokens 10.0 / 11.4 -> 9.4 / 10.8,
 // the same from 32 tokens on.  The caller's expert ids are not read again: those of absent tokens
 // need not exist, so fetching them would have to wait for the token count.
 struct CopyPlan {
-    int row, send_off, dst_off;
+    int to, dst_off;
     unsigned meta;
     __device__ inline void load(const Dims &D, const Tables &W, int s, size_t pair0, int lane) {
-        row = -1; meta = 0; send_off = 0x7fffffff; dst_off = 0;
+        to = -1; meta = 0; dst_off = 0;
         if (lane < D.K) {
-            row = W.send_row[pair0 + lane];
+            to = W.send_to[pair0 + lane];
             meta = W.pair_meta[pair0 + lane];
         }
-        if (lane < D.N) {
-            send_off = W.send_off[(size_t)s * (D.N + 1) + lane];
-            dst_off = W.dst_off[(size_t)s * D.N + lane];
-        }
+        if (lane < D.N) dst_off = W.dst_off[(size_t)s * D.N + lane];
     }
     // destination rank of this lane's expert, and the row in its receive buffer when the token's copy
     // for that rank belongs to this lane (the first of its experts there), else -1; whole wave
     __device__ inline int target(const Dims &D, int s, int *dst) const {
-        int d = ~row;                          // named by the entry itself ...
-        for (int k = 0; k < D.K; ++k) {        // ... or the last rank whose copies start at or before this one
-            const int n = __builtin_amdgcn_readlane(row, k);
-            const int at = __popcll(__ballot(send_off <= n)) - 1;
-            if (row >= 0 && (int)(threadIdx.x & (kWave - 1)) == k) d = at;
-        }
+        const int d = to >= 0 ? to >> 24 : ~to;
         *dst = d;
-        const int first = __shfl(send_off, d), shared = __shfl(dst_off, d);
-        return row >= 0 ? recv_buffer_row(D.N, D.P, s, row - first, shared) : -1;
+        const int shared = __shfl(dst_off, d);
+        return to >= 0 ? recv_buffer_row(D.N, D.P, s, to & 0xFFFFFF, shared) : -1;
     }
 };
 
@@ -863,7 +855,7 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // weight * expert output over the token's experts on d, rounded to bf16.  The
 // share of received row number i from source s goes back to row
 // ret_off[d][s] + i of s's combine receive buffer, the position of the token copy among
-// all copies s sent, so s finds it through its own send_row table.
+// all copies s sent, so s finds it through its own send_to table.
 //
 // A wave works alone on its share of a row, as in the unpack and combine pack kernels: the
 // row's source by a ballot, lane k for the sidecar's k-th entry, its expert row and its weight,
@@ -1092,7 +1084,7 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
 constexpr int kReduceMaxThreads = 1024;
 //
 // PARTIAL (sender-side partial sums): the token's rows are the shares of its
-// distinct expert ranks, found at send_row[s][t][k] for every k that is the first
+// distinct expert ranks, found through send_to[s][t][k] for every k that is the first
 // of its rank; they are added in that order in fp32 (a fused multiply-add with
 // weight 1 is an exact add), the weights having been applied on the expert ranks.
 template <bool FENCED, bool PARTIAL>
@@ -1116,19 +1108,21 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     const int k = tid - kWave;
     int pf_pos = -1;
     float pf_w = 1.0f;
+    const int sent = PARTIAL && fetcher && k < N ? W.send_off[(size_t)s * (N + 1) + k] : 0;   // lane d: copies for lower ranks
     // token t's row positions (and weights): the load, then, once it has landed, the LDS copy
     auto fetch = [&](int t) {
         if (k >= K) { pf_pos = -1; return; }
         const size_t pair = ((size_t)s * D.T + t) * K + k;
-        if (PARTIAL) pf_pos = W.send_row[pair];               // share rows: first k of each expert rank
+        if (PARTIAL) pf_pos = W.send_to[pair];                // share rows: first k of each expert rank
         else { pf_pos = W.comb_pos[pair]; pf_w = weights[pair]; }
     };
     auto publish = [&](int buf) {
         if (PARTIAL) {                                        // compacted in k order, weight 1: an exact add
             const unsigned long long have = __ballot(pf_pos >= 0);
+            const int first = __shfl(sent, pf_pos >= 0 ? pf_pos >> 24 : 0);
             if (pf_pos >= 0) {
                 const int at = __popcll(have & ((1ull << k) - 1));
-                pos[buf][at] = pf_pos;
+                pos[buf][at] = first + (pf_pos & 0xFFFFFF);
                 w[buf][at] = 1.0f;
             }
             if (k == 0) n_shares[buf] = __popcll(have);
