@@ -398,7 +398,7 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
  *   knob 2 = accepted without effect (it shaped a copy kernel that is no longer launched)
  *   knob 3 = workgroups per token in the pack kernel (0 = chosen from the row size, at most 16)
  *   knob 4 = size in MiB of all ranks' replies above which combine_send uses streaming instead
- *            of cached stores (default 1024; half of it when a call serves part of the ranks)
+ *            of write-through stores (default 1024; half of it when a call serves part of the ranks)
  *   knob 5 = percentage of the rows uniform routing would bring to a rank that the grids of the
  *            receive-side and reply kernels are sized for (default: the mean plus six standard
  *            deviations; 0 = the whole capacity; a rank that holds more is served by the
@@ -429,7 +429,7 @@ typedef struct fl_moe_launch_plan {
     int32_t unpack_by_chunks;    /* 1: dispatch_recv moves rows by workgroups that plan a chunk of rows,
                                     0: by waves on their own                                        */
     int32_t replies_by_chunks;   /* the same of combine_send                                        */
-    int32_t replies_cached;      /* combine_send stores replies through the caches (0: past them)   */
+    int32_t replies_cached;      /* combine_send writes replies through the caches (0: streams them) */
     int32_t layout_blocks;       /* counting blocks per source of the layout call ...               */
     int32_t layout_tiles;        /* ... and the tiles of tokens they share out, in equal runs       */
     int64_t recv_grid_rows;      /* received rows per rank that the grid of dispatch_recv is sized for  */

@@ -27,7 +27,7 @@ struct Dims {
     int tune_rows;        // rows per block of the kernels that take chunks of rows (0 = by row size)
     int tune_reduce;      // loads in flight per thread in the reduce kernel (0 = all K)
     int tune_slices;      // blocks per token in the pack kernel (0 = by row size)
-    int tune_cached_mb;   // combine replies are stored through the caches up to this many MiB of the group (replies_cached)
+    int tune_cached_mb;   // combine replies are written through up to this many MiB of the group, then streamed (replies_cached)
     int tune_grid_pct;    // row-kernel grids cover this percentage of the rows uniform routing would bring
                           // (0 = the whole capacity, -1 = the mean and six standard deviations); kernels
                           // loop over whatever is beyond
@@ -104,8 +104,8 @@ constexpr unsigned kNoEntry = 0xFFFFFFFFu;
 // invalidates its caches (agent-scope acquire) before touching the payload.
 // FENCED = false covers the other two modes, where whole kernels order payload and
 // counters: the announce kernel behind the payload kernels (default), or the
-// caller's stream order (FL_FLAG_STREAM_ORDERED); payload stores are then ordinary
-// stores and the in-kernel counter accesses relaxed atomics.
+// caller's stream order (FL_FLAG_STREAM_ORDERED); nothing waits for the payload stores
+// inside the kernels then, and the in-kernel counter accesses are relaxed atomics.
 __device__ inline unsigned ld_relaxed(const unsigned *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -231,34 +231,37 @@ __device__ inline int seg_of_short(const int *off, int n, int x, int *start) {
 
 // ---------------------------------------------------------------- row copies
 // 16-byte streaming accesses.  The payload of every copy kernel is touched once
-// per kernel, so loads, and stores of results, carry the non-temporal hint; on this part a
+// per kernel, so loads, and the unpack kernel's stores, carry the non-temporal hint; on this part a
 // plain copy with these hints and four independent loads per thread in flight
 // measured fastest (more loads in flight per CU than that overruns the L2).
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 __device__ inline v4u ld_stream(const v4u *p) { return __builtin_nontemporal_load(p); }
 __device__ inline void st_stream(v4u *p, v4u v) { __builtin_nontemporal_store(v, p); }
-// Payload store into a peer's receive buffer.  FENCED (progressive mode): device scope,
-// written through to memory so that another XCD can see it without an L2 write-back.
-// CACHED: an ordinary store, so that the last-level cache may hold the rows until the
-// receive kernel reads them (what the kernel leaves dirty in the L2s is written back at
-// its end); otherwise a streaming store.  Measured with both sides' steps in turns:
-//   dispatch, DeepSeek-V3 rows, us of send + unpack, streaming -> cached: 32 tokens per
-//     rank 72 -> 63, 128: 247 -> 229, 512: 996 -> 985, 2048: 4013 -> 3959, so always cached;
-//   combine send + reduce: 32 tokens per rank 72 -> 64, 128: 252 -> 228, 256 (0.9 GB of
-//     replies): 503 -> 489, 512 (1.9 GB): 1020 -> 1035, 1024: 2026 -> 2152.
-// The kernels that write what the caller reads keep streaming stores: cached there, the
-// write-backs land on the kernel after (128 tokens, cached unpack: step 474 -> 513 us).
-template <bool FENCED, bool CACHED>
+// 16-byte store at device scope: written through the XCD's L2 to memory, where every XCD sees it once it
+// has been acknowledged.  No dirty line is left for the end of the kernel, which otherwise waits until the
+// L2s have written theirs back (32 ranks x 4 tokens: 3.9 us from the pack kernel's last store to the next
+// kernel's first instruction, 1.5 behind a kernel without dirty lines).
+__device__ inline void st_through(v4u *p, v4u v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+}
+// Payload store into a peer's receive buffer: written through (THROUGH), so that the last-level cache may
+// hold the rows until the receive kernel reads them, or a streaming store.  us of a DeepSeek-V3 step with
+// ordinary stores in the send kernels -> written through: 4 tokens per rank 47.2 -> 46.2, 32: 136.8 -> 135.8,
+// 128: 465 -> 455, e4m3 128: 368 -> 362, 256: 990 -> 964; replies streamed instead: 128 487, 256 975 (larger
+// calls: replies_cached).  Dispatch rows never lose written through.  Of the kernels that write what the caller
+// reads, the reduce kernel writes through as well (128: 455 -> 452, 32: 135.8 -> 134.0, 16 ranks x 256 tokens of
+// 4 KB 123.4 -> 120.3, e4m3 512: 1523 -> 1478), the unpack kernel streams (written through, 128: 505, e4m3 393;
+// ordinary stores 490: the write-backs land on the kernel after).
+template <bool THROUGH>
 __device__ inline void st_payload(v4u *p, v4u v) {
-    if (FENCED) asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
-    else if (CACHED) *p = v;
-    else __builtin_nontemporal_store(v, p);
+    if (THROUGH) st_through(p, v);
+    else st_stream(p, v);
 }
 
 // A block copies `nrows` rows of `nvec` vectors each; vector v of the chunk lies
 // in row v / nvec.  src_of(row) / dst_of(row) return the row's byte address.
 // All loads of a batch are issued before its stores.
-template <int NT, bool FENCED, bool CACHED, class SrcFn, class DstFn>
+template <int NT, bool THROUGH, class SrcFn, class DstFn>
 __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of, DstFn dst_of) {
     if (nrows == 1) {                          // one row per block: addresses are uniform
         const v4u *s = (const v4u *)src_of(0);
@@ -270,7 +273,7 @@ __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of
                 if (b + i * NT < nvec) r[i] = ld_stream(s + b + i * NT);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (b + i * NT < nvec) st_payload<FENCED, CACHED>(d + b + i * NT, r[i]);
+                if (b + i * NT < nvec) st_payload<THROUGH>(d + b + i * NT, r[i]);
         }
         return;
     }
@@ -290,7 +293,7 @@ __device__ inline void copy_rows_flat(int nrows, int nvec, int tid, SrcFn src_of
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int v = b + i * NT;
-            if (v < total) st_payload<FENCED, CACHED>((v4u *)dst_of(row[i]) + col[i], r[i]);
+            if (v < total) st_payload<THROUGH>((v4u *)dst_of(row[i]) + col[i], r[i]);
         }
     }
 }

@@ -256,14 +256,14 @@ long long reply_grid_rows(const Dims &D) {       // rows a rank sends back: one 
     return D.flags & FL_FLAG_PARTIAL_SUMS ? recv_grid_rows(D) : grid_rows(D, D.expert_cap, D.typ_pair_rows);
 }
 
-// Whether a combine_send call over `rank_count` ranks stores its replies through the caches (st_payload).  All
+// Whether a combine_send call over `rank_count` ranks writes its replies through (st_payload) or streams them.  All
 // ranks' replies are written before the first reduce, whatever number of calls they come in, so the bytes of the
 // whole group decide; calls for part of the ranks gain nothing earlier already.  us of a step, rows of 14 KB,
-// streaming against cached:
-//   one call: 0.9 GiB of replies 1004 and 997, 1.75 GiB 2018 and 2049
-//   rank by rank: 0.44 GiB 1217 and 1220, 0.9 GiB 1721 and 1761, 1.75 GiB 2704 and 2794, 3.5 GiB 4622 and 4834
-// Partial sums write fewer rows but read as many; counted by pairs as well, the line fits them too (0.9 GiB of
-// pairs 988 and 968, 1.3 GiB 1236 and 1248).
+// streaming against written through:
+//   one call: 0.44 GiB of replies 487 and 452, 0.9 GiB 975 and 941, 1.3 GiB 1413 and 1443, 3.5 GiB 3772 and 3835
+//   rank by rank: 0.9 GiB 1679 and 1679, 1.75 GiB 2630 and 2686
+// (1.75 GiB in one call 1990 and 1911; allocations at other addresses move steps of this size by 4 %.)
+// Partial sums write fewer rows but read as many; counted by pairs as well.
 bool replies_cached(const Dims &D, int rank_count) {
     const long long limit = (long long)D.tune_cached_mb << 20;
     return (long long)D.N * D.T * D.K * D.Bc <= (rank_count < D.N ? limit / 2 : limit);

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (b + i * kPackThreads < v1)
-                    st_payload<FENCED, true>(dst + b + i * kPackThreads, r[i]);
+                    st_payload<true>(dst + b + i * kPackThreads, r[i]);
         }
     }
     // Ready-made e4m3 codes (section Kernel Microbenchmarks: the dispatched token is 7168
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                     const int row = s_row[k];
                     if (row < 0) continue;
                     char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
-                    st_payload<FENCED, true>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    st_payload<true>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
                 }
             }
         } else {
@@ -334,10 +334,10 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         const int row = s_row[k];
         if (row < 0) continue;
         char *dst = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes + (size_t)row * D.Bw;
-        if (live) st_payload<FENCED, true>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
+        if (live) st_payload<true>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
         if (scale_vectors) {
             if (tid < nsv)
-                st_payload<FENCED, true>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
+                st_payload<true>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
                                                  ((const v4u *)s_scale)[tid]);
         } else if (live && sub == 0) {
             st_word<FENCED>((int *)(dst + D.Be) + blk, __float_as_int(scale));
@@ -742,7 +742,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
 // Bound by memory traffic from 32 tokens on (6.5 TB/s at 128 tokens, the plain copy's rate),
 // by the chain below.  Before -> now: 4 tokens 11.6 -> 11.0 us, 8: 15.9 -> 15.0, 32: 40.7 -> 39.5,
 // 128: 144.5 -> 144, 512: 649 -> 631 (672 with eight workgroups per unit).
-template <bool CACHED>   // CACHED: see st_payload
+template <bool THROUGH>   // THROUGH: see st_payload
 __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
@@ -783,7 +783,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
                 if (b + u * step < nvec) val[u] = ld_stream(src + b + u * step);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (b + u * step < nvec) st_payload<false, CACHED>(dst + b + u * step, val[u]);
+                if (b + u * step < nvec) st_payload<THROUGH>(dst + b + u * step, val[u]);
         }
     }
 }
@@ -791,7 +791,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
 // Short rows, and every row in progressive mode: a workgroup per chunk of rows, as in the unpack kernels.
 // FENCED (progressive mode): written through, and the workgroup adds each row's units
 // to arrive[source][this rank] itself, once per row rather than once per wave.
-template <bool FENCED, bool CACHED>
+template <bool FENCED, bool THROUGH>
 __global__ __launch_bounds__(kCopyThreads) void combine_pack_chunk_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_chunk_kernel(
             push_to[tid] = make_int2(s, W.comb_dst_off[(size_t)d * N + s] + (q - off[s]));
         }
         __syncthreads();
-        copy_rows_flat<kCopyThreads, FENCED, CACHED>(
+        copy_rows_flat<kCopyThreads, THROUGH>(
             q1 - q0, nvec, tid,
             [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
             [&](int r) {
@@ -873,7 +873,7 @@ __device__ inline int sidecar_expert_row(const Dims &D, const Tables &W, int d, 
     return (int)min(row, (unsigned)D.expert_cap - 1u);
 }
 
-template <bool CACHED>   // CACHED: see st_payload
+template <bool THROUGH>   // THROUGH: see st_payload
 __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
@@ -930,15 +930,15 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
                     v4u o;
                     o.x = pack_bf16x2(acc[u][0], acc[u][1]); o.y = pack_bf16x2(acc[u][2], acc[u][3]);
                     o.z = pack_bf16x2(acc[u][4], acc[u][5]); o.w = pack_bf16x2(acc[u][6], acc[u][7]);
-                    st_payload<false, CACHED>((v4u *)dst + b + u * step, o);
+                    st_payload<THROUGH>((v4u *)dst + b + u * step, o);
                 }
         }
     }
 }
 
-// Short rows, and every row in progressive mode: a workgroup per chunk of rows; FENCED, CACHED as in
+// Short rows, and every row in progressive mode: a workgroup per chunk of rows; FENCED, THROUGH as in
 // combine_pack_chunk_kernel.
-template <bool FENCED, bool CACHED>
+template <bool FENCED, bool THROUGH>
 __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int rows_per_block) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
@@ -1009,7 +1009,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
                 o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
                 o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
                 char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Bc;
-                st_payload<FENCED, CACHED>((v4u *)dst + col[u], o);
+                st_payload<THROUGH>((v4u *)dst + col[u], o);
             }
         }
         if (FENCED) {
@@ -1049,7 +1049,7 @@ __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos,
         v4u o;
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
-        st_stream(out + v, o);
+        st_through(out + v, o);
     }
 }
 
@@ -1074,7 +1074,7 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
         v4u o;
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
-        st_stream(out + v, o);
+        st_through(out + v, o);
     }
 }
 
