@@ -269,12 +269,11 @@ int fl_moe_layout(fl_moe_ctx *ctx, int rank_begin, int rank_count, const int32_t
 
 /* fl_moe_layout for callers that cannot allocate device memory or hold a context:
  * code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc.  It needs no fl_moe_ctx and no workspace: the route records, message
- * counters and per-pair tables that fl_moe_layout keeps in the caller's workspace
+ * hipMalloc.  It needs no fl_moe_ctx and no workspace: the records its two kernels exchange
  * live in an array of FL_STATIC_SCRATCH_BYTES bytes inside the library's device
  * image (every GPU the library runs on holds one copy until the process ends),
  * and the call itself allocates nothing (no hipMalloc / hipFree, no events, no host
- * allocation).  It acts for all cfg->n_ranks ranks in one launch and writes the
+ * allocation).  It acts for all cfg->n_ranks ranks and writes the
  * same tables, with the same contents, that fl_moe_layout's view points to, into
  * the caller's buffers:
  *   counts [N][E], dedup_counts [N][N], tokens_per_expert [N][E/N],
@@ -284,10 +283,10 @@ int fl_moe_layout(fl_moe_ctx *ctx, int rank_begin, int rank_count, const int32_t
  * Capacities, expert_align, max_private_rows and the flags of cfg are honoured
  * as in fl_moe_layout (capacity overflow and bad expert ids clear plan_ok on every
  * rank and set the status bits).  Returns FL_ERR_STATIC_LIMIT, and enqueues
- * nothing, when the configuration's tables do not fit the array (it holds the
- * 32-rank, 256-expert, top-8 shape up to about 3000 tokens per rank).  The call
- * only enqueues kernels on `stream`; the scratch is cleared by a kernel of the
- * call, not by a memset.  The first call on each device looks up the array's
+ * nothing, when the tables that fl_moe_layout keeps for the configuration would not fit
+ * the array (it holds the 32-rank, 256-expert, top-8 shape up to about 3000 tokens per
+ * rank).  The call only enqueues kernels on `stream` and relies on nothing that an earlier
+ * call left in the array.  The first call on each device looks up the array's
  * address (hipGetSymbolAddress); make that call outside graph capture.
  * Every call on one GPU uses that GPU's one array: calls that overlap in time on
  * the same GPU (different streams, or a graph replay racing an eager call) race

@@ -17,15 +17,10 @@
 
 using namespace flmoe;
 
-// A configuration fits fl_moe_layout_static when its tables, with E + 2N + 1 words per route record, fit
-// FL_STATIC_SCRATCH_BYTES.  Records are shorter than that except for a few ranks with a few experts, where
-// they may take up to 12 words more (N <= 9: under 4 KB in all): the slack behind the array.
-constexpr int kStaticSlack = 64 << 10;
-
 // Scratch of fl_moe_layout_static, part of the device image: every GPU the library
 // is loaded on holds its own copy at its own address.  In host code this name is
 // only a handle for hipGetSymbolAddress, never a device address.
-static __device__ __align__(256) unsigned char scratch[FL_STATIC_SCRATCH_BYTES + kStaticSlack];
+static __device__ __align__(256) unsigned char scratch[FL_STATIC_SCRATCH_BYTES];
 
 namespace {
 
@@ -405,37 +400,26 @@ int static_scratch(void **ptr) {
     return FL_OK;
 }
 
-// What route_layout_kernel keeps outside the caller-visible tables, carved from
-// `base` (nullptr: measure only).  The counters come first, in one run of
-// *clear_words 32-bit words at `base` that every call clears.  Returns the bytes needed
-// with `record_words` words per route record.
-size_t carve_static(const Dims &D, void *base, Tables *W, size_t *clear_words, int record_words) {
-    Carver c(base);
-    const size_t N = D.N, El = D.El, T = D.T, K = D.K;
-    W->epoch_route = c.take<unsigned>(N);
-    W->arrive_route = c.take<unsigned>(N * N);
-    W->expect_disp = c.take<unsigned>(N * N);
-    W->expect_comb = c.take<unsigned>(N * N);
-    *clear_words = align_up(c.cur, 256) / sizeof(unsigned);
-    W->routes = c.take<int>(N * N * record_words);
-    W->recv_shared_off = c.take<int>(N * N);
-    W->dst_off = c.take<int>(N * N);
-    W->comb_dst_off = c.take<int>(N * N);
-    W->ret_off = c.take<int>(N * N);
-    W->base_x = c.take<int>(N * El * N);
-    W->cs_base = c.take<int>(N * N * El);
-    W->cs_off = c.take<int>(N * (N + 1));
-    W->send_to = c.take<int>(N * T * K);
-    W->pair_meta = c.take<unsigned>(N * T * K);
-    return align_up(c.cur, 256);
+// Whether fl_moe_layout_static takes a configuration: when what fl_moe_layout keeps beside the caller-visible tables
+// (counters, route records of E + 2N + 1 words, offsets, per-pair tables) would fit the array.  The call itself
+// needs less, a record per counting block (static_parts).
+bool fits_static(const Dims &D) {
+    const size_t N = D.N, El = D.El, pairs = (size_t)D.T * D.K * N;
+    size_t sum = 0;
+    for (size_t words : {N, N * N, N * N, N * N, N * N * (D.E + 2 * N + 1), N * N, N * N, N * N, N * N, N * El * N, N * N * El,
+                         N * (N + 1), pairs, pairs})
+        sum = align_up(sum, 256) + words * sizeof(int);
+    return align_up(sum, 256) <= FL_STATIC_SCRATCH_BYTES;
 }
 
-// Zeroes the counters of the static scratch and the caller's status word (a kernel,
-// not a memset node: the call may be captured in a HIP graph).
-__global__ void clear_words_kernel(unsigned *words, size_t n, int *status) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) words[i] = 0u;
-    if (i == 0) *status = 0;
+// Tile size and blocks per source of fl_moe_layout_static: about kStaticBlocks over all sources, each with an
+// equal run of tiles.  At most 128 records of at most 1088 words: 0.6 MB of the array.
+int static_parts(Dims *D) {
+    const int want = std::min(kStaticMaxParts, std::max(1, kStaticBlocks / D->N));
+    const int per_part = ((D->T + want - 1) / want + 31) / 32 * 32;
+    D->TT = std::min(D->TT, per_part);
+    const int tiles = (D->T + D->TT - 1) / D->TT, per = (tiles + want - 1) / want;
+    return (tiles + per - 1) / per;
 }
 
 }  // namespace
@@ -549,25 +533,21 @@ int fl_moe_layout_static(const fl_moe_config *cfg, const int32_t *indices, const
     Dims D;
     int e = resolve(cfg, &D);
     if (e != FL_OK) return e;
-    Tables W;
-    memset(&W, 0, sizeof(W));
-    size_t clear_words = 0;
-    if (carve_static(D, nullptr, &W, &clear_words, D.E + 2 * D.N + 1) > FL_STATIC_SCRATCH_BYTES)
-        return FL_ERR_STATIC_LIMIT;
+    if (!fits_static(D)) return FL_ERR_STATIC_LIMIT;
     void *ptr = nullptr;
     e = static_scratch(&ptr);
     if (e != FL_OK) return e;
-    carve_static(D, ptr, &W, &clear_words, D.route_len);
-    W.C = out->counts; W.M = out->dedup_counts; W.G = out->tokens_per_expert;
-    W.send_off = out->send_off; W.recv_off = out->recv_off; W.expert_off = out->expert_off;
-    W.comb_off = out->comb_off; W.comb_pos = out->comb_pos; W.plan_ok = out->plan_ok;
-    W.status = out->status;
+    const int parts = static_parts(&D);
+    int *records = (int *)ptr, *invalid = records + (size_t)D.N * parts * static_record_words(D.E, D.N, D.T);
+    const StaticOut tables{out->counts, out->dedup_counts, out->tokens_per_expert, out->send_off, out->recv_off,
+                           out->expert_off, out->comb_off, out->comb_pos, out->plan_ok, out->status};
     hipStream_t st = (hipStream_t)stream;
-    // The array keeps what the last call left (possibly of another shape): the message
-    // counters and epochs must start at zero, everything else is written before it is read.
-    clear_words_kernel<<<dim3((unsigned)((clear_words + 255) / 256)), dim3(256), 0, st>>>(
-        (unsigned *)ptr, clear_words, W.status);
-    launch_layout(D, W, kComputeUnits, 0, D.N, indices, num_tokens, st);
+    static_count_kernel<<<dim3(D.N * parts), dim3(kStaticCountThreads),
+                          (size_t)2 * static_record_words(D.E, D.N, D.T) * sizeof(int), st>>>(
+        D, parts, indices, num_tokens, records, invalid);
+    auto kernel = route_wide(D.T) ? static_tables_kernel<true> : static_tables_kernel<false>;
+    kernel<<<dim3(D.N * parts + 1), dim3(kRouteThreads), static_tables_lds_bytes(D.E, D.N, D.K, D.TT), st>>>(
+        D, tables, parts, indices, num_tokens, records, invalid);
     return launch_status();
 }
 

@@ -46,6 +46,36 @@ __host__ __device__ inline int route_record_words(int E, int N, int T) {
 __device__ inline unsigned div_magic(int El) { return ((1u << 20) + El - 1) / (unsigned)El; }
 __device__ inline int div_by(unsigned e, unsigned m) { return (int)((e * m) >> 20); }
 
+// Counts the tokens [t0, t1) of one source, one per thread and turn: hit(t, row) for every expert that token t
+// lists and, once each, for every rank (row E + rank) with one of its experts.  A token counts once per expert and
+// once per rank, as in the bit matrices below; ids outside the range or repeated raise *bad.  KT >= K: with a loop of
+// the largest top-k there is, comparing ids took most of the time (2048 tokens x top 8: 10 us of the layout kernel).
+template <int KT, class HitFn>
+__device__ __forceinline__ void count_tokens(const int *__restrict__ ids, int t0, int t1, int threads, int E, int K,
+                                             unsigned by_el, int *bad, HitFn hit) {
+    bool wrong = false;
+    for (int t = t0 + (int)threadIdx.x; t < t1; t += threads) {
+        int id[KT];
+#pragma unroll
+        for (int k = 0; k < KT; ++k) id[k] = k < K ? ids[(size_t)t * K + k] : -1;
+        unsigned long long ranks = 0;                      // N <= 64
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+            if (k < K) {
+                bool again = (unsigned)id[k] >= (unsigned)E;
+#pragma unroll
+                for (int k2 = 0; k2 < k; ++k2) again |= id[k2] == id[k];
+                wrong |= again;
+                if (again) continue;
+                hit(t, id[k]);
+                const int d = div_by(id[k], by_el);
+                if (!(ranks >> d & 1)) hit(t, E + d);
+                ranks |= 1ull << d;
+            }
+    }
+    if (wrong) *bad = 1;
+}
+
 // Block `part` of the `parts` blocks of source rank s.
 //
 // For every tile of TT tokens a block keeps two LDS bit matrices: row e of the
@@ -154,36 +184,12 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
         // total in its lower and the hits before this block's tiles in its upper half
         const bool wide = route_wide(D.T);
         const int mine = min(tile0 * D.TT, Ts);
-        for (int t = tid; t < Ts; t += kRouteThreads) {
-            const int one = !wide && t < mine ? 0x10001 : 1;
-            int id[FL_MAX_TOPK], owner[FL_MAX_TOPK];
-#pragma unroll
-            for (int k = 0; k < FL_MAX_TOPK; ++k) id[k] = k < K ? idx_s[(size_t)t * K + k] : 0;
-#pragma unroll
-            for (int k = 0; k < FL_MAX_TOPK; ++k) {
-                const int e = id[k];
-                const bool ok = e >= 0 && e < E;
-                owner[k] = ok ? div_by(e, by_el) : -1;
-                if (k < K) {
-                    bool first = true, again = !ok;
-#pragma unroll
-                    for (int k2 = 0; k2 < FL_MAX_TOPK; ++k2)
-                        if (k2 < k) {
-                            again |= id[k2] == e;          // same expert twice in one token
-                            first &= owner[k2] != owner[k];
-                        }
-                    if (again) bad = 1;
-                    else {                                 // a token counts once per expert, as in the bit matrices
-                        atomicAdd(&count[e], one);
-                        if (first) atomicAdd(&count[E + owner[k]], one);
-                        if (wide && t < mine) {
-                            atomicAdd(&base[e], 1);
-                            if (first) atomicAdd(&base[E + owner[k]], 1);
-                        }
-                    }
-                }
-            }
-        }
+        auto hit = [&](int t, int row) {
+            atomicAdd(&count[row], !wide && t < mine ? 0x10001 : 1);
+            if (wide && t < mine) atomicAdd(&base[row], 1);
+        };
+        if (K <= 8) count_tokens<8>(idx_s, 0, Ts, kRouteThreads, E, K, by_el, &bad, hit);
+        else count_tokens<FL_MAX_TOPK>(idx_s, 0, Ts, kRouteThreads, E, K, by_el, &bad, hit);
         if (!wide) {
             __syncthreads();
             for (int r = tid; r < rows; r += kRouteThreads) {
@@ -497,6 +503,283 @@ __global__ __launch_bounds__(kRouteThreads) void route_layout_kernel(
         route_plan_block<true>(D, W, rank_begin + b - rank_count * parts, lds);
     else
         route_plan_block<false>(D, W, rank_begin + b - rank_count * parts, lds);
+}
+
+// ------------------------------------------------------------------ the layout step without a context
+// Two kernels instead of one: the boundary between them does what the message counters and the wait do above, so
+// nothing has to be cleared before a call or trusted from the call before.  Bound by latency like the kernel above:
+// a chain of load, count, scan, store.  The first counts every tile of tokens once, a block each; the second
+// scans (every block of a source for itself, from its parts' counts) and writes the pairs' positions, one block more
+// derives the receivers' tables for all ranks.  The call, against a kernel that cleared counters and the single
+// kernel behind it (32 ranks x 256 experts, top 8): 16 tokens per rank 12.7 -> 9.5 us (what two launches take the
+// host), 512: 14.8 -> 10.4, 2048: 23.2 -> 12.8; 8 ranks x 128 experts, 3000 tokens 31.4 -> 9.6.
+constexpr int kStaticCountThreads = 256;
+// Counting blocks a call aims at, over all sources: with more, the tables take longer to read than the tiles to
+// count (2048 tokens, 64 / 128 / 256 / 512 blocks: 18.0 / 12.8 / 13.4 / 16.9 us).
+constexpr int kStaticBlocks = 128;
+constexpr int kStaticMaxParts = 64;
+
+struct StaticOut {                           // the caller's tables
+    int *C, *M, *G, *send_off, *recv_off, *expert_off, *comb_off, *comb_pos, *plan_ok, *status;
+};
+
+// Counts of one block: E + N numbers, 16 bits each unless a count may need more; whole 16-byte vectors.
+__host__ __device__ inline int static_record_words(int E, int N, int T) {
+    return ((route_wide(T) ? E + N : (E + N + 1) / 2) + 3) / 4 * 4;
+}
+
+__host__ __device__ inline size_t static_tables_lds_bytes(int E, int N, int K, int TT) {
+    const size_t rows = (size_t)E + N;
+    const size_t block = ((size_t)E * route_row_stride(TT) * 2 + 3 * rows + E + 20) * sizeof(int) + (size_t)TT * K * 2;
+    const size_t plan = ((size_t)E + (size_t)N * N + N) * sizeof(int);
+    return block > plan ? block : plan;
+}
+
+// Block (source s, part): its tiles' tokens; *record and the part's verdict on its ids.
+__global__ __launch_bounds__(kStaticCountThreads) void static_count_kernel(
+    Dims D, int parts, const int *__restrict__ indices, const int *__restrict__ num_tokens, int *__restrict__ records,
+    int *__restrict__ invalid) {
+    extern __shared__ __align__(16) unsigned lds[];
+    __shared__ int bad;
+    const int s = blockIdx.x / parts, part = blockIdx.x - s * parts, tid = threadIdx.x;
+    const int words = static_record_words(D.E, D.N, D.T);
+    int *count = (int *)lds;                               // [2 * words], of which E + N count
+    const int given = num_tokens[s];
+    for (int r = tid; r < 2 * words; r += kStaticCountThreads) count[r] = 0;
+    if (tid == 0) bad = given < 0 || given > D.T;
+    const int Ts = max(0, min(given, D.T));
+    const int tiles = (D.T + D.TT - 1) / D.TT, per = (tiles + parts - 1) / parts;
+    const int t0 = min(part * per * D.TT, Ts), t1 = min((part + 1) * per * D.TT, Ts);
+    __syncthreads();
+    auto hit = [&](int, int row) { atomicAdd(&count[row], 1); };
+    const int *ids = indices + (size_t)s * D.T * D.K;
+    if (D.K <= 8) count_tokens<8>(ids, t0, t1, kStaticCountThreads, D.E, D.K, div_magic(D.El), &bad, hit);
+    else count_tokens<FL_MAX_TOPK>(ids, t0, t1, kStaticCountThreads, D.E, D.K, div_magic(D.El), &bad, hit);
+    __syncthreads();
+    int *record = records + (size_t)blockIdx.x * words;
+    for (int w = tid; w < words; w += kStaticCountThreads)
+        record[w] = route_wide(D.T) ? count[w] : (int)((unsigned)count[2 * w] | (unsigned)count[2 * w + 1] << 16);
+    if (tid == 0) invalid[blockIdx.x] = bad;
+}
+
+// Blocks [0, N * parts): the tables of their source (part 0) and the positions of their tiles' pairs; the last
+// block: what the receivers know, for every rank.
+template <bool WIDE>
+__device__ __forceinline__ void static_positions_block(const Dims &D, const StaticOut &out, int s, int part, int parts,
+                                                       const int *__restrict__ indices, const int *__restrict__ num_tokens,
+                                                       const int *__restrict__ records, unsigned *lds) {
+    const int tid = threadIdx.x, E = D.E, N = D.N, El = D.El, K = D.K, rows = E + N;
+    const int words = static_record_words(E, N, D.T);
+    const int Wn = D.TT / 32, Wd = route_row_stride(D.TT);
+    unsigned *bits = lds;                                  // [E][Wd]
+    unsigned *pre = bits + (size_t)E * Wd;                 // [E][Wd] popcount prefix inside the tile
+    int *count = (int *)(pre + (size_t)E * Wd);            // [rows] over all parts
+    int *start = count + rows;                             // [rows] exclusive scan of count
+    int *base = start + rows;                              // [rows] hits before the current tile
+    int *hits = base + rows;                               // [E] of the current tile
+    int *scan_tmp = hits + E;                              // [17]
+    unsigned short *ids = (unsigned short *)(scan_tmp + 20);   // [TT * K]
+    const int *idx_s = indices + (size_t)s * D.T * K;
+    const unsigned by_k = 0xFFFFFFFFu / (unsigned)K + 1u;      // p / K for p < 2^16 by the high half of a product (K > 1)
+    const int tiles = (D.T + D.TT - 1) / D.TT, per = (tiles + parts - 1) / parts, tile0 = part * per;
+    const int Ts = max(0, min(num_tokens[s], D.T));
+    int early[kRoutePreload];                              // as in route_count_block
+#pragma unroll
+    for (int i = 0; i < kRoutePreload; ++i) {
+        const int p = tid + i * kRouteThreads;
+        early[i] = p < min(D.TT, Ts - tile0 * D.TT) * K ? idx_s[(size_t)tile0 * D.TT * K + p] : -1;
+    }
+    for (int r = tid; r < rows; r += kRouteThreads) {
+        int all = 0, before = 0;
+        for (int p0 = 0; p0 < parts; p0 += 8) {
+            int c[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int *rec = records + (size_t)(s * parts + min(p0 + i, parts - 1)) * words;
+                c[i] = WIDE ? rec[r] : (int)((const unsigned short *)rec)[r];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (p0 + i < parts) { all += c[i]; before += p0 + i < part ? c[i] : 0; }
+        }
+        count[r] = all;
+        base[r] = before;
+    }
+    for (int i = tid; i < E * Wd; i += kRouteThreads) bits[i] = 0;
+    __syncthreads();
+    {
+        const int a = 2 * tid < rows ? count[2 * tid] : 0, b = 2 * tid + 1 < rows ? count[2 * tid + 1] : 0;
+        int total;
+        const int ex = block_excl_scan(a + b, scan_tmp, &total, (rows + 2 * kWave - 1) / (2 * kWave));
+        if (2 * tid < rows) start[2 * tid] = ex;
+        if (2 * tid + 1 < rows) start[2 * tid + 1] = ex + a;
+    }
+    const int used = (Ts + D.TT - 1) / D.TT;
+    for (int tile = tile0; tile < min(tile0 + per, used); ++tile) {
+        const int t0 = tile * D.TT, nt = min(D.TT, Ts - t0);
+        if (tile > tile0) {
+            __syncthreads();
+            for (int r = tid; r < E; r += kRouteThreads) base[r] += hits[r];
+            for (int i = tid; i < E * Wd; i += kRouteThreads) bits[i] = 0;
+            __syncthreads();
+        }
+        auto take = [&](int p, int e) {
+            const bool ok = e >= 0 && e < E;
+            ids[p] = (unsigned short)(ok ? e : 0xFFFF);
+            const int tl = K > 1 ? (int)__umulhi((unsigned)p, by_k) : p;
+            if (ok) atomicOr(&bits[(size_t)e * Wd + (tl >> 5)], 1u << (tl & 31));
+        };
+#pragma unroll
+        for (int i = 0; i < kRoutePreload; ++i) {
+            const int p = tid + i * kRouteThreads;
+            if (p < nt * K) take(p, tile == tile0 ? early[i] : idx_s[(size_t)t0 * K + p]);
+        }
+        for (int p = tid + kRoutePreload * kRouteThreads; p < nt * K; p += kRouteThreads)
+            take(p, idx_s[(size_t)t0 * K + p]);
+        __syncthreads();
+        for (int r = tid; r < E; r += kRouteThreads) {
+            int run = 0;
+            for (int w = 0; w < Wn; ++w) {
+                pre[(size_t)r * Wd + w] = run;
+                run += __popc(bits[(size_t)r * Wd + w]);
+            }
+            hits[r] = run;
+        }
+        __syncthreads();
+        for (int p = tid; p < nt * K; p += kRouteThreads) {
+            const int e = ids[p];
+            if (e == 0xFFFF) continue;
+            const int tl = K > 1 ? (int)__umulhi((unsigned)p, by_k) : p, w = tl >> 5;
+            out.comb_pos[((size_t)s * D.T + t0) * K + p] =
+                start[e] + base[e] + (int)pre[(size_t)e * Wd + w] +
+                __popc(bits[(size_t)e * Wd + w] & ((1u << (tl & 31)) - 1u));
+        }
+    }
+    if (part == 0) {
+        __syncthreads();                                   // start, also when the source has no tile in use
+        const int pairs = start[E];
+        for (int e = tid; e < E; e += kRouteThreads) out.C[(size_t)s * E + e] = count[e];
+        if (tid < N) {
+            out.M[(size_t)s * N + tid] = count[E + tid];
+            out.send_off[(size_t)s * (N + 1) + tid] = start[E + tid] - pairs;
+            out.comb_off[(size_t)s * (N + 1) + tid] = start[tid * El];
+        }
+        if (tid == 0) {
+            out.send_off[(size_t)s * (N + 1) + N] = start[E + N - 1] + count[E + N - 1] - pairs;
+            out.comb_off[(size_t)s * (N + 1) + N] = pairs;
+        }
+    }
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void static_plan_block(const Dims &D, const StaticOut &out, int parts,
+                                                  const int *__restrict__ records, const int *__restrict__ invalid,
+                                                  unsigned *lds) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    constexpr int kWaves = kRouteThreads / kWave;
+    const int E = D.E, N = D.N, El = D.El, words = static_record_words(E, N, D.T), recs = N * parts;
+    int *G = (int *)lds;                                   // [E]
+    int *M = G + E;                                        // [N][N]
+    __shared__ int wrong, over;
+    auto entry = [&](int rec, int f) -> int {
+        return WIDE ? records[(size_t)rec * words + f] : (int)((const unsigned short *)(records + (size_t)rec * words))[f];
+    };
+    for (int e = tid; e < E; e += kRouteThreads) G[e] = 0;
+    if (tid == 0) { wrong = 0; over = 0; }
+    int bad = 0;
+    for (int i = tid; i < recs; i += kRouteThreads) bad |= invalid[i];
+    for (int i = tid; i < N * N; i += kRouteThreads) {     // (source, rank): over the source's parts
+        const int s = i / N, d = i - s * N;
+        int m = 0;
+        for (int p0 = 0; p0 < parts; p0 += 8) {
+            int c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = entry(s * parts + min(p0 + u, parts - 1), E + d);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) m += p0 + u < parts ? c[u] : 0;
+        }
+        M[i] = m;
+    }
+    __syncthreads();
+    {   // experts: the threads of one 16-byte column share the records out
+        constexpr int kPer = WIDE ? 4 : 8;                 // counts per vector; the last one may reach into the rank counts
+        const int vecs = (E + kPer - 1) / kPer, groups = kRouteThreads / vecs, v = tid % vecs, first = tid / vecs;
+        int acc[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) acc[i] = 0;
+        if (first < groups && first < recs) {
+            for (int r0 = first; r0 < recs; r0 += 8 * groups) {
+                v4u q[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    q[u] = ((const v4u *)(records + (size_t)min(r0 + u * groups, recs - 1) * words))[v];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (r0 + u * groups >= recs) continue;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        if (WIDE) acc[w % kPer] += (int)q[u][w];
+                        else { acc[2 * w % kPer] += (int)(q[u][w] & 0xFFFFu); acc[(2 * w + 1) % kPer] += (int)(q[u][w] >> 16); }
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                if (v * kPer + i < E) atomicAdd(&G[v * kPer + i], acc[i]);
+        }
+    }
+    if (bad) wrong = 1;
+    __syncthreads();
+    if (wrong) {
+        if (tid < N) out.plan_ok[tid] = 0;
+        if (tid == 0) *out.status = FL_STATUS_BAD_INDEX;
+        return;
+    }
+    const unsigned al = (unsigned)D.align;
+    for (int d = wid; d < N; d += kWaves) {                // a wave per rank
+        const int m = lane < N ? M[lane * N + d] : 0;
+        const int inc = wave_incl_scan(m), beyond = wave_incl_scan(max(m - D.P, 0));
+        if (lane < N) out.recv_off[(size_t)d * (N + 1) + lane] = inc - m;
+        if (lane == N - 1) {
+            out.recv_off[(size_t)d * (N + 1) + N] = inc;
+            if (beyond > D.recv_cap) over = 1;
+        }
+        unsigned long long rows = 0;                       // of its expert layout, padding included
+        for (int j0 = 0; j0 < El; j0 += kWave) {
+            const int j = j0 + lane;
+            const unsigned g = j < El ? (unsigned)G[d * El + j] : 0u;
+            if (j < El) out.G[(size_t)d * El + j] = (int)g;
+            const unsigned room = j + 1 < El && al > 1 ? (g + al - 1) / al * al : g;
+            rows += (unsigned)__shfl(wave_incl_scan((int)room), kWave - 1);
+        }
+        if (lane == 0 && rows > (unsigned long long)D.expert_cap) over = 1;
+    }
+    __syncthreads();
+    if (!over)
+        for (int d = wid; d < N; d += kWaves) {
+            unsigned carry = 0;
+            for (int j0 = 0; j0 < El; j0 += kWave) {
+                const int j = j0 + lane;
+                const unsigned g = j < El ? (unsigned)G[d * El + j] : 0u;
+                const unsigned room = j + 1 < El && al > 1 ? (g + al - 1) / al * al : g;
+                const unsigned inc = (unsigned)wave_incl_scan((int)room);
+                if (j < El) out.expert_off[(size_t)d * (El + 1) + j] = (int)(carry + inc - room);
+                if (j == El - 1) out.expert_off[(size_t)d * (El + 1) + El] = (int)(carry + inc);
+                carry += (unsigned)__shfl((int)inc, kWave - 1);
+            }
+        }
+    if (tid < N) out.plan_ok[tid] = over ? 0 : 1;
+    if (tid == 0) *out.status = over ? FL_STATUS_CAPACITY : 0;
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(kRouteThreads) void static_tables_kernel(
+    Dims D, StaticOut out, int parts, const int *__restrict__ indices, const int *__restrict__ num_tokens,
+    const int *__restrict__ records, const int *__restrict__ invalid) {
+    extern __shared__ __align__(16) unsigned lds[];
+    const int b = blockIdx.x - 1;                          // the longest chain starts first
+    if (b < 0) static_plan_block<WIDE>(D, out, parts, records, invalid, lds);
+    else static_positions_block<WIDE>(D, out, b / parts, b % parts, parts, indices, num_tokens, records, lds);
 }
 
 }  // namespace flmoe

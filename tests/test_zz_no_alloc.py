@@ -87,6 +87,17 @@ def test_decode_shape_fits_and_matches():
     static_call_and_compare(wlmod.make_inputs(wlmod.WORKLOADS["dsv3_decode"]))
 
 
+# (ranks, experts, tokens, top-k): one token and one expert; a tile exactly and one token more; several tiles per
+# block; no whole vector of counts; the most rows and the largest top-k; 16- and 32-bit records, the largest that fits
+@pytest.mark.parametrize("ragged", [False, True])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 1, 33, 1), (4, 32, 1024, 4), (4, 32, 1025, 4), (3, 9, 600, 5), (32, 1024, 60, 2),
+                                   (16, 1024, 70, 16), (64, 64, 130, 9), (2, 4, 65535, 2), (2, 4, 65536, 2), (1, 256, 40000, 8),
+                                   (32, 256, 2048, 8)], ids=str)
+def test_tables_at_the_edges_of_tiles_parts_and_records(shape, ragged):
+    N, E, T, K = shape
+    static_call_and_compare(wlmod.make_inputs(wlmod.custom("static_edges", N, E, T, 8, K, seed=T + K, ragged=ragged)), expert_align=4)
+
+
 def test_bad_index_and_capacity_are_reported_in_the_callers_status_word():
     inp = wlmod.make_inputs(wlmod.custom("static_c", 4, 32, 50, 64, 4, seed=43))
     dev = harness.to_device(inp)
