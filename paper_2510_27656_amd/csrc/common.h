@@ -14,7 +14,7 @@ struct Dims {
     int N, E, El, T, K, H;
     int dtype, align, flags;
     int TT;               // tokens per LDS tile of the counting blocks (multiple of 32)
-    int route_len;        // ints of one route record (route_record_words)
+    int route_len;        // 8-byte words of one route record (route_record_words)
     int scales_per_row;   // 0 or H/128
     long long recv_cap, expert_cap, send_cap;   // rows per rank
     int P;                // private rows per (source, destination) at the head of a receive buffer
@@ -50,7 +50,7 @@ __host__ __device__ inline int recv_buffer_row(int N, int P, int s, int i, int s
 struct Tables {
     int *status;
     unsigned *epoch_route;                                    // [N] layout calls of each rank
-    unsigned *arrive_route;                                   // [N dst][N src] route records received
+    unsigned *arrive_route;                                   // [N dst][N src] step of the last route record received
     // Payload counters, monotone: a completed transfer adds its payload in 16-byte units
     // plus one (default: by the announce kernel behind the payload kernels; stream-ordered
     // callers: by the send kernel's first block; progressive mode: the units by every
@@ -58,7 +58,7 @@ struct Tables {
     // counts it was sent, so a receiver waits for arrive >= expect per source.
     unsigned *arrive_disp, *arrive_comb;                      // [N dst][N src]
     unsigned *expect_disp, *expect_comb;                      // [N dst][N src]
-    int *routes;          // [N receiver][N source][route_len]
+    unsigned long long *routes;   // [N receiver][N source][route_len], in words that carry their step's number
     // written by the source side of the layout step
     int *C;               // [N][E]
     int *M;               // [N][N]

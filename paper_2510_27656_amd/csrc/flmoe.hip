@@ -153,7 +153,7 @@ size_t carve(const Dims &D, void *base, Tables *W, size_t *total) {
     W->plan_ok = c.take<int>(N);
     W->gate_disp = c.take<int>(N);
     W->gate_comb = c.take<int>(N);
-    W->routes = c.take<int>(N * N * D.route_len);
+    W->routes = c.take<unsigned long long>(N * N * D.route_len);
     W->C = c.take<int>(N * E);
     W->M = c.take<int>(N * N);
     W->send_off = c.take<int>(N * (N + 1));
@@ -335,8 +335,8 @@ void launch_layout(const Dims &D, const Tables &W, int cu_count, int rb, int rc,
                    const int32_t *num_tokens, hipStream_t st) {
     const int parts = layout_parts(D, cu_count, rc);
     const size_t lds = std::max(route_count_lds_bytes(D.E, D.N, D.K, D.TT), route_plan_lds_bytes(D.E, D.N, D.El));
-    route_layout_kernel<<<dim3(rc * (parts + 1)), dim3(kRouteThreads), lds, st>>>(D, W, rb, rc, parts, indices,
-                                                                                  num_tokens);
+    auto kernel = route_wide(D.T) ? route_layout_kernel<true> : route_layout_kernel<false>;
+    kernel<<<dim3(rc * (parts + 1)), dim3(kRouteThreads), lds, st>>>(D, W, rb, rc, parts, indices, num_tokens);
 }
 
 // Ranks one launch of a payload kernel serves.  A launch that walks many GB runs
@@ -805,6 +805,9 @@ int fl_moe_reset(fl_moe_ctx *ctx, void *stream) {
     // status word and every counter: the contiguous head of the workspace up to plan_ok
     const size_t bytes = (size_t)((char *)ctx->W.plan_ok - (char *)ctx->W.status);
     if (hipMemsetAsync(ctx->W.status, 0, bytes, st) != hipSuccess) return FL_ERR_HIP;
+    // and the route records, whose words name steps that are now to come
+    const size_t records = (size_t)ctx->D.N * ctx->D.N * ctx->D.route_len * sizeof(*ctx->W.routes);
+    if (hipMemsetAsync(ctx->W.routes, 0, records, st) != hipSuccess) return FL_ERR_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) return FL_ERR_HIP;
     return FL_OK;
 }

@@ -6,13 +6,13 @@
 // buffer (Architecture).  The paper computes the ranges on a host proxy; here
 // both halves run on the device.
 //
-// Bound by latency: a few KB per rank go through one chain of load, count, scan,
-// exchange, scan.  So every link is one round of independent loads or one pass of
-// all the block's threads, and what can be worked out before a wait is.  32 ranks, 256
-// experts, top 8, kernel time with one counting block per source, 32-bit records stored
-// word by word and tables that single threads walked -> now: 4 tokens per rank 17.2 ->
-// 11.7 us, 128: 17.8 -> 12.3, 2048: 66.4 -> 22.3 (10 of them the count of all tokens);
-// several tiles per counting block, the call: 8192 tokens 243 -> 54.
+// Bound by latency: a few KB per rank go through one chain of load, count, exchange, scan.
+// So every link is one round of independent loads or one pass of all the block's
+// threads.  32 ranks, 256 experts, top 8, from the first block's first instruction to the last
+// one's last, message counters behind the route records -> words that carry their step: 4 tokens
+// per rank 9.9 -> 8.4 us (ids there 1.6, counts 2.3, records pushed 2.9, received 5.3, sums 6.7),
+// 128: 10.9 -> 9.2; 2 ranks x 16 tokens 7.2 -> 5.8.  2048 tokens 22 (a third of it the count of
+// all tokens in every counting block).
 #pragma once
 #include "common.h"
 
@@ -27,18 +27,37 @@ __host__ __device__ inline int route_row_stride(int TT) { return (TT / 32) | 1; 
 
 __host__ __device__ inline size_t route_count_lds_bytes(int E, int N, int K, int TT) {
     size_t rows = (size_t)E + N;
-    return rows * route_row_stride(TT) * 2 * sizeof(unsigned) + rows * 4 * sizeof(int) +
-           (rows + 4) * sizeof(int) + 32 * sizeof(int) + (size_t)TT * K * sizeof(unsigned short);
+    return rows * route_row_stride(TT) * 2 * sizeof(unsigned) + rows * 5 * sizeof(int) + 32 * sizeof(int) +
+           (size_t)TT * K * sizeof(unsigned short);
 }
 
-// Route record, one per (receiver, source): a 16-byte head (valid, first row of the
-// receiver's reply in the source's combine receive buffer), then the source's E expert
-// counts and N per-rank counts.  Counts are at most T, so they travel as 16-bit
-// numbers (32-bit where T does not fit): 592 bytes at 256 experts and 32 ranks.
+// Route record, one per (receiver, source), of 8-byte words that each say which step they belong to: the source's E
+// expert counts and N per-rank counts, three 16-bit counts a word (one of 32 bits where T does not fit), behind a
+// head, which is known last: the first row of the receiver's reply in the source's combine receive buffer.
+// A word is stored whole, so a receiver that finds this step's tag in it has the word's counts: the exchange costs
+// one store and one load, where a message counter behind the record cost the sender an acknowledgement and an add
+// and the receiver a poll, an invalidation of its caches and another load.
+// The tag: bit 15 marks a word as written, bit 14 says whether the source's ids were valid, below are the lowest
+// bits of the step's number.  Every step writes every word, so what a receiver may find is the step before, this
+// one, or, when calls that contain nothing but the layout step run ahead on another stream, the next.
+typedef unsigned long long route_word;
 __host__ __device__ inline bool route_wide(int T) { return T > 65535; }
+__host__ __device__ inline int route_per_word(bool wide) { return wide ? 1 : 3; }
 __host__ __device__ inline int route_record_words(int E, int N, int T) {
-    const int words = route_wide(T) ? E + N : (E + N + 1) / 2;
-    return 4 + (words + 3) / 4 * 4;
+    const int per = route_per_word(route_wide(T));
+    return 1 + (E + N + per - 1) / per;
+}
+__device__ inline unsigned route_tag(unsigned step) { return 0x8000u | (step & 0x3FFFu); }
+constexpr unsigned kRouteValid = 0x4000u;
+__device__ inline bool route_ready(route_word w, unsigned tag) {
+    const unsigned have = (unsigned)(w >> 48);
+    return (have & 0x8000u) && ((have - tag) & 0x3FFFu) <= 1u;
+}
+__device__ inline route_word ld_route(const route_word *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void st_route(route_word *p, route_word v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // e / El for 0 <= e < 1024 and El <= 256 by a multiplication: m = ceil(2^20 / El),
@@ -96,9 +115,9 @@ __device__ __forceinline__ void count_tokens(const int *__restrict__ ids, int t0
 // the E + N totals gives the offsets.  The last pass writes every pair's final positions.
 //
 // Outputs for rank s: by part 0, C[s][.], M[s][.], send_off[s][.], comb_off[s][.] and the
-// route record, which is pushed into every peer's routes[peer][s] before
-// arrive_route[peer][s] is bumped; by every part, send_to / pair_meta / comb_pos of the
-// pairs of its tiles.
+// route record, which is pushed into every peer's routes[peer][s]; by every part, send_to /
+// pair_meta / comb_pos of the pairs of its tiles.
+template <bool WIDE>
 __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W, int s, int part, int parts,
                                                   const int *__restrict__ indices,
                                                   const int *__restrict__ num_tokens, unsigned *lds) {
@@ -108,8 +127,8 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
     const int Wn = D.TT / 32;                              // words in use per row
     const int Wd = route_row_stride(D.TT);                 // row stride in words
     const unsigned by_el = div_magic(El);
-    unsigned *record = lds;                                // [4 + rows] packed counts, 16-byte aligned
-    unsigned *bits = record + (rows + 4 + 3) / 4 * 4;      // [rows][Wd]
+    const unsigned by_k = 0xFFFFFFFFu / (unsigned)K + 1u;  // p / K for p < 2^16 by the high half of a product (K > 1)
+    unsigned *bits = lds;                                  // [rows][Wd]
     unsigned *pre = bits + (size_t)rows * Wd;              // [rows][Wd] popcount prefix inside the tile
     int *count = (int *)(pre + (size_t)rows * Wd);         // [rows] hits over all tiles (C | M)
     int *start = count + rows;                             // [rows] exclusive scan of count
@@ -124,6 +143,8 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
     const int per = (tiles + parts - 1) / parts;
     const int tile0 = part * per;
     int Ts = num_tokens[s];                                // on its way while the counters are cleared
+    // its planning block counts the step once this one's record is there
+    const unsigned tag = part == 0 ? route_tag(W.epoch_route[s] + 1u) : 0u;
     for (int r = tid; r < rows; r += kRouteThreads) { count[r] = 0; base[r] = 0; }
     if (tid == 0) bad = (Ts < 0 || Ts > D.T) ? 1 : 0;
     Ts = max(0, min(Ts, D.T));
@@ -140,12 +161,12 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
     __syncthreads();
 
     // bits (already cleared), ids, in-tile popcount prefixes and row totals of one tile
-    auto fill_tile = [&](int t0, int nt) {
+    auto fill_tile = [&](int t0, int nt, int *totals) {
         auto take = [&](int p, int e) {
             const bool ok = e >= 0 && e < E;
             ids[p] = (unsigned short)(ok ? e : 0xFFFF);
             if (!ok) { bad = 1; return; }
-            const int tl = p / K;
+            const int tl = K > 1 ? (int)__umulhi((unsigned)p, by_k) : p;
             const unsigned bit = 1u << (tl & 31);
             const unsigned old = atomicOr(&bits[(size_t)e * Wd + (tl >> 5)], bit);
             if (old & bit) bad = 1;                        // same expert twice in one token
@@ -171,71 +192,65 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
                     run += __popc(b[i]);
                 }
             }
-            hits[r] = run;
+            totals[r] = run;
         }
         __syncthreads();
     };
 
     if (tiles == 1) {
-        fill_tile(0, Ts);
-        for (int r = tid; r < rows; r += kRouteThreads) count[r] = hits[r];
+        fill_tile(0, Ts, count);
     } else {                                               // one token per thread and turn
         // the LDS adds are what this pass takes its time for: where both counts fit, one word holds the
         // total in its lower and the hits before this block's tiles in its upper half
-        const bool wide = route_wide(D.T);
         const int mine = min(tile0 * D.TT, Ts);
         auto hit = [&](int t, int row) {
-            atomicAdd(&count[row], !wide && t < mine ? 0x10001 : 1);
-            if (wide && t < mine) atomicAdd(&base[row], 1);
+            atomicAdd(&count[row], !WIDE && t < mine ? 0x10001 : 1);
+            if (WIDE && t < mine) atomicAdd(&base[row], 1);
         };
         if (K <= 8) count_tokens<8>(idx_s, 0, Ts, kRouteThreads, E, K, by_el, &bad, hit);
         else count_tokens<FL_MAX_TOPK>(idx_s, 0, Ts, kRouteThreads, E, K, by_el, &bad, hit);
-        if (!wide) {
-            __syncthreads();
+        __syncthreads();
+        if (!WIDE) {
             for (int r = tid; r < rows; r += kRouteThreads) {
                 const unsigned c = (unsigned)count[r];
                 count[r] = (int)(c & 0xFFFFu);
                 base[r] = (int)(c >> 16);
             }
+            __syncthreads();
         }
     }
-    __syncthreads();
 
-    // one exclusive scan over the E + N totals (two slots per thread); the record is packed on the way
+    // The counts go out as soon as they are known (every index was seen, so `bad` is final as well); the record's head
+    // follows the scan.  The peers' planning overlaps with what is left to do here, the pair tables that
+    // only this rank's later kernels read.
+    route_word *to = W.routes + (size_t)s * D.route_len;   // in peer p's table: + p * N * route_len
+    const size_t peer_step = (size_t)N * D.route_len;
+    const route_word stamp = (route_word)(tag | (bad ? 0u : kRouteValid)) << 48;
+    if (part == 0) {
+        constexpr int kPer = WIDE ? 1 : 3;
+        const int words = D.route_len - 1;
+        for (int f = tid & (kWave - 1); f < words; f += kWave) {
+            route_word v = stamp;                          // beyond the last count: whatever follows, never looked at
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                v |= WIDE ? (route_word)(unsigned)count[f] : (route_word)((unsigned)count[f * kPer + i] & 0xFFFFu) << (16 * i);
+            for (int peer = tid / kWave; peer < N; peer += kRouteThreads / kWave) st_route(to + peer * peer_step + 1 + f, v);
+        }
+    }
+    // one exclusive scan over the E + N totals (two slots per thread)
     {
         const int a = 2 * tid < rows ? count[2 * tid] : 0;
         const int b = 2 * tid + 1 < rows ? count[2 * tid + 1] : 0;
         int total;
         const int ex = block_excl_scan(a + b, scan_tmp, &total, (rows + 2 * kWave - 1) / (2 * kWave));
-        if (2 * tid < rows) {
-            start[2 * tid] = ex;
-            if (route_wide(D.T)) record[4 + 2 * tid] = (unsigned)a;
-            else record[4 + tid] = (unsigned)a | (unsigned)b << 16;
-        }
-        if (2 * tid + 1 < rows) {
-            start[2 * tid + 1] = ex + a;
-            if (route_wide(D.T)) record[4 + 2 * tid + 1] = (unsigned)b;
-        }
+        if (2 * tid < rows) start[2 * tid] = ex;
+        if (2 * tid + 1 < rows) start[2 * tid + 1] = ex + a;
     }
     __syncthreads();
     // start[e] = first combine-receive row of expert e; start[E + d] = pairs + send_off[d]
     const int pairs_total = start[E];
     if (part == 0) {
-        // Everything a peer needs is known now (every index was seen, so `bad` is final): the
-        // record goes out before the pair tables, which only this rank's later kernels read, so
-        // the peers' planning overlaps with them.
-        const int valid = bad ? 0 : 1;
-        const int R2 = D.route_len / 2;                    // stored as 8-byte words
-        for (int i = tid; i < N * R2; i += kRouteThreads) {
-            const int peer = i / R2, f = i - peer * R2;
-            unsigned long long v = ((const unsigned long long *)record)[f];
-            if (f == 0) v = (unsigned long long)(unsigned)start[peer * El] << 32 | (unsigned)valid;
-            __hip_atomic_store((unsigned long long *)(W.routes + ((size_t)peer * N + s) * D.route_len) + f, v,
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        stores_done<true>();
-        __syncthreads();
-        if (tid < N) add_counter(W.arrive_route + (size_t)tid * N + s, 1u);
+        if (tid < N) st_route(to + tid * peer_step, stamp | (unsigned)start[tid * El]);
         if (bad && tid == 0) latch_status(W.status, FL_STATUS_BAD_INDEX);
         if (tid < E) W.C[(size_t)s * E + tid] = count[tid];
         if (tid < N) {
@@ -259,10 +274,10 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
                 for (int i = tid; i < rows * Wd; i += kRouteThreads) bits[i] = 0;
                 __syncthreads();
             }
-            fill_tile(t0, nt);
+            fill_tile(t0, nt, hits);
         }
         for (int p = tid; p < nt * K; p += kRouteThreads) {
-            const int tl = p / K, k = p - tl * K;
+            const int tl = K > 1 ? (int)__umulhi((unsigned)p, by_k) : p, k = p - tl * K;
             const int e = ids[p];
             if (e == 0xFFFF) continue;
             const int d = div_by(e, by_el);
@@ -287,13 +302,12 @@ __device__ __forceinline__ void route_count_block(const Dims &D, const Tables &W
 }
 
 __host__ __device__ inline size_t route_plan_lds_bytes(int E, int N, int El) {
-    return ((size_t)3 * E /*all ranks' totals, own columns, own row*/ + (size_t)N * N /*M*/ + El + 1 +
-            3 * (size_t)N + 8) * sizeof(int) + (size_t)N * sizeof(unsigned long long);
+    return ((size_t)3 * E /*all ranks' totals, own columns, own row*/ + (size_t)N * (N + 1) /*M*/ + El + 1 + (size_t)N) * sizeof(int);
 }
 
-// One block per rank r: waits for the route records of all sources, fetches what
-// it needs from them with one wide round of loads, then derives every
-// table rank r needs for the step.  All ranks see the same records, so all reach
+// One block per rank r: takes the route records of all sources as they arrive (bounded),
+// then derives every table rank r needs for the step: one phase of sums and scans, a wave
+// each, and one that uses them.  All ranks see the same records, so all reach
 // the same verdict on validity and capacity: a bad step is skipped by everyone
 // without further communication.
 template <bool WIDE>
@@ -301,111 +315,83 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     constexpr int kWaves = kRouteThreads / kWave;
     const int E = D.E, N = D.N, El = D.El, RL = D.route_len;
-    unsigned long long *ptot = (unsigned long long *)lds;   // [N] rows of each rank's expert layout, padding included
-    int *G_all = (int *)(ptot + N);       // [E]      tokens per expert over all sources
-    int *Cown = G_all + E;                // [N][El]  counts of rank r's experts per source
+    int *G_all = (int *)lds;              // [E]      tokens per expert over all sources
+    int *Cown = G_all + E;                // [El][N]  counts of rank r's experts per source
     int *Crow = Cown + E;                 // [E]      rank r's own counts
-    int *Mall = Crow + E;                 // [N][N]   de-duplicated counts, [source][destination]
-    int *eoff = Mall + N * N;             // [El+1]   expert offsets of rank r
+    const int MS = N + 1;                 // row stride: a column's entries on different LDS banks
+    int *Mall = Crow + E;                 // [N][MS]  de-duplicated counts, [source][destination]
+    int *eoff = Mall + N * MS;            // [El+1]   expert offsets of rank r
     int *csoff = eoff + El + 1;           // [N]      first combine-send row of each source
-    int *len = csoff + N;                 // [N]      pairs of each source on rank r
-    int *mine = len + N;                  // [N]      pairs of rank r on each rank
-    __shared__ int flag, invalid, over;
-    const int *rt = W.routes + (size_t)r * N * RL;
-    const unsigned by_el = div_magic(El);
-    // entry f (counts of experts, then of ranks) of source s's record: its place, and the count there
-    auto place = [&](int s, int f) { return s * RL * (WIDE ? 1 : 2) + (WIDE ? 4 : 8) + f; };
-    auto entry = [&](int at) -> int { return WIDE ? rt[at] : (int)((const unsigned short *)rt)[at]; };
-    // where this thread's loads will go, worked out before the wait
-    constexpr int kPer = WIDE ? 4 : 8;                 // counts per 16-byte vector
-    const int vecs = (E + kPer - 1) / kPer;            // the last one may reach into the rank counts
-    const int parts = kRouteThreads / vecs;
-    const int v = tid % vecs, part = tid / vecs;
-    const int te = tid < E ? tid : 0, td = div_by(te, by_el);
-    const int own_at = place(td, r * El + te - td * El), row_at = place(r, te);
-    int m_at[4];                                       // N * N <= 4096
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int at = tid + i * kRouteThreads;
-        m_at[i] = at < N * N ? place(at / N, E + at % N) : -1;
-    }
-
-    if (tid == 0) { flag = 0; invalid = 0; over = 0; }
+    __shared__ int late, invalid, over;
+    const route_word *rt = W.routes + (size_t)r * N * RL;
+    // Rank r has planned epoch_route[r] steps so far (only this block touches the word, and only
+    // once its own source's record of the step is there or given up).
+    const unsigned expect = W.epoch_route[r] + 1u, tag = route_tag(expect);
+    if (tid == 0) { late = 0; invalid = 0; over = 0; }
     for (int e = tid; e < E; e += kRouteThreads) G_all[e] = 0;
-    if (tid < N) { ptot[tid] = 0; len[tid] = 0; mine[tid] = 0; }
     __syncthreads();
-    if (wid == 0) {
-        // Rank r has planned epoch_route[r] steps so far (only this block touches the
-        // word); this step is complete when every source's message count has caught up.
-        const unsigned expect = W.epoch_route[r] + 1u;
-        if (lane == 0) W.epoch_route[r] = expect;
-        if (!wave_wait_counters<2>(W.arrive_route + (size_t)r * N, nullptr, expect, N, D.spin_limit)) {
-            if (lane == 0) { flag = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
-        }
-        acquire_payload<true>();
-    }
-    __syncthreads();
-    if (flag) {
-        if (tid == 0) W.plan_ok[r] = 0;
-        return;
-    }
-
-    // One wide round of loads, all independent.  Expert totals: a thread takes one 16-byte vector of
-    // counts from every `parts`-th source, LDS adds the parts.
     {
-        int acc[kPer];
+        // A thread takes one word of every `parts`-th source's record, four at a time.
+        constexpr int kPer = WIDE ? 1 : 3;                 // counts per word
+        const int words = RL - 1, cols = min(words, kRouteThreads), parts = kRouteThreads / cols;
+        const int part = tid / cols;
+        long long spins = 0;
+        bool ok = true;
+        unsigned valid = kRouteValid;
+        for (int f = tid - part * cols; f < words && part < parts && ok; f += cols) {
+            int acc[kPer];
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) acc[i] = 0;
-        if (part < parts)
-            for (int s0 = part; s0 < N; s0 += 4 * parts) {
-                v4u q[4];
+            for (int i = 0; i < kPer; ++i) acc[i] = 0;
+            for (int s0 = part; s0 < N && ok; s0 += 4 * parts) {
+                route_word q[4];
+                for (;;) {
+                    bool here = true;
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (s0 + u * parts < N) q[u] = ((const v4u *)(rt + (size_t)(s0 + u * parts) * RL))[1 + v];
-                    else q[u] = v4u{0u, 0u, 0u, 0u};
+                    for (int u = 0; u < 4; ++u) q[u] = ld_route(rt + (size_t)min(s0 + u * parts, N - 1) * RL + 1 + f);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+                    for (int u = 0; u < 4; ++u) here &= route_ready(q[u], tag);
+                    if (here) break;
+                    if (++spins > D.spin_limit) { ok = false; break; }
+                    __builtin_amdgcn_s_sleep(2);
+                }
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        if (WIDE) acc[w % kPer] += (int)q[u][w];
-                        else { acc[2 * w % kPer] += (int)(q[u][w] & 0xFFFFu); acc[(2 * w + 1) % kPer] += (int)(q[u][w] >> 16); }
+                for (int u = 0; u < 4; ++u) {
+                    const int s = s0 + u * parts;
+                    if (s >= N) continue;
+                    valid &= (unsigned)(q[u] >> 48);
+#pragma unroll
+                    for (int i = 0; i < kPer; ++i) {
+                        const int c = WIDE ? (int)(unsigned)q[u] : (int)(q[u] >> (16 * i) & 0xFFFFu), at = f * kPer + i;
+                        if (at < E) {
+                            acc[i] += c;
+                            if (s == r) Crow[at] = c;
+                            if ((unsigned)(at - r * El) < (unsigned)El) Cown[(at - r * El) * N + s] = c;
+                        } else if (at < E + N) Mall[s * MS + at - E] = c;
                     }
+                }
             }
-        const int own = entry(own_at), row = entry(row_at);
-        int m[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) m[i] = m_at[i] >= 0 ? entry(m_at[i]) : 0;
-        if (tid < N) {
-            if (rt[(size_t)tid * RL] == 0) invalid = 1;
-            W.comb_dst_off[(size_t)r * N + tid] = rt[(size_t)tid * RL + 1];
-        }
-        if (tid < E) { Cown[tid] = own; Crow[tid] = row; }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (m_at[i] >= 0) Mall[tid + i * kRouteThreads] = m[i];
-        if (part < parts && part < N)
 #pragma unroll
             for (int i = 0; i < kPer; ++i)
-                if (v * kPer + i < E) atomicAdd(&G_all[v * kPer + i], acc[i]);
+                if (f * kPer + i < E) atomicAdd(&G_all[f * kPer + i], acc[i]);
+        }
+        if (!ok) late = 1;
+        else if (!(valid & kRouteValid)) invalid = 1;
     }
     __syncthreads();
+    if (tid == 0) W.epoch_route[r] = expect;
+    if (late) {
+        if (tid == 0) { W.plan_ok[r] = 0; latch_status(W.status, FL_STATUS_TIMEOUT); }
+        return;
+    }
     if (invalid) {
         if (tid == 0) W.plan_ok[r] = 0;       // the offending source latched BAD_INDEX
         return;
     }
 
-    // sums over the experts of a rank: rows of its layout, pairs each way (E <= 1024: one turn)
-    if (tid < E) {
-        const int d = td, j = tid - d * El;
-        const unsigned g = (unsigned)G_all[tid], al = (unsigned)D.align;
-        atomicAdd(&ptot[d], (unsigned long long)(j + 1 < El && al > 1 ? (g + al - 1) / al * al : g));
-        atomicAdd(&len[d], Cown[tid]);        // index (source, local expert)
-        atomicAdd(&mine[d], Crow[tid]);
-    }
     // wave = destination d, lane = source: the shared-range rows of lower sources
     const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
     for (int d = wid; d < N; d += kWaves) {
-        const int m = lane < N ? Mall[lane * N + d] : 0;
+        const int m = lane < N ? Mall[lane * MS + d] : 0;
         const int beyond = max(m - D.P, 0);   // rows past the source's private slots
         int inc = wave_incl_scan(beyond);
         if (lane == r) W.dst_off[(size_t)r * N + d] = inc - beyond;
@@ -419,36 +405,55 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
     }
     if (partial)                              // wave = source, lane = rank: rows the source sent to ranks below r
         for (int s = wid; s < N; s += kWaves) {
-            const int m = lane < N ? Mall[s * N + lane] : 0;
+            const int m = lane < N ? Mall[s * MS + lane] : 0;
             const int inc = wave_incl_scan(m);
             if (lane == r) W.ret_off[(size_t)r * N + s] = inc - m;
         }
-    __syncthreads();
-
-    unsigned exp_units = 0;       // wave 0: lane = source; wave 1: lane = peer answering in combine
-    if (wid == 0) {
+    // sums over the experts of a rank, lane = rank (the last rank's again in lanes beyond)
+    const int of = min(lane, N - 1);
+    auto over_experts = [&](auto sum, auto term) {
+        for (int j0 = 0; j0 < El; j0 += 8) {
+            unsigned v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = (unsigned)term(min(j0 + i, El - 1));
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum += j0 + i < El ? v[i] : 0u;
+        }
+        return sum;
+    };
+    const unsigned al = (unsigned)D.align;
+    auto room = [&](int j, int g) { return j + 1 < El && al > 1 ? ((unsigned)g + al - 1) / al * al : (unsigned)g; };
+    unsigned exp_units = 0;       // last wave: lane = source; the one before: lane = peer answering in combine
+    if (wid == kWaves - 1) {
         // what source s will have added once its transfer to this rank is complete: the
         // payload in 16-byte units, plus one for the transfer itself (an empty one still counts)
-        if (lane < N) exp_units = (unsigned)Mall[lane * N + r] * (unsigned)(D.Bw / 16) + 1u;
-        const int n = lane < N ? len[lane] : 0;
+        if (lane < N) exp_units = (unsigned)Mall[lane * MS + r] * (unsigned)(D.Bw / 16) + 1u;
+        const int n = lane < N ? (int)over_experts(0u, [&](int j) { return Cown[j * N + of]; }) : 0;
         const int inc = wave_incl_scan(n);
         if (lane < N) { csoff[lane] = inc - n; W.cs_off[(size_t)r * (N + 1) + lane] = inc - n; }
         if (lane == N - 1) W.cs_off[(size_t)r * (N + 1) + N] = inc;
-    } else if (wid == 1) {
-        if (lane < N) {           // with partial sums one share per row r sent to the peer
-            exp_units = (unsigned)(partial ? Mall[r * N + lane] : mine[lane]) * (unsigned)(D.Bc / 16) + 1u;
-            if (ptot[lane] > (unsigned long long)D.expert_cap) over = 1;
+    } else if (wid == kWaves - 2) {
+        // with partial sums one share per row r sent to the peer, else one reply per pair
+        const unsigned pairs = over_experts(0u, [&](int j) { return Crow[of * El + j]; });
+        if (lane < N) exp_units = (partial ? (unsigned)Mall[r * MS + lane] : pairs) * (unsigned)(D.Bc / 16) + 1u;
+    } else if (wid == kWaves - 4) {        // rows of every rank's expert layout, padding included
+        if (over_experts(0ull, [&](int j) { return room(j, G_all[of * El + j]); }) > (unsigned long long)D.expert_cap) over = 1;
+    } else if (wid == kWaves - 5) {        // the sources' heads, there by now or soon
+        route_word head = 0;
+        long long spins = 0;
+        while (lane < N && !route_ready(head = ld_route(rt + (size_t)lane * RL), tag)) {
+            if (++spins > D.spin_limit) { late = 1; break; }
+            __builtin_amdgcn_s_sleep(2);
         }
-    } else if (wid == 2) {        // offsets of rank r's experts, 64 at a time
-        const unsigned al = (unsigned)D.align;
+        if (lane < N) { W.comb_dst_off[(size_t)r * N + lane] = (int)(unsigned)head; W.arrive_route[(size_t)r * N + lane] = expect; }
+    } else if (wid == kWaves - 3) {        // offsets of rank r's experts, 64 at a time
         unsigned carry = 0;
         for (int j0 = 0; j0 < El; j0 += kWave) {
             const int j = j0 + lane;
-            const unsigned g = j < El ? (unsigned)G_all[r * El + j] : 0u;
-            const unsigned room = j + 1 < El && al > 1 ? (g + al - 1) / al * al : g;
-            const unsigned inc = (unsigned)wave_incl_scan((int)room);
+            const unsigned g = j < El ? (unsigned)G_all[r * El + j] : 0u, rows = j < El ? room(j, (int)g) : 0u;
+            const unsigned inc = (unsigned)wave_incl_scan((int)rows);
             if (j < El) {
-                eoff[j] = (int)(carry + inc - room);
+                eoff[j] = (int)(carry + inc - rows);
                 if (j == El - 1) eoff[El] = (int)(carry + inc);
                 W.G[(size_t)r * El + j] = (int)g;
             }
@@ -456,8 +461,8 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
         }
     }
     __syncthreads();
-    if (over) {
-        if (tid == 0) { W.plan_ok[r] = 0; latch_status(W.status, FL_STATUS_CAPACITY); }
+    if (late || over) {
+        if (tid == 0) { W.plan_ok[r] = 0; latch_status(W.status, late ? FL_STATUS_TIMEOUT : FL_STATUS_CAPACITY); }
         return;
     }
     for (int j = tid; j <= El; j += kRouteThreads) W.expert_off[(size_t)r * (El + 1) + j] = eoff[j];
@@ -465,44 +470,41 @@ __device__ __forceinline__ void route_plan_block(const Dims &D, const Tables &W,
     // cs_base[s][j] = cs_off[s] + rows of lower experts for source s (a wave per source, lane = expert)
     for (int job = wid; job < El + N; job += kWaves) {
         if (job < El) {
-            const int c = lane < N ? Cown[lane * El + job] : 0;
+            const int c = lane < N ? Cown[job * N + lane] : 0;
             const int inc = wave_incl_scan(c);
             if (lane < N) W.base_x[((size_t)r * El + job) * N + lane] = eoff[job] + inc - c;
         } else {
             const int s = job - El;
             int carry = csoff[s];
             for (int j0 = 0; j0 < El; j0 += kWave) {
-                const int c = j0 + lane < El ? Cown[s * El + j0 + lane] : 0;
+                const int c = j0 + lane < El ? Cown[(j0 + lane) * N + s] : 0;
                 const int inc = wave_incl_scan(c);
                 if (j0 + lane < El) W.cs_base[((size_t)r * N + s) * El + j0 + lane] = carry + inc - c;
                 carry += __shfl(inc, kWave - 1);
             }
         }
     }
-    if (wid == 0 && lane < N) W.expect_disp[(size_t)r * N + lane] += exp_units;
-    if (wid == 1 && lane < N) W.expect_comb[(size_t)r * N + lane] += exp_units;
+    if (wid == kWaves - 1 && lane < N) W.expect_disp[(size_t)r * N + lane] += exp_units;
+    if (wid == kWaves - 2 && lane < N) W.expect_comb[(size_t)r * N + lane] += exp_units;
     if (tid == 0) W.plan_ok[r] = 1;
 }
 
 // One launch for both halves of the layout step: the first rank_count * parts blocks
 // count (the first rank_count of them, part 0 of every source, push the route records),
-// the last rank_count plan for their rank as soon as the records of all sources have
-// arrived.  The planning blocks poll the message counters (bounded) while the counting
-// blocks run: workgroups are dispatched in index order, so every counting block has its
-// place before a poller takes one, and a poller never keeps a counter from starting.
-// Records cross compute dies inside one kernel, hence device-scope stores and one cache
-// invalidation per planning block in every mode.
+// the last rank_count plan for their rank from the records of all sources, which they poll
+// (bounded) while the counting blocks run: workgroups are dispatched in index order, so every
+// counting block has its place before a poller takes one, and a poller never keeps a counter
+// from starting.  Records cross compute dies inside one kernel, in words stored and loaded at device scope.
+template <bool WIDE>
 __global__ __launch_bounds__(kRouteThreads) void route_layout_kernel(
     Dims D, Tables W, int rank_begin, int rank_count, int parts, const int *__restrict__ indices,
     const int *__restrict__ num_tokens) {
     extern __shared__ __align__(16) unsigned lds[];
     const int b = blockIdx.x;
     if (b < rank_count * parts)
-        route_count_block(D, W, rank_begin + b % rank_count, b / rank_count, parts, indices, num_tokens, lds);
-    else if (route_wide(D.T))
-        route_plan_block<true>(D, W, rank_begin + b - rank_count * parts, lds);
+        route_count_block<WIDE>(D, W, rank_begin + b % rank_count, b / rank_count, parts, indices, num_tokens, lds);
     else
-        route_plan_block<false>(D, W, rank_begin + b - rank_count * parts, lds);
+        route_plan_block<WIDE>(D, W, rank_begin + b - rank_count * parts, lds);
 }
 
 // ------------------------------------------------------------------ the layout step without a context
