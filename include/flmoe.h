@@ -95,7 +95,9 @@ extern "C" {
  *     small kernel that adds each whole (sender, receiver) transfer to the receiver's
  *     counter with release semantics: it starts once the payload kernels have ended
  *     (the sender's own stream order, as a NIC posts the immediate after its WRITE),
- *     so the counter never runs ahead of the payload.
+ *     so the counter never runs ahead of the payload.  In a small step the last workgroup of a
+ *     sender's payload kernel adds the transfers instead: payload is written through to memory,
+ *     and a workgroup counts as done once its stores have been acknowledged.
  *   - A receive call first enqueues a gate kernel of one wave per rank that polls the
  *     rank's counters with acquire semantics until every source has delivered what
  *     the exchanged counts promised (bounded: FL_STATUS_TIMEOUT), and behind it the
@@ -412,7 +414,9 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
  *            2 = starting in the middle and wrapping round; a test switch: nothing may depend on
  *            the order in which transfers are carried out)
  *   knob 9 = workgroups that share one token in combine_reduce, each summing a slice of the row
- *            (0 = chosen from the row size) */
+ *            (0 = chosen from the row size)
+ *   knob 10 = workgroups of a send call up to which its payload kernel announces the transfers itself
+ *            instead of having an announce kernel launched behind it (default 4096; 0 = never) */
 int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value);
 
 /* Diagnostic, host only (no GPU needed): how a payload call over `rank_count` ranks of

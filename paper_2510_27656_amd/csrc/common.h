@@ -34,6 +34,7 @@ struct Dims {
     long long typ_recv_rows, typ_pair_rows;   // per rank, under uniform routing: received rows, pairs
     int tune_parts;       // workgroups per token in the reduce kernel (0 = by row size)
     int tune_order;       // test switch: order in which the send kernels take their rows
+    int tune_self;        // send calls of up to this many workgroups announce their transfers themselves (announces_itself)
     int tune_cap8;        // progressive receivers: eighths of the machine's block slots their grids may take
 };
 
@@ -58,6 +59,7 @@ struct Tables {
     // counts it was sent, so a receiver waits for arrive >= expect per source.
     unsigned *arrive_disp, *arrive_comb;                      // [N dst][N src]
     unsigned *expect_disp, *expect_comb;                      // [N dst][N src]
+    unsigned *done_disp, *done_comb;  // [N][kDoneWords] workgroups of a sender's kernel that have ended (announce_when_last)
     unsigned long long *routes;   // [N receiver][N source][route_len], in words that carry their step's number
     // written by the source side of the layout step
     int *C;               // [N][E]
@@ -90,6 +92,9 @@ struct Tables {
 };
 
 constexpr unsigned kNoEntry = 0xFFFFFFFFu;
+constexpr int kDoneParts = 16;                           // partial counts, then their count, ...
+constexpr int kDoneLine = 32;                            // ... each on a 128-byte line of its own
+constexpr int kDoneWords = (kDoneParts + 1) * kDoneLine;
 
 // ---------------------------------------------------------------- atomics
 // FENCED names the progressive mode, in which senders and receivers overlap in time
@@ -102,10 +107,11 @@ constexpr unsigned kNoEntry = 0xFFFFFFFFu;
 // waits until its own stores are acknowledged, and only then updates the counter;
 // the receiver polls the counter with device-scope loads and, once it has arrived,
 // invalidates its caches (agent-scope acquire) before touching the payload.
-// FENCED = false covers the other two modes, where whole kernels order payload and
-// counters: the announce kernel behind the payload kernels (default), or the
-// caller's stream order (FL_FLAG_STREAM_ORDERED); nothing waits for the payload stores
-// inside the kernels then, and the in-kernel counter accesses are relaxed atomics.
+// FENCED = false covers the other two modes.  Default: the announce kernel behind the payload
+// kernels orders payload and counters, or, in small steps, the last workgroup to have seen its
+// stores acknowledged (announce_when_last), and the receive kernels start behind a gate kernel.
+// FL_FLAG_STREAM_ORDERED: the caller's stream order does; nothing waits for the payload
+// stores inside the kernels then, and the in-kernel counter accesses are relaxed atomics.
 __device__ inline unsigned ld_relaxed(const unsigned *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -114,24 +120,19 @@ __device__ inline unsigned ld_relaxed(const unsigned *p) {
 __device__ inline void add_counter(unsigned *p, unsigned v) {
     (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// After a wave's last payload store and before its add_counter: in progressive mode,
-// wait until every store of this wave (including the device-scope ones issued
-// from inline assembly, which the compiler does not count) has been acknowledged.
-template <bool FENCED>
+// After a wave's last payload store and before the add that vouches for it: waits until every
+// store of this wave (including the device-scope ones issued from inline assembly, which
+// the compiler does not count) has been acknowledged.
 __device__ inline void stores_done() {
-    if (FENCED) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 template <bool FENCED>
 __device__ inline void acquire_payload() {
     if (FENCED) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
-template <bool FENCED>
-__device__ inline void st_word(int *p, int v) {        // small table entries pushed to a peer
-    if (FENCED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = v;
+__device__ inline void st_word(int *p, int v) {        // small table entries pushed to a peer: written through, as rows are
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline void latch_status(int *status, int bit) {
     __hip_atomic_fetch_or(status, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -43,6 +43,7 @@ constexpr size_t kBigPage = 2u << 20;
 constexpr int kComputeUnits = 256;                // of the part, where a context has not asked the device
 constexpr int kCachedReplyMiB = 1024;             // see replies_cached
 constexpr int kLaunchMiB = 860;
+constexpr int kSelfAnnounceBlocks = 4096;         // see announces_itself
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Walks the workspace; with base == nullptr it only measures.
@@ -127,6 +128,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->tune_slices = 0;
     D->tune_cached_mb = kCachedReplyMiB;
     D->tune_grid_pct = -1;
+    D->tune_self = kSelfAnnounceBlocks;
     D->tune_cap8 = 3;
     D->tune_order = 0;
     D->tune_parts = 0;
@@ -150,6 +152,8 @@ size_t carve(const Dims &D, void *base, Tables *W, size_t *total) {
     W->arrive_comb = c.take<unsigned>(N * N);
     W->expect_disp = c.take<unsigned>(N * N);
     W->expect_comb = c.take<unsigned>(N * N);
+    W->done_disp = c.take<unsigned>(N * kDoneWords);
+    W->done_comb = c.take<unsigned>(N * kDoneWords);
     W->plan_ok = c.take<int>(N);
     W->gate_disp = c.take<int>(N);
     W->gate_comb = c.take<int>(N);
@@ -262,6 +266,16 @@ long long reply_grid_rows(const Dims &D) {       // rows a rank sends back: one 
 bool replies_cached(const Dims &D, int rank_count) {
     const long long limit = (long long)D.tune_cached_mb << 20;
     return (long long)D.N * D.T * D.K * D.Bc <= (rank_count < D.N ? limit / 2 : limit);
+}
+
+// Whether the send kernels of a call, of `workgroups` per sender, announce their transfers themselves
+// (announce_when_last) rather than having a kernel launched behind them: while they all fit on the machine at once
+// (4096 workgroups of two waves), waiting for their own stores keeps no others out.  us of a step, with announce kernels
+// and without: 2 ranks x 16 tokens of 512 bytes (16 workgroups) 34.0 and 28.6; 8 ranks, 64 tokens of 8 KB, rank by rank
+// (324 a call) 277 and 215; 32 ranks, 14 KB rows: 4 tokens (2176) 45.6 and 44.6, 8 (3616) 57.0 and 56.3, 16 (7168) 81.3
+// and 82.6, 32 (14 336) 131.5 and 133.8, 128 (57 344) 452 and 468.
+bool announces_itself(const Dims &D, long long workgroups, int rank_count) {
+    return !(D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED)) && workgroups * rank_count <= D.tune_self;
 }
 
 // Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
@@ -568,15 +582,17 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
     // the payload kernels in this (the sender's) stream.
     const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;
     const char *xp = (const char *)x;
+    bool self;
     if (D.dtype == FL_DTYPE_E4M3_BLOCK128 && !ready_scales) {
         LaunchTimer t(ctx, KID_DISPATCH_PACK_E4M3, st);
         auto go = [&](auto threads) {
             constexpr int QT = decltype(threads)::value;
             const int per_block = QT / kQuantLanes;              // quantisation blocks per workgroup
             const int slices = (D.scales_per_row + per_block - 1) / per_block;
+            self = announces_itself(D, (long long)D.T * slices, call.rank_count);
             auto kernel = fenced ? dispatch_pack_e4m3_kernel<true, QT> : dispatch_pack_e4m3_kernel<false, QT>;
-            kernel<<<dim3((unsigned)D.T * slices, rc), dim3(QT), 0, st>>>(D, W, rb, xp, ctx->num_tokens, slices,
-                                                                          weights);
+            kernel<<<dim3((unsigned)D.T * slices, rc), dim3(QT), 0, st>>>(D, W, rb, xp, ctx->num_tokens, slices, weights,
+                                                                          self ? W.done_disp : nullptr);
         };
         if (D.scales_per_row > 256 / kQuantLanes) go(std::integral_constant<int, 512>{});
         else go(std::integral_constant<int, 256>{});
@@ -585,11 +601,12 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
         // bf16 rows, or e4m3 codes the caller quantised itself (their scales go along)
         const long long src_row = ready_scales ? D.Be : D.Bx;
         const int slices = pack_slices(src_row, D.tune_slices);
+        self = announces_itself(D, (long long)D.T * slices, call.rank_count);
         auto kernel = fenced ? dispatch_pack_kernel<true> : dispatch_pack_kernel<false>;
         kernel<<<dim3((unsigned)D.T * slices, rc), dim3(kPackThreads), 0, st>>>(
-            D, W, rb, xp, ctx->num_tokens, slices, weights, src_row, ready_scales);
+            D, W, rb, xp, ctx->num_tokens, slices, weights, src_row, ready_scales, self ? W.done_disp : nullptr);
     }
-    if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {   // once, behind every payload kernel of the call
+    if (!self && !fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {   // once, behind every payload kernel of the call
         LaunchTimer t(ctx, KID_ANNOUNCE_DISPATCH, st);
         announce_kernel<<<dim3(call.rank_count), dim3(kWave), 0, st>>>(D, W, call.rank_begin, W.send_off,
                                                                         W.arrive_disp, (unsigned)(D.Bw / 16));
@@ -682,7 +699,7 @@ int fl_moe_dispatch_recv(fl_moe_ctx *ctx, int rb, int rc, void *expert_x, float 
     });
 }
 
-static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *expert_y, bool cached,
+static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *expert_y, bool cached, bool self,
                               void *stream) {
     int e = check_ranks(ctx, rb, rc);
     if (e != FL_OK) return e;
@@ -711,10 +728,10 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
             auto kernel = partial ? cached ? combine_partial_pack_kernel<true> : combine_partial_pack_kernel<false>
                                   : cached ? combine_pack_kernel<true> : combine_pack_kernel<false>;
             // partial sums read several rows per row written: no need to hold back workgroups (see the kernel)
-            kernel<<<dim3(gw, rc), block, partial ? 0 : kRowWavesLdsBytes, st>>>(D, W, rb, yp, G);
+            kernel<<<dim3(gw, rc), block, partial ? 0 : kRowWavesLdsBytes, st>>>(D, W, rb, yp, G, self ? W.done_comb : nullptr);
         }
     }
-    if (!fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {
+    if (!self && !fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {
         LaunchTimer t(ctx, KID_ANNOUNCE_COMBINE, st);
         announce_kernel<<<dim3(call.rank_count), dim3(kWave), 0, st>>>(
             D, W, call.rank_begin, partial ? W.recv_off : W.cs_off, W.arrive_comb, (unsigned)(D.Bc / 16));
@@ -724,9 +741,13 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
 
 int fl_moe_combine_send(fl_moe_ctx *ctx, int rb, int rc, const void *expert_y, void *stream) {
     if (!ctx) return FL_ERR_INVALID_ARG;
-    const bool cached = replies_cached(ctx->D, rc);
+    const Dims &D = ctx->D;
+    const bool cached = replies_cached(D, rc);
+    const long long workgroups = (reply_grid_rows(D) * waves_per_row(D.Bc / 16) * kWave + kCopyThreads - 1) / kCopyThreads;
+    // one answer for all launches of the call (a group of its ranks has fewer rows, so it takes waves where the call does)
+    const bool self = announces_itself(D, workgroups, rc) && !replies_by_chunks(D, ctx->cu_count, rc);
     return for_rank_groups(ctx, rb, rc, [&](int r, int n, CallSpan call) {
-        return combine_send_range(ctx, r, n, call, expert_y, cached, stream);
+        return combine_send_range(ctx, r, n, call, expert_y, cached, self, stream);
     });
 }
 
@@ -881,6 +902,7 @@ int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value) {
         case 7: if (value > 8 || value == 0) return FL_ERR_INVALID_ARG; ctx->D.tune_cap8 = dflt ? 3 : value; break;
         case 8: if (value > 2) return FL_ERR_INVALID_ARG; ctx->D.tune_order = dflt ? 0 : value; break;
         case 9: if (value > 64) return FL_ERR_INVALID_ARG; ctx->D.tune_parts = dflt ? 0 : value; break;
+        case 10: ctx->D.tune_self = dflt ? kSelfAnnounceBlocks : value; break;
         default: return FL_ERR_INVALID_ARG;
     }
     return FL_OK;

@@ -48,6 +48,32 @@ __device__ inline void announce_transfers(const int *off, unsigned *arrive, unsi
     }
 }
 
+// Default mode, small steps: the last workgroup of a sender's payload kernel announces its whole transfers, so that
+// no kernel has to be launched for it.  Every workgroup waits until what it stored has been acknowledged (payload and
+// sidecars are written through, so it is in memory then, where every XCD sees it) and counts itself; the one that
+// completes the count adds to the receivers' counters.  Adds to one word take 12 ns each, so a
+// workgroup counts on one of kDoneParts words, whose last one counts on the word for all; who completes a word clears
+// it for the next call.  done: the sender's words; number: this workgroup's, of `workgroups`; lane p < N of the first
+// wave holds the rows for receiver p.  Where the line to an announce kernel lies: announces_itself in flmoe.hip.
+__device__ inline void announce_when_last(unsigned *done, unsigned number, unsigned workgroups, unsigned *arrive, int rows,
+                                          unsigned units_per_row, int sender, int N) {
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    auto completes = [&](unsigned *word, unsigned all) {
+        unsigned before = 0;
+        if (threadIdx.x == 0) before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane(before) + 1 != all) return false;
+        if (threadIdx.x == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return true;
+    };
+    const unsigned part = number % kDoneParts;
+    if (!completes(done + part * kDoneLine, (workgroups - part + kDoneParts - 1) / kDoneParts)) return;
+    if (!completes(done + kDoneParts * kDoneLine, min(workgroups, (unsigned)kDoneParts))) return;
+    const int p = threadIdx.x;
+    if (p < N) add_counter(arrive + (size_t)p * N + sender, (unsigned)rows * units_per_row + 1u);
+}
+
 // Test switch (knob 8): the order in which a send kernel takes its `n` units of work.  Nothing may
 // depend on it: 0 = ascending, 1 = descending, 2 = starting in the middle and wrapping round.
 __device__ inline int in_order(int order, int i, int n) {
@@ -102,7 +128,8 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ x, const int *__restrict__ num_tokens, int slices,
     const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */,
     long long src_row_bytes /* bytes of one row of x: 2*H, or H for ready-made e4m3 codes */,
-    const float *__restrict__ src_scales /* [N][T][H/128] with ready-made codes, else null */) {
+    const float *__restrict__ src_scales /* [N][T][H/128] with ready-made codes, else null */,
+    unsigned *done /* announce_when_last; null: announced elsewhere */) {
     const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
     const int t = in_order(D.tune_order, blockIdx.x / slices, D.T);
     const int tid = threadIdx.x;
@@ -122,12 +149,19 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     CopyPlan plan;
     if (tid < kWave) plan.load(D, W, s, pair0, tid);
     const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
+    const int sent = done && tid < D.N ? W.M[(size_t)s * D.N + tid] : 0;
     // the sender's first block announces the transfers (a sender without tokens still announces
     // its empty ones), unless an announce kernel will
     if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,
                            tid, kPackThreads, FENCED);
-    if (!plan_ok || t >= tokens) return;
+    if (!plan_ok) return;
+    const unsigned workgroups = (unsigned)(tokens * slices);   // of this sender that have a token
+    if (t >= tokens) {
+        if (done && tokens == 0 && blockIdx.x == 0)            // none has: one announces the empty transfers
+            announce_when_last(done + s * kDoneWords, 0u, 1u, W.arrive_disp, sent, (unsigned)(D.Bw / 16), s, D.N);
+        return;
+    }
     __shared__ int s_row[FL_MAX_TOPK];
     __shared__ int s_dst[FL_MAX_TOPK];
     __shared__ unsigned s_meta[FL_MAX_TOPK];
@@ -142,12 +176,12 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
         int m = 0;
         for (int k = 0; k < K; ++k)
             if (s_dst[k] == my_d) {
-                st_word<FENCED>((int *)meta + m, (int)s_meta[k]);
+                st_word((int *)meta + m, (int)s_meta[k]);
                 if (D.MW > D.KM)   // the weight of that expert, for the expert rank's partial sum
-                    st_word<FENCED>((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
+                    st_word((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
                 ++m;
             }
-        for (; m < D.KM; ++m) st_word<FENCED>((int *)meta + m, (int)kNoEntry);
+        for (; m < D.KM; ++m) st_word((int *)meta + m, (int)kNoEntry);
     }
     for (int b = v0 + tid; b < v1; b += 4 * kPackThreads) {
         if (b != v0 + tid) {                   // later batches (rows beyond 8 KB per slice)
@@ -188,17 +222,20 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                     const int row = s_row[k];
                     if (row < 0) continue;
                     char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
-                    st_word<FENCED>((int *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    st_word((int *)(base + (size_t)row * D.Bw + D.Be) + v, val);
                 }
             }
         }
     }
     if (FENCED) {                      // what this block delivered, per destination
-        stores_done<FENCED>();
+        stores_done();
         __syncthreads();
         const unsigned units = (unsigned)(v1 - v0) + (with_scales ? (unsigned)((D.Bw - D.Be) / 16) : 0u);
         if (tid < K && target >= 0 && units > 0)
             add_counter(W.arrive_disp + (size_t)my_d * D.N + s, units);
+    } else if (done) {
+        announce_when_last(done + s * kDoneWords, (unsigned)(t * slices + slice), workgroups, W.arrive_disp, sent,
+                           (unsigned)(D.Bw / 16), s, D.N);
     }
 }
 
@@ -251,7 +288,8 @@ constexpr int kQuantLanes = 8;     // lanes per 128-element block: 16 bf16 value
 template <bool FENCED, int QT>   // FENCED as in dispatch_pack_kernel
 __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ x, const int *__restrict__ num_tokens, int slices,
-    const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */) {
+    const float *__restrict__ weights /* [N][T][K], only when the sidecar carries them */,
+    unsigned *done /* as in dispatch_pack_kernel */) {
     constexpr int kQuantThreads = QT;
     const int s = rank_begin + blockIdx.y, slice = blockIdx.x % slices;
     const int t = in_order(D.tune_order, blockIdx.x / slices, D.T);
@@ -272,10 +310,17 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     CopyPlan plan;
     if (tid < kWave) plan.load(D, W, s, pair0, tid);
     const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
+    const int sent = done && tid < D.N ? W.M[(size_t)s * D.N + tid] : 0;
     if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)   // as in dispatch_pack_kernel
         announce_transfers(W.send_off + (size_t)s * (D.N + 1), W.arrive_disp, (unsigned)(D.Bw / 16), s, D.N,
                            tid, kQuantThreads, FENCED);
-    if (!plan_ok || t >= tokens) return;
+    if (!plan_ok) return;
+    const unsigned workgroups = (unsigned)(tokens * slices);   // of this sender that have a token
+    if (t >= tokens) {
+        if (done && tokens == 0 && blockIdx.x == 0)            // none has: one announces the empty transfers
+            announce_when_last(done + s * kDoneWords, 0u, 1u, W.arrive_disp, sent, (unsigned)(D.Bw / 16), s, D.N);
+        return;
+    }
     __shared__ int s_row[FL_MAX_TOPK];
     __shared__ int s_dst[FL_MAX_TOPK];
     __shared__ unsigned s_meta[FL_MAX_TOPK];
@@ -290,12 +335,12 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         int m = 0;
         for (int k = 0; k < K; ++k)
             if (s_dst[k] == my_d) {
-                st_word<FENCED>((int *)meta + m, (int)s_meta[k]);
+                st_word((int *)meta + m, (int)s_meta[k]);
                 if (D.MW > D.KM)   // the weight of that expert, for the expert rank's partial sum
-                    st_word<FENCED>((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
+                    st_word((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
                 ++m;
             }
-        for (; m < D.KM; ++m) st_word<FENCED>((int *)meta + m, (int)kNoEntry);
+        for (; m < D.KM; ++m) st_word((int *)meta + m, (int)kNoEntry);
     }
     float f[16];
     const unsigned w[8] = {in0.x, in0.y, in0.z, in0.w, in1.x, in1.y, in1.z, in1.w};
@@ -340,7 +385,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
                 st_payload<true>((v4u *)(dst + D.Be) + blk0 / 4 + tid,
                                                  ((const v4u *)s_scale)[tid]);
         } else if (live && sub == 0) {
-            st_word<FENCED>((int *)(dst + D.Be) + blk, __float_as_int(scale));
+            st_word((int *)(dst + D.Be) + blk, __float_as_int(scale));
         }
     }
     if (FENCED) {
@@ -348,7 +393,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         // 16-byte units its scales fall into (blocks start on multiples of 32 scales, so
         // no unit is shared between blocks; the row's last unit may be part padding).
         const int n_live = min(nblk - blk0, kQuantThreads / kQuantLanes);
-        stores_done<FENCED>();
+        stores_done();
         __syncthreads();
         // the padding that brings a wire row to a whole number of 128-byte lines is nobody's
         // to write; the first block claims it so that a row's units add up to Bw / 16
@@ -356,6 +401,9 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
         if (tid < K && target >= 0 && n_live > 0)
             add_counter(W.arrive_disp + (size_t)my_d * D.N + s,
                         (unsigned)(n_live * 8 + (n_live + 3) / 4 + (slice == 0 ? pad_units : 0)));
+    } else if (done) {
+        announce_when_last(done + s * kDoneWords, (unsigned)(t * slices + slice), workgroups, W.arrive_disp, sent,
+                           (unsigned)(D.Bw / 16), s, D.N);
     }
 }
 
@@ -744,7 +792,8 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
 // 128: 144.5 -> 144, 512: 649 -> 631 (672 with eight workgroups per unit).
 template <bool THROUGH>   // THROUGH: see st_payload
 __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
-    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
+    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row,
+    unsigned *done /* as in dispatch_pack_kernel */) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
     const int lane = tid & (kWave - 1);
     const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -785,6 +834,11 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
             for (int u = 0; u < 4; ++u)
                 if (b + u * step < nvec) st_payload<THROUGH>(dst + b + u * step, val[u]);
         }
+    }
+    if (done) {
+        const int next = __shfl_down(off, 1);
+        announce_when_last(done + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
+                           d, N);
     }
 }
 
@@ -831,7 +885,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_chunk_kernel(
                 return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Bc;
             });
         if (FENCED) {
-            stores_done<FENCED>();
+            stores_done();
             __syncthreads();
             if (tid < q1 - q0) add_counter(W.arrive_comb + (size_t)push_to[tid].x * N + d, (unsigned)nvec);
         }
@@ -875,7 +929,8 @@ __device__ inline int sidecar_expert_row(const Dims &D, const Tables &W, int d, 
 
 template <bool THROUGH>   // THROUGH: see st_payload
 __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
-    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
+    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row,
+    unsigned *done /* as in dispatch_pack_kernel */) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
     const int lane = tid & (kWave - 1);
     const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -933,6 +988,11 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
                     st_payload<THROUGH>((v4u *)dst + b + u * step, o);
                 }
         }
+    }
+    if (done) {
+        const int next = __shfl_down(off, 1);
+        announce_when_last(done + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
+                           d, N);
     }
 }
 
@@ -1013,7 +1073,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
             }
         }
         if (FENCED) {
-            stores_done<FENCED>();
+            stores_done();
             __syncthreads();
             if (tid < r1 - r0) add_counter(W.arrive_comb + (size_t)share_to[tid].x * N + d, (unsigned)nvec);
         }

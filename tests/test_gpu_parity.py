@@ -45,7 +45,7 @@ def check_tables(sh, ref, N):
 
 def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_split=False,
                     ordering="counters", private_rows=0, push=False, partial=False, launch_mb=None,
-                    capacities=None, cached_mb=None, grid_pct=None):
+                    capacities=None, cached_mb=None, grid_pct=None, self_blocks=None):
     """ordering: "counters" = the default mode (the arrival counters are the only ordering:
     announce and gate kernels), "stream" = FL_FLAG_STREAM_ORDERED, "progressive" =
     FL_FLAG_PROGRESSIVE_RECV."""
@@ -65,6 +65,8 @@ def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_sp
             flmoe.fl_moe_debug_tune(sh.ctx, 6, launch_mb)
         if cached_mb is not None:        # all ranks' replies above which they are stored past the caches
             flmoe.fl_moe_debug_tune(sh.ctx, 4, cached_mb)
+        if self_blocks is not None:      # workgroups of a send call up to which it announces itself
+            flmoe.fl_moe_debug_tune(sh.ctx, 10, self_blocks)
         if grid_pct is not None:         # grids for this percentage of the rows uniform routing brings
             flmoe.fl_moe_debug_tune(sh.ctx, 5, grid_pct)
         if wl.dispatch_dtype == "bf16":
@@ -245,6 +247,33 @@ def test_replies_past_the_caches(name, partial):
     """Calls that write more than a GiB of replies use streaming stores; here every call does."""
     sh, _, _ = run_and_compare(wlmod.make_inputs(CASES[name]()), partial=partial, cached_mb=0)
     sh.close()
+
+
+# (ranks, experts, tokens, hidden, top-k, dtype): fewer workgroups per sender than partial counts, as many, one more,
+# many; several slices per token
+@pytest.mark.parametrize("self_blocks", [0, 1 << 30])
+@pytest.mark.parametrize("kw", [dict(), dict(ranks_split=True), dict(partial=True, private_rows=3), dict(launch_mb=1)],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("shape", [(4, 32, 3, 64, 4, "bf16"), (4, 32, 16, 520, 4, "bf16"), (4, 32, 17, 520, 4, "bf16"),
+                                   (4, 32, 300, 2056, 4, "bf16"), (64, 64, 5, 64, 8, "bf16"), (4, 32, 40, 4224, 4, "e4m3")],
+                         ids=str)
+def test_transfers_announced_by_the_last_workgroup_or_by_a_kernel(shape, kw, self_blocks):
+    """Both ways of announcing, at counts of workgroups around those of the partial counts; the counters end where
+    the receivers expect them, step after step."""
+    N, E, T, H, K, dtype = shape
+    wl = wlmod.custom("announce", N, E, T, H, K, seed=T, ragged=True, dispatch_dtype=dtype)
+    inp = wlmod.make_inputs(wl)
+    inp.num_tokens[1] = 0                               # a sender without tokens announces all the same
+    sh, dev, first = run_and_compare(inp, self_blocks=self_blocks, **kw)
+    try:
+        for _ in range(2):
+            out = harness.run_step(sh, dev)
+            torch.cuda.synchronize()
+            assert (bits(out) == first).all() and sh.status() == 0
+        dbg = sh.debug()
+        assert (dbg["arrive_disp"] == dbg["expect_disp"]).all() and (dbg["arrive_comb"] == dbg["expect_comb"]).all()
+    finally:
+        sh.close()
 
 
 def test_rank_subsets_give_the_same_result():
