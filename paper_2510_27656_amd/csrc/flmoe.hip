@@ -46,6 +46,16 @@ constexpr int kLaunchMiB = 860;
 constexpr int kSelfAnnounceBlocks = 4096;         // see announces_itself
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// From row to row of a receive buffer: rows start on 128-byte lines where that takes at most a sixteenth more room.
+// Stores that begin inside lines cost more than loads that do.  us of a step of 32 ranks, rows packed and rows on lines
+// (slices as before): 14 352-byte rows, 128 tokens 538 and 507; 10 000 bytes 368 and 345; 2064 bytes 117.3 and 111.9;
+// 2032 bytes, 1024 tokens 647 and 623.  Where padding takes more room the lines themselves cost: 1552 bytes (112 of
+// padding) 500 and 513, 272 bytes 177 and 196.
+int row_stride(long long row_bytes) {
+    const long long lines = (long long)align_up((size_t)row_bytes, 128);
+    return (int)((lines - row_bytes) * 16 <= row_bytes ? lines : row_bytes);
+}
+
 // Walks the workspace; with base == nullptr it only measures.
 struct Carver {
     char *base; size_t cur = 0;
@@ -109,7 +119,9 @@ int resolve(const fl_moe_config *c, Dims *D) {
         D->Bw = (long long)align_up((size_t)(D->H + 4ll * D->scales_per_row), 128);
     }
     // bufA receives the combine replies, bufB the dispatched rows.
-    const size_t need_a = (size_t)D->T * D->K * D->Bc, need_b = (size_t)D->recv_rows * D->Bw;
+    D->Sw = row_stride(D->Bw);
+    D->Sc = row_stride(D->Bc);
+    const size_t need_a = (size_t)D->T * D->K * D->Sc, need_b = (size_t)D->recv_rows * D->Sw;
     // Large payload buffers start on 2 MB boundaries of the workspace, rank by rank (the
     // page size the driver maps big allocations with): measured 3 % faster unpack at the
     // decode shape than 256-byte packing.  Small ones stay packed.
@@ -194,7 +206,8 @@ int pack_slices(long long row_bytes, int tune_slices) {
     // measured: rows up to 8 KB are fastest with two vectors per thread (4 KB rows: one block,
     // 30 -> 25 us; 7 KB rows of e4m3 codes: two blocks, 61 -> 54 us), longer rows with one
     if (nvec <= 4 * kPackThreads) return (int)((nvec + 2 * kPackThreads - 1) / (2 * kPackThreads));
-    long long s = (nvec + kPackThreads - 1) / kPackThreads;   // one vector per thread
+    // about one vector per thread; a slice more for the last few vectors costs (14 352-byte rows: 7 slices 483, 8 499 us a step)
+    long long s = (nvec + kPackThreads / 2) / kPackThreads;
     return (int)(s < 1 ? 1 : s > 16 ? 16 : s);
 }
 
@@ -779,7 +792,7 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
         // rows of 4 KB and less gain nothing; capped polling grids keep one workgroup per token
         int parts = D.tune_parts > 0 ? D.tune_parts : (nvec >= 512 && !progressive ? (nvec + kWave - 1) / kWave : 1);
         if (parts > nvec) parts = nvec;
-        const int per = (nvec + parts - 1) / parts;
+        const int per = whole_lines((nvec + parts - 1) / parts);
         int nt = (per + kWave - 1) / kWave * kWave;
         if (nt > kReduceMaxThreads) nt = kReduceMaxThreads;
         if (nt < 2 * kWave) nt = 2 * kWave;      // wave 0 waits, wave 1 fetches positions and weights

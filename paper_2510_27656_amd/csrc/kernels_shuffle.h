@@ -138,8 +138,8 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     // entries: everything the block needs is fetched in one round (x has T rows per rank, so
     // the loads are in bounds for absent tokens too).
     const int nvec = (int)(src_row_bytes / 16);
-    const int per = (nvec + slices - 1) / slices;          // vectors of this slice: [v0, v1)
-    const int v0 = slice * per, v1 = min(v0 + per, nvec);
+    const int per = whole_lines((nvec + slices - 1) / slices); // vectors of this slice: [v0, v1)
+    const int v0 = min(slice * per, nvec), v1 = min(v0 + per, nvec);
     const v4u *src = (const v4u *)(x + ((size_t)s * D.T + t) * src_row_bytes);
     v4u r[4];
 #pragma unroll
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
             const int row = s_row[k];          // uniform: one copy per distinct destination
             if (row < 0) continue;
             char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
-            v4u *dst = (v4u *)(base + (size_t)row * D.Bw);
+            v4u *dst = (v4u *)(base + (size_t)row * D.Sw);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 if (b + i * kPackThreads < v1)
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                     const int row = s_row[k];
                     if (row < 0) continue;
                     char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
-                    st_payload<true>((v4u *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    st_payload<true>((v4u *)(base + (size_t)row * D.Sw + D.Be) + v, val);
                 }
             }
         } else {
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                     const int row = s_row[k];
                     if (row < 0) continue;
                     char *base = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes;
-                    st_word((int *)(base + (size_t)row * D.Bw + D.Be) + v, val);
+                    st_word((int *)(base + (size_t)row * D.Sw + D.Be) + v, val);
                 }
             }
         }
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     for (int k = 0; k < K; ++k) {
         const int row = s_row[k];
         if (row < 0) continue;
-        char *dst = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes + (size_t)row * D.Bw;
+        char *dst = W.bufB + (size_t)s_dst[k] * D.bufB_rank_bytes + (size_t)row * D.Sw;
         if (live) st_payload<true>((v4u *)dst + (size_t)blk * kQuantLanes + sub, out);
         if (scale_vectors) {
             if (tid < nsv)
@@ -523,7 +523,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     v4u val[U];
     unsigned m = kNoEntry;
     auto load_batch = [&](int phys, int b) {
-        const v4u *src = (const v4u *)(recv + (size_t)phys * D.Bw);
+        const v4u *src = (const v4u *)(recv + (size_t)phys * D.Sw);
 #pragma unroll
         for (int i = 0; i < U; ++i)
             if (b + i * step < rowvec) val[i] = ld_stream(src + b + i * step);
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
             }
         }
         if (D.scales_per_row && !scales_as_vectors && sub == 0) {   // odd scale counts: element by element
-            const float *ssrc = (const float *)(recv + (size_t)phys * D.Bw + D.Be);
+            const float *ssrc = (const float *)(recv + (size_t)phys * D.Sw + D.Be);
             for (int b = 0; b < D.scales_per_row; b += kWave) {
                 const int v = b + lane;
                 const float sc = v < D.scales_per_row ? ssrc[v] : 0.f;
@@ -695,7 +695,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
                     row[i] = v / rowvec;
                     col[i] = v - row[i] * rowvec;
                     const int pr = PRIVATE ? src_phys[row[i]] : r0 + row[i];
-                    val[i] = ld_stream((const v4u *)(recv + (size_t)pr * D.Bw) + col[i]);
+                    val[i] = ld_stream((const v4u *)(recv + (size_t)pr * D.Sw) + col[i]);
                 }
             }
         };
@@ -768,7 +768,7 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
             for (int v = tid; v < (r1 - r0) * D.scales_per_row; v += kCopyThreads) {
                 const int row = v / D.scales_per_row, col = v - row * D.scales_per_row;
                 const int pr = PRIVATE ? src_phys[row] : r0 + row;
-                const float val = ((const float *)(recv + (size_t)pr * D.Bw + D.Be))[col];
+                const float val = ((const float *)(recv + (size_t)pr * D.Sw + D.Be))[col];
                 for (int i = 0; i < dst_cnt[row]; ++i)
                     expert_scales[((size_t)d * D.expert_cap + dst_rows[row][i]) * D.scales_per_row + col] = val;
             }
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
         }
         const v4u *src = (const v4u *)(yd + (size_t)src_row * D.Bc);
         v4u *dst = (v4u *)(W.bufA + (size_t)s * D.bufA_rank_bytes +
-                           (size_t)(__builtin_amdgcn_readlane(reply, s) + q - __builtin_amdgcn_readlane(off, s)) * D.Bc);
+                           (size_t)(__builtin_amdgcn_readlane(reply, s) + q - __builtin_amdgcn_readlane(off, s)) * D.Sc);
         for (int b = v0; b < nvec; b += 4 * step) {
             v4u val[4];
 #pragma unroll
@@ -882,7 +882,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_pack_chunk_kernel(
             q1 - q0, nvec, tid,
             [&](int r) { return yd + (size_t)src_row[r] * D.Bc; },
             [&](int r) {
-                return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Bc;
+                return W.bufA + (size_t)push_to[r].x * D.bufA_rank_bytes + (size_t)push_to[r].y * D.Sc;
             });
         if (FENCED) {
             stores_done();
@@ -958,7 +958,7 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
         const int n = __popcll(__ballot(m != kNoEntry));       // entries come first in the sidecar
         int place = 0;
         if (m != kNoEntry) place = sidecar_expert_row(D, W, d, s, m);
-        char *dst = W.bufA + (size_t)s * D.bufA_rank_bytes + (size_t)(__builtin_amdgcn_readlane(ret, s) + i) * D.Bc;
+        char *dst = W.bufA + (size_t)s * D.bufA_rank_bytes + (size_t)(__builtin_amdgcn_readlane(ret, s) + i) * D.Sc;
         constexpr int U = 4;
         // the whole wave, as in the unpack kernel; lanes beyond the row sum its last vector and store nothing
         for (int b0 = v0; b0 < nvec; b0 += U * step) {
@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
                 v4u o;
                 o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
                 o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
-                char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Bc;
+                char *dst = W.bufA + (size_t)share_to[row[u]].x * D.bufA_rank_bytes + (size_t)share_to[row[u]].y * D.Sc;
                 st_payload<THROUGH>((v4u *)dst + col[u], o);
             }
         }
@@ -1090,7 +1090,7 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
 // itself always runs k = 0..K-1.
 template <int KT>
 __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos, const float *w,
-                                  int K, long long Bc, int v0, int nvec, v4u *__restrict__ out, int tid) {
+                                  int K, long long stride, int v0, int nvec, v4u *__restrict__ out, int tid) {
     for (int v = v0 + tid; v < nvec; v += (int)blockDim.x) {
         float acc[8];
 #pragma unroll
@@ -1100,12 +1100,12 @@ __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos,
             v4u y[KT];
 #pragma unroll
             for (int k = 0; k < KT; ++k)
-                y[k] = ld_stream((const v4u *)(recv + (size_t)pos[k0 + k] * Bc) + v);
+                y[k] = ld_stream((const v4u *)(recv + (size_t)pos[k0 + k] * stride) + v);
 #pragma unroll
             for (int k = 0; k < KT; ++k) fma8(acc, w[k0 + k], y[k]);
         }
         for (; k0 < K; ++k0)
-            fma8(acc, w[k0], ld_stream((const v4u *)(recv + (size_t)pos[k0] * Bc) + v));
+            fma8(acc, w[k0], ld_stream((const v4u *)(recv + (size_t)pos[k0] * stride) + v));
         v4u o;
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
@@ -1116,7 +1116,7 @@ __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos,
 // The same sum for a row count only known on the device (partial sums: one row per
 // distinct expert rank of the token): batches of up to 8 loads, predicated.
 __device__ inline void reduce_row_counted(const char *__restrict__ recv, const int *pos,
-                                          const float *w, int n, long long Bc, int v0, int nvec,
+                                          const float *w, int n, long long stride, int v0, int nvec,
                                           v4u *__restrict__ out, int tid) {
     for (int v = v0 + tid; v < nvec; v += (int)blockDim.x) {
         float acc[8];
@@ -1126,7 +1126,7 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
             v4u y[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k)
-                if (k0 + k < n) y[k] = ld_stream((const v4u *)(recv + (size_t)pos[k0 + k] * Bc) + v);
+                if (k0 + k < n) y[k] = ld_stream((const v4u *)(recv + (size_t)pos[k0 + k] * stride) + v);
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 if (k0 + k < n) fma8(acc, w[k0 + k], y[k]);
@@ -1207,7 +1207,7 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     if (timed_out) return;
     const char *recv = W.bufA + (size_t)s * D.bufA_rank_bytes;
     const int nvec_row = (int)(D.Bc / 16);
-    const int per = (nvec_row + parts - 1) / parts;            // this block's slice: [v0, nvec)
+    const int per = whole_lines((nvec_row + parts - 1) / parts);   // this block's slice: [v0, nvec)
     const int v0 = part * per, nvec = min(v0 + per, nvec_row);
     const int kt = D.tune_reduce ? D.tune_reduce : K;
     // one token per block unless the grid was made smaller than the token count
@@ -1216,11 +1216,11 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         const int next = t + t_step;
         if (fetcher && next < Ts) fetch(next);                // in flight while the rows are summed
         v4u *o = (v4u *)(out + ((size_t)s * D.T + t) * D.Bc);
-        if (PARTIAL) reduce_row_counted(recv, pos[cur], w[cur], n_shares[cur], D.Bc, v0, nvec, o, tid);
-        else if (kt >= 8) reduce_row<8>(recv, pos[cur], w[cur], K, D.Bc, v0, nvec, o, tid);
-        else if (kt >= 4) reduce_row<4>(recv, pos[cur], w[cur], K, D.Bc, v0, nvec, o, tid);
-        else if (kt >= 2) reduce_row<2>(recv, pos[cur], w[cur], K, D.Bc, v0, nvec, o, tid);
-        else reduce_row<1>(recv, pos[cur], w[cur], K, D.Bc, v0, nvec, o, tid);
+        if (PARTIAL) reduce_row_counted(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid);
+        else if (kt >= 8) reduce_row<8>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
+        else if (kt >= 4) reduce_row<4>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
+        else if (kt >= 2) reduce_row<2>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
+        else reduce_row<1>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
         if (next >= Ts) break;
         if (fetcher) publish(cur ^ 1);
         __syncthreads();                       // the other set is complete; this one may be rewritten

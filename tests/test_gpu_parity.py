@@ -220,6 +220,21 @@ def test_rows_at_the_edges_of_a_waves_share(shape, kw):
     sh.close()
 
 
+# rows that are padded to whole lines in the receive buffers (496, 2032, 4112, 14 352 bytes), one that just is and one
+# that just is not (1808, 1776), and rows whose last slice would begin behind their end
+@pytest.mark.parametrize("kw", [dict(), dict(ordering="stream"), dict(ordering="progressive"), dict(private_rows=5),
+                                dict(partial=True), dict(partial=True, ordering="progressive", private_rows=3),
+                                dict(ranks_split=True, self_blocks=0)],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("tokens,hidden", [(20, 248), (700, 248), (20, 1016), (700, 1016), (20, 904), (20, 888), (20, 2056),
+                                           (20, 7176), (20, 16456)])
+def test_rows_that_do_not_end_on_a_line(tokens, hidden, kw):
+    """Row strides of the receive buffers apart from the rows' own bytes, by waves and by chunks: bit for bit."""
+    wl = wlmod.custom("strides", 8, 64, tokens, hidden, 8, seed=hidden, ragged=True)
+    sh, _, _ = run_and_compare(wlmod.make_inputs(wl), align=4, zero_pad=True, capacity_factor=2.5, **kw)
+    sh.close()
+
+
 # (tokens, hidden, dtype) at 8 ranks x 64 experts, top 8, enough rows for the kernels that take chunks of rows:
 # one vector per row, rows that share a load instruction and do not divide the workgroup, the longest rows that
 # go by chunks; e4m3 rows whose scales are and are not whole vectors
