@@ -101,7 +101,8 @@ extern "C" {
  *   - A receive call first enqueues a gate kernel of one wave per rank that polls the
  *     rank's counters with acquire semantics until every source has delivered what
  *     the exchanged counts promised (bounded: FL_STATUS_TIMEOUT), and behind it the
- *     receive kernel proper, on a full grid.  Waiting occupies one wave per rank.
+ *     receive kernel proper, on a full grid.  Waiting occupies one wave per rank.  A receive
+ *     kernel so small that its waves take little of the machine waits itself instead.
  * What a rank still orders itself is its OWN five calls of a step, and one step after
  * the other (one stream per rank does that, or events).  That also covers the re-use of
  * the receive buffers (the paper puts a barrier before buffers are re-used, section
@@ -416,7 +417,10 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
  *   knob 9 = workgroups that share one token in combine_reduce, each summing a slice of the row
  *            (0 = chosen from the row size)
  *   knob 10 = workgroups of a send call up to which its payload kernel announces the transfers itself
- *            instead of having an announce kernel launched behind it (default 4096; 0 = never) */
+ *            instead of having an announce kernel launched behind it (default 4096; 0 = never)
+ *   knob 11 = waves of a receive launch up to which it waits for the arrival counters itself instead
+ *            of having a gate kernel launched in front (default: half of the GPU's wave slots over the
+ *            number of hardware queues, 1024 on a whole MI355X with 4 queues; 0 = never) */
 int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value);
 
 /* Diagnostic, host only (no GPU needed): how a payload call over `rank_count` ranks of

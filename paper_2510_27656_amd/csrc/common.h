@@ -36,6 +36,7 @@ struct Dims {
     int tune_parts;       // workgroups per token in the reduce kernel (0 = by row size)
     int tune_order;       // test switch: order in which the send kernels take their rows
     int tune_self;        // send calls of up to this many workgroups announce their transfers themselves (announces_itself)
+    int tune_wait;        // receive launches of up to this many waves wait for the counters themselves (waits_itself)
     int tune_cap8;        // progressive receivers: eighths of the machine's block slots their grids may take
 };
 
@@ -239,6 +240,14 @@ __device__ inline int seg_of_short(const int *off, int n, int x, int *start) {
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 __device__ inline v4u ld_stream(const v4u *p) { return __builtin_nontemporal_load(p); }
 __device__ inline void st_stream(v4u *p, v4u v) { __builtin_nontemporal_store(v, p); }
+// 16-byte load at device scope from a row whose address is the same in the whole wave: what another XCD has written
+// through is seen whatever the caches here hold, as by the counters' own loads (with the streaming hint it takes as
+// long as ld_stream).
+__device__ inline v4u ld_coherent(const char *row, int vec) {
+    constexpr int kDeviceScopeStreaming = 0x12;             // sc1, nt
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, 0x7FFFFFFF, 0x00020000);
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, vec * 16, 0, kDeviceScopeStreaming);
+}
 // 16-byte store at device scope: written through the XCD's L2 to memory, where every XCD sees it once it
 // has been acknowledged.  No dirty line is left for the end of the kernel, which otherwise waits until the
 // L2s have written theirs back (32 ranks x 4 tokens: 3.9 us from the pack kernel's last store to the next

@@ -44,6 +44,7 @@ constexpr int kComputeUnits = 256;                // of the part, where a contex
 constexpr int kCachedReplyMiB = 1024;             // see replies_cached
 constexpr int kLaunchMiB = 860;
 constexpr int kSelfAnnounceBlocks = 4096;         // see announces_itself
+constexpr int kWavesPerUnit = 32;                 // wave slots of a compute unit
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // From row to row of a receive buffer: rows start on 128-byte lines where that takes at most a sixteenth more room.
@@ -54,6 +55,15 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 int row_stride(long long row_bytes) {
     const long long lines = (long long)align_up((size_t)row_bytes, 128);
     return (int)((lines - row_bytes) * 16 <= row_bytes ? lines : row_bytes);
+}
+
+// Waves of a receive launch that may wait inside the kernel (waits_itself): a hardware queue runs one such launch at a
+// time, so if every queue but one holds one (4 queues unless the environment says otherwise) they take less than
+// half of the machine's wave slots, and a sender's workgroup, the layout step's sixteen waves included, still finds room.
+int self_wait_waves(int cu_count) {
+    const char *set = getenv("GPU_MAX_HW_QUEUES");
+    const int queues = std::max(set ? atoi(set) : 0, 4);
+    return cu_count * kWavesPerUnit / 2 / queues;
 }
 
 // Walks the workspace; with base == nullptr it only measures.
@@ -141,6 +151,7 @@ int resolve(const fl_moe_config *c, Dims *D) {
     D->tune_cached_mb = kCachedReplyMiB;
     D->tune_grid_pct = -1;
     D->tune_self = kSelfAnnounceBlocks;
+    D->tune_wait = self_wait_waves(kComputeUnits);
     D->tune_cap8 = 3;
     D->tune_order = 0;
     D->tune_parts = 0;
@@ -291,6 +302,24 @@ bool announces_itself(const Dims &D, long long workgroups, int rank_count) {
     return !(D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED)) && workgroups * rank_count <= D.tune_self;
 }
 
+// The whole rank range of a call, and where in it the current launch group sits: the
+// gate kernel of a receive call runs once, before the first group, for all its ranks,
+// and the announce kernel of a send call once, behind the last group (a receiver needs
+// every sender's rows anyway, so announcing group by group would let nobody start earlier).
+struct CallSpan {
+    int rank_begin, rank_count;
+    bool first, last;
+};
+
+// Whether a receive launch of `waves` waits for the arrival counters itself instead of having a gate kernel in front:
+// if the waves that wait leave the senders room whatever else waits (self_wait_waves: 1024 on a whole MI355X).  us of a
+// step with gate kernels and without: 2 ranks x 16 tokens of 512 bytes 28.2 and 24.5, 8 x 4 tokens of 4 KB 32.7 and 28.5,
+// 8 ranks one by one: 8 tokens of 14 KB 225 and 165, 64 tokens of 8 KB 225 and 200.
+bool waits_itself(const Dims &D, long long waves, const CallSpan &call, int rank_count) {
+    return !(D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED)) && rank_count == call.rank_count &&
+           waves * rank_count <= D.tune_wait;
+}
+
 // Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
 // to four vectors per lane.
 int waves_per_row(long long vecs) {
@@ -384,15 +413,6 @@ int ranks_per_launch(const Dims &D, int launch_mb, int rc) {
     if (launches > rc) launches = rc;
     return (int)((rc + launches - 1) / launches);
 }
-
-// The whole rank range of a call, and where in it the current launch group sits: the
-// gate kernel of a receive call runs once, before the first group, for all its ranks,
-// and the announce kernel of a send call once, behind the last group (a receiver needs
-// every sender's rows anyway, so announcing group by group would let nobody start earlier).
-struct CallSpan {
-    int rank_begin, rank_count;
-    bool first, last;
-};
 
 // Runs f(rank_begin, rank_count, span) over the rank groups of one call.
 template <class F>
@@ -502,6 +522,7 @@ int fl_moe_create(const fl_moe_config *cfg, void *workspace, size_t workspace_by
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
             cus > 0)
             ctx->cu_count = cus;
+        ctx->D.tune_wait = self_wait_waves(ctx->cu_count);
     }
     for (int i = 0; i < kEventPool; ++i) {      // created when profiling is first enabled
         ctx->ev_start[i] = nullptr;
@@ -662,11 +683,18 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
     hipStream_t st = (hipStream_t)stream;
     const bool gated = !(D.flags & FL_FLAG_STREAM_ORDERED);
     const bool progressive = D.flags & FL_FLAG_PROGRESSIVE_RECV;
+    const long long rows = recv_grid_rows(D);
+    const bool chunks = unpack_by_chunks(D, ctx->cu_count, rc);
+    const int G = waves_per_row(D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0));
+    const int wpb = kCopyThreads / kWave;
+    unsigned gx = capped_grid((rows * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);     // of the wave kernel
+    if (gx < (unsigned)D.El) gx = (unsigned)((D.El + G - 1) / G * G);    // the first El-1 blocks also clear padding rows
+    const bool waits = !chunks && waits_itself(D, (long long)gx * wpb, call, rc);
     // Default: a gate kernel of one wave per rank polls the rank's arrival counters, and the
     // unpack kernel runs behind it in the stream on a full grid.  Stream-ordered callers need
     // no gate.
     const int *gate = nullptr;
-    if (gated && !progressive) {
+    if (gated && !progressive && !waits) {
         if (call.first) {
             LaunchTimer t(ctx, KID_GATE_DISPATCH, st);
             arrival_gate_kernel<<<dim3(call.rank_count), dim3(kWave), 0, st>>>(
@@ -674,10 +702,9 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
         }
         gate = ctx->W.gate_disp;
     }
-    const long long rows = recv_grid_rows(D);
     char *ex = (char *)expert_x;
     LaunchTimer t(ctx, KID_DISPATCH_UNPACK, st);
-    if (unpack_by_chunks(D, ctx->cu_count, rc)) {
+    if (chunks) {
         // Progressive: the unpack kernel polls itself and starts on each
         // source's rows as they land; it may be running while senders still need somewhere to
         // run, so it takes at most three eighths of the resident-block slots (measured best), and
@@ -687,20 +714,18 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
             long long n = (32768 + D.Bw - 1) / D.Bw;
             rbk = (int)(n > kMaxRowsPerBlock ? kMaxRowsPerBlock : n);
         }
-        unsigned gx = capped_grid((rows + rbk - 1) / rbk, rc,
+        gx = capped_grid((rows + rbk - 1) / rbk, rc,
                                   progressive ? (long long)ctx->cu_count * D.tune_cap8 : kMaxRowBlocks);
         if (gx < (unsigned)D.El) gx = D.El;      // the first El-1 blocks also clear padding rows
         auto kernel = progressive ? D.P ? dispatch_unpack_chunk_kernel<true, true> : dispatch_unpack_chunk_kernel<false, true>
                                   : D.P ? dispatch_unpack_chunk_kernel<true, false> : dispatch_unpack_chunk_kernel<false, false>;
         kernel<<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, ctx->W, rb, ex, expert_scales, tokens_per_expert, rbk, gate);
     } else {
-        const int G = waves_per_row(D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0));
-        const int wpb = kCopyThreads / kWave;
-        unsigned gx = capped_grid((rows * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);
-        if (gx < (unsigned)D.El) gx = (unsigned)((D.El + G - 1) / G * G);
-        auto kernel = D.P ? dispatch_unpack_kernel<true> : dispatch_unpack_kernel<false>;
-        kernel<<<dim3(gx, rc), dim3(kCopyThreads), kRowWavesLdsBytes, st>>>(D, ctx->W, rb, ex, expert_scales,
-                                                                          tokens_per_expert, G, gate);
+        auto kernel = waits ? D.P ? dispatch_unpack_kernel<true, true> : dispatch_unpack_kernel<false, true>
+                            : D.P ? dispatch_unpack_kernel<true, false> : dispatch_unpack_kernel<false, false>;
+        // a launch that waits holds as little as it can
+        kernel<<<dim3(gx, rc), dim3(kCopyThreads), waits ? 0 : kRowWavesLdsBytes, st>>>(D, ctx->W, rb, ex, expert_scales,
+                                                                                      tokens_per_expert, G, gate);
     }
     return launch_status();
 }
@@ -775,8 +800,25 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
     const Dims &D = ctx->D;
     const bool gated = !(D.flags & FL_FLAG_STREAM_ORDERED), partial = D.flags & FL_FLAG_PARTIAL_SUMS;
     const bool progressive = D.flags & FL_FLAG_PROGRESSIVE_RECV;
+    // `parts` workgroups share a token, each taking a slice of the row
+    const int nvec = (int)(D.Bc / 16);
+    // measured: long rows are summed fastest by many small workgroups, one payload wave each
+    // (7168-wide rows: 14 workgroups of 2 waves 86 us, 2 of 7 waves 90 us, 1 of 14 waves 92 us);
+    // rows of 4 KB and less gain nothing; capped polling grids keep one workgroup per token
+    int parts = D.tune_parts > 0 ? D.tune_parts : (nvec >= 512 && !progressive ? (nvec + kWave - 1) / kWave : 1);
+    if (parts > nvec) parts = nvec;
+    const int per = whole_lines((nvec + parts - 1) / parts);
+    int nt = (per + kWave - 1) / kWave * kWave;
+    if (nt > kReduceMaxThreads) nt = kReduceMaxThreads;
+    if (nt < 2 * kWave) nt = 2 * kWave;      // wave 0 waits, wave 1 fetches positions and weights
+    // progressive (polling) receivers take at most three eighths of the machine's wave slots
+    const unsigned gx = progressive ? capped_grid(D.T, rc, (long long)ctx->cu_count * 256 * D.tune_cap8 / nt / parts)
+                                    : (unsigned)D.T;
+    const dim3 grid(gx * parts, rc);
+    char *o = (char *)out;
+    const bool waits = waits_itself(D, (long long)gx * parts * (nt / kWave), call, rc);
     const int *gate = nullptr;
-    if (gated && !progressive) {         // as in dispatch_recv: a gate kernel, then the full grid
+    if (gated && !progressive && !waits) {         // as in dispatch_recv: a gate kernel, then the full grid
         if (call.first) {
             LaunchTimer t(ctx, KID_GATE_COMBINE, st);
             arrival_gate_kernel<<<dim3(call.rank_count), dim3(kWave), 0, st>>>(
@@ -784,33 +826,16 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
         }
         gate = ctx->W.gate_comb;
     }
-    {
-        LaunchTimer t(ctx, KID_COMBINE_REDUCE, st);
-        // `parts` workgroups share a token, each taking a slice of the row
-        const int nvec = (int)(D.Bc / 16);
-        // measured: long rows are summed fastest by many small workgroups, one payload wave each
-        // (7168-wide rows: 14 workgroups of 2 waves 86 us, 2 of 7 waves 90 us, 1 of 14 waves 92 us);
-        // rows of 4 KB and less gain nothing; capped polling grids keep one workgroup per token
-        int parts = D.tune_parts > 0 ? D.tune_parts : (nvec >= 512 && !progressive ? (nvec + kWave - 1) / kWave : 1);
-        if (parts > nvec) parts = nvec;
-        const int per = whole_lines((nvec + parts - 1) / parts);
-        int nt = (per + kWave - 1) / kWave * kWave;
-        if (nt > kReduceMaxThreads) nt = kReduceMaxThreads;
-        if (nt < 2 * kWave) nt = 2 * kWave;      // wave 0 waits, wave 1 fetches positions and weights
-        // progressive (polling) receivers take at most three eighths of the machine's wave slots
-        const unsigned gx = progressive ? capped_grid(D.T, rc, (long long)ctx->cu_count * 256 * D.tune_cap8 / nt / parts)
-                                        : (unsigned)D.T;
-        const dim3 grid(gx * parts, rc);
-        char *o = (char *)out;
-        if (progressive && partial)
-            combine_reduce_kernel<true, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
-        else if (progressive)
-            combine_reduce_kernel<true, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
-        else if (partial)
-            combine_reduce_kernel<false, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
-        else
-            combine_reduce_kernel<false, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
-    }
+    LaunchTimer t(ctx, KID_COMBINE_REDUCE, st);
+    const bool fenced = progressive || waits;
+    if (fenced && partial)
+        combine_reduce_kernel<true, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+    else if (fenced)
+        combine_reduce_kernel<true, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+    else if (partial)
+        combine_reduce_kernel<false, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+    else
+        combine_reduce_kernel<false, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
     return launch_status();
 }
 
@@ -916,6 +941,7 @@ int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value) {
         case 7: if (value > 8 || value == 0) return FL_ERR_INVALID_ARG; ctx->D.tune_cap8 = dflt ? 3 : value; break;
         case 8: if (value > 2) return FL_ERR_INVALID_ARG; ctx->D.tune_order = dflt ? 0 : value; break;
         case 9: if (value > 64) return FL_ERR_INVALID_ARG; ctx->D.tune_parts = dflt ? 0 : value; break;
+        case 11: ctx->D.tune_wait = dflt ? self_wait_waves(ctx->cu_count) : value; break;
         case 10: ctx->D.tune_self = dflt ? kSelfAnnounceBlocks : value; break;
         default: return FL_ERR_INVALID_ARG;
     }

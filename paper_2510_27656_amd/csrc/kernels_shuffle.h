@@ -502,7 +502,11 @@ __device__ inline void unpack_extras(const Dims &D, const Tables &W, int d, int 
 // steps and shorter rows measure the same).  Against a block that planned its rows in LDS
 // first: 4 tokens 12.0 -> 9.7 us, 128: 151 -> 147, e4m3 75 -> 72, 6.7 KB rows 31 -> 29.
 constexpr int kRowWavesLdsBytes = 32 << 10;
-template <bool PRIVATE>   // the receive buffer has private slots (P > 0): a row's place depends on its source
+//
+// WAIT (small launches in the default mode): no gate kernel ran; every wave waits (bounded) until all of the rank's
+// sources have delivered, and reads rows and sidecars at device scope, because the launch may have been running when
+// they landed.  Which launches: waits_itself in flmoe.hip.
+template <bool PRIVATE, bool WAIT>   // PRIVATE: the receive buffer has private slots (P > 0): a row's place depends on its source
 __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
     float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int waves_per_row,
@@ -523,13 +527,14 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     v4u val[U];
     unsigned m = kNoEntry;
     auto load_batch = [&](int phys, int b) {
-        const v4u *src = (const v4u *)(recv + (size_t)phys * D.Sw);
+        const char *src = recv + (size_t)phys * D.Sw;
 #pragma unroll
         for (int i = 0; i < U; ++i)
-            if (b + i * step < rowvec) val[i] = ld_stream(src + b + i * step);
+            if (b + i * step < rowvec) val[i] = WAIT ? ld_coherent(src, b + i * step) : ld_stream((const v4u *)src + b + i * step);
     };
     auto load_meta = [&](int phys) {
-        m = lane < K ? W.recv_meta[((size_t)d * D.recv_rows + phys) * D.MW + lane] : kNoEntry;
+        const unsigned *meta = W.recv_meta + ((size_t)d * D.recv_rows + phys) * D.MW + lane;
+        m = lane < K ? WAIT ? ld_relaxed(meta) : *meta : kNoEntry;
     };
     // first round of loads, all independent
     int r = wave / G;
@@ -543,13 +548,18 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
         have = ld_relaxed(W.arrive_disp + (size_t)d * N + lane);
     }
     if (!plan_ok || !gate_ok) return;               // step skipped, or the arrival wait timed out (already latched)
+    if (WAIT && !__all(lane >= N || arrived(have, want)) &&
+        !wave_wait_counters<16>(W.arrive_disp + (size_t)d * N, W.expect_disp + (size_t)d * N, 0u, N, D.spin_limit)) {
+        if (lane == 0) latch_status(W.status, FL_STATUS_TIMEOUT);
+        return;
+    }
     char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
     unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
     for (; r < total; r += row_step) {              // capacities are upper bounds: the grid may be smaller than the rows
         const int s = __popcll(__ballot(off <= r)) - 1;
         const int in_source = r - __builtin_amdgcn_readlane(off, s);
         const int phys = PRIVATE ? recv_buffer_row(N, D.P, s, in_source, __builtin_amdgcn_readlane(shared_off, s)) : r;
-        if (!gate) {                                // stream order has made it so; checked, bounded
+        if (!WAIT && !gate) {                       // stream order has made it so; checked, bounded
             const unsigned expected = (unsigned)__builtin_amdgcn_readlane(want, s);
             bool landed = arrived((unsigned)__builtin_amdgcn_readlane(have, s), expected);
             if (!landed) {
@@ -590,7 +600,8 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
             const float *ssrc = (const float *)(recv + (size_t)phys * D.Sw + D.Be);
             for (int b = 0; b < D.scales_per_row; b += kWave) {
                 const int v = b + lane;
-                const float sc = v < D.scales_per_row ? ssrc[v] : 0.f;
+                const float sc = v >= D.scales_per_row ? 0.f
+                                 : WAIT ? __uint_as_float(ld_relaxed((const unsigned *)ssrc + v)) : ssrc[v];
                 for (int k = 0; k < n; ++k) {
                     const size_t dr = (size_t)__builtin_amdgcn_readlane(place, k);
                     if (v < D.scales_per_row) expert_scales[((size_t)d * D.expert_cap + dr) * D.scales_per_row + v] = sc;
@@ -1143,6 +1154,9 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
 // flight at once.
 constexpr int kReduceMaxThreads = 1024;
 //
+// FENCED: the kernel waits for the counters itself and invalidates the caches before it reads the rows: progressive
+// mode, and small launches of the default mode (waits_itself in flmoe.hip), which have no gate kernel.
+//
 // PARTIAL (sender-side partial sums): the token's rows are the shares of its
 // distinct expert ranks, found through send_to[s][t][k] for every k that is the first
 // of its rank; they are added in that order in fp32 (a fused multiply-add with
@@ -1192,7 +1206,9 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         }
     };
     if (fetcher) fetch(t0);
-    if (!plan_ok || !gate_ok || t0 >= Ts) return;
+    // in the default mode a rank without tokens waits for its (empty) replies all the same
+    const bool waiter = FENCED && blockIdx.x == 0 && !(D.flags & FL_FLAG_PROGRESSIVE_RECV);
+    if (!plan_ok || !gate_ok || (t0 >= Ts && !waiter)) return;
     if (tid == 0) timed_out = 0;               // wave 0 itself is the only one that may raise it
     if (fetcher) publish(0);
     // behind a gate kernel the counters were already seen complete, for every source of this rank

@@ -45,7 +45,7 @@ def check_tables(sh, ref, N):
 
 def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_split=False,
                     ordering="counters", private_rows=0, push=False, partial=False, launch_mb=None,
-                    capacities=None, cached_mb=None, grid_pct=None, self_blocks=None):
+                    capacities=None, cached_mb=None, grid_pct=None, self_blocks=None, wait_waves=None):
     """ordering: "counters" = the default mode (the arrival counters are the only ordering:
     announce and gate kernels), "stream" = FL_FLAG_STREAM_ORDERED, "progressive" =
     FL_FLAG_PROGRESSIVE_RECV."""
@@ -67,6 +67,8 @@ def run_and_compare(inp, align=1, zero_pad=False, capacity_factor=None, ranks_sp
             flmoe.fl_moe_debug_tune(sh.ctx, 4, cached_mb)
         if self_blocks is not None:      # workgroups of a send call up to which it announces itself
             flmoe.fl_moe_debug_tune(sh.ctx, 10, self_blocks)
+        if wait_waves is not None:       # waves of a receive launch up to which it waits itself
+            flmoe.fl_moe_debug_tune(sh.ctx, 11, wait_waves)
         if grid_pct is not None:         # grids for this percentage of the rows uniform routing brings
             flmoe.fl_moe_debug_tune(sh.ctx, 5, grid_pct)
         if wl.dispatch_dtype == "bf16":
@@ -285,6 +287,40 @@ def test_transfers_announced_by_the_last_workgroup_or_by_a_kernel(shape, kw, sel
             out = harness.run_step(sh, dev)
             torch.cuda.synchronize()
             assert (bits(out) == first).all() and sh.status() == 0
+        dbg = sh.debug()
+        assert (dbg["arrive_disp"] == dbg["expect_disp"]).all() and (dbg["arrive_comb"] == dbg["expect_comb"]).all()
+    finally:
+        sh.close()
+
+
+# rows in several waves, more tokens than workgroups of the reduce kernel have waves; e4m3 with whole and odd vectors of scales
+@pytest.mark.parametrize("wait_waves", [0, 1 << 20])
+@pytest.mark.parametrize("kw", [dict(), dict(ranks_split=True), dict(partial=True, private_rows=3), dict(launch_mb=1)],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("shape", [(4, 32, 3, 64, 4, "bf16"), (4, 32, 16, 2056, 4, "bf16"), (16, 64, 5, 4096, 8, "bf16"),
+                                   (4, 32, 20, 384, 4, "e4m3"), (4, 32, 9, 4608, 4, "e4m3")], ids=str)
+def test_receivers_that_wait_themselves_or_behind_a_gate_kernel(shape, kw, wait_waves):
+    """Both ways of waiting, a rank without tokens included; then with the senders on another stream, step after step."""
+    N, E, T, H, K, dtype = shape
+    wl = wlmod.custom("wait", N, E, T, H, K, seed=T, ragged=True, dispatch_dtype=dtype)
+    inp = wlmod.make_inputs(wl)
+    inp.num_tokens[1] = 0
+    sh, dev, first = run_and_compare(inp, align=4, zero_pad=True, wait_waves=wait_waves, **kw)
+    try:
+        streams = (torch.cuda.Stream(), torch.cuda.Stream())
+        torch.cuda.synchronize()
+        for _ in range(4):
+            sh.out.view(torch.int16).fill_(POISON)
+            torch.cuda.synchronize()
+            if kw.get("partial"):
+                out = harness.run_step(sh, dev)
+            else:
+                out = harness.run_step_two_streams(sh, dev, streams=streams)
+            torch.cuda.synchronize()
+            assert sh.status() == 0
+            for s in range(N):
+                n = inp.num_tokens[s]
+                assert (bits(out)[s, :n] == first[s, :n]).all()
         dbg = sh.debug()
         assert (dbg["arrive_disp"] == dbg["expect_disp"]).all() and (dbg["arrive_comb"] == dbg["expect_comb"]).all()
     finally:
