@@ -91,12 +91,14 @@ __device__ inline int in_order(int order, int i, int n) {
 // need not exist, so fetching them would have to wait for the token count.
 struct CopyPlan {
     int to, dst_off;
-    unsigned meta;
-    __device__ inline void load(const Dims &D, const Tables &W, int s, size_t pair0, int lane) {
-        to = -1; meta = 0; dst_off = 0;
+    unsigned meta, weight;
+    __device__ inline void load(const Dims &D, const Tables &W, int s, size_t pair0, int lane,
+                                const float *__restrict__ weights /* null: they do not travel */) {
+        to = -1; meta = 0; dst_off = 0; weight = 0;
         if (lane < D.K) {
             to = W.send_to[pair0 + lane];
             meta = W.pair_meta[pair0 + lane];
+            if (weights) weight = __float_as_uint(weights[pair0 + lane]);
         }
         if (lane < D.N) dst_off = W.dst_off[(size_t)s * D.N + lane];
     }
@@ -107,6 +109,35 @@ struct CopyPlan {
         *dst = d;
         const int shared = __shfl(dst_off, d);
         return to >= 0 ? recv_buffer_row(D.N, D.P, s, to & 0xFFFFFF, shared) : -1;
+    }
+    // Sidecars of the token's copies, behind the payload stores: K words that name, for every expert of the token on the
+    // copy's rank, the local expert and the token's rank among the source's tokens of that expert (and as many weights of
+    // those experts, for the expert rank's partial sum), then kNoEntry.  A lane per word, which finds its entry by looking
+    // through the experts' lanes; whole first wave.  row, dst: what target() gave this lane.  A lane per copy that
+    // read the others' entries from LDS and stored its words one by one, in front of the payload, made
+    // the workgroup of a token's first slice the slowest: us of a step, 32 ranks x 4 tokens of 14 KB 45.3 -> 44.3,
+    // 128: 454.6 -> 450.2, 16 ranks x 1024 tokens of 512 bytes 122 -> 110.
+    __device__ inline void write_sidecars(const Dims &D, const Tables &W, int row, int dst, int lane) const {
+        const int per_copy = (65536 + D.KM - 1) / D.KM;    // i / KM for i < K * KM <= 256 by a product: KM = 4, 8, 12, 16
+        for (int i0 = 0; i0 < D.K * D.KM; i0 += kWave) {
+            const int i = i0 + lane, copy = (i * per_copy) >> 16, m = i - copy * D.KM;
+            const int to_row = __shfl(row, copy & (kWave - 1)), d = __shfl(dst, copy & (kWave - 1));
+            unsigned entry = kNoEntry, w = 0;
+            int seen = 0;
+            for (int k = 0; k < D.K; ++k) {
+                const bool here = __builtin_amdgcn_readlane(dst, k) == d;
+                if (here && seen == m) {
+                    entry = (unsigned)__builtin_amdgcn_readlane(meta, k);
+                    w = (unsigned)__builtin_amdgcn_readlane(weight, k);
+                }
+                seen += here;
+            }
+            if (copy < D.K && to_row >= 0) {
+                unsigned *to_meta = W.recv_meta + ((size_t)d * D.recv_rows + to_row) * D.MW + m;
+                st_word((int *)to_meta, (int)entry);
+                if (D.MW > D.KM && entry != kNoEntry) st_word((int *)to_meta + D.KM, (int)w);
+            }
+        }
     }
 };
 
@@ -147,7 +178,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
         if (v0 + tid + i * kPackThreads < v1) r[i] = ld_stream(src + v0 + tid + i * kPackThreads);
     const size_t pair0 = ((size_t)s * D.T + t) * K;
     CopyPlan plan;
-    if (tid < kWave) plan.load(D, W, s, pair0, tid);
+    if (tid < kWave) plan.load(D, W, s, pair0, tid, D.MW > D.KM ? weights : nullptr);
     const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
     const int sent = done && tid < D.N ? W.M[(size_t)s * D.N + tid] : 0;
     // the sender's first block announces the transfers (a sender without tokens still announces
@@ -164,25 +195,12 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     }
     __shared__ int s_row[FL_MAX_TOPK];
     __shared__ int s_dst[FL_MAX_TOPK];
-    __shared__ unsigned s_meta[FL_MAX_TOPK];
     int target = -1, my_d = 0;                 // of this lane's copy: row in rank my_d's receive buffer
     if (tid < kWave) {
         target = plan.target(D, s, &my_d);
-        if (tid < K) { s_row[tid] = target; s_dst[tid] = my_d; s_meta[tid] = plan.meta; }
+        if (tid < K) { s_row[tid] = target; s_dst[tid] = my_d; }
     }
     __syncthreads();
-    if (slice == 0 && tid < K && target >= 0) {   // sidecar of this copy
-        unsigned *meta = W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW;
-        int m = 0;
-        for (int k = 0; k < K; ++k)
-            if (s_dst[k] == my_d) {
-                st_word((int *)meta + m, (int)s_meta[k]);
-                if (D.MW > D.KM)   // the weight of that expert, for the expert rank's partial sum
-                    st_word((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
-                ++m;
-            }
-        for (; m < D.KM; ++m) st_word((int *)meta + m, (int)kNoEntry);
-    }
     for (int b = v0 + tid; b < v1; b += 4 * kPackThreads) {
         if (b != v0 + tid) {                   // later batches (rows beyond 8 KB per slice)
 #pragma unroll
@@ -200,6 +218,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
                     st_payload<true>(dst + b + i * kPackThreads, r[i]);
         }
     }
+    if (slice == 0 && tid < kWave) plan.write_sidecars(D, W, target, my_d, tid);
     // Ready-made e4m3 codes (section Kernel Microbenchmarks: the dispatched token is 7168
     // fp8 values and 56 fp32 scaling factors): the scales follow the codes in the wire row.
     const bool with_scales = src_scales != nullptr && slice == 0;
@@ -308,7 +327,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     }
     const size_t pair0 = ((size_t)s * D.T + t) * K;
     CopyPlan plan;
-    if (tid < kWave) plan.load(D, W, s, pair0, tid);
+    if (tid < kWave) plan.load(D, W, s, pair0, tid, D.MW > D.KM ? weights : nullptr);
     const int plan_ok = W.plan_ok[s], tokens = num_tokens[s];
     const int sent = done && tid < D.N ? W.M[(size_t)s * D.N + tid] : 0;
     if ((FENCED || (D.flags & FL_FLAG_STREAM_ORDERED)) && blockIdx.x == 0 && plan_ok)   // as in dispatch_pack_kernel
@@ -323,25 +342,12 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     }
     __shared__ int s_row[FL_MAX_TOPK];
     __shared__ int s_dst[FL_MAX_TOPK];
-    __shared__ unsigned s_meta[FL_MAX_TOPK];
     int target = -1, my_d = 0;
     if (tid < kWave) {
         target = plan.target(D, s, &my_d);
-        if (tid < K) { s_row[tid] = target; s_dst[tid] = my_d; s_meta[tid] = plan.meta; }
+        if (tid < K) { s_row[tid] = target; s_dst[tid] = my_d; }
     }
     __syncthreads();
-    if (slice == 0 && tid < K && target >= 0) {
-        unsigned *meta = W.recv_meta + ((size_t)my_d * D.recv_rows + target) * D.MW;
-        int m = 0;
-        for (int k = 0; k < K; ++k)
-            if (s_dst[k] == my_d) {
-                st_word((int *)meta + m, (int)s_meta[k]);
-                if (D.MW > D.KM)   // the weight of that expert, for the expert rank's partial sum
-                    st_word((int *)meta + D.KM + m, __float_as_int(weights[pair0 + k]));
-                ++m;
-            }
-        for (; m < D.KM; ++m) st_word((int *)meta + m, (int)kNoEntry);
-    }
     float f[16];
     const unsigned w[8] = {in0.x, in0.y, in0.z, in0.w, in1.x, in1.y, in1.z, in1.w};
 #pragma unroll
@@ -388,6 +394,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
             st_word((int *)(dst + D.Be) + blk, __float_as_int(scale));
         }
     }
+    if (slice == 0 && tid < kWave) plan.write_sidecars(D, W, target, my_d, tid);
     if (FENCED) {
         // Units of the row this block wrote: 8 per quantisation block of codes, and the
         // 16-byte units its scales fall into (blocks start on multiples of 32 scales, so
