@@ -571,7 +571,7 @@ def main():
         }, steps=max(20, min(args.steps, 100)))
         interleaved = interleaved_caller_work(workloads, harness, torch)
         others = {}
-        for name, note in [("tiny", "launch-bound: nine kernels on a few KB"),
+        for name, note in [("tiny", "launch-bound: five kernels on a few KB"),
                            ("qwen3_skew", "cache-assisted: the working set partly fits the 256 MB last-level cache"),
                            ("dsv3_fp8", "e4m3 dispatch quantised on the fly, bf16 combine"),
                            ("dsv3_prefill", "4096 tokens per rank, payload calls cut into launches of 2 ranks")]:

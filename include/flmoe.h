@@ -117,7 +117,7 @@ extern "C" {
  *
  * FL_FLAG_STREAM_ORDERED: the caller promises that each send call precedes the matching
  * receive call in stream order (one stream, or events between streams).  The library
- * then launches no announce and no gate kernels (four launches fewer per step): the
+ * then launches no announce and no gate kernels (up to four launches fewer per step): the
  * first block of a sender's payload kernel advances the counters while other blocks may
  * still be storing, so here the counters are bookkeeping that only the
  * kernel boundary makes trustworthy - they are still checked (bounded) by the

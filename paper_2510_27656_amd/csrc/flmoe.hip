@@ -612,8 +612,8 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
     const Dims &D = ctx->D;
     const Tables &W = ctx->W;
     // fenced: every block reports what it delivered (progressive receivers).  Otherwise the send kernel's
-    // first block advances the counters (stream-ordered callers), or a kernel of its own does, behind
-    // the payload kernels in this (the sender's) stream.
+    // first block advances the counters (stream-ordered callers), its last one does (small calls), or a kernel
+    // of its own behind the payload kernels in this (the sender's) stream.
     const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;
     const char *xp = (const char *)x;
     bool self;
@@ -692,7 +692,7 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
     const bool waits = !chunks && waits_itself(D, (long long)gx * wpb, call, rc);
     // Default: a gate kernel of one wave per rank polls the rank's arrival counters, and the
     // unpack kernel runs behind it in the stream on a full grid.  Stream-ordered callers need
-    // no gate.
+    // no gate, and small launches wait themselves.
     const int *gate = nullptr;
     if (gated && !progressive && !waits) {
         if (call.first) {

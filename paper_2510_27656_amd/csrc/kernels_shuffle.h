@@ -33,10 +33,7 @@ constexpr int kMaxRowsPerBlock = 64;
 // transfer, like the single immediate a NIC delivers after a WRITE (section
 // TransferEngine, ImmCounter).  It is issued once per sender inside the send kernel:
 // receivers are ordered after that kernel by the stream, so they find counters and
-// payload complete together, and no extra launch is spent.  (Per-block announcements, as
-// in progressive mode, cost more than they give here: adds to one counter from many
-// compute dies serialise at about 0.2 us each, which made skewed routing several times
-// slower.)
+// payload complete together, and no extra launch is spent.
 // off = the sender's row of the segment table ([N + 1] row offsets by receiver);
 // threads first, first + step, ... each take one receiver.  only_the_ones: the
 // payload units are reported by the waves that deliver them (progressive mode).
@@ -152,8 +149,8 @@ struct CopyPlan {
 //
 // FENCED (progressive mode): device-scope stores, and the block adds the 16-byte
 // units it wrote to arrive[destination][source] itself once they are acknowledged;
-// stream-ordered, the sender's first block announces the whole transfers; otherwise
-// the announce kernel does.
+// stream-ordered, the sender's first block announces the whole transfers; otherwise its
+// last one does (done given) or the announce kernel.
 template <bool FENCED>
 __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     Dims D, Tables W, int rank_begin, const char *__restrict__ x, const int *__restrict__ num_tokens, int slices,
