@@ -255,14 +255,21 @@ __device__ inline v4u ld_coherent(const char *row, int vec) {
 __device__ inline void st_through(v4u *p, v4u v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
 }
+// The same with the streaming hint, for whole lines: what the unpack kernel hands the caller.  Neither dirty lines at
+// the end of the kernel nor lines kept for nobody.  us of a step, streaming stores -> this: 128 tokens of 14 KB 451.4 -> 448.4,
+// 32: 132.7 -> 131.8, 45 ready-made e4m3 tokens 145.2 -> 143.2, 2048: 7789 -> 7535; rows that end inside lines lose
+// (6672 bytes, 301 tokens 96.6 -> 101.3) and keep the streaming stores.
+__device__ inline void st_through_stream(v4u *p, v4u v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+}
 // Payload store into a peer's receive buffer: written through (THROUGH), so that the last-level cache may
 // hold the rows until the receive kernel reads them, or a streaming store.  us of a DeepSeek-V3 step with
 // ordinary stores in the send kernels -> written through: 4 tokens per rank 47.2 -> 46.2, 32: 136.8 -> 135.8,
 // 128: 465 -> 455, e4m3 128: 368 -> 362, 256: 990 -> 964; replies streamed instead: 128 487, 256 975 (larger
 // calls: replies_cached).  Dispatch rows never lose written through.  Of the kernels that write what the caller
 // reads, the reduce kernel writes through as well (128: 455 -> 452, 32: 135.8 -> 134.0, 16 ranks x 256 tokens of
-// 4 KB 123.4 -> 120.3, e4m3 512: 1523 -> 1478), the unpack kernel streams (written through, 128: 505, e4m3 393;
-// ordinary stores 490: the write-backs land on the kernel after).
+// 4 KB 123.4 -> 120.3, e4m3 512: 1523 -> 1478), the unpack kernel streams (written through without the streaming hint,
+// 128: 505, e4m3 393; ordinary stores 490: the write-backs land on the kernel after).
 template <bool THROUGH>
 __device__ inline void st_payload(v4u *p, v4u v) {
     if (THROUGH) st_through(p, v);

@@ -526,6 +526,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     // the same loop (the vectors after the code bytes go to expert_scales)
     const bool scales_as_vectors = D.scales_per_row > 0 && D.scales_per_row % 4 == 0;
     const int rowvec = nvec + (scales_as_vectors ? D.scales_per_row / 4 : 0);
+    const bool whole = D.Be % 128 == 0 && ((uintptr_t)expert_x & 127) == 0;    // expert rows are whole lines
     const int v0 = sub * kWave, step = G * kWave;          // the wave's first vectors of the row, distance to the next
     constexpr int U = 4;
     v4u val[U];
@@ -593,7 +594,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
 #pragma unroll
                 for (int i = 0; i < U; ++i) {
                     const int v = b + i * step;
-                    if (v < nvec) st_stream(dst + v, val[i]);
+                    if (v < nvec) { if (whole) st_through_stream(dst + v, val[i]); else st_stream(dst + v, val[i]); }
                     else if (v < rowvec)
                         st_stream((v4u *)(expert_scales + ((size_t)d * D.expert_cap + dr) * D.scales_per_row) + (v - nvec),
                                   val[i]);
