@@ -95,9 +95,10 @@ extern "C" {
  *     small kernel that adds each whole (sender, receiver) transfer to the receiver's
  *     counter with release semantics: it starts once the payload kernels have ended
  *     (the sender's own stream order, as a NIC posts the immediate after its WRITE),
- *     so the counter never runs ahead of the payload.  In a small step the last workgroup of a
- *     sender's payload kernel adds the transfers instead: payload is written through to memory,
- *     and a workgroup counts as done once its stores have been acknowledged.
+ *     so the counter never runs ahead of the payload.  In a small call whose payload is written
+ *     through to memory the last workgroup of a sender's payload kernel adds the transfers instead:
+ *     a workgroup counts as done once its stores have been acknowledged.  (Replies that are streamed
+ *     rather than written through always have the kernel behind them.)
  *   - A receive call first enqueues a gate kernel of one wave per rank that polls the
  *     rank's counters with acquire semantics until every source has delivered what
  *     the exchanged counts promised (bounded: FL_STATUS_TIMEOUT), and behind it the
@@ -400,7 +401,8 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
  *   knob 2 = accepted without effect (it shaped a copy kernel that is no longer launched)
  *   knob 3 = workgroups per token in the pack kernel (0 = chosen from the row size, at most 16)
  *   knob 4 = size in MiB of all ranks' replies above which combine_send uses streaming instead
- *            of write-through stores (default 1024; half of it when a call serves part of the ranks)
+ *            of write-through stores (default 1024; half of it when a call serves part of the ranks; a small
+ *            call for part of the ranks that announces itself, knob 10, always writes through)
  *   knob 5 = percentage of the rows uniform routing would bring to a rank that the grids of the
  *            receive-side and reply kernels are sized for (default: the mean plus six standard
  *            deviations; 0 = the whole capacity; a rank that holds more is served by the
@@ -436,7 +438,8 @@ typedef struct fl_moe_launch_plan {
     int32_t unpack_by_chunks;    /* 1: dispatch_recv moves rows by workgroups that plan a chunk of rows,
                                     0: by waves on their own                                        */
     int32_t replies_by_chunks;   /* the same of combine_send                                        */
-    int32_t replies_cached;      /* combine_send writes replies through the caches (0: streams them) */
+    int32_t replies_cached;      /* few enough replies in the whole group that combine_send writes them through
+                                    to memory (0: streams them, unless it announces them itself)    */
     int32_t layout_blocks;       /* counting blocks per source of the layout call ...               */
     int32_t layout_tiles;        /* ... and the tiles of tokens they share out, in equal runs       */
     int64_t recv_grid_rows;      /* received rows per rank that the grid of dispatch_recv is sized for  */
@@ -444,6 +447,18 @@ typedef struct fl_moe_launch_plan {
 } fl_moe_launch_plan;
 int fl_moe_debug_launch_plan(const fl_moe_config *cfg /*host*/, int rank_count,
                              fl_moe_launch_plan *out /*host*/);
+
+/* Diagnostic, host only (no GPU needed): how the send calls over `rank_count` ranks of this configuration order
+ * what they store and the counters, on a whole MI355X.  cached_mb as knob 4 above (-1 = the default).  Without a
+ * kernel behind it that announces, a payload kernel of the default mode announces its transfers itself, which it may
+ * only when it writes through. */
+typedef struct fl_moe_ordering_plan {
+    int32_t dispatch_announce_kernel;   /* 1: dispatch_send (not of ready-made e4m3 tokens) launches an announce kernel */
+    int32_t replies_written_through;    /* 1: combine_send writes replies through to memory (0: streams them)          */
+    int32_t combine_announce_kernel;    /* 1: combine_send launches an announce kernel                                */
+} fl_moe_ordering_plan;
+int fl_moe_debug_ordering_plan(const fl_moe_config *cfg /*host*/, int rank_count, int cached_mb,
+                               fl_moe_ordering_plan *out /*host*/);
 
 /* Diagnostic: plain linear device copy of `bytes` bytes with 16-byte accesses
  * (multiple of 16, both pointers 16-byte aligned), in the launch shape that measured

@@ -279,6 +279,22 @@ long long reply_grid_rows(const Dims &D) {       // rows a rank sends back: one 
     return D.flags & FL_FLAG_PARTIAL_SUMS ? recv_grid_rows(D) : grid_rows(D, D.expert_cap, D.typ_pair_rows);
 }
 
+// Workgroups per sender of the dispatch pack kernel; ready: the caller quantised the rows itself.
+int quant_threads(const Dims &D) { return D.scales_per_row > 256 / kQuantLanes ? 512 : 256; }
+int dispatch_slices(const Dims &D, bool ready) {
+    const int per_block = quant_threads(D) / kQuantLanes;            // quantisation blocks per workgroup
+    if (D.dtype == FL_DTYPE_E4M3_BLOCK128 && !ready) return (D.scales_per_row + per_block - 1) / per_block;
+    return pack_slices(ready ? D.Be : D.Bx, D.tune_slices);
+}
+long long dispatch_workgroups(const Dims &D, bool ready) { return (long long)D.T * dispatch_slices(D, ready); }
+
+// Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
+// to four vectors per lane.
+int waves_per_row(long long vecs) {
+    const long long w = (vecs + 4 * kWave - 1) / (4 * kWave);
+    return (int)(w > 16 ? 16 : w);
+}
+
 // Whether a combine_send call over `rank_count` ranks writes its replies through (st_payload) or streams them.  All
 // ranks' replies are written before the first reduce, whatever number of calls they come in, so the bytes of the
 // whole group decide; calls for part of the ranks gain nothing earlier already.  us of a step, rows of 14 KB,
@@ -302,6 +318,20 @@ bool announces_itself(const Dims &D, long long workgroups, int rank_count) {
     return !(D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED)) && workgroups * rank_count <= D.tune_self;
 }
 
+// The form of a combine_send call over `rank_count` ranks, one for all its launches (a group of its ranks has fewer
+// rows, so it takes waves where the call does).  A call announces itself only if it writes through, so a small one for part
+// of the ranks does both whatever the group's replies come to: us of a step rank by rank, 32 ranks, rows of 14 KB, streamed
+// and announced by a kernel against written through and announcing itself: 160 tokens 1306 and 1261, 256: 1680 and 1633, 448:
+// 2388 and 2363.  One call of that few workgroups but more replies than replies_cached allows (rows of megabytes) gains
+// nothing by it (4 ranks x 40 tokens of 2 MB 1512 and 1520).
+ReplyForm reply_form(const Dims &D, int cu_count, int rank_count) {
+    const bool cached = replies_cached(D, rank_count);
+    const long long workgroups = (reply_grid_rows(D) * waves_per_row(D.Bc / 16) * kWave + kCopyThreads - 1) / kCopyThreads;
+    if ((cached || rank_count < D.N) && announces_itself(D, workgroups, rank_count) && !replies_by_chunks(D, cu_count, rank_count))
+        return kRepliesThroughAnnounced;
+    return cached ? kRepliesThrough : kRepliesStreamed;
+}
+
 // The whole rank range of a call, and where in it the current launch group sits: the
 // gate kernel of a receive call runs once, before the first group, for all its ranks,
 // and the announce kernel of a send call once, behind the last group (a receiver needs
@@ -318,13 +348,6 @@ struct CallSpan {
 bool waits_itself(const Dims &D, long long waves, const CallSpan &call, int rank_count) {
     return !(D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED)) && rank_count == call.rank_count &&
            waves * rank_count <= D.tune_wait;
-}
-
-// Waves that share a row of `vecs` 16-byte vectors in the unpack and the combine pack kernel: up
-// to four vectors per lane.
-int waves_per_row(long long vecs) {
-    const long long w = (vecs + 4 * kWave - 1) / (4 * kWave);
-    return (int)(w > 16 ? 16 : w);
 }
 
 int rows_per_block(long long row_bytes, int tune_rows) {
@@ -616,26 +639,22 @@ static int dispatch_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, c
     // of its own behind the payload kernels in this (the sender's) stream.
     const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;
     const char *xp = (const char *)x;
-    bool self;
+    const int slices = dispatch_slices(D, ready_scales != nullptr);
+    const bool self = announces_itself(D, dispatch_workgroups(D, ready_scales != nullptr), call.rank_count);
     if (D.dtype == FL_DTYPE_E4M3_BLOCK128 && !ready_scales) {
         LaunchTimer t(ctx, KID_DISPATCH_PACK_E4M3, st);
         auto go = [&](auto threads) {
             constexpr int QT = decltype(threads)::value;
-            const int per_block = QT / kQuantLanes;              // quantisation blocks per workgroup
-            const int slices = (D.scales_per_row + per_block - 1) / per_block;
-            self = announces_itself(D, (long long)D.T * slices, call.rank_count);
             auto kernel = fenced ? dispatch_pack_e4m3_kernel<true, QT> : dispatch_pack_e4m3_kernel<false, QT>;
             kernel<<<dim3((unsigned)D.T * slices, rc), dim3(QT), 0, st>>>(D, W, rb, xp, ctx->num_tokens, slices, weights,
                                                                           self ? W.done_disp : nullptr);
         };
-        if (D.scales_per_row > 256 / kQuantLanes) go(std::integral_constant<int, 512>{});
+        if (quant_threads(D) == 512) go(std::integral_constant<int, 512>{});
         else go(std::integral_constant<int, 256>{});
     } else {
         LaunchTimer t(ctx, KID_DISPATCH_PACK, st);
         // bf16 rows, or e4m3 codes the caller quantised itself (their scales go along)
         const long long src_row = ready_scales ? D.Be : D.Bx;
-        const int slices = pack_slices(src_row, D.tune_slices);
-        self = announces_itself(D, (long long)D.T * slices, call.rank_count);
         auto kernel = fenced ? dispatch_pack_kernel<true> : dispatch_pack_kernel<false>;
         kernel<<<dim3((unsigned)D.T * slices, rc), dim3(kPackThreads), 0, st>>>(
             D, W, rb, xp, ctx->num_tokens, slices, weights, src_row, ready_scales, self ? W.done_disp : nullptr);
@@ -737,7 +756,7 @@ int fl_moe_dispatch_recv(fl_moe_ctx *ctx, int rb, int rc, void *expert_x, float 
     });
 }
 
-static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *expert_y, bool cached, bool self,
+static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, const void *expert_y, ReplyForm form,
                               void *stream) {
     int e = check_ranks(ctx, rb, rc);
     if (e != FL_OK) return e;
@@ -749,6 +768,7 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
     const int rbk = rows_per_block(D.Bc, D.tune_rows);
     const bool fenced = D.flags & FL_FLAG_PROGRESSIVE_RECV;      // as in dispatch_send_range
     const bool partial = D.flags & FL_FLAG_PARTIAL_SUMS;
+    const bool self = form == kRepliesThroughAnnounced;
     const long long reply_grid = reply_grid_rows(D);
     const unsigned gx = capped_grid((reply_grid + rbk - 1) / rbk, rc, kMaxRowBlocks);
     {
@@ -757,17 +777,22 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
         LaunchTimer t(ctx, partial ? KID_COMBINE_PARTIAL_PACK : KID_COMBINE_PACK, st);
         if (replies_by_chunks(D, ctx->cu_count, rc)) {
             auto kernel = fenced   ? partial ? combine_partial_pack_chunk_kernel<true, true> : combine_pack_chunk_kernel<true, true>
-                          : cached ? partial ? combine_partial_pack_chunk_kernel<false, true> : combine_pack_chunk_kernel<false, true>
-                                   : partial ? combine_partial_pack_chunk_kernel<false, false> : combine_pack_chunk_kernel<false, false>;
+                          : form == kRepliesStreamed
+                              ? partial ? combine_partial_pack_chunk_kernel<false, false> : combine_pack_chunk_kernel<false, false>
+                              : partial ? combine_partial_pack_chunk_kernel<false, true> : combine_pack_chunk_kernel<false, true>;
             kernel<<<grid, block, 0, st>>>(D, W, rb, yp, rbk);
         } else {
             const int G = waves_per_row(D.Bc / 16), wpb = kCopyThreads / kWave;
             const unsigned gw = capped_grid((reply_grid * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);
-            auto kernel = partial ? cached ? combine_partial_pack_kernel<true> : combine_partial_pack_kernel<false>
-                                  : cached ? combine_pack_kernel<true> : combine_pack_kernel<false>;
+            auto kernel = form == kRepliesStreamed
+                              ? partial ? combine_partial_pack_kernel<kRepliesStreamed> : combine_pack_kernel<kRepliesStreamed>
+                          : form == kRepliesThrough
+                              ? partial ? combine_partial_pack_kernel<kRepliesThrough> : combine_pack_kernel<kRepliesThrough>
+                              : partial ? combine_partial_pack_kernel<kRepliesThroughAnnounced>
+                                        : combine_pack_kernel<kRepliesThroughAnnounced>;
             // No need to hold workgroups back where partial sums read several rows per row written (see the kernel) or
             // in a small call, whose workgroups wait for their stores (4 tokens per rank, step 44.2 -> 43.1 us).
-            kernel<<<dim3(gw, rc), block, partial || self ? 0 : kRowWavesLdsBytes, st>>>(D, W, rb, yp, G, self ? W.done_comb : nullptr);
+            kernel<<<dim3(gw, rc), block, partial || self ? 0 : kRowWavesLdsBytes, st>>>(D, W, rb, yp, G);
         }
     }
     if (!self && !fenced && !(D.flags & FL_FLAG_STREAM_ORDERED) && call.last) {
@@ -780,13 +805,9 @@ static int combine_send_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, co
 
 int fl_moe_combine_send(fl_moe_ctx *ctx, int rb, int rc, const void *expert_y, void *stream) {
     if (!ctx) return FL_ERR_INVALID_ARG;
-    const Dims &D = ctx->D;
-    const bool cached = replies_cached(D, rc);
-    const long long workgroups = (reply_grid_rows(D) * waves_per_row(D.Bc / 16) * kWave + kCopyThreads - 1) / kCopyThreads;
-    // one answer for all launches of the call (a group of its ranks has fewer rows, so it takes waves where the call does)
-    const bool self = announces_itself(D, workgroups, rc) && !replies_by_chunks(D, ctx->cu_count, rc);
+    const ReplyForm form = reply_form(ctx->D, ctx->cu_count, rc);
     return for_rank_groups(ctx, rb, rc, [&](int r, int n, CallSpan call) {
-        return combine_send_range(ctx, r, n, call, expert_y, cached, self, stream);
+        return combine_send_range(ctx, r, n, call, expert_y, form, stream);
     });
 }
 
@@ -971,6 +992,21 @@ int fl_moe_debug_launch_plan(const fl_moe_config *cfg, int rank_count, fl_moe_la
     out->layout_tiles = (D.T + D.TT - 1) / D.TT;
     out->recv_grid_rows = recv_grid_rows(D);
     out->reply_grid_rows = reply_grid_rows(D);
+    return FL_OK;
+}
+
+int fl_moe_debug_ordering_plan(const fl_moe_config *cfg, int rank_count, int cached_mb, fl_moe_ordering_plan *out) {
+    if (!out || cached_mb < -1) return FL_ERR_INVALID_ARG;
+    Dims D;
+    int e = resolve(cfg, &D);
+    if (e != FL_OK) return e;
+    if (rank_count < 1 || rank_count > D.N) return FL_ERR_INVALID_ARG;
+    if (cached_mb >= 0) D.tune_cached_mb = cached_mb;
+    const bool own = D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED);    // modes without announce kernels
+    const ReplyForm form = reply_form(D, kComputeUnits, rank_count);
+    out->dispatch_announce_kernel = !own && !announces_itself(D, dispatch_workgroups(D, false), rank_count);
+    out->replies_written_through = (D.flags & FL_FLAG_PROGRESSIVE_RECV) || form != kRepliesStreamed;
+    out->combine_announce_kernel = !own && form != kRepliesThroughAnnounced;
     return FL_OK;
 }
 

@@ -793,6 +793,15 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
     }
 }
 
+// How a combine_send call stores its replies and who announces them: one choice (reply_form in flmoe.hip), because
+// a workgroup's acknowledged stores are in memory only when they are written through.  Streamed replies may still be
+// dirty in an L2 until their kernel ends, so only the announce kernel behind it can vouch for them.
+enum ReplyForm {
+    kRepliesStreamed,            // announced behind the kernel
+    kRepliesThrough,             // written through (st_payload), announced behind the kernel
+    kRepliesThroughAnnounced     // written through, and the sender's last workgroup announces them (announce_when_last)
+};
+
 // ------------------------------------------------------------------ combine: pack
 // Rank d sends every source s the rows of its experts that belong to s (contiguous
 // per expert in the grouped layout) as one contiguous reply, into s's combine receive
@@ -806,10 +815,9 @@ __global__ __launch_bounds__(kCopyThreads) void dispatch_unpack_chunk_kernel(
 // Bound by memory traffic from 32 tokens on (6.5 TB/s at 128 tokens, the plain copy's rate),
 // by the chain below.  Before -> now: 4 tokens 11.6 -> 11.0 us, 8: 15.9 -> 15.0, 32: 40.7 -> 39.5,
 // 128: 144.5 -> 144, 512: 649 -> 631 (672 with eight workgroups per unit).
-template <bool THROUGH>   // THROUGH: see st_payload
+template <int FORM>   // ReplyForm
 __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
-    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row,
-    unsigned *done /* as in dispatch_pack_kernel */) {
+    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El;
     const int lane = tid & (kWave - 1);
     const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -848,12 +856,12 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
                 if (b + u * step < nvec) val[u] = ld_stream(src + b + u * step);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
-                if (b + u * step < nvec) st_payload<THROUGH>(dst + b + u * step, val[u]);
+                if (b + u * step < nvec) st_payload<FORM != kRepliesStreamed>(dst + b + u * step, val[u]);
         }
     }
-    if (done) {
+    if (FORM == kRepliesThroughAnnounced) {
         const int next = __shfl_down(off, 1);
-        announce_when_last(done + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
+        announce_when_last(W.done_comb + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
                            d, N);
     }
 }
@@ -943,10 +951,9 @@ __device__ inline int sidecar_expert_row(const Dims &D, const Tables &W, int d, 
     return (int)min(row, (unsigned)D.expert_cap - 1u);
 }
 
-template <bool THROUGH>   // THROUGH: see st_payload
+template <int FORM>   // ReplyForm
 __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
-    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row,
-    unsigned *done /* as in dispatch_pack_kernel */) {
+    Dims D, Tables W, int rank_begin, const char *__restrict__ expert_y, int waves_per_row) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
     const int lane = tid & (kWave - 1);
     const int wave = blockIdx.x * (kCopyThreads / kWave) + __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -1001,13 +1008,13 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
                     v4u o;
                     o.x = pack_bf16x2(acc[u][0], acc[u][1]); o.y = pack_bf16x2(acc[u][2], acc[u][3]);
                     o.z = pack_bf16x2(acc[u][4], acc[u][5]); o.w = pack_bf16x2(acc[u][6], acc[u][7]);
-                    st_payload<THROUGH>((v4u *)dst + b + u * step, o);
+                    st_payload<FORM != kRepliesStreamed>((v4u *)dst + b + u * step, o);
                 }
         }
     }
-    if (done) {
+    if (FORM == kRepliesThroughAnnounced) {
         const int next = __shfl_down(off, 1);
-        announce_when_last(done + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
+        announce_when_last(W.done_comb + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
                            d, N);
     }
 }

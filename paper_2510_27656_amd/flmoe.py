@@ -72,6 +72,11 @@ class fl_moe_launch_plan(C.Structure):
                 ("recv_grid_rows", C.c_int64), ("reply_grid_rows", C.c_int64)]
 
 
+class fl_moe_ordering_plan(C.Structure):
+    _fields_ = [("dispatch_announce_kernel", C.c_int32), ("replies_written_through", C.c_int32),
+                ("combine_announce_kernel", C.c_int32)]
+
+
 EXPORTS = ["fl_moe_query_sizes", "fl_moe_create", "fl_moe_destroy", "fl_moe_layout",
            "fl_moe_layout_static",
            "fl_moe_dispatch_send", "fl_moe_dispatch_send_weighted", "fl_moe_dispatch_send_e4m3",
@@ -79,7 +84,7 @@ EXPORTS = ["fl_moe_query_sizes", "fl_moe_create", "fl_moe_destroy", "fl_moe_layo
            "fl_moe_combine_send",
            "fl_moe_combine_reduce", "fl_moe_status", "fl_moe_reset", "fl_moe_required_capacities",
            "fl_moe_strerror", "fl_moe_debug_views",
-           "fl_moe_debug_tune", "fl_moe_debug_launch_groups", "fl_moe_debug_launch_plan",
+           "fl_moe_debug_tune", "fl_moe_debug_launch_groups", "fl_moe_debug_launch_plan", "fl_moe_debug_ordering_plan",
            "fl_moe_debug_copy", "fl_moe_debug_fill", "fl_moe_debug_read", "fl_moe_profile_enable", "fl_moe_profile_collect", "fl_moe_profile_read",
            "fl_moe_kernel_name", "fl_moe_build_id"]
 
@@ -123,6 +128,7 @@ def lib():
         L.fl_moe_debug_tune.argtypes = [vp, i32, i32]
         L.fl_moe_debug_launch_groups.argtypes = [C.POINTER(fl_moe_config), i32, i32, C.POINTER(C.c_int)]
         L.fl_moe_debug_launch_plan.argtypes = [C.POINTER(fl_moe_config), i32, C.POINTER(fl_moe_launch_plan)]
+        L.fl_moe_debug_ordering_plan.argtypes = [C.POINTER(fl_moe_config), i32, i32, C.POINTER(fl_moe_ordering_plan)]
         L.fl_moe_debug_copy.argtypes = [vp, vp, C.c_size_t, vp]
         L.fl_moe_debug_fill.argtypes = [vp, C.c_size_t, vp]
         L.fl_moe_debug_read.argtypes = [vp, C.c_size_t, vp, vp]
@@ -276,6 +282,13 @@ def fl_moe_debug_launch_groups(cfg: fl_moe_config, rank_count: int, launch_mb: i
 def fl_moe_debug_launch_plan(cfg: fl_moe_config, rank_count: int) -> fl_moe_launch_plan:
     out = fl_moe_launch_plan()
     _check(lib().fl_moe_debug_launch_plan(C.byref(cfg), rank_count, C.byref(out)), "fl_moe_debug_launch_plan")
+    return out
+
+
+def fl_moe_debug_ordering_plan(cfg: fl_moe_config, rank_count: int, cached_mb: int = -1) -> fl_moe_ordering_plan:
+    out = fl_moe_ordering_plan()
+    _check(lib().fl_moe_debug_ordering_plan(C.byref(cfg), rank_count, cached_mb, C.byref(out)),
+           "fl_moe_debug_ordering_plan")
     return out
 
 

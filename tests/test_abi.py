@@ -199,6 +199,39 @@ def test_replies_are_cached_by_the_size_of_the_whole_group():
     assert not cached(512, 32) and not cached(512, 16) and not cached(512, 1)
 
 
+# ranks x tokens of 7168 values, top 8, one rank a call: 320 workgroups and many, replies of 35 MiB to 1.75 GiB
+@pytest.mark.parametrize("N,T", [(32, 128), (32, 147), (32, 160), (32, 256), (32, 465), (64, 128), (16, 320), (16, 400), (8, 700),
+                                 (4, 16), (32, 512)])
+@pytest.mark.parametrize("flags", [0, flmoe.FL_FLAG_PARTIAL_SUMS, flmoe.FL_FLAG_ZERO_PAD])
+def test_a_reply_kernel_that_streams_never_announces(N, T, flags):
+    """Streamed replies are in memory when their kernel ends, not when its workgroups have seen them acknowledged."""
+    for hidden in (7168, 64, 1 << 20):
+        c = cfg(n_ranks=N, n_experts=8 * N, max_tokens=T if hidden < 1 << 20 else 2, hidden=hidden, flags=flags)
+        for ranks in {1, 2, N // 2, N}:
+            for cached_mb in (-1, 0, 1, 64, 1 << 20):
+                plan = flmoe.fl_moe_debug_ordering_plan(c, ranks, cached_mb)
+                assert plan.replies_written_through or plan.combine_announce_kernel, (hidden, ranks, cached_mb)
+
+
+def test_which_calls_announce_with_a_kernel():
+    plan = lambda ranks=32, mb=-1, **kw: flmoe.fl_moe_debug_ordering_plan(cfg(**kw), ranks, mb)
+    small, large = plan(max_tokens=4), plan(max_tokens=128)
+    assert (small.dispatch_announce_kernel, small.replies_written_through, small.combine_announce_kernel) == (0, 1, 0)
+    assert (large.dispatch_announce_kernel, large.replies_written_through, large.combine_announce_kernel) == (1, 1, 1)
+    apart = plan(ranks=1, max_tokens=256)                   # few workgroups a call, 896 MiB of replies in the group
+    assert (apart.replies_written_through, apart.combine_announce_kernel) == (1, 0)
+    for streamed in (plan(ranks=1, max_tokens=512), plan(max_tokens=4, mb=0)):
+        assert (streamed.replies_written_through, streamed.combine_announce_kernel) == (0, 1)
+    for flag in (flmoe.FL_FLAG_STREAM_ORDERED, flmoe.FL_FLAG_PROGRESSIVE_RECV):
+        own = plan(max_tokens=512, flags=flag)
+        assert (own.dispatch_announce_kernel, own.combine_announce_kernel) == (0, 0)
+        assert own.replies_written_through == (flag == flmoe.FL_FLAG_PROGRESSIVE_RECV)
+    lib, out = flmoe.lib(), flmoe.fl_moe_ordering_plan()
+    for ranks, mb in ((0, -1), (33, -1), (32, -2)):
+        assert lib.fl_moe_debug_ordering_plan(C.byref(cfg()), ranks, mb, C.byref(out)) == flmoe.FL_ERR_INVALID_ARG
+    assert lib.fl_moe_debug_ordering_plan(C.byref(cfg()), 32, -1, None) == flmoe.FL_ERR_INVALID_ARG
+
+
 @pytest.mark.parametrize("N,El,T", [(64, 4, 4096), (32, 8, 8192), (32, 8, 2048), (1, 8, 1 << 20), (8, 16, 40000), (4, 4, 1),
                                     (64, 16, 3000)])
 def test_every_counting_block_of_the_layout_owns_a_tile(N, El, T):

@@ -266,6 +266,50 @@ def test_replies_past_the_caches(name, partial):
     sh.close()
 
 
+@pytest.mark.parametrize("kw", [dict(), dict(wait_waves=0), dict(wait_waves=1 << 20), dict(partial=True)],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("one_by_one", [False, True])
+def test_small_calls_past_the_streaming_limit_reach_receivers_on_another_stream(one_by_one, kw):
+    """Senders on one stream, receivers on another, calls small enough to announce themselves, the streaming limit so low
+    that all of them are past it: either written through, or announced by a kernel.  A reply that was announced before
+    it had left its L2 would show as the step before's."""
+    wl = wlmod.custom("streamed", 8, 64, 24, 7168, 8, seed=83, ragged=True)
+    inp = wlmod.make_inputs(wl)
+    N, partial = wl.n_ranks, kw.get("partial", False)
+    ref = oracle_step(inp, partial=partial)
+    want = ref.out_partial if partial else ref.out
+    dev = harness.to_device(inp)
+    sh = harness.make_shuffle(inp, partial_sums=partial)
+    ranks = 1 if one_by_one else N
+    assert flmoe.fl_moe_debug_ordering_plan(sh.cfg, ranks).combine_announce_kernel == 0
+    plan = flmoe.fl_moe_debug_ordering_plan(sh.cfg, ranks, 0)
+    assert (plan.replies_written_through, plan.combine_announce_kernel) == ((1, 0) if one_by_one else (0, 1))
+    flmoe.fl_moe_debug_tune(sh.ctx, 4, 0)
+    if "wait_waves" in kw:
+        flmoe.fl_moe_debug_tune(sh.ctx, 11, kw["wait_waves"])
+    streams = (torch.cuda.Stream(), torch.cuda.Stream())
+    rng = np.random.default_rng(83)
+    gains = [dev["gain"], dev["gain"] * 2]                  # a factor of two: only the replies' exponents change
+    try:
+        for step in range(30):
+            dev["gain"] = gains[step % 2]
+            sh.out.view(torch.int16).fill_(POISON)
+            order = [(int(r), 1) for r in rng.permutation(N)] if one_by_one else None
+            flmoe.fl_moe_profile_enable(sh.ctx, step == 0)
+            out = harness.run_step_two_streams(sh, dev, send_order=order, streams=streams)
+            torch.cuda.synchronize()
+            if step == 0:
+                flmoe.fl_moe_profile_collect(sh.ctx)
+                assert flmoe.fl_moe_profile_read(sh.ctx)["announce_kernel(combine)"][1] == plan.combine_announce_kernel
+            assert sh.status() == 0
+            got = bits((out.float() / (1 + step % 2)).to(torch.bfloat16))
+            for s in range(N):
+                n = inp.num_tokens[s]
+                assert (got[s, :n] == want[s, :n]).all(), (step, s)
+    finally:
+        sh.close()
+
+
 # (ranks, experts, tokens, hidden, top-k, dtype): fewer workgroups per sender than partial counts, as many, one more,
 # many; several slices per token
 @pytest.mark.parametrize("self_blocks", [0, 1 << 30])
