@@ -148,13 +148,14 @@ __device__ inline bool arrived(unsigned have, unsigned want) { return (int)(have
 // its expectation (wrap-safe comparison; `expect` is either one value for all or,
 // with expect_arr, one per counter).  Returns true when all n counters arrived,
 // false when the poll budget ran out.  Every lane of the wave must call it.
-// SLEEP: pause between polls in units of 64 clocks.  Payload waits may last as long
-// as a copy kernel and must not crowd out the senders they wait for (about 2 us);
-// the route exchange inside the layout kernel is a few microseconds long (short pause).
-template <int SLEEP = 64>
+// Polls are 64 * 64 clocks apart (with the load about 1.8 us): a wait may last as long as a copy kernel and must not
+// crowd out the senders it waits for.  QUICK polls before those, not counted, are a quarter as far apart: a small
+// receive launch is mostly there a few microseconds before its senders are done.
+template <int QUICK = 0>
 __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *expect_arr,
                                           unsigned expect, int n, long long spin_limit) {
     const int lane = threadIdx.x & (kWave - 1);
+    int quick = QUICK;
     for (int base = 0; base < n; base += kWave) {
         const int i = base + lane;
         long long spins = 0;
@@ -163,8 +164,13 @@ __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *e
             bool ok = true;
             if (i < n) ok = arrived(ld_relaxed(ctr + i), expect);
             if (__all(ok)) break;
+            if (quick > 0) {
+                --quick;
+                __builtin_amdgcn_s_sleep(16);
+                continue;
+            }
             if (++spins > spin_limit) return false;
-            __builtin_amdgcn_s_sleep(SLEEP);
+            __builtin_amdgcn_s_sleep(64);
         }
     }
     return true;

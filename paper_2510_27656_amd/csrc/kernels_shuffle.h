@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     }
     if (!plan_ok || !gate_ok) return;               // step skipped, or the arrival wait timed out (already latched)
     if (WAIT && !__all(lane >= N || arrived(have, want)) &&
-        !wave_wait_counters<16>(W.arrive_disp + (size_t)d * N, W.expect_disp + (size_t)d * N, 0u, N, D.spin_limit)) {
+        !wave_wait_counters<64>(W.arrive_disp + (size_t)d * N, W.expect_disp + (size_t)d * N, 0u, N, D.spin_limit)) {
         if (lane == 0) latch_status(W.status, FL_STATUS_TIMEOUT);
         return;
     }

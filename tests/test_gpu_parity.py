@@ -5,6 +5,8 @@ Bars: bit-exact for counts, offsets, positions and dispatched rows; combined
 output within 1 bf16 step of the oracle (fp32 fused multiply-add in k order on
 both sides, so bit-equality is expected and its fraction is reported).
 """
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -1581,6 +1583,36 @@ def test_withheld_arrival_counter_times_out_then_recovers(kw):
         for r in range(inp.wl.n_ranks):
             n = inp.num_tokens[r]
             assert (bits(out)[r, :n] == ref.out[r, :n]).all()
+    finally:
+        sh.close()
+
+
+@pytest.mark.parametrize("wait_waves", [0, 1 << 20])
+def test_receive_calls_wait_as_long_as_the_spin_limit_says(wait_waves):
+    """Behind a gate kernel or by themselves: polls are about 2 us apart, so 300 000 of them outlast senders that are
+    0.35 s late (at 0.6 us a poll a wait ends after 0.19 s)."""
+    inp = wlmod.make_inputs(wlmod.custom("late", 4, 32, 16, 520, 4, seed=5))
+    dev, ref = harness.to_device(inp), oracle_step(inp)
+    sh = harness.make_shuffle(inp, spin_limit=300000)
+    flmoe.fl_moe_debug_tune(sh.ctx, 11, wait_waves)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    try:
+        sh.layout(dev["indices"], dev["num_tokens"])
+        torch.cuda.synchronize()
+        sh.dispatch_recv(stream=a)
+        time.sleep(0.35)
+        sh.dispatch_send(dev["x"], stream=b)
+        torch.cuda.synchronize()
+        assert sh.status() == 0
+        y = harness.expert_stage(sh, dev["gain"])
+        torch.cuda.synchronize()
+        sh.combine_reduce(dev["weights"], stream=a)
+        time.sleep(0.35)
+        sh.combine_send(y, stream=b)
+        torch.cuda.synchronize()
+        assert sh.status() == 0
+        for r in range(4):
+            assert (bits(sh.out)[r] == ref.out[r]).all()
     finally:
         sh.close()
 
