@@ -558,6 +558,9 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
         if (lane == 0) latch_status(W.status, FL_STATUS_TIMEOUT);
         return;
     }
+    // the counters are read by relaxed loads: nothing else keeps the compiler from moving the rows' loads in front of them
+    // (no cache needs to be invalidated, the rows are read at device scope)
+    if (WAIT) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
     unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
     for (; r < total; r += row_step) {              // capacities are upper bounds: the grid may be smaller than the rows
