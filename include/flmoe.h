@@ -44,10 +44,13 @@
  *   - A context is not thread-safe: its calls come from one host thread at a
  *     time.  Several contexts (each with its own workspace) are independent.
  *   - Return value: FL_OK or a negative FL_ERR_* for errors the host can see
- *     (nothing is enqueued then).  Errors found on the device (bad expert id,
- *     capacity overflow, arrival time-out) make the affected step a no-op on every
- *     rank and latch a bit that fl_moe_status reports; they never cause an
- *     out-of-bounds access or an unbounded wait.
+ *     (nothing is enqueued then).  Errors found on the device latch a bit that
+ *     fl_moe_status reports; they never cause an out-of-bounds access or an unbounded
+ *     wait.  A bad expert id or a capacity overflow makes the step a no-op on every
+ *     rank.  A receive call whose arrival wait ends (FL_STATUS_TIMEOUT) writes nothing
+ *     for the rank that waited in vain; with FL_FLAG_STREAM_ORDERED or
+ *     FL_FLAG_PROGRESSIVE_RECV, whose workgroups wait one by one, it may have written
+ *     a part.
  */
 #ifndef FLMOE_H
 #define FLMOE_H

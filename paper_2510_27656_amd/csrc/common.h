@@ -61,7 +61,8 @@ struct Tables {
     // counts it was sent, so a receiver waits for arrive >= expect per source.
     unsigned *arrive_disp, *arrive_comb;                      // [N dst][N src]
     unsigned *expect_disp, *expect_comb;                      // [N dst][N src]
-    unsigned *done_disp, *done_comb;  // [N][kDoneWords] workgroups of a sender's kernel that have ended (announce_when_last)
+    unsigned *done_disp, *done_comb;  // [N][kDoneWords] workgroups of a sender's kernel that have ended (announce_when_last);
+                                      // behind them [N] verdicts of receive launches that wait themselves (verdict_of)
     unsigned long long *routes;   // [N receiver][N source][route_len], in words that carry their step's number
     // written by the source side of the layout step
     int *C;               // [N][E]
@@ -149,13 +150,10 @@ __device__ inline bool arrived(unsigned have, unsigned want) { return (int)(have
 // with expect_arr, one per counter).  Returns true when all n counters arrived,
 // false when the poll budget ran out.  Every lane of the wave must call it.
 // Polls are 64 * 64 clocks apart (with the load about 1.8 us): a wait may last as long as a copy kernel and must not
-// crowd out the senders it waits for.  QUICK polls before those, not counted, are a quarter as far apart: a small
-// receive launch is mostly there a few microseconds before its senders are done.
-template <int QUICK = 0>
+// crowd out the senders it waits for.
 __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *expect_arr,
                                           unsigned expect, int n, long long spin_limit) {
     const int lane = threadIdx.x & (kWave - 1);
-    int quick = QUICK;
     for (int base = 0; base < n; base += kWave) {
         const int i = base + lane;
         long long spins = 0;
@@ -164,16 +162,88 @@ __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *e
             bool ok = true;
             if (i < n) ok = arrived(ld_relaxed(ctr + i), expect);
             if (__all(ok)) break;
-            if (quick > 0) {
-                --quick;
-                __builtin_amdgcn_s_sleep(16);
-                continue;
-            }
             if (++spins > spin_limit) return false;
             __builtin_amdgcn_s_sleep(64);
         }
     }
     return true;
+}
+
+// The same wait by many waves of one launch which must all come to one verdict, so that a delivery at the very end of
+// the wait does not leave part of a rank's output written: every wave may go ahead, or none.
+// One wave of the launch decides.  When its polls are used up it writes `closing` into *word, waits until the store is in
+// memory, looks once more, and writes what it found.  Every other wave reads the word after it has seen the counters
+// arrive.  If it reads no `closing`, its look at the counters came before the deciding wave's last one, which
+// therefore sees them arrived as well: it may go ahead.  Otherwise it waits for what the deciding wave finds.
+// So a launch whose senders come in time writes nothing here, and a wave's verdict costs one more load, which need
+// not have returned before the wave's first store (verdict_read, verdict_allows).
+// ticket: names this launch in the word, so that nothing has to be cleared.
+typedef unsigned long long verdict_word;
+constexpr unsigned kVerdictClosing = 1, kVerdictCame = 2, kVerdictGaveUp = 3;
+__device__ inline verdict_word launch_ticket(unsigned step, unsigned launch) {
+    return (verdict_word)step << 32 | (verdict_word)(launch & 0x3FFFFFFFu) << 2;
+}
+// of rank r; done: done_disp, done_comb.  (Two more pointers in Tables took the kernels' arguments past 768 bytes and
+// 0.1 us a launch: 8 ranks one by one 196.2 -> 199.3 us a step.)
+__host__ __device__ inline size_t done_words(int N) { return (size_t)N * kDoneWords + 2 * (size_t)N; }
+__device__ inline verdict_word *verdict_of(unsigned *done, int N, int r) {
+    return (verdict_word *)(done + (size_t)N * kDoneWords) + r;
+}
+__device__ inline verdict_word verdict_read(const verdict_word *word) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");      // after the counters
+    return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// w: the word as read after the counters had arrived.  Whether the wave may go ahead; the deciding wave is between its
+// two stores where this has to wait (bounded all the same).
+__device__ inline bool verdict_allows(const verdict_word *word, verdict_word ticket, verdict_word w) {
+    for (int polls = 0; w == (ticket | kVerdictClosing) && polls < 65536; ++polls) {
+        __builtin_amdgcn_s_sleep(16);
+        w = verdict_read(word);
+    }
+    return w != (ticket | kVerdictClosing) && w != (ticket | kVerdictGaveUp);
+}
+// The wait of a wave whose first look at the counters (have, lane = counter) did not find them all arrived.
+// A wave that finds no verdict in four times the polls gives up by itself: only if the deciding wave, in the rank's first
+// workgroup, never ran.  The first 64 polls are a quarter as far apart and are not counted: a small receive launch is
+// mostly there a few microseconds before its senders are done.  n <= 64; whole wave.
+__device__ inline bool wave_wait_together(const unsigned *ctr, unsigned have, unsigned want, int n, long long spin_limit,
+                                          verdict_word *word, verdict_word ticket, bool decides, int *status) {
+    const int lane = threadIdx.x & (kWave - 1);
+    auto came = [&]() { return __all(lane >= n || arrived(have, want)) != 0; };
+    auto look = [&]() { if (lane < n) have = ld_relaxed(ctr + lane); };
+    auto write = [&](unsigned verdict) {
+        if (lane == 0) __hip_atomic_store(word, ticket | verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stores_done();
+    };
+    long long spins = 0;
+    for (int quick = 64; !came();) {
+        if (spins > spin_limit) {
+            if (decides) {
+                write(kVerdictClosing);
+                look();
+                const bool late = came();
+                write(late ? kVerdictCame : kVerdictGaveUp);
+                if (!late && lane == 0) latch_status(status, FL_STATUS_TIMEOUT);
+                return late;
+            }
+            const verdict_word w = verdict_read(word);
+            if (w == (ticket | kVerdictCame)) return true;
+            if (w == (ticket | kVerdictGaveUp)) return false;
+            if ((spins - 1024) >> 2 > spin_limit) {
+                if (lane == 0) latch_status(status, FL_STATUS_TIMEOUT);
+                return false;
+            }
+        }
+        if (quick > 0) {
+            --quick;
+            __builtin_amdgcn_s_sleep(16);
+        } else {
+            ++spins;
+            __builtin_amdgcn_s_sleep(64);
+        }
+        look();
+    }
+    return decides || verdict_allows(word, ticket, verdict_read(word));
 }
 
 // ---------------------------------------------------------------- scans / search

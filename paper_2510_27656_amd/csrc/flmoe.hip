@@ -175,8 +175,8 @@ size_t carve(const Dims &D, void *base, Tables *W, size_t *total) {
     W->arrive_comb = c.take<unsigned>(N * N);
     W->expect_disp = c.take<unsigned>(N * N);
     W->expect_comb = c.take<unsigned>(N * N);
-    W->done_disp = c.take<unsigned>(N * kDoneWords);
-    W->done_comb = c.take<unsigned>(N * kDoneWords);
+    W->done_disp = c.take<unsigned>(done_words(D.N));
+    W->done_comb = c.take<unsigned>(done_words(D.N));
     W->plan_ok = c.take<int>(N);
     W->gate_disp = c.take<int>(N);
     W->gate_comb = c.take<int>(N);
@@ -366,6 +366,7 @@ struct fl_moe_ctx {
     size_t workspace_bytes;
     const int32_t *indices = nullptr;
     const int32_t *num_tokens = nullptr;
+    unsigned recv_launches = 0;   // names a receive launch that waits itself (launch_ticket)
     int cu_count = kComputeUnits;
     int launch_mb = kLaunchMiB;   // payload a launch should move per direction, see ranks_per_launch
     // profiling
@@ -744,7 +745,7 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
                             : D.P ? dispatch_unpack_kernel<true, false> : dispatch_unpack_kernel<false, false>;
         // a launch that waits holds as little as it can
         kernel<<<dim3(gx, rc), dim3(kCopyThreads), waits ? 0 : kRowWavesLdsBytes, st>>>(D, ctx->W, rb, ex, expert_scales,
-                                                                                      tokens_per_expert, G, gate);
+                                                                                      tokens_per_expert, G, ++ctx->recv_launches, gate);
     }
     return launch_status();
 }
@@ -849,14 +850,15 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
     }
     LaunchTimer t(ctx, KID_COMBINE_REDUCE, st);
     const bool fenced = progressive || waits;
+    const unsigned launch = ++ctx->recv_launches;
     if (fenced && partial)
-        combine_reduce_kernel<true, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+        combine_reduce_kernel<true, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
     else if (fenced)
-        combine_reduce_kernel<true, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+        combine_reduce_kernel<true, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
     else if (partial)
-        combine_reduce_kernel<false, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+        combine_reduce_kernel<false, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
     else
-        combine_reduce_kernel<false, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts);
+        combine_reduce_kernel<false, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
     return launch_status();
 }
 

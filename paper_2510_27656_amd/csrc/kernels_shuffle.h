@@ -509,11 +509,12 @@ constexpr int kRowWavesLdsBytes = 32 << 10;
 //
 // WAIT (small launches in the default mode): no gate kernel ran; every wave waits (bounded) until all of the rank's
 // sources have delivered, and reads rows and sidecars at device scope, because the launch may have been running when
-// they landed.  Which launches: waits_itself in flmoe.hip.
+// they landed; all waves of a rank reach one verdict (wave_wait_together).  Which launches: waits_itself in flmoe.hip.
 template <bool PRIVATE, bool WAIT>   // PRIVATE: the receive buffer has private slots (P > 0): a row's place depends on its source
 __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     Dims D, Tables W, int rank_begin, char *__restrict__ expert_x,
     float *__restrict__ expert_scales, int *__restrict__ tokens_per_expert, int waves_per_row,
+    unsigned launch /* WAIT: number of this launch */,
     const int *__restrict__ gate /* [N] or null: a gate kernel's verdict, 0 = its wait gave up */) {
     const int d = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, El = D.El, K = D.K;
     const int lane = tid & (kWave - 1);
@@ -547,22 +548,36 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     const int total = W.recv_off[(size_t)d * (N + 1) + N];
     const int off = lane < N ? W.recv_off[(size_t)d * (N + 1) + lane] : 0x7fffffff;
     const int shared_off = PRIVATE && lane < N ? W.recv_shared_off[(size_t)d * N + lane] : 0;
+    const unsigned step_no = WAIT ? W.epoch_route[d] : 0u;
     unsigned want = 0, have = 0;
     if (!gate && lane < N) {
         want = W.expect_disp[(size_t)d * N + lane];
         have = ld_relaxed(W.arrive_disp + (size_t)d * N + lane);
     }
     if (!plan_ok || !gate_ok) return;               // step skipped, or the arrival wait timed out (already latched)
-    if (WAIT && !__all(lane >= N || arrived(have, want)) &&
-        !wave_wait_counters<64>(W.arrive_disp + (size_t)d * N, W.expect_disp + (size_t)d * N, 0u, N, D.spin_limit)) {
-        if (lane == 0) latch_status(W.status, FL_STATUS_TIMEOUT);
-        return;
+    // The counters are read by relaxed loads: the fence in verdict_read also keeps the compiler from moving the rows' loads in
+    // front of them (no cache needs to be invalidated, the rows are read at device scope).
+    const verdict_word ticket = WAIT ? launch_ticket(step_no, launch) : 0;
+    verdict_word verdict = 0;
+    bool go = !WAIT;                                // whether this wave may store
+    if (WAIT) {
+        if (__all(lane >= N || arrived(have, want))) {
+            verdict = verdict_read(verdict_of(W.done_disp, N, d));         // on its way while the first row is loaded
+        } else {
+            if (!wave_wait_together(W.arrive_disp + (size_t)d * N, have, want, N, D.spin_limit, verdict_of(W.done_disp, N, d), ticket,
+                                    wave == 0, W.status))
+                return;
+            go = true;
+        }
     }
-    // the counters are read by relaxed loads: nothing else keeps the compiler from moving the rows' loads in front of them
-    // (no cache needs to be invalidated, the rows are read at device scope)
-    if (WAIT) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    auto may_store = [&]() {
+        if (!WAIT || go) return true;
+        asm volatile("" : "+v"(verdict));           // looked at here and not where it is read
+        go = verdict_allows(verdict_of(W.done_disp, N, d), ticket, verdict);
+        return go;
+    };
     char *xd = expert_x + (size_t)d * D.expert_cap * D.Be;
-    unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
+    if (!WAIT) unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
     for (; r < total; r += row_step) {              // capacities are upper bounds: the grid may be smaller than the rows
         const int s = __popcll(__ballot(off <= r)) - 1;
         const int in_source = r - __builtin_amdgcn_readlane(off, s);
@@ -583,6 +598,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
         }
         load_batch(phys, v0 + lane);
         load_meta(phys);
+        if (!may_store()) return;
         // copies of this row: entries come first in the sidecar
         const int n = __popcll(__ballot(m != kNoEntry));
         int place = 0;
@@ -617,6 +633,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
             }
         }
     }
+    if (WAIT && may_store()) unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
 }
 
 // Short rows, and every row in progressive mode: a block takes a chunk of received rows at a time,
@@ -1180,7 +1197,8 @@ template <bool FENCED, bool PARTIAL>
 __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     Dims D, Tables W, int rank_begin, const float *__restrict__ weights, char *__restrict__ out,
     const int *__restrict__ num_tokens, const int *__restrict__ gate /* as in dispatch_unpack_kernel */,
-    int parts /* workgroups that share one token, each taking a slice of the row */) {
+    int parts /* workgroups that share one token, each taking a slice of the row */,
+    unsigned launch /* number of this launch where it waits in the default mode */) {
     const int s = rank_begin + blockIdx.y, tid = threadIdx.x, N = D.N, K = D.K;
     const int t0 = blockIdx.x / parts, part = blockIdx.x - t0 * parts, t_step = gridDim.x / parts;
     // two sets of positions and weights: while the block sums one token, wave 1 already
@@ -1193,6 +1211,13 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     // every load the block needs before its rows go out in ONE round: the verdicts, the token
     // count and (wave 1) the first token's positions and weights, which exist for every t < T
     const int plan_ok = W.plan_ok[s], gate_ok = gate ? gate[s] : 1, Ts = num_tokens[s];
+    const bool alone = FENCED && !(D.flags & FL_FLAG_PROGRESSIVE_RECV);      // waits in place of a gate kernel
+    const unsigned *ctr = W.arrive_comb + (size_t)s * N;
+    unsigned step_no = 0, have = 0, want = 0;
+    if (alone) {
+        step_no = W.epoch_route[s];
+        if (tid < N) { want = W.expect_comb[(size_t)s * N + tid]; have = ld_relaxed(ctr + tid); }
+    }
     const bool fetcher = tid >= kWave && tid < 2 * kWave;     // wave 1
     const int k = tid - kWave;
     int pf_pos = -1;
@@ -1222,14 +1247,16 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     };
     if (fetcher) fetch(t0);
     // in the default mode a rank without tokens waits for its (empty) replies all the same
-    const bool waiter = FENCED && blockIdx.x == 0 && !(D.flags & FL_FLAG_PROGRESSIVE_RECV);
-    if (!plan_ok || !gate_ok || (t0 >= Ts && !waiter)) return;
+    if (!plan_ok || !gate_ok || (t0 >= Ts && !(alone && blockIdx.x == 0))) return;
     if (tid == 0) timed_out = 0;               // wave 0 itself is the only one that may raise it
     if (fetcher) publish(0);
     // behind a gate kernel the counters were already seen complete, for every source of this rank
     if (!gate && tid < kWave) {
-        if (!wave_wait_counters(W.arrive_comb + (size_t)s * N, W.expect_comb + (size_t)s * N, 0u, N,
-                                D.spin_limit)) {
+        if (alone) {                           // one verdict for all of the rank's workgroups
+            if (!wave_wait_together(ctr, have, want, N, D.spin_limit, verdict_of(W.done_comb, N, s), launch_ticket(step_no, launch),
+                                    blockIdx.x == 0, W.status) && tid == 0)
+                timed_out = 1;
+        } else if (!wave_wait_counters(ctr, W.expect_comb + (size_t)s * N, 0u, N, D.spin_limit)) {
             if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
         }
         acquire_payload<FENCED>();

@@ -1587,6 +1587,18 @@ def test_withheld_arrival_counter_times_out_then_recovers(kw):
         sh.close()
 
 
+def sleep_cycles_per_second():
+    begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)
+    begin.record()
+    torch.cuda._sleep(1_000_000)
+    end.record()
+    torch.cuda.synchronize()
+    return 1e9 / begin.elapsed_time(end)
+
+
+# In both tests what the receivers wait for is enqueued first: on a hardware queue that the two streams share, the
+# receivers then start late and find everything there.
 @pytest.mark.parametrize("wait_waves", [0, 1 << 20])
 def test_receive_calls_wait_as_long_as_the_spin_limit_says(wait_waves):
     """Behind a gate kernel or by themselves: polls are about 2 us apart, so 300 000 of them outlast senders that are
@@ -1596,23 +1608,89 @@ def test_receive_calls_wait_as_long_as_the_spin_limit_says(wait_waves):
     sh = harness.make_shuffle(inp, spin_limit=300000)
     flmoe.fl_moe_debug_tune(sh.ctx, 11, wait_waves)
     a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    late = int(0.35 * sleep_cycles_per_second())
     try:
         sh.layout(dev["indices"], dev["num_tokens"])
         torch.cuda.synchronize()
-        sh.dispatch_recv(stream=a)
-        time.sleep(0.35)
+        with torch.cuda.stream(b):
+            torch.cuda._sleep(late)
         sh.dispatch_send(dev["x"], stream=b)
+        sh.dispatch_recv(stream=a)
         torch.cuda.synchronize()
         assert sh.status() == 0
         y = harness.expert_stage(sh, dev["gain"])
         torch.cuda.synchronize()
-        sh.combine_reduce(dev["weights"], stream=a)
-        time.sleep(0.35)
+        with torch.cuda.stream(b):
+            torch.cuda._sleep(late)
         sh.combine_send(y, stream=b)
+        sh.combine_reduce(dev["weights"], stream=a)
         torch.cuda.synchronize()
         assert sh.status() == 0
         for r in range(4):
             assert (bits(sh.out)[r] == ref.out[r]).all()
+    finally:
+        sh.close()
+
+
+@pytest.mark.parametrize("call", ["dispatch_recv", "combine_reduce"])
+@pytest.mark.parametrize("wait_waves", [0, 1 << 20])
+def test_a_delivery_at_the_end_of_the_wait_counts_for_a_whole_rank_or_not_at_all(wait_waves, call):
+    """Behind a gate kernel or by themselves: one notification is withheld until about when the wait ends, many times
+    over around that moment.  The rank's output is then complete, or untouched and the time-out reported."""
+    wl = wlmod.custom("verdict", 4, 32, 300, 520, 4, seed=9)
+    inp = wlmod.make_inputs(wl)
+    dev, ref = harness.to_device(inp), oracle_step(inp, zero_pad=True)
+    sh = harness.make_shuffle(inp, zero_pad=True, spin_limit=500)
+    flmoe.fl_moe_debug_tune(sh.ctx, 11, wait_waves)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    dispatch = call == "dispatch_recv"
+    rng = np.random.default_rng(9)
+    rank, peer = 1, 2
+    per_second = sleep_cycles_per_second()
+    try:
+        sh.layout(dev["indices"], dev["num_tokens"])
+        sh.dispatch_send(dev["x"])
+        if not dispatch:
+            sh.dispatch_recv()
+            sh.combine_send(harness.expert_stage(sh, dev["gain"]))
+        torch.cuda.synchronize()
+        word = sh.debug()["arrive_disp" if dispatch else "arrive_comb"].view(torch.int32)[rank, peer:peer + 1]
+        want_x = torch.from_numpy(ref.expert_rows[rank].view(np.int16)).cuda()
+        want_out = torch.from_numpy(ref.out[rank].view(np.int16)).cuda()
+
+        def in_time(seconds):
+            sh.expert_x.view(torch.int16).fill_(POISON)
+            sh.out.view(torch.int16).fill_(POISON)
+            sh.tokens_per_expert.fill_(-1)
+            word.sub_(1)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(b):
+                torch.cuda._sleep(int(seconds * per_second))
+                word.add_(1)
+            if dispatch:
+                sh.dispatch_recv((rank, 1), stream=a)
+            else:
+                sh.combine_reduce(dev["weights"], (rank, 1), stream=a)
+            torch.cuda.synchronize()
+            if dispatch:
+                got = sh.expert_x[rank].view(torch.int16)
+                n = want_x.shape[0]
+                whole = bool((got[:n] == want_x).all()) and bool((sh.tokens_per_expert[rank] >= 0).all())
+                none = bool((got == POISON).all()) and bool((sh.tokens_per_expert[rank] == -1).all())
+            else:
+                got = sh.out[rank].view(torch.int16)
+                whole, none = bool((got == want_out).all()), bool((got == POISON).all())
+            status = sh.status()
+            assert (whole and status == 0) or (none and status == flmoe.FL_STATUS_TIMEOUT), (whole, none, status, seconds)
+            return whole
+
+        in_time(0.0)                                        # kernels are loaded by now
+        lo, hi = 0.0, 4e-3                                  # 500 polls last about 0.9 ms
+        for _ in range(10):                                 # halve towards the moment, then stay around it
+            mid = (lo + hi) / 2
+            lo, hi = (mid, hi) if in_time(mid) else (lo, mid)
+        seen = [in_time(max(0.0, lo + rng.uniform(-40e-6, 40e-6))) for _ in range(150)]
+        print(f"{call}: turn at {lo * 1e3:.2f} ms, {sum(seen)} of {len(seen)} in time")
     finally:
         sh.close()
 
