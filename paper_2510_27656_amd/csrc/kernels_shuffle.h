@@ -50,25 +50,24 @@ __device__ inline void announce_transfers(const int *off, unsigned *arrive, unsi
 // sidecars are written through, so it is in memory then, where every XCD sees it) and counts itself; the one that
 // completes the count adds to the receivers' counters.  Adds to one word take 12 ns each, so a
 // workgroup counts on one of kDoneParts words, whose last one counts on the word for all; who completes a word clears
-// it for the next call.  done: the sender's words; number: this workgroup's, of `workgroups`; lane p < N of the first
-// wave holds the rows for receiver p.  Where the line to an announce kernel lies: announces_itself in flmoe.hip.
+// it for the next call.  done: the sender's words; number: this workgroup's, of `workgroups`; rows: lane p < N of the
+// first wave holds those for receiver p.  Where the line to an announce kernel lies: announces_itself in flmoe.hip.
 __device__ inline void announce_when_last(unsigned *done, unsigned number, unsigned workgroups, unsigned *arrive, int rows,
-                                          unsigned units_per_row, int sender, int N) {
+                                          unsigned units_per_row, int sender, int N, int lane, bool first_wave) {
     stores_done();
     __syncthreads();
-    if (threadIdx.x >= kWave) return;
+    if (!first_wave) return;
     auto completes = [&](unsigned *word, unsigned all) {
         unsigned before = 0;
-        if (threadIdx.x == 0) before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (__builtin_amdgcn_readfirstlane(before) + 1 != all) return false;
-        if (threadIdx.x == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return true;
     };
     const unsigned part = number % kDoneParts;
     if (!completes(done + part * kDoneLine, (workgroups - part + kDoneParts - 1) / kDoneParts)) return;
     if (!completes(done + kDoneParts * kDoneLine, min(workgroups, (unsigned)kDoneParts))) return;
-    const int p = threadIdx.x;
-    if (p < N) add_counter(arrive + (size_t)p * N + sender, (unsigned)rows * units_per_row + 1u);
+    if (lane < N) add_counter(arrive + (size_t)lane * N + sender, (unsigned)rows * units_per_row + 1u);
 }
 
 // Test switch (knob 8): the order in which a send kernel takes its `n` units of work.  Nothing may
@@ -187,7 +186,8 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
     const unsigned workgroups = (unsigned)(tokens * slices);   // of this sender that have a token
     if (t >= tokens) {
         if (done && tokens == 0 && blockIdx.x == 0)            // none has: one announces the empty transfers
-            announce_when_last(done + s * kDoneWords, 0u, 1u, W.arrive_disp, sent, (unsigned)(D.Bw / 16), s, D.N);
+            announce_when_last(done + s * kDoneWords, 0u, 1u, W.arrive_disp, sent, (unsigned)(D.Bw / 16), s, D.N, tid & (kWave - 1),
+                               tid < kWave);
         return;
     }
     __shared__ int s_row[FL_MAX_TOPK];
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kPackThreads) void dispatch_pack_kernel(
             add_counter(W.arrive_disp + (size_t)my_d * D.N + s, units);
     } else if (done) {
         announce_when_last(done + s * kDoneWords, (unsigned)(t * slices + slice), workgroups, W.arrive_disp, sent,
-                           (unsigned)(D.Bw / 16), s, D.N);
+                           (unsigned)(D.Bw / 16), s, D.N, tid & (kWave - 1), tid < kWave);
     }
 }
 
@@ -334,7 +334,8 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
     const unsigned workgroups = (unsigned)(tokens * slices);   // of this sender that have a token
     if (t >= tokens) {
         if (done && tokens == 0 && blockIdx.x == 0)            // none has: one announces the empty transfers
-            announce_when_last(done + s * kDoneWords, 0u, 1u, W.arrive_disp, sent, (unsigned)(D.Bw / 16), s, D.N);
+            announce_when_last(done + s * kDoneWords, 0u, 1u, W.arrive_disp, sent, (unsigned)(D.Bw / 16), s, D.N, tid & (kWave - 1),
+                               tid < kWave);
         return;
     }
     __shared__ int s_row[FL_MAX_TOPK];
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(QT) void dispatch_pack_e4m3_kernel(
                         (unsigned)(n_live * 8 + (n_live + 3) / 4 + (slice == 0 ? pad_units : 0)));
     } else if (done) {
         announce_when_last(done + s * kDoneWords, (unsigned)(t * slices + slice), workgroups, W.arrive_disp, sent,
-                           (unsigned)(D.Bw / 16), s, D.N);
+                           (unsigned)(D.Bw / 16), s, D.N, tid & (kWave - 1), tid < kWave);
     }
 }
 
@@ -880,9 +881,9 @@ __global__ __launch_bounds__(kCopyThreads, 8) void combine_pack_kernel(
         }
     }
     if (FORM == kRepliesThroughAnnounced) {
-        const int next = __shfl_down(off, 1);
-        announce_when_last(W.done_comb + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
-                           d, N);
+        const int *rows = W.cs_off + (size_t)d * (N + 1) + lane;
+        announce_when_last(W.done_comb + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, lane < N ? rows[1] - rows[0] : 0,
+                           (unsigned)nvec, d, N, lane, wave % (kCopyThreads / kWave) == 0);
     }
 }
 
@@ -961,7 +962,9 @@ __device__ inline void fma8(float *acc, float wk, v4u y) {
 // same five per unit as the plain copy takes measured 30 us where all eight take 26 (6.7 KB rows).
 // Against a workgroup that planned its rows in LDS: 301 tokens x 8 ranks, 6.7 KB rows 30.6 -> 26.1 us;
 // 14 KB rows, 32 ranks: 8 tokens 20.4 -> 16.1, 128: 147 -> 136, 512: 641 -> 627.  The launch bound keeps
-// it at 72 registers; one more and only six workgroups fit a unit: 2 KB rows, step 277 -> 286 us.
+// it at 72 registers; one more and only six workgroups fit a unit: 2 KB rows, step 277 -> 286 us.  So nothing that announcing
+// needs is held over the row loop, and calls that do not announce themselves carry none of it: with both in every variant
+// three registers were spilled; us of a step without: 8 tokens of 14 KB 58.6 -> 57.7, 301 of 6.7 KB 92.5 -> 91.7, 128: 445 -> 442.
 //
 // A sidecar is what a sender stored, and behind an arrival wait that gave up (the caller's calls are all
 // enqueued by then) it holds whatever was there before: the expert row it names is kept inside expert_y.
@@ -1032,10 +1035,10 @@ __global__ __launch_bounds__(kCopyThreads, 7) void combine_partial_pack_kernel(
                 }
         }
     }
-    if (FORM == kRepliesThroughAnnounced) {
-        const int next = __shfl_down(off, 1);
-        announce_when_last(W.done_comb + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, (lane + 1 < N ? next : total) - off, (unsigned)nvec,
-                           d, N);
+    if (FORM == kRepliesThroughAnnounced) {        // the offsets again, not held over the loop
+        const int *rows = W.recv_off + (size_t)d * (N + 1) + lane;
+        announce_when_last(W.done_comb + d * kDoneWords, blockIdx.x, gridDim.x, W.arrive_comb, lane < N ? rows[1] - rows[0] : 0,
+                           (unsigned)nvec, d, N, lane, wave % (kCopyThreads / kWave) == 0);
     }
 }
 

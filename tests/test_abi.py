@@ -280,6 +280,22 @@ def test_host_only_queries_work_on_a_torch_without_gpu_functions():
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=100)
 
 
+def test_no_kernel_spills_registers():
+    """The compiler's resource report of the sources: scratch memory in a row loop costs more than any register saved."""
+    from paper_2510_27656_amd import build
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("no compiler here")
+    report = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                             "-packed-fp32-ops", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", "-o",
+                             os.devnull] + [os.path.join(build.CSRC, f) for f in build.SOURCES],
+                            check=True, capture_output=True, text=True, timeout=300).stderr
+    names = re.findall(r"Function Name: (\S+)", report)
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", report)]
+    assert len(names) == len(scratch) >= 30
+    assert not [n for n, v in zip(names, scratch) if v]
+
+
 def test_loaded_library_was_built_from_the_sources_in_the_tree():
     from paper_2510_27656_amd import build
     assert flmoe.fl_moe_build_id() == build.source_hash() and len(build.source_hash()) == 16
