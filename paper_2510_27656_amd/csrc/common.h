@@ -328,15 +328,19 @@ __device__ inline v4u ld_coherent(const char *row, int vec) {
 // has been acknowledged.  No dirty line is left for the end of the kernel, which otherwise waits until the
 // L2s have written theirs back (32 ranks x 4 tokens: 3.9 us from the pack kernel's last store to the next
 // kernel's first instruction, 1.5 behind a kernel without dirty lines).
+// The hardware reads the data of a 128-bit store a little after it has issued: a vector instruction may overwrite those
+// registers two wait states later at the earliest.  The compiler sees to that behind its own stores, not behind inline
+// assembly, hence the s_nop.  (Buffer stores, which take the same cache bits as a builtin, need one base for the whole wave;
+// here every lane may store into another rank's buffer.)
 __device__ inline void st_through(v4u *p, v4u v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 // The same with the streaming hint, for whole lines: what the unpack kernel hands the caller.  Neither dirty lines at
 // the end of the kernel nor lines kept for nobody.  us of a step, streaming stores -> this: 128 tokens of 14 KB 451.4 -> 448.4,
 // 32: 132.7 -> 131.8, 45 ready-made e4m3 tokens 145.2 -> 143.2, 2048: 7789 -> 7535; rows that end inside lines lose
 // (6672 bytes, 301 tokens 96.6 -> 101.3) and keep the streaming stores.
 __device__ inline void st_through_stream(v4u *p, v4u v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");      // as in st_through
 }
 // Payload store into a peer's receive buffer: written through (THROUGH), so that the last-level cache may
 // hold the rows until the receive kernel reads them, or a streaming store.  us of a DeepSeek-V3 step with

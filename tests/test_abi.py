@@ -280,20 +280,47 @@ def test_host_only_queries_work_on_a_torch_without_gpu_functions():
     subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=100)
 
 
-def test_no_kernel_spills_registers():
-    """The compiler's resource report of the sources: scratch memory in a row loop costs more than any register saved."""
+@pytest.fixture(scope="module")
+def compiled(tmp_path_factory):
+    """(the compiler's resource report, the assembly) of the kernels in the tree."""
     from paper_2510_27656_amd import build
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not os.path.exists(hipcc):
         pytest.skip("no compiler here")
+    out = str(tmp_path_factory.mktemp("asm") / "kernels.s")
     report = subprocess.run([hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
-                             "-packed-fp32-ops", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c", "-o",
-                             os.devnull] + [os.path.join(build.CSRC, f) for f in build.SOURCES],
+                             "-packed-fp32-ops", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-S", "-o",
+                             out] + [os.path.join(build.CSRC, f) for f in build.SOURCES],
                             check=True, capture_output=True, text=True, timeout=300).stderr
-    names = re.findall(r"Function Name: (\S+)", report)
-    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", report)]
+    return report, open(out).read()
+
+
+def test_no_kernel_spills_registers(compiled):
+    """Scratch memory in a row loop costs more than any register saved."""
+    names = re.findall(r"Function Name: (\S+)", compiled[0])
+    scratch = [int(v) for v in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", compiled[0])]
     assert len(names) == len(scratch) >= 30
     assert not [n for n, v in zip(names, scratch) if v]
+
+
+def test_nothing_overwrites_the_data_of_a_store_while_it_is_read(compiled):
+    """Two wait states between a 128-bit store and a vector instruction that writes its data registers; the compiler
+    keeps them only behind the stores that it makes itself."""
+    code = [line.split(";")[0].strip() for line in compiled[1].splitlines()]
+    code = [line for line in code if line and not line.startswith(".") or re.match(r"\.LBB\S*:$", line)]
+    stores = [i for i, line in enumerate(code) if re.match(r"global_store_dwordx4 .*\bsc1\b", line)]
+    assert len(stores) > 30
+    for i in stores:
+        first, last = map(int, re.search(r"\], v\[(\d+):(\d+)\]", code[i]).groups())
+        states = 0
+        for line in code[i + 1:]:
+            nop = re.match(r"s_nop (\d+)", line)
+            states += int(nop.group(1)) + 1 if nop else 0 if line.endswith(":") else 1
+            if states >= 2:
+                break
+            for lo, hi in re.findall(r"^v_\S+ v\[?(\d+):?(\d*)", line):
+                assert not (int(lo) <= last and int(hi or lo) >= first), (code[i], line)
+            assert not line.startswith("s_cbranch") and not line.startswith("s_branch"), (code[i], line)
 
 
 def test_loaded_library_was_built_from_the_sources_in_the_tree():
