@@ -1134,9 +1134,9 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
 
 // KT = number of row loads issued together (then consumed in k order); the sum
 // itself always runs k = 0..K-1.
-template <int KT>
+template <int KT, class MayFn>
 __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos, const float *w,
-                                  int K, long long stride, int v0, int nvec, v4u *__restrict__ out, int tid) {
+                                  int K, long long stride, int v0, int nvec, v4u *__restrict__ out, int tid, MayFn may_store) {
     for (int v = v0 + tid; v < nvec; v += (int)blockDim.x) {
         float acc[8];
 #pragma unroll
@@ -1155,15 +1155,17 @@ __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos,
         v4u o;
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
+        if (!may_store()) return;
         st_through(out + v, o);
     }
 }
 
 // The same sum for a row count only known on the device (partial sums: one row per
 // distinct expert rank of the token): batches of up to 8 loads, predicated.
+template <class MayFn>
 __device__ inline void reduce_row_counted(const char *__restrict__ recv, const int *pos,
                                           const float *w, int n, long long stride, int v0, int nvec,
-                                          v4u *__restrict__ out, int tid) {
+                                          v4u *__restrict__ out, int tid, MayFn may_store) {
     for (int v = v0 + tid; v < nvec; v += (int)blockDim.x) {
         float acc[8];
 #pragma unroll
@@ -1180,6 +1182,7 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
         v4u o;
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
+        if (!may_store()) return;
         st_through(out + v, o);
     }
 }
@@ -1216,9 +1219,12 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     const int plan_ok = W.plan_ok[s], gate_ok = gate ? gate[s] : 1, Ts = num_tokens[s];
     const bool alone = FENCED && !(D.flags & FL_FLAG_PROGRESSIVE_RECV);      // waits in place of a gate kernel
     const unsigned *ctr = W.arrive_comb + (size_t)s * N;
-    unsigned step_no = 0, have = 0, want = 0;
+    verdict_word *word = verdict_of(W.done_comb, N, s);
+    verdict_word ticket = 0;
+    unsigned have = 0, want = 0;
+    const int lane = tid & (kWave - 1);
     if (alone) {
-        step_no = W.epoch_route[s];
+        ticket = launch_ticket(W.epoch_route[s], launch);
         if (tid < N) { want = W.expect_comb[(size_t)s * N + tid]; have = ld_relaxed(ctr + tid); }
     }
     const bool fetcher = tid >= kWave && tid < 2 * kWave;     // wave 1
@@ -1256,8 +1262,8 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     // behind a gate kernel the counters were already seen complete, for every source of this rank
     if (!gate && tid < kWave) {
         if (alone) {                           // one verdict for all of the rank's workgroups
-            if (!wave_wait_together(ctr, have, want, N, D.spin_limit, verdict_of(W.done_comb, N, s), launch_ticket(step_no, launch),
-                                    blockIdx.x == 0, W.status) && tid == 0)
+            if (!__all(lane >= N || arrived(have, want)) &&
+                !wave_wait_together(ctr, have, want, N, D.spin_limit, word, ticket, blockIdx.x == 0, W.status) && tid == 0)
                 timed_out = 1;
         } else if (!wave_wait_counters(ctr, W.expect_comb + (size_t)s * N, 0u, N, D.spin_limit)) {
             if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
@@ -1266,6 +1272,14 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     }
     __syncthreads();
     if (timed_out) return;
+    verdict_word verdict = alone ? verdict_read(word) : 0;   // on its way while the rows are
+    bool go = !alone;
+    auto may_store = [&]() {
+        if (!FENCED || go) return true;
+        asm volatile("" : "+v"(verdict));      // looked at here and not where it is read
+        go = verdict_allows(word, ticket, verdict);
+        return go;
+    };
     const char *recv = W.bufA + (size_t)s * D.bufA_rank_bytes;
     const int nvec_row = (int)(D.Bc / 16);
     const int per = whole_lines((nvec_row + parts - 1) / parts);   // this block's slice: [v0, nvec)
@@ -1277,11 +1291,11 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         const int next = t + t_step;
         if (fetcher && next < Ts) fetch(next);                // in flight while the rows are summed
         v4u *o = (v4u *)(out + ((size_t)s * D.T + t) * D.Bc);
-        if (PARTIAL) reduce_row_counted(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid);
-        else if (kt >= 8) reduce_row<8>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
-        else if (kt >= 4) reduce_row<4>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
-        else if (kt >= 2) reduce_row<2>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
-        else reduce_row<1>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid);
+        if (PARTIAL) reduce_row_counted(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 8) reduce_row<8>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 4) reduce_row<4>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 2) reduce_row<2>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else reduce_row<1>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
         if (next >= Ts) break;
         if (fetcher) publish(cur ^ 1);
         __syncthreads();                       // the other set is complete; this one may be rewritten
