@@ -346,9 +346,10 @@ __device__ inline void st_through_stream(v4u *p, v4u v) {
 // hold the rows until the receive kernel reads them, or a streaming store.  us of a DeepSeek-V3 step with
 // ordinary stores in the send kernels -> written through: 4 tokens per rank 47.2 -> 46.2, 32: 136.8 -> 135.8,
 // 128: 465 -> 455, e4m3 128: 368 -> 362, 256: 990 -> 964; replies streamed instead: 128 487, 256 975 (larger
-// calls: replies_cached).  Dispatch rows never lose written through.  Of the kernels that write what the caller
-// reads, the reduce kernel writes through as well (128: 455 -> 452, 32: 135.8 -> 134.0, 16 ranks x 256 tokens of
-// 4 KB 123.4 -> 120.3, e4m3 512: 1523 -> 1478), the unpack kernel streams (written through without the streaming hint,
+// calls: replies_cached).  Dispatch rows never lose written through.  All of top 8.  Of the kernels that write what the
+// caller reads, the reduce kernel writes through as well (128: 455 -> 452, 32: 135.8 -> 134.0, 16 ranks x 256 tokens of
+// 4 KB 123.4 -> 120.3, e4m3 512: 1523 -> 1478), with the streaming hint where one or two rows make up a sum (see there);
+// the unpack kernel writes whole lines through with the hint and streams other rows (written through without the hint,
 // 128: 505, e4m3 393; ordinary stores 490: the write-backs land on the kernel after).
 template <bool THROUGH>
 __device__ inline void st_payload(v4u *p, v4u v) {

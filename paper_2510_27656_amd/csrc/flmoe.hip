@@ -308,6 +308,11 @@ bool replies_cached(const Dims &D, int rank_count) {
     return (long long)D.N * D.T * D.K * D.Bc <= (rank_count < D.N ? limit / 2 : limit);
 }
 
+// Whether the reduce kernel writes its output with the streaming hint: one or two rows per sum and the group's output larger
+// than this (both sides at the kernel).
+constexpr long long kStreamedOutputBytes = 40ll << 20;
+bool output_streamed(const Dims &D) { return D.K <= 2 && (long long)D.N * D.T * D.Bc > kStreamedOutputBytes; }
+
 // Whether the send kernels of a call, of `workgroups` per sender, announce their transfers themselves
 // (announce_when_last) rather than having a kernel launched behind them: while they all fit on the machine at once
 // (4096 workgroups of two waves), waiting for their own stores keeps no others out.  us of a step, with announce kernels
@@ -851,14 +856,15 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
     LaunchTimer t(ctx, KID_COMBINE_REDUCE, st);
     const bool fenced = progressive || waits;
     const unsigned launch = ++ctx->recv_launches;
-    if (fenced && partial)
-        combine_reduce_kernel<true, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
-    else if (fenced)
-        combine_reduce_kernel<true, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
-    else if (partial)
-        combine_reduce_kernel<false, true><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
-    else
-        combine_reduce_kernel<false, false><<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
+    auto go = [&](auto fence, auto shares) {
+        constexpr bool F = decltype(fence)::value, P = decltype(shares)::value;
+        auto kernel = output_streamed(D) ? combine_reduce_kernel<F, P, true> : combine_reduce_kernel<F, P, false>;
+        kernel<<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (fenced) partial ? go(yes, yes) : go(yes, no);
+    else partial ? go(no, yes) : go(no, no);
     return launch_status();
 }
 

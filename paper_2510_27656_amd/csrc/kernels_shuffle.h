@@ -1132,9 +1132,17 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
 //   out[s][t] = bf16( sum_k w[k] * float(row comb_pos[s][t][k]) ), fp32 fused
 // multiply-add, k ascending, one final rounding.
 
+// With one or two rows per sum the output is a third of the traffic or more: where it is large it is written through with
+// the streaming hint, so that lines nobody reads again do not push out rows that are.  us of a step of 32 ranks, 14 KB rows,
+// without the hint and with it: top 1: 48 tokens (22 MB of output) 66.0 and 66.5, 80: 88.5 and 88.5, 112: 112.3 and 111.8, 144:
+// 137.6 and 133.6, 256: 226 and 217 (ordinary streaming stores 218), 1024: 851 and 833; top 2: 80 tokens 112.5 and 112.3, 112: 147.5
+// and 145.3, 208: 259 and 245, 1024: 1238 and 1226; 16 ranks, 4 KB rows, 33 MB top 2 95.6 and 96.7, 84 MB 212 and 196.
+// More rows per sum gain nothing (top 3, 256 tokens 416 and 418; top 8, 128: 449 and 451).
+// (A choice inside the kernel cost what it gained.  Rule: output_streamed in flmoe.hip.)
+
 // KT = number of row loads issued together (then consumed in k order); the sum
 // itself always runs k = 0..K-1.
-template <int KT, class MayFn>
+template <int KT, bool STREAMED, class MayFn>
 __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos, const float *w,
                                   int K, long long stride, int v0, int nvec, v4u *__restrict__ out, int tid, MayFn may_store) {
     for (int v = v0 + tid; v < nvec; v += (int)blockDim.x) {
@@ -1156,13 +1164,13 @@ __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos,
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
         if (!may_store()) return;
-        st_through(out + v, o);
+        if (STREAMED) st_through_stream(out + v, o); else st_through(out + v, o);
     }
 }
 
 // The same sum for a row count only known on the device (partial sums: one row per
 // distinct expert rank of the token): batches of up to 8 loads, predicated.
-template <class MayFn>
+template <bool STREAMED, class MayFn>
 __device__ inline void reduce_row_counted(const char *__restrict__ recv, const int *pos,
                                           const float *w, int n, long long stride, int v0, int nvec,
                                           v4u *__restrict__ out, int tid, MayFn may_store) {
@@ -1183,7 +1191,7 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
         if (!may_store()) return;
-        st_through(out + v, o);
+        if (STREAMED) st_through_stream(out + v, o); else st_through(out + v, o);
     }
 }
 
@@ -1199,7 +1207,7 @@ constexpr int kReduceMaxThreads = 1024;
 // distinct expert ranks, found through send_to[s][t][k] for every k that is the first
 // of its rank; they are added in that order in fp32 (a fused multiply-add with
 // weight 1 is an exact add), the weights having been applied on the expert ranks.
-template <bool FENCED, bool PARTIAL>
+template <bool FENCED, bool PARTIAL, bool STREAMED>
 __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     Dims D, Tables W, int rank_begin, const float *__restrict__ weights, char *__restrict__ out,
     const int *__restrict__ num_tokens, const int *__restrict__ gate /* as in dispatch_unpack_kernel */,
@@ -1291,11 +1299,11 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         const int next = t + t_step;
         if (fetcher && next < Ts) fetch(next);                // in flight while the rows are summed
         v4u *o = (v4u *)(out + ((size_t)s * D.T + t) * D.Bc);
-        if (PARTIAL) reduce_row_counted(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid, may_store);
-        else if (kt >= 8) reduce_row<8>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
-        else if (kt >= 4) reduce_row<4>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
-        else if (kt >= 2) reduce_row<2>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
-        else reduce_row<1>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        if (PARTIAL) reduce_row_counted<STREAMED>(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 8) reduce_row<8, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 4) reduce_row<4, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 2) reduce_row<2, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else reduce_row<1, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
         if (next >= Ts) break;
         if (fetcher) publish(cur ^ 1);
         __syncthreads();                       // the other set is complete; this one may be rewritten

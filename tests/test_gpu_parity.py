@@ -268,6 +268,18 @@ def test_replies_past_the_caches(name, partial):
     sh.close()
 
 
+# one or two rows per sum and more than 40 MiB of output, just not as much, and more rows per sum
+@pytest.mark.parametrize("kw", [dict(), dict(partial=True), dict(ordering="progressive"), dict(ranks_split=True, wait_waves=1 << 20)],
+                         ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
+@pytest.mark.parametrize("shape", [(2, 8, 1463, 7168, 1), (2, 8, 1462, 7168, 1), (4, 16, 1572, 3336, 2), (3, 9, 977, 7176, 2),
+                                   (4, 16, 800, 7168, 3)], ids=str)
+def test_large_output_of_few_rows_per_sum(shape, kw):
+    N, E, T, H, K = shape
+    wl = wlmod.custom("streamed_output", N, E, T, H, K, seed=T, ragged=T > 1500)
+    sh, _, _ = run_and_compare(wlmod.make_inputs(wl), **kw)
+    sh.close()
+
+
 @pytest.mark.parametrize("kw", [dict(), dict(wait_waves=0), dict(wait_waves=1 << 20), dict(partial=True)],
                          ids=lambda kw: "-".join(f"{k}={v}" for k, v in kw.items()) or "default")
 @pytest.mark.parametrize("one_by_one", [False, True])
