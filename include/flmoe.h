@@ -451,14 +451,16 @@ typedef struct fl_moe_launch_plan {
 int fl_moe_debug_launch_plan(const fl_moe_config *cfg /*host*/, int rank_count,
                              fl_moe_launch_plan *out /*host*/);
 
-/* Diagnostic, host only (no GPU needed): how the send calls over `rank_count` ranks of this configuration order
- * what they store and the counters, on a whole MI355X.  cached_mb as knob 4 above (-1 = the default).  Without a
+/* Diagnostic, host only (no GPU needed): how the calls over `rank_count` ranks of this configuration order
+ * payload and counters, on a whole MI355X.  cached_mb as knob 4 above (-1 = the default).  Without a
  * kernel behind it that announces, a payload kernel of the default mode announces its transfers itself, which it may
  * only when it writes through. */
 typedef struct fl_moe_ordering_plan {
     int32_t dispatch_announce_kernel;   /* 1: dispatch_send (not of ready-made e4m3 tokens) launches an announce kernel */
     int32_t replies_written_through;    /* 1: combine_send writes replies through to memory (0: streams them)          */
     int32_t combine_announce_kernel;    /* 1: combine_send launches an announce kernel                                */
+    int32_t dispatch_gate_kernel;       /* 1: dispatch_recv launches a gate kernel (0 in the default mode: it waits itself) */
+    int32_t combine_gate_kernel;        /* 1: combine_reduce does                                                     */
 } fl_moe_ordering_plan;
 int fl_moe_debug_ordering_plan(const fl_moe_config *cfg /*host*/, int rank_count, int cached_mb,
                                fl_moe_ordering_plan *out /*host*/);

@@ -355,6 +355,46 @@ bool waits_itself(const Dims &D, long long waves, const CallSpan &call, int rank
            waves * rank_count <= D.tune_wait;
 }
 
+// Workgroups per rank of a dispatch_recv launch whose waves work alone, `share` of them to a row.
+unsigned unpack_workgroups(const Dims &D, int rank_count, int *share) {
+    const int G = waves_per_row(D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0));
+    const int wpb = kCopyThreads / kWave;
+    unsigned gx = capped_grid((recv_grid_rows(D) * G + wpb - 1) / wpb, rank_count, kMaxRowBlocks, G);
+    if (gx < (unsigned)D.El) gx = (unsigned)((D.El + G - 1) / G * G);    // the first El-1 blocks also clear padding rows
+    *share = G;
+    return gx;
+}
+bool unpack_waits(const Dims &D, int cu_count, const CallSpan &call, int rank_count) {
+    int share;
+    return !unpack_by_chunks(D, cu_count, rank_count) &&
+           waits_itself(D, (long long)unpack_workgroups(D, rank_count, &share) * (kCopyThreads / kWave), call, rank_count);
+}
+
+// A combine_reduce launch: `parts` workgroups of `threads` share a token, each taking a slice of the row; `groups` such sets
+// per rank walk the tokens.
+struct ReduceShape {
+    int parts, threads;
+    unsigned groups;
+    long long waves() const { return (long long)groups * parts * (threads / kWave); }
+};
+ReduceShape reduce_shape(const Dims &D, int cu_count, int rank_count) {
+    const bool progressive = D.flags & FL_FLAG_PROGRESSIVE_RECV;
+    const int nvec = (int)(D.Bc / 16);
+    // measured: long rows are summed fastest by many small workgroups, one payload wave each
+    // (7168-wide rows: 14 workgroups of 2 waves 86 us, 2 of 7 waves 90 us, 1 of 14 waves 92 us);
+    // rows of 4 KB and less gain nothing; capped polling grids keep one workgroup per token
+    int parts = D.tune_parts > 0 ? D.tune_parts : (nvec >= 512 && !progressive ? (nvec + kWave - 1) / kWave : 1);
+    if (parts > nvec) parts = nvec;
+    const int per = whole_lines((nvec + parts - 1) / parts);
+    int nt = (per + kWave - 1) / kWave * kWave;
+    if (nt > kReduceMaxThreads) nt = kReduceMaxThreads;
+    if (nt < 2 * kWave) nt = 2 * kWave;      // wave 0 waits, wave 1 fetches positions and weights
+    // progressive (polling) receivers take at most three eighths of the machine's wave slots
+    const unsigned gx = progressive ? capped_grid(D.T, rank_count, (long long)cu_count * 256 * D.tune_cap8 / nt / parts)
+                                    : (unsigned)D.T;
+    return {parts, nt, gx};
+}
+
 int rows_per_block(long long row_bytes, int tune_rows) {
     long long rb = tune_rows > 0 ? tune_rows : 16384 / row_bytes;
     if (rb < 1) rb = 1;
@@ -708,13 +748,8 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
     hipStream_t st = (hipStream_t)stream;
     const bool gated = !(D.flags & FL_FLAG_STREAM_ORDERED);
     const bool progressive = D.flags & FL_FLAG_PROGRESSIVE_RECV;
-    const long long rows = recv_grid_rows(D);
     const bool chunks = unpack_by_chunks(D, ctx->cu_count, rc);
-    const int G = waves_per_row(D.Be / 16 + (D.scales_per_row % 4 == 0 ? D.scales_per_row / 4 : 0));
-    const int wpb = kCopyThreads / kWave;
-    unsigned gx = capped_grid((rows * G + wpb - 1) / wpb, rc, kMaxRowBlocks, G);     // of the wave kernel
-    if (gx < (unsigned)D.El) gx = (unsigned)((D.El + G - 1) / G * G);    // the first El-1 blocks also clear padding rows
-    const bool waits = !chunks && waits_itself(D, (long long)gx * wpb, call, rc);
+    const bool waits = unpack_waits(D, ctx->cu_count, call, rc);
     // Default: a gate kernel of one wave per rank polls the rank's arrival counters, and the
     // unpack kernel runs behind it in the stream on a full grid.  Stream-ordered callers need
     // no gate, and small launches wait themselves.
@@ -739,13 +774,15 @@ static int dispatch_recv_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, v
             long long n = (32768 + D.Bw - 1) / D.Bw;
             rbk = (int)(n > kMaxRowsPerBlock ? kMaxRowsPerBlock : n);
         }
-        gx = capped_grid((rows + rbk - 1) / rbk, rc,
+        unsigned gx = capped_grid((recv_grid_rows(D) + rbk - 1) / rbk, rc,
                                   progressive ? (long long)ctx->cu_count * D.tune_cap8 : kMaxRowBlocks);
         if (gx < (unsigned)D.El) gx = D.El;      // the first El-1 blocks also clear padding rows
         auto kernel = progressive ? D.P ? dispatch_unpack_chunk_kernel<true, true> : dispatch_unpack_chunk_kernel<false, true>
                                   : D.P ? dispatch_unpack_chunk_kernel<true, false> : dispatch_unpack_chunk_kernel<false, false>;
         kernel<<<dim3(gx, rc), dim3(kCopyThreads), 0, st>>>(D, ctx->W, rb, ex, expert_scales, tokens_per_expert, rbk, gate);
     } else {
+        int G;
+        const unsigned gx = unpack_workgroups(D, rc, &G);
         auto kernel = waits ? D.P ? dispatch_unpack_kernel<true, true> : dispatch_unpack_kernel<false, true>
                             : D.P ? dispatch_unpack_kernel<true, false> : dispatch_unpack_kernel<false, false>;
         // a launch that waits holds as little as it can
@@ -827,23 +864,10 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
     const Dims &D = ctx->D;
     const bool gated = !(D.flags & FL_FLAG_STREAM_ORDERED), partial = D.flags & FL_FLAG_PARTIAL_SUMS;
     const bool progressive = D.flags & FL_FLAG_PROGRESSIVE_RECV;
-    // `parts` workgroups share a token, each taking a slice of the row
-    const int nvec = (int)(D.Bc / 16);
-    // measured: long rows are summed fastest by many small workgroups, one payload wave each
-    // (7168-wide rows: 14 workgroups of 2 waves 86 us, 2 of 7 waves 90 us, 1 of 14 waves 92 us);
-    // rows of 4 KB and less gain nothing; capped polling grids keep one workgroup per token
-    int parts = D.tune_parts > 0 ? D.tune_parts : (nvec >= 512 && !progressive ? (nvec + kWave - 1) / kWave : 1);
-    if (parts > nvec) parts = nvec;
-    const int per = whole_lines((nvec + parts - 1) / parts);
-    int nt = (per + kWave - 1) / kWave * kWave;
-    if (nt > kReduceMaxThreads) nt = kReduceMaxThreads;
-    if (nt < 2 * kWave) nt = 2 * kWave;      // wave 0 waits, wave 1 fetches positions and weights
-    // progressive (polling) receivers take at most three eighths of the machine's wave slots
-    const unsigned gx = progressive ? capped_grid(D.T, rc, (long long)ctx->cu_count * 256 * D.tune_cap8 / nt / parts)
-                                    : (unsigned)D.T;
-    const dim3 grid(gx * parts, rc);
+    const ReduceShape shape = reduce_shape(D, ctx->cu_count, rc);
+    const dim3 grid(shape.groups * shape.parts, rc);
     char *o = (char *)out;
-    const bool waits = waits_itself(D, (long long)gx * parts * (nt / kWave), call, rc);
+    const bool waits = waits_itself(D, shape.waves(), call, rc);
     const int *gate = nullptr;
     if (gated && !progressive && !waits) {         // as in dispatch_recv: a gate kernel, then the full grid
         if (call.first) {
@@ -859,7 +883,7 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
     auto go = [&](auto fence, auto shares) {
         constexpr bool F = decltype(fence)::value, P = decltype(shares)::value;
         auto kernel = output_streamed(D) ? combine_reduce_kernel<F, P, true> : combine_reduce_kernel<F, P, false>;
-        kernel<<<grid, dim3(nt), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, parts, launch);
+        kernel<<<grid, dim3(shape.threads), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, shape.parts, launch);
     };
     const std::true_type yes;
     const std::false_type no;
@@ -1015,6 +1039,10 @@ int fl_moe_debug_ordering_plan(const fl_moe_config *cfg, int rank_count, int cac
     out->dispatch_announce_kernel = !own && !announces_itself(D, dispatch_workgroups(D, false), rank_count);
     out->replies_written_through = (D.flags & FL_FLAG_PROGRESSIVE_RECV) || form != kRepliesStreamed;
     out->combine_announce_kernel = !own && form != kRepliesThroughAnnounced;
+    const CallSpan call{0, rank_count, true, true};
+    const int group = ranks_per_launch(D, kLaunchMiB, rank_count);
+    out->dispatch_gate_kernel = !own && !unpack_waits(D, kComputeUnits, call, group);
+    out->combine_gate_kernel = !own && !waits_itself(D, reduce_shape(D, kComputeUnits, group).waves(), call, group);
     return FL_OK;
 }
 

@@ -74,7 +74,8 @@ class fl_moe_launch_plan(C.Structure):
 
 class fl_moe_ordering_plan(C.Structure):
     _fields_ = [("dispatch_announce_kernel", C.c_int32), ("replies_written_through", C.c_int32),
-                ("combine_announce_kernel", C.c_int32)]
+                ("combine_announce_kernel", C.c_int32), ("dispatch_gate_kernel", C.c_int32),
+                ("combine_gate_kernel", C.c_int32)]
 
 
 EXPORTS = ["fl_moe_query_sizes", "fl_moe_create", "fl_moe_destroy", "fl_moe_layout",

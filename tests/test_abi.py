@@ -232,6 +232,18 @@ def test_which_calls_announce_with_a_kernel():
     assert lib.fl_moe_debug_ordering_plan(C.byref(cfg()), 32, -1, None) == flmoe.FL_ERR_INVALID_ARG
 
 
+def test_which_calls_wait_behind_a_gate_kernel():
+    """Receive launches of up to 1024 waves wait themselves: 32 ranks x 1 token of 14 waves each, not 2; 8 rows of a rank."""
+    gates = lambda ranks, **kw: (lambda p: (p.dispatch_gate_kernel, p.combine_gate_kernel))(
+        flmoe.fl_moe_debug_ordering_plan(cfg(**kw), ranks))
+    tiny = dict(n_ranks=2, n_experts=8, max_tokens=16, top_k=2, hidden=256)
+    assert gates(2, **tiny) == (0, 0) and gates(32, max_tokens=4) == (1, 1) and gates(1, max_tokens=4) == (0, 0)
+    assert gates(32, max_tokens=1)[1] == 0 and gates(32, max_tokens=2)[1] == 1
+    assert gates(1, max_tokens=4096) == (1, 1)
+    for flag in (flmoe.FL_FLAG_STREAM_ORDERED, flmoe.FL_FLAG_PROGRESSIVE_RECV):
+        assert gates(32, max_tokens=128, flags=flag) == (0, 0)
+
+
 @pytest.mark.parametrize("N,El,T", [(64, 4, 4096), (32, 8, 8192), (32, 8, 2048), (1, 8, 1 << 20), (8, 16, 40000), (4, 4, 1),
                                     (64, 16, 3000)])
 def test_every_counting_block_of_the_layout_owns_a_tile(N, El, T):
