@@ -232,13 +232,14 @@ typedef struct fl_moe_layout_view {
     const int32_t *plan_ok;           /* [N] 1 when the step is valid for the rank                     */
 } fl_moe_layout_view;
 
-/* Test/diagnostic view of internal buffers (layouts are the library's own). */
+/* Test/diagnostic view of internal buffers (layouts are the library's own; how far apart the rows of
+ * buf_a and buf_b lie is what fl_moe_debug_row_strides says, not their own bytes). */
 typedef struct fl_moe_debug_view {
     void *buf_a;              /* per rank: combine receive buffer                         */
     void *buf_b;              /* per rank: dispatch receive buffer                        */
     int64_t buf_a_rank_bytes;
     int64_t buf_b_rank_bytes;
-    uint32_t *arrive_route;   /* [N][N] route records received, [destination][source]      */
+    uint32_t *arrive_route;   /* [N][N] step of the last route record received, [destination][source] */
     uint32_t *epoch_route;    /* [N] number of layout calls of each rank                   */
     uint32_t *arrive_disp;    /* [N][N] monotone payload counters, [destination][source]:  */
     uint32_t *arrive_comb;    /*        16-byte units delivered, plus one per transfer     */
@@ -395,6 +396,12 @@ int fl_moe_reset(fl_moe_ctx *ctx, void *stream);
 const char *fl_moe_strerror(int code);
 
 int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out /*host*/);
+
+/* Diagnostic, host only (no GPU needed): bytes from row to row of the receive buffers of this configuration, of a dispatched
+ * row in buf_b and of a reply in buf_a.  At least wire_row_bytes and combine_row_bytes; more where rows are padded
+ * to whole 128-byte lines. */
+int fl_moe_debug_row_strides(const fl_moe_config *cfg /*host*/, int64_t *dispatch_bytes /*host*/,
+                             int64_t *combine_bytes /*host*/);
 
 /* Diagnostic: overrides a launch-shape knob of the row kernels (results never change; a
  * value of -1 restores a knob's default).

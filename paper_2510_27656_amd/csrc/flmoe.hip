@@ -980,6 +980,16 @@ int fl_moe_debug_views(fl_moe_ctx *ctx, fl_moe_debug_view *out) {
     return FL_OK;
 }
 
+int fl_moe_debug_row_strides(const fl_moe_config *cfg, int64_t *dispatch_bytes, int64_t *combine_bytes) {
+    if (!dispatch_bytes || !combine_bytes) return FL_ERR_INVALID_ARG;
+    Dims D;
+    int e = resolve(cfg, &D);
+    if (e != FL_OK) return e;
+    *dispatch_bytes = D.Sw;
+    *combine_bytes = D.Sc;
+    return FL_OK;
+}
+
 int fl_moe_debug_tune(fl_moe_ctx *ctx, int knob, int value) {
     if (!ctx || value < -1) return FL_ERR_INVALID_ARG;
     const bool dflt = value == -1;             // -1 = back to the default

@@ -84,7 +84,7 @@ EXPORTS = ["fl_moe_query_sizes", "fl_moe_create", "fl_moe_destroy", "fl_moe_layo
            "fl_moe_dispatch_recv",
            "fl_moe_combine_send",
            "fl_moe_combine_reduce", "fl_moe_status", "fl_moe_reset", "fl_moe_required_capacities",
-           "fl_moe_strerror", "fl_moe_debug_views",
+           "fl_moe_strerror", "fl_moe_debug_views", "fl_moe_debug_row_strides",
            "fl_moe_debug_tune", "fl_moe_debug_launch_groups", "fl_moe_debug_launch_plan", "fl_moe_debug_ordering_plan",
            "fl_moe_debug_copy", "fl_moe_debug_fill", "fl_moe_debug_read", "fl_moe_profile_enable", "fl_moe_profile_collect", "fl_moe_profile_read",
            "fl_moe_kernel_name", "fl_moe_build_id"]
@@ -126,6 +126,7 @@ def lib():
         L.fl_moe_strerror.argtypes = [i32]
         L.fl_moe_strerror.restype = C.c_char_p
         L.fl_moe_debug_views.argtypes = [vp, C.POINTER(fl_moe_debug_view)]
+        L.fl_moe_debug_row_strides.argtypes = [C.POINTER(fl_moe_config), C.POINTER(C.c_int64), C.POINTER(C.c_int64)]
         L.fl_moe_debug_tune.argtypes = [vp, i32, i32]
         L.fl_moe_debug_launch_groups.argtypes = [C.POINTER(fl_moe_config), i32, i32, C.POINTER(C.c_int)]
         L.fl_moe_debug_launch_plan.argtypes = [C.POINTER(fl_moe_config), i32, C.POINTER(fl_moe_launch_plan)]
@@ -291,6 +292,13 @@ def fl_moe_debug_ordering_plan(cfg: fl_moe_config, rank_count: int, cached_mb: i
     _check(lib().fl_moe_debug_ordering_plan(C.byref(cfg), rank_count, cached_mb, C.byref(out)),
            "fl_moe_debug_ordering_plan")
     return out
+
+
+def fl_moe_debug_row_strides(cfg: fl_moe_config):
+    """(dispatch, combine): bytes from row to row of the receive buffers."""
+    dispatch, combine = C.c_int64(), C.c_int64()
+    _check(lib().fl_moe_debug_row_strides(C.byref(cfg), C.byref(dispatch), C.byref(combine)), "fl_moe_debug_row_strides")
+    return dispatch.value, combine.value
 
 
 def fl_moe_debug_copy(dst, src, nbytes, stream=None):

@@ -244,6 +244,21 @@ def test_which_calls_wait_behind_a_gate_kernel():
         assert gates(32, max_tokens=128, flags=flag) == (0, 0)
 
 
+@pytest.mark.parametrize("hidden,dtype,dispatch,combine", [
+    (7168, flmoe.FL_DTYPE_BF16, 14336, 14336), (7176, flmoe.FL_DTYPE_BF16, 14464, 14464), (1016, flmoe.FL_DTYPE_BF16, 2048, 2048),
+    (520, flmoe.FL_DTYPE_BF16, 1040, 1040), (8, flmoe.FL_DTYPE_BF16, 16, 16), (7168, flmoe.FL_DTYPE_E4M3_BLOCK128, 7424, 14336)])
+def test_row_strides_of_the_receive_buffers(hidden, dtype, dispatch, combine):
+    """Rows start on 128-byte lines where that takes at most a sixteenth more room, else they are packed."""
+    assert flmoe.fl_moe_debug_row_strides(cfg(hidden=hidden, dispatch_dtype=dtype)) == (dispatch, combine)
+
+
+def test_row_strides_refuse_what_cannot_be():
+    lib, v = flmoe.lib(), C.c_int64()
+    assert lib.fl_moe_debug_row_strides(C.byref(cfg()), None, C.byref(v)) == flmoe.FL_ERR_INVALID_ARG
+    assert lib.fl_moe_debug_row_strides(C.byref(cfg()), C.byref(v), None) == flmoe.FL_ERR_INVALID_ARG
+    assert lib.fl_moe_debug_row_strides(C.byref(cfg(hidden=7)), C.byref(v), C.byref(v)) < 0
+
+
 @pytest.mark.parametrize("N,El,T", [(64, 4, 4096), (32, 8, 8192), (32, 8, 2048), (1, 8, 1 << 20), (8, 16, 40000), (4, 4, 1),
                                     (64, 16, 3000)])
 def test_every_counting_block_of_the_layout_owns_a_tile(N, El, T):

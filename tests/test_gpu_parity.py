@@ -5,6 +5,7 @@ Bars: bit-exact for counts, offsets, positions and dispatched rows; combined
 output within 1 bf16 step of the oracle (fp32 fused multiply-add in k order on
 both sides, so bit-equality is expected and its fraction is reported).
 """
+import dataclasses
 import time
 
 import numpy as np
@@ -1070,14 +1071,15 @@ def test_private_slots_named_decode_workload():
     sh.close()
 
 
+@pytest.mark.parametrize("hidden", [520, 1016])     # rows packed, and 2032 bytes padded to whole lines
 @pytest.mark.parametrize("P", [3, 12, 1000])
-def test_receive_buffer_holds_private_slots_then_shared_range(P):
+def test_receive_buffer_holds_private_slots_then_shared_range(P, hidden):
     """Where the scatter put every row, read back from the receive buffers and
     compared with the layout the interface documents: source s's first P rows for
     rank d at rows s*P.., later ones at N*P + (rows of lower sources beyond their
     P) + (i - P); every other row of the buffer untouched."""
-    inp = wlmod.make_inputs(CASES["ragged_520"]())
-    wl = inp.wl
+    wl = dataclasses.replace(CASES["ragged_520"](), hidden=hidden)
+    inp = wlmod.make_inputs(wl)
     N, E, K, H = wl.n_ranks, wl.n_experts, wl.top_k, wl.hidden
     dev = harness.to_device(inp)
     sh = harness.make_shuffle(inp, max_private_rows=P)
@@ -1093,10 +1095,14 @@ def test_receive_buffer_holds_private_slots_then_shared_range(P):
         assert sh.status() == 0
         got = buf.cpu().numpy()
         Bw = 2 * H
+        stride, _ = flmoe.fl_moe_debug_row_strides(sh.cfg)
+        assert (stride > Bw) == (hidden == 1016)
         xb = inp.x.view(np.uint8).reshape(N, wl.tokens, Bw)
         M = orc.layout(N, E, K, inp.num_tokens, inp.indices).M
         for d in range(N):
-            rows = got[d, :sh.sizes.recv_buffer_rows * Bw].reshape(-1, Bw)
+            rows = got[d, :sh.sizes.recv_buffer_rows * stride].reshape(-1, stride)
+            assert (rows[:, Bw:] == 0xA5).all(), f"rank {d}: the padding between rows was written"
+            rows = rows[:, :Bw]
             touched = np.zeros(rows.shape[0], bool)
             sr, st, _ = orc.recv_order(d, N, E, K, inp.num_tokens, inp.indices)
             shared_start = 0
