@@ -115,7 +115,9 @@ extern "C" {
  * run, so s's combine_reduce of the step before has ended; and rank s issues the next
  * step's dispatch_send after its combine_reduce, whose gate passed only after every
  * peer's announce kernel had run behind its combine kernels, so no peer reads its dispatch
- * receive buffer or the sidecars any more when the next step's rows are written there.
+ * receive buffer or the sidecars any more when the next step's rows are written there.  (Where a small
+ * call announces or waits itself, the same is said of its last workgroup and of its own wait: a
+ * workgroup counts as done once it has read all it reads and its stores are acknowledged.)
  * (On one GPU a waiting gate kernel occupies its hardware queue: enqueue the sends of a
  * phase before the receives that wait for them whenever streams may share a queue.)
  *

@@ -55,9 +55,9 @@ struct Tables {
     unsigned *epoch_route;                                    // [N] layout calls of each rank
     unsigned *arrive_route;                                   // [N dst][N src] step of the last route record received
     // Payload counters, monotone: a completed transfer adds its payload in 16-byte units
-    // plus one (default: by the announce kernel behind the payload kernels; stream-ordered
-    // callers: by the send kernel's first block; progressive mode: the units by every
-    // copying block); expect_* is advanced by the receiver's own planning block from the
+    // plus one (default: by the announce kernel behind the payload kernels, or their last
+    // workgroup; stream-ordered callers: by the send kernel's first block; progressive mode: the
+    // units by every copying block); expect_* is advanced by the receiver's own planning block from the
     // counts it was sent, so a receiver waits for arrive >= expect per source.
     unsigned *arrive_disp, *arrive_comb;                      // [N dst][N src]
     unsigned *expect_disp, *expect_comb;                      // [N dst][N src]
@@ -111,8 +111,9 @@ constexpr int kDoneWords = (kDoneParts + 1) * kDoneLine;
 // the receiver polls the counter with device-scope loads and, once it has arrived,
 // invalidates its caches (agent-scope acquire) before touching the payload.
 // FENCED = false covers the other two modes.  Default: the announce kernel behind the payload
-// kernels orders payload and counters, or, in small steps, the last workgroup to have seen its
-// stores acknowledged (announce_when_last), and the receive kernels start behind a gate kernel.
+// kernels orders payload and counters, or, in small calls that write through, the last workgroup to have
+// seen its stores acknowledged (announce_when_last); the receive kernels start behind a gate kernel, or,
+// in small launches, wait as in progressive mode (wave_wait_together; the reduce kernel is then the FENCED one).
 // FL_FLAG_STREAM_ORDERED: the caller's stream order does; nothing waits for the payload
 // stores inside the kernels then, and the in-kernel counter accesses are relaxed atomics.
 __device__ inline unsigned ld_relaxed(const unsigned *p) {
@@ -337,8 +338,8 @@ __device__ inline void st_through(v4u *p, v4u v) {
 }
 // The same with the streaming hint, for whole lines: what the unpack kernel hands the caller.  Neither dirty lines at
 // the end of the kernel nor lines kept for nobody.  us of a step, streaming stores -> this: 128 tokens of 14 KB 451.4 -> 448.4,
-// 32: 132.7 -> 131.8, 45 ready-made e4m3 tokens 145.2 -> 143.2, 2048: 7789 -> 7535; rows that end inside lines lose
-// (6672 bytes, 301 tokens 96.6 -> 101.3) and keep the streaming stores.
+// 32: 132.7 -> 131.8; 2048 tokens and 45 ready-made e4m3 tokens: no difference beyond noise (1 %); rows that end inside
+// lines lose (6672 bytes, 301 tokens 96.6 -> 101.3) and keep the streaming stores.
 __device__ inline void st_through_stream(v4u *p, v4u v) {
     asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");      // as in st_through
 }

@@ -314,11 +314,15 @@ constexpr long long kStreamedOutputBytes = 40ll << 20;
 bool output_streamed(const Dims &D) { return D.K <= 2 && (long long)D.N * D.T * D.Bc > kStreamedOutputBytes; }
 
 // Whether the send kernels of a call, of `workgroups` per sender, announce their transfers themselves
-// (announce_when_last) rather than having a kernel launched behind them: while they all fit on the machine at once
-// (4096 workgroups of two waves), waiting for their own stores keeps no others out.  us of a step, with announce kernels
-// and without: 2 ranks x 16 tokens of 512 bytes (16 workgroups) 34.0 and 28.6; 8 ranks, 64 tokens of 8 KB, rank by rank
-// (324 a call) 277 and 215; 32 ranks, 14 KB rows: 4 tokens (2176) 45.6 and 44.6, 8 (3616) 57.0 and 56.3, 16 (7168) 81.3
-// and 82.6, 32 (14 336) 131.5 and 133.8, 128 (57 344) 452 and 468.
+// (announce_when_last) rather than having a kernel launched behind them: up to a number of workgroups that was measured.
+// A workgroup that waits for its stores holds its place meanwhile, which costs more than a launch once a call has several
+// times as many as fit on the machine (4096 of the dispatch pack's two waves, 2048 of the combine packs' four, 1024 or 2048
+// of the quantising pack's eight or four).  us of a step, with announce kernels and without: 2 ranks x 16 tokens of 512
+// bytes (16 workgroups) 34.0 and 28.6; 8 ranks, 64 tokens of 8 KB, rank by rank (324 a call) 277 and 215; 32 ranks, 14 KB
+// rows, both calls, by the combine pack's workgroups: 4 tokens (2176) 45.6 and 44.6, 8 (3616) 57.0 and 56.3, 16 (7168)
+// 81.3 and 82.6, 32 (14 336) 131.5 and 133.8, 128 (57 344) 452 and 468; the dispatch pack alone: 4 tokens (896) 46.6 and
+// 46.1, 8 (1792) 57.7 and 56.7, 16 (3584) 81.5 and 80.9.  The quantising pack gains up to 512 workgroups (73.2 and 72.4)
+// and does not care on either side of the line: 2048 196.3 and 196.6, 4096 356.8 and 357.1, 8192 719.3 and 721.1 (noise 0.4).
 bool announces_itself(const Dims &D, long long workgroups, int rank_count) {
     return !(D.flags & (FL_FLAG_PROGRESSIVE_RECV | FL_FLAG_STREAM_ORDERED)) && workgroups * rank_count <= D.tune_self;
 }

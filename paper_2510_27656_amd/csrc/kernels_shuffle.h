@@ -441,8 +441,9 @@ __global__ __launch_bounds__(kWave) void announce_kernel(Dims D, Tables W, int r
 // Dispatch: it first waits until all transfers are complete, the proxy raising a
 // flag once the ImmCounter has reached its expectation).  The receive kernel
 // proper follows in the same stream: it starts after this kernel has ended, with
-// clean caches, so what it reads is what the counters vouched for (the senders'
-// payload kernels had ended, their stores written back, before the release adds).
+// clean caches, so what it reads is what the counters vouched for: when they were added to, the
+// senders' payload kernels had ended and their stores were written back (announce kernel), or all
+// their stores had been written through and acknowledged (announce_when_last).
 // Waiting costs one wave per rank instead of a grid of pollers, so senders that
 // run at the same time keep the machine.
 __global__ __launch_bounds__(kWave) void arrival_gate_kernel(Dims D, Tables W, int rank_begin,
