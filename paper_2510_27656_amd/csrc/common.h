@@ -62,7 +62,7 @@ struct Tables {
     unsigned *arrive_disp, *arrive_comb;                      // [N dst][N src]
     unsigned *expect_disp, *expect_comb;                      // [N dst][N src]
     unsigned *done_disp, *done_comb;  // [N][kDoneWords] workgroups of a sender's kernel that have ended (announce_when_last);
-                                      // behind them [N] verdicts of receive launches that wait themselves (verdict_of)
+                                      // behind them verdicts of receive launches that wait themselves (done_words)
     unsigned long long *routes;   // [N receiver][N source][route_len], in words that carry their step's number
     // written by the source side of the layout step
     int *C;               // [N][E]
@@ -178,7 +178,8 @@ __device__ inline bool wave_wait_counters(const unsigned *ctr, const unsigned *e
 // therefore sees them arrived as well: it may go ahead.  Otherwise it waits for what the deciding wave finds.
 // So a launch whose senders come in time writes nothing here, and a wave's verdict costs one more load, which need
 // not have returned before the wave's first store (verdict_read, verdict_allows).
-// ticket: names this launch in the word, so that nothing has to be cleared.
+// ticket: names this launch in the word, so that nothing has to be cleared on the way.  A graph that holds the receive call
+// but not the layout repeats the ticket, so a verdict to give up is cleared by the last wave that leaves on it (verdict_left).
 typedef unsigned long long verdict_word;
 constexpr unsigned kVerdictClosing = 1, kVerdictCame = 2, kVerdictGaveUp = 3;
 __device__ inline verdict_word launch_ticket(unsigned step, unsigned launch) {
@@ -186,7 +187,8 @@ __device__ inline verdict_word launch_ticket(unsigned step, unsigned launch) {
 }
 // of rank r; done: done_disp, done_comb.  (Two more pointers in Tables took the kernels' arguments past 768 bytes and
 // 0.1 us a launch: 8 ranks one by one 196.2 -> 199.3 us a step.)
-__host__ __device__ inline size_t done_words(int N) { return (size_t)N * kDoneWords + 2 * (size_t)N; }
+// Behind the verdicts, as many words of verdict_left.
+__host__ __device__ inline size_t done_words(int N) { return (size_t)N * kDoneWords + 4 * (size_t)N; }
 __device__ inline verdict_word *verdict_of(unsigned *done, int N, int r) {
     return (verdict_word *)(done + (size_t)N * kDoneWords) + r;
 }
@@ -202,6 +204,19 @@ __device__ inline bool verdict_allows(const verdict_word *word, verdict_word tic
         w = verdict_read(word);
     }
     return w != (ticket | kVerdictClosing) && w != (ticket | kVerdictGaveUp);
+}
+// Counts `waves` of the `all` waves of a rank's launch that leave without having stored; each is counted once, after it
+// has read the word for the last time, and the last one clears the word.  One lane calls it, only after a wait that gave up.
+__device__ inline void verdict_left(verdict_word *word, int N, verdict_word ticket, unsigned waves, unsigned all) {
+    constexpr verdict_word kCount = (1u << 20) - 1;
+    verdict_word *left = word + N;
+    const verdict_word mine = ticket << 18 & ~kCount;           // the launch's number and the low bits of the step's
+    verdict_word old = __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+    do next = ((old & ~kCount) == mine ? old : mine) + waves;
+    while (!__hip_atomic_compare_exchange_strong(left, &old, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if ((next & kCount) != all) return;
+    __hip_atomic_store(left, (verdict_word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(word, (verdict_word)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // The wait of a wave whose first look at the counters (have, lane = counter) did not find them all arrived.
 // A wave that finds no verdict in four times the polls gives up by itself: only if the deciding wave, in the rank's first

@@ -562,13 +562,18 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
     const verdict_word ticket = WAIT ? launch_ticket(step_no, launch) : 0;
     verdict_word verdict = 0;
     bool go = !WAIT;                                // whether this wave may store
+    auto leave = [&]() {                            // it may not
+        if (lane == 0) verdict_left(verdict_of(W.done_disp, N, d), N, ticket, 1u, gridDim.x * (kCopyThreads / kWave));
+    };
     if (WAIT) {
         if (__all(lane >= N || arrived(have, want))) {
             verdict = verdict_read(verdict_of(W.done_disp, N, d));         // on its way while the first row is loaded
         } else {
             if (!wave_wait_together(W.arrive_disp + (size_t)d * N, have, want, N, D.spin_limit, verdict_of(W.done_disp, N, d), ticket,
-                                    wave == 0, W.status))
+                                    wave == 0, W.status)) {
+                leave();
                 return;
+            }
             go = true;
         }
     }
@@ -600,7 +605,7 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
         }
         load_batch(phys, v0 + lane);
         load_meta(phys);
-        if (!may_store()) return;
+        if (!may_store()) { leave(); return; }
         // copies of this row: entries come first in the sidecar
         const int n = __popcll(__ballot(m != kNoEntry));
         int place = 0;
@@ -635,7 +640,10 @@ __global__ __launch_bounds__(kCopyThreads, 8) void dispatch_unpack_kernel(
             }
         }
     }
-    if (WAIT && may_store()) unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
+    if (WAIT) {
+        if (may_store()) unpack_extras(D, W, d, tid, xd, expert_scales, tokens_per_expert);
+        else leave();
+    }
 }
 
 // Short rows, and every row in progressive mode: a block takes a chunk of received rows at a time,
@@ -1280,7 +1288,14 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         acquire_payload<FENCED>();
     }
     __syncthreads();
-    if (timed_out) return;
+    auto leave = [&](unsigned waves) {         // of the rank's workgroups that have a token, or of its first one
+        const unsigned groups = max(1u, min(gridDim.x, (unsigned)(Ts * parts)));
+        verdict_left(word, N, ticket, waves, groups * (blockDim.x / kWave));
+    };
+    if (timed_out) {
+        if (alone && tid == 0) leave(blockDim.x / kWave);
+        return;
+    }
     verdict_word verdict = alone ? verdict_read(word) : 0;   // on its way while the rows are
     bool go = !alone;
     auto may_store = [&]() {
@@ -1310,6 +1325,7 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         __syncthreads();                       // the other set is complete; this one may be rewritten
         cur ^= 1;
     }
+    if (FENCED && !may_store() && lane == 0) leave(1u);
 }
 
 // ------------------------------------------------------------------ diagnostic copy

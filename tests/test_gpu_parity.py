@@ -1713,6 +1713,53 @@ def test_a_delivery_at_the_end_of_the_wait_counts_for_a_whole_rank_or_not_at_all
         sh.close()
 
 
+@pytest.mark.parametrize("tokens", [300, 0])            # of the rank that waits
+@pytest.mark.parametrize("call", ["dispatch_recv", "combine_reduce"])
+@pytest.mark.parametrize("wait_waves", [0, 1 << 20])
+def test_a_replayed_receive_call_finds_what_came_after_its_time_out(wait_waves, call, tokens):
+    """A graph of the receive call alone is replayed within one step: with a notification withheld it writes nothing for that
+    rank and reports the time-out, and once it is there the next replay is complete."""
+    inp = wlmod.make_inputs(wlmod.custom("replayed", 4, 32, 300, 520, 4, seed=19, expert="identity"))
+    inp.num_tokens[1] = tokens
+    dev, ref = harness.to_device(inp), oracle_step(inp, zero_pad=True)
+    sh = harness.make_shuffle(inp, zero_pad=True, spin_limit=300)
+    flmoe.fl_moe_debug_tune(sh.ctx, 11, wait_waves)
+    dispatch = call == "dispatch_recv"
+    try:
+        harness.run_hot_path(sh, dev)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            if dispatch:
+                sh.dispatch_recv()
+            else:
+                sh.combine_reduce(dev["weights"])
+        word = sh.debug()["arrive_disp" if dispatch else "arrive_comb"].view(torch.int32)[1, 2:3]
+        for _ in range(3):
+            for withheld in (True, False):
+                sh.expert_x.view(torch.int16).fill_(POISON)
+                sh.out.view(torch.int16).fill_(POISON)
+                sh.tokens_per_expert.fill_(-1)
+                word.add_(-1 if withheld else 1)
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert sh.status() == (flmoe.FL_STATUS_TIMEOUT if withheld else 0)
+                for r in range(4):
+                    got = bits(sh.expert_x)[r] if dispatch else bits(sh.out)[r]
+                    if withheld and r == 1:
+                        assert (got.view(np.int16) == POISON).all()
+                        assert not dispatch or bool((sh.tokens_per_expert[r] == -1).all())
+                    elif dispatch:
+                        n = ref.expert_rows[r].shape[0]
+                        assert (got[:n] == ref.expert_rows[r]).all() and bool((sh.tokens_per_expert[r] >= 0).all())
+                    else:
+                        n = inp.num_tokens[r]
+                        assert (got[:n] == ref.out[r, :n]).all()
+    finally:
+        sh.close()
+
+
 @pytest.mark.parametrize("near", [0x7FFFFFFE, 0xFFFFFFFE])
 @pytest.mark.parametrize("kw", [dict(), dict(stream_ordered=True), dict(progressive_recv=True)])
 def test_withheld_transfer_is_noticed_while_the_counters_pass_a_sign_or_zero(kw, near):
