@@ -308,10 +308,13 @@ bool replies_cached(const Dims &D, int rank_count) {
     return (long long)D.N * D.T * D.K * D.Bc <= (rank_count < D.N ? limit / 2 : limit);
 }
 
-// Whether the reduce kernel writes its output with the streaming hint: one or two rows per sum and the group's output larger
-// than this (both sides at the kernel).
+// How the reduce kernel writes its output: written through, but with one or two rows per sum and a group's output larger than
+// this with the streaming hint, and not written through where rows begin or end inside lines (all sides at the kernel).
 constexpr long long kStreamedOutputBytes = 40ll << 20;
-bool output_streamed(const Dims &D) { return D.K <= 2 && (long long)D.N * D.T * D.Bc > kStreamedOutputBytes; }
+OutputStores output_stores(const Dims &D, const void *out) {
+    if (D.K > 2 || (long long)D.N * D.T * D.Bc <= kStreamedOutputBytes) return kOutThrough;
+    return D.Bc % 128 == 0 && ((uintptr_t)out & 127) == 0 ? kOutThroughHint : kOutHint;
+}
 
 // Whether the send kernels of a call, of `workgroups` per sender, announce their transfers themselves
 // (announce_when_last) rather than having a kernel launched behind them: up to a number of workgroups that was measured.
@@ -886,7 +889,10 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
     const unsigned launch = ++ctx->recv_launches;
     auto go = [&](auto fence, auto shares) {
         constexpr bool F = decltype(fence)::value, P = decltype(shares)::value;
-        auto kernel = output_streamed(D) ? combine_reduce_kernel<F, P, true> : combine_reduce_kernel<F, P, false>;
+        const OutputStores stores = output_stores(D, out);
+        auto kernel = stores == kOutThrough       ? combine_reduce_kernel<F, P, kOutThrough>
+                      : stores == kOutThroughHint ? combine_reduce_kernel<F, P, kOutThroughHint>
+                                                  : combine_reduce_kernel<F, P, kOutHint>;
         kernel<<<grid, dim3(shape.threads), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, shape.parts, launch);
     };
     const std::true_type yes;

@@ -1146,12 +1146,23 @@ __global__ __launch_bounds__(kCopyThreads) void combine_partial_pack_chunk_kerne
 // without the hint and with it: top 1: 48 tokens (22 MB of output) 66.0 and 66.5, 80: 88.5 and 88.5, 112: 112.3 and 111.8, 144:
 // 137.6 and 133.6, 256: 226 and 217 (ordinary streaming stores 218), 1024: 851 and 833; top 2: 80 tokens 112.5 and 112.3, 112: 147.5
 // and 145.3, 208: 259 and 245, 1024: 1238 and 1226; 16 ranks, 4 KB rows, 33 MB top 2 95.6 and 96.7, 84 MB 212 and 196.
+// Rows that begin or end inside lines lose by writing through in parts: streaming stores there.  us of a step written through,
+// with the hint as well, with the hint alone: 16 ranks x 1000 tokens of 6672 bytes top 1 181, 188.5, 180.4, top 2 273.5, 273.6,
+// 264.5; 32 ranks x 512 of 14 352 top 1 437, 432, 425, top 2 652, 635, 635; 32 x 2032 of 2352 top 1 251.6, 255, 250.1 (256 tokens,
+// 19 MB: 63.2, 64.4, 64.0).  Whole lines, 16 x 1024 of 4 KB top 2 163.6, 164.4, 165.1.
 // More rows per sum gain nothing (top 3, 256 tokens 416 and 418; top 8, 128: 449 and 451).
-// (A choice inside the kernel cost what it gained.  Rule: output_streamed in flmoe.hip.)
+// (A choice inside the kernel cost what it gained.  Rule: output_stores in flmoe.hip.)
+enum OutputStores { kOutThrough, kOutThroughHint, kOutHint };      // OUT: output_stores in flmoe.hip
+template <int OUT>
+__device__ inline void st_output(v4u *p, v4u v) {
+    if (OUT == kOutThrough) st_through(p, v);
+    else if (OUT == kOutThroughHint) st_through_stream(p, v);
+    else st_stream(p, v);
+}
 
 // KT = number of row loads issued together (then consumed in k order); the sum
 // itself always runs k = 0..K-1.
-template <int KT, bool STREAMED, class MayFn>
+template <int KT, int OUT, class MayFn>
 __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos, const float *w,
                                   int K, long long stride, int v0, int nvec, v4u *__restrict__ out, int tid, MayFn may_store) {
     for (int v = v0 + tid; v < nvec; v += (int)blockDim.x) {
@@ -1173,13 +1184,13 @@ __device__ inline void reduce_row(const char *__restrict__ recv, const int *pos,
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
         if (!may_store()) return;
-        if (STREAMED) st_through_stream(out + v, o); else st_through(out + v, o);
+        st_output<OUT>(out + v, o);
     }
 }
 
 // The same sum for a row count only known on the device (partial sums: one row per
 // distinct expert rank of the token): batches of up to 8 loads, predicated.
-template <bool STREAMED, class MayFn>
+template <int OUT, class MayFn>
 __device__ inline void reduce_row_counted(const char *__restrict__ recv, const int *pos,
                                           const float *w, int n, long long stride, int v0, int nvec,
                                           v4u *__restrict__ out, int tid, MayFn may_store) {
@@ -1200,7 +1211,7 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
         o.x = pack_bf16x2(acc[0], acc[1]); o.y = pack_bf16x2(acc[2], acc[3]);
         o.z = pack_bf16x2(acc[4], acc[5]); o.w = pack_bf16x2(acc[6], acc[7]);
         if (!may_store()) return;
-        if (STREAMED) st_through_stream(out + v, o); else st_through(out + v, o);
+        st_output<OUT>(out + v, o);
     }
 }
 
@@ -1216,7 +1227,7 @@ constexpr int kReduceMaxThreads = 1024;
 // distinct expert ranks, found through send_to[s][t][k] for every k that is the first
 // of its rank; they are added in that order in fp32 (a fused multiply-add with
 // weight 1 is an exact add), the weights having been applied on the expert ranks.
-template <bool FENCED, bool PARTIAL, bool STREAMED>
+template <bool FENCED, bool PARTIAL, int OUT>
 __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     Dims D, Tables W, int rank_begin, const float *__restrict__ weights, char *__restrict__ out,
     const int *__restrict__ num_tokens, const int *__restrict__ gate /* as in dispatch_unpack_kernel */,
@@ -1315,11 +1326,11 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         const int next = t + t_step;
         if (fetcher && next < Ts) fetch(next);                // in flight while the rows are summed
         v4u *o = (v4u *)(out + ((size_t)s * D.T + t) * D.Bc);
-        if (PARTIAL) reduce_row_counted<STREAMED>(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid, may_store);
-        else if (kt >= 8) reduce_row<8, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
-        else if (kt >= 4) reduce_row<4, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
-        else if (kt >= 2) reduce_row<2, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
-        else reduce_row<1, STREAMED>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        if (PARTIAL) reduce_row_counted<OUT>(recv, pos[cur], w[cur], n_shares[cur], D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 8) reduce_row<8, OUT>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 4) reduce_row<4, OUT>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else if (kt >= 2) reduce_row<2, OUT>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
+        else reduce_row<1, OUT>(recv, pos[cur], w[cur], K, D.Sc, v0, nvec, o, tid, may_store);
         if (next >= Ts) break;
         if (fetcher) publish(cur ^ 1);
         __syncthreads();                       // the other set is complete; this one may be rewritten
