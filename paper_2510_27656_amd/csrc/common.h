@@ -113,7 +113,7 @@ constexpr int kDoneWords = (kDoneParts + 1) * kDoneLine;
 // FENCED = false covers the other two modes.  Default: the announce kernel behind the payload
 // kernels orders payload and counters, or, in small calls that write through, the last workgroup to have
 // seen its stores acknowledged (announce_when_last); the receive kernels start behind a gate kernel, or,
-// in small launches, wait as in progressive mode (wave_wait_together; the reduce kernel is then the FENCED one).
+// in small launches, wait as in progressive mode, with one verdict per rank (wave_wait_together).
 // FL_FLAG_STREAM_ORDERED: the caller's stream order does; nothing waits for the payload
 // stores inside the kernels then, and the in-kernel counter accesses are relaxed atomics.
 __device__ inline unsigned ld_relaxed(const unsigned *p) {

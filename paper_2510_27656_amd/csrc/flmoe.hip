@@ -885,20 +885,23 @@ static int combine_reduce_range(fl_moe_ctx *ctx, int rb, int rc, CallSpan call, 
         gate = ctx->W.gate_comb;
     }
     LaunchTimer t(ctx, KID_COMBINE_REDUCE, st);
-    const bool fenced = progressive || waits;
     const unsigned launch = ++ctx->recv_launches;
-    auto go = [&](auto fence, auto shares) {
-        constexpr bool F = decltype(fence)::value, P = decltype(shares)::value;
+    auto go = [&](auto form, auto shares) {
+        constexpr int W = decltype(form)::value;
+        constexpr bool P = decltype(shares)::value;
         const OutputStores stores = output_stores(D, out);
-        auto kernel = stores == kOutThrough       ? combine_reduce_kernel<F, P, kOutThrough>
-                      : stores == kOutThroughHint ? combine_reduce_kernel<F, P, kOutThroughHint>
-                                                  : combine_reduce_kernel<F, P, kOutHint>;
+        auto kernel = stores == kOutThrough       ? combine_reduce_kernel<W, P, kOutThrough>
+                      : stores == kOutThroughHint ? combine_reduce_kernel<W, P, kOutThroughHint>
+                                                  : combine_reduce_kernel<W, P, kOutHint>;
         kernel<<<grid, dim3(shape.threads), 0, st>>>(D, ctx->W, rb, weights, o, ctx->num_tokens, gate, shape.parts, launch);
     };
-    const std::true_type yes;
-    const std::false_type no;
-    if (fenced) partial ? go(yes, yes) : go(yes, no);
-    else partial ? go(no, yes) : go(no, no);
+    auto with = [&](auto form) {
+        if (partial) go(form, std::true_type{});
+        else go(form, std::false_type{});
+    };
+    if (progressive) with(std::integral_constant<int, kProgressive>{});
+    else if (waits) with(std::integral_constant<int, kWaitsItself>{});
+    else with(std::integral_constant<int, kBehindGate>{});
     return launch_status();
 }
 

@@ -1220,14 +1220,18 @@ __device__ inline void reduce_row_counted(const char *__restrict__ recv, const i
 // flight at once.
 constexpr int kReduceMaxThreads = 1024;
 //
-// FENCED: the kernel waits for the counters itself and invalidates the caches before it reads the rows: progressive
-// mode, and small launches of the default mode (waits_itself in flmoe.hip), which have no gate kernel.
+// WAITS: kBehindGate when the rows have landed before the kernel starts (or in the caller's stream order: checked, bounded).
+// The other two wait for the counters themselves and invalidate the caches before they read the rows: kProgressive,
+// every workgroup for itself; kWaitsItself, small launches of the default mode (waits_itself in flmoe.hip), all waves of a rank
+// with one verdict.  What the verdict needs costs registers (65, one workgroup of 14 waves per unit instead of two), so the
+// progressive form carries none of it: 32 ranks x 128 tokens of 14 KB on two streams 647 us a step with it, 616 without.
+enum ReduceWaits { kBehindGate, kProgressive, kWaitsItself };
 //
 // PARTIAL (sender-side partial sums): the token's rows are the shares of its
 // distinct expert ranks, found through send_to[s][t][k] for every k that is the first
 // of its rank; they are added in that order in fp32 (a fused multiply-add with
 // weight 1 is an exact add), the weights having been applied on the expert ranks.
-template <bool FENCED, bool PARTIAL, int OUT>
+template <int WAITS, bool PARTIAL, int OUT>
 __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     Dims D, Tables W, int rank_begin, const float *__restrict__ weights, char *__restrict__ out,
     const int *__restrict__ num_tokens, const int *__restrict__ gate /* as in dispatch_unpack_kernel */,
@@ -1245,7 +1249,7 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     // every load the block needs before its rows go out in ONE round: the verdicts, the token
     // count and (wave 1) the first token's positions and weights, which exist for every t < T
     const int plan_ok = W.plan_ok[s], gate_ok = gate ? gate[s] : 1, Ts = num_tokens[s];
-    const bool alone = FENCED && !(D.flags & FL_FLAG_PROGRESSIVE_RECV);      // waits in place of a gate kernel
+    constexpr bool alone = WAITS == kWaitsItself;             // in place of a gate kernel
     const unsigned *ctr = W.arrive_comb + (size_t)s * N;
     verdict_word *word = verdict_of(W.done_comb, N, s);
     verdict_word ticket = 0;
@@ -1296,7 +1300,7 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         } else if (!wave_wait_counters(ctr, W.expect_comb + (size_t)s * N, 0u, N, D.spin_limit)) {
             if (tid == 0) { timed_out = 1; latch_status(W.status, FL_STATUS_TIMEOUT); }
         }
-        acquire_payload<FENCED>();
+        acquire_payload<WAITS != kBehindGate>();
     }
     __syncthreads();
     auto leave = [&](unsigned waves) {         // of the rank's workgroups that have a token, or of its first one
@@ -1310,7 +1314,7 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
     verdict_word verdict = alone ? verdict_read(word) : 0;   // on its way while the rows are
     bool go = !alone;
     auto may_store = [&]() {
-        if (!FENCED || go) return true;
+        if (!alone || go) return true;
         asm volatile("" : "+v"(verdict));      // looked at here and not where it is read
         go = verdict_allows(word, ticket, verdict);
         return go;
@@ -1336,7 +1340,7 @@ __global__ __launch_bounds__(kReduceMaxThreads, 7) void combine_reduce_kernel(
         __syncthreads();                       // the other set is complete; this one may be rewritten
         cur ^= 1;
     }
-    if (FENCED && !may_store() && lane == 0) leave(1u);
+    if (alone && !may_store() && lane == 0) leave(1u);
 }
 
 // ------------------------------------------------------------------ diagnostic copy

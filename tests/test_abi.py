@@ -330,6 +330,12 @@ def test_no_kernel_spills_registers(compiled):
     assert not [n for n, v in zip(names, scratch) if v]
 
 
+def test_two_workgroups_of_the_polling_reduce_kernel_fit_a_unit(compiled):
+    """Its grid is capped, its workgroups have up to 16 waves: more than 64 registers halve the waves that sum."""
+    registers = re.findall(r"Function Name: \S*combine_reduce_kernelILi1E.*?\bVGPRs: (\d+)", compiled[0], re.S)
+    assert len(registers) == 6 and all(int(v) <= 64 for v in registers), registers
+
+
 def test_nothing_overwrites_the_data_of_a_store_while_it_is_read(compiled):
     """Two wait states between a 128-bit store and a vector instruction that writes its data registers; the compiler
     keeps them only behind the stores that it makes itself."""
